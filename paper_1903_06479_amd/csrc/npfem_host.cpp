@@ -1671,11 +1671,10 @@ struct npfem_net {
   float* theta = nullptr;
   float* adam_m = nullptr;
   float* adam_v = nullptr;
-  uint16_t *We = nullptr, *Wl = nullptr, *WsT = nullptr, *WnT = nullptr, *Wd = nullptr;
+  NetPackDst packed{};
   const NetMeshDev* d_meshes = nullptr;
-  int n_pad_max = 0, nb_deg_max = 0;
-  size_t fwd_lds = 0;                       // LDS of the resident forward variant (0: not used)
-  size_t inf_lds = 0;                       // LDS of the resident inference (0: not used)
+  int n_pad_max = 0;
+  bool resident = false, resident_train = false;   // every mesh fits the resident kernels
   int adam_t = 0;
   // inference scratch: per workgroup, features and two activation planes
   DeviceBuffers ibuf;
@@ -1684,9 +1683,9 @@ struct npfem_net {
   // training scratch, sized for the largest minibatch seen
   DeviceBuffers tbuf;
   int tcap = 0, bgrid = 0;
-  uint16_t *tfeat = nullptr, *tH = nullptr, *tZ = nullptr, *dZ = nullptr;
+  uint16_t *tfeat = nullptr, *tH = nullptr, *tZ = nullptr, *tA = nullptr, *tmask = nullptr, *dZ = nullptr;
   double *tframe = nullptr, *tloss = nullptr;
-  float *tout = nullptr, *tdout = nullptr, *dH = nullptr, *Q = nullptr, *partial = nullptr;
+  float *tout = nullptr, *tdout = nullptr, *dH = nullptr, *Q = nullptr, *partial = nullptr, *cellpart = nullptr;
 
   NetWeights weights() const {
     NetWeights w;
@@ -1694,16 +1693,23 @@ struct npfem_net {
     w.force_floor = force_floor;
     w.shape_scale = shape_scale;
     w.theta = theta;
-    w.We = We;
-    w.Wl = Wl;
-    w.WsT = WsT;
-    w.WnT = WnT;
-    w.Wd = Wd;
+    w.We = packed.We;
+    w.Wl = packed.Wl;
+    w.WsT = packed.WsT;
+    w.WnT = packed.WnT;
+    w.Wd = packed.Wd;
+    w.WeA = packed.WeA;
+    w.WlA = packed.WlA;
+    w.WsTA = packed.WsTA;
+    w.WnTA = packed.WnTA;
+    w.WdA = packed.WdA;
     return w;
   }
 };
 
 namespace {
+
+constexpr int kNetGradSlots = 64;
 
 bool net_config_ok(const npfem_net_config* c) {
   return c && c->hidden == kNetH && c->layers >= 1 && c->layers <= kNetMaxLayers && c->force_floor > 0.0 &&
@@ -1716,10 +1722,79 @@ npfem_status net_upload_params(npfem_net* net, const float* theta, hipStream_t s
   HIP_TRY(hipMemcpy(net->theta, theta, net->lay.count * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(launch_fill_zero(net->adam_m, net->lay.count, s));
   HIP_TRY(launch_fill_zero(net->adam_v, net->lay.count, s));
-  HIP_TRY(launch_net_pack(net->weights(), net->We, net->Wl, net->WsT, net->WnT, net->Wd, s));
+  HIP_TRY(launch_net_pack(net->weights(), net->packed, s));
   HIP_TRY(hipStreamSynchronize(s));
   net->adam_t = 0;
   return NPFEM_OK;
+}
+
+// The mesh's node order for the resident kernels: reverse Cuthill-McKee positions, each
+// 32-position block's window of neighbours and adjacency, and the inverse degrees.
+npfem_status net_upload_order(npfem_net* net, const npfem_mesh* m, const MeshPlan& mp, const std::vector<double>& Xc,
+                              NetMeshDev& d) {
+  const int n = m->n, np = mp.n_pad, nblk = np / 32;
+  std::vector<int> perm(np), pos(n);
+  const std::vector<int> ord = rcm_order(m);
+  for (int i = 0; i < np; ++i) perm[i] = i < n ? ord[i] : i;
+  for (int i = 0; i < n; ++i) pos[perm[i]] = i;
+  std::vector<int> blk(2 * (size_t)nblk, 0);
+  int ks_max = 1;
+  for (int b = 0; b < nblk; ++b) {
+    int lo = np, hi = 0;
+    for (int p = 32 * b; p < std::min(n, 32 * b + 32); ++p)
+      for (int q = m->nb_ptr[perm[p]]; q < m->nb_ptr[perm[p] + 1]; ++q) {
+        lo = std::min(lo, pos[m->nb_idx[q]]);
+        hi = std::max(hi, pos[m->nb_idx[q]] + 1);
+      }
+    if (lo >= hi) lo = 0, hi = 1;
+    lo = lo / 8 * 8;
+    const int ks = (hi - lo + 31) / 32;            // 1 .. nblk
+    blk[2 * b] = std::min(lo, np - 32 * ks);
+    blk[2 * b + 1] = ks;
+    ks_max = std::max(ks_max, ks);
+  }
+  d.adj_dw = (ks_max + 3) / 4;
+  std::vector<uint32_t> adj((size_t)nblk * d.adj_dw * 128, 0u);
+  std::vector<float> ideg(np, 0.f);
+  std::vector<uint16_t> wdeg(3 * (size_t)np, 0);
+  std::vector<double> rest(4 * (size_t)np, 0.0);
+  std::vector<float> restf(4 * (size_t)np, 0.f);
+  std::vector<uint32_t> nbp((size_t)(d.nb_deg + 1) / 2 * np, 0xffffffffu);   // read where n_pad <= 768 only
+  for (int p = 0; p < n; ++p) {
+    const int v = perm[p], b = p / 32;
+    for (int q = m->nb_ptr[v]; q < m->nb_ptr[v + 1]; ++q) {
+      const int at = pos[m->nb_idx[q]] - blk[2 * b], s = at / 32, lane = (at % 32) / 8 * 16 + p % 16;
+      adj[(((size_t)b * d.adj_dw + s / 4) * 2 + (p % 32) / 16) * 64 + lane] |= 1u << (4 * (s % 4) + at % 8 / 2 + 16 * (at % 2));
+    }
+    for (int k = 0; k < 3; ++k) rest[4 * p + k] = Xc[3 * v + k];
+    rest[4 * p + 3] = mp.mass[v];
+    for (int k = 0; k < 3; ++k) restf[4 * p + k] = (float)Xc[3 * v + k];
+    restf[4 * p + 3] = (float)(1.0 / mp.mass[v]);
+    for (int q = m->nb_ptr[v]; q < m->nb_ptr[v + 1]; ++q) {
+      const int e = q - m->nb_ptr[v], sh = 16 * (e & 1);
+      uint32_t& w = nbp[(size_t)(e / 2) * np + p];
+      w = (w & ~(0xffffu << sh)) | (uint32_t)(pos[m->nb_idx[q]] & 0xffff) << sh;
+    }
+    ideg[p] = 1.0f / (float)(m->nb_ptr[v + 1] - m->nb_ptr[v]);
+    float rest = ideg[p];
+    for (int k = 0; k < 3; ++k) {
+      const uint16_t bits = to_bf16(rest);
+      wdeg[(size_t)k * np + p] = bits;
+      const uint32_t u = (uint32_t)bits << 16;
+      float part;
+      std::memcpy(&part, &u, 4);
+      rest -= part;
+    }
+  }
+  npfem_status s;
+  if ((s = net->buf.upload(perm.data(), perm.size(), &d.perm))) return s;
+  if ((s = net->buf.upload(blk.data(), blk.size(), &d.blk))) return s;
+  if ((s = net->buf.upload(adj.data(), adj.size(), &d.adj))) return s;
+  if ((s = net->buf.upload(rest.data(), rest.size(), &d.rest))) return s;
+  if ((s = net->buf.upload(restf.data(), restf.size(), &d.restf))) return s;
+  if ((s = net->buf.upload(nbp.data(), nbp.size(), &d.nbp))) return s;
+  if ((s = net->buf.upload(ideg.data(), ideg.size(), &d.ideg))) return s;
+  return net->buf.upload(wdeg.data(), wdeg.size(), &d.wdeg);
 }
 
 npfem_status net_check_batch(const npfem_net* net, const npfem_batch* b) {
@@ -1728,7 +1803,7 @@ npfem_status net_check_batch(const npfem_net* net, const npfem_batch* b) {
 }
 
 npfem_status net_inference_scratch(npfem_net* net) {
-  if (net->ibuf.ptrs.size()) return NPFEM_OK;
+  if (net->resident || net->ibuf.ptrs.size()) return NPFEM_OK;
   net->igrid = 4 * net->plan->cu_count;
   const size_t np = (size_t)net->n_pad_max;
   void* p;
@@ -1745,32 +1820,40 @@ npfem_status net_training_scratch(npfem_net* net, int cells) {
   net->tbuf.release();
   net->tcap = 0;
   const size_t np = (size_t)net->n_pad_max, L1 = (size_t)net->lay.layers + 1, C = (size_t)cells;
-  net->bgrid = std::max(1, std::min(cells, net->plan->cu_count));
-  const size_t G = (size_t)net->bgrid;
-  void* p;
+  const size_t P = (size_t)net->lay.count;
   npfem_status s;
-  if ((s = net->tbuf.alloc(C * np * kNetFeatPad * 2, &p))) return s;
-  net->tfeat = static_cast<uint16_t*>(p);
-  if ((s = net->tbuf.alloc(C * L1 * np * kNetH * 2, &p))) return s;
-  net->tH = static_cast<uint16_t*>(p);
-  if ((s = net->tbuf.alloc(C * L1 * np * kNetH * 2, &p))) return s;
-  net->tZ = static_cast<uint16_t*>(p);
-  if ((s = net->tbuf.alloc(C * 12 * sizeof(double), &p))) return s;
-  net->tframe = static_cast<double*>(p);
-  if ((s = net->tbuf.alloc(C * sizeof(double), &p))) return s;
-  net->tloss = static_cast<double*>(p);
-  if ((s = net->tbuf.alloc(C * np * 3 * sizeof(float), &p))) return s;
-  net->tout = static_cast<float*>(p);
-  if ((s = net->tbuf.alloc(C * np * 3 * sizeof(float), &p))) return s;
-  net->tdout = static_cast<float*>(p);
-  if ((s = net->tbuf.alloc(G * 2 * np * kNetH * sizeof(float), &p))) return s;
-  net->dH = static_cast<float*>(p);
-  if ((s = net->tbuf.alloc(G * np * kNetH * sizeof(float), &p))) return s;
-  net->Q = static_cast<float*>(p);
-  if ((s = net->tbuf.alloc(G * np * kNetH * 2, &p))) return s;
-  net->dZ = static_cast<uint16_t*>(p);
-  if ((s = net->tbuf.alloc(G * (size_t)net->lay.count * sizeof(float), &p))) return s;
-  net->partial = static_cast<float*>(p);
+  auto get = [&](size_t bytes, auto** dst) {
+    void* p = nullptr;
+    if (!s) s = net->tbuf.alloc(bytes, &p);
+    *dst = static_cast<std::remove_reference_t<decltype(**dst)>*>(p);
+  };
+  s = NPFEM_OK;
+  get(C * np * kNetFeatPad * 2, &net->tfeat);
+  get(C * L1 * np * kNetH * 2, &net->tH);
+  get(C * L1 * np * kNetH * 2, &net->tZ);
+  get(C * kNetFrame * sizeof(double), &net->tframe);
+  get(C * sizeof(double), &net->tloss);
+  get(C * np * 3 * sizeof(float), &net->tout);
+  get(C * np * 3 * sizeof(float), &net->tdout);
+  if (net->resident_train) {
+    // weight-gradient slots: enough workgroups per layer to keep the memory busy, few enough
+    // that summing them stays cheap
+    net->bgrid = std::max(1, std::min(cells, kNetGradSlots));
+    get(C * (L1 - 1) * np * kNetH * 2, &net->tA);
+    get(C * L1 * np / 16 * 64 * 2, &net->tmask);
+    get(C * net_cell_part(net->lay.layers) * sizeof(float), &net->cellpart);
+  } else {
+    net->bgrid = std::max(1, std::min(cells, net->plan->cu_count));
+    const size_t G = (size_t)net->bgrid;
+    get(G * 2 * np * kNetH * sizeof(float), &net->dH);
+    get(G * np * kNetH * sizeof(float), &net->Q);
+    get(G * np * kNetH * 2, &net->dZ);
+  }
+  get((size_t)net->bgrid * P * sizeof(float), &net->partial);
+  if (s) {
+    net->tbuf.release();
+    return s;
+  }
   net->tcap = cells;
   return NPFEM_OK;
 }
@@ -1788,13 +1871,12 @@ NetFwdArgs<Real> net_fwd_args(const npfem_net* net, const npfem_batch* b, const 
   a.v = static_cast<const Real*>(v);
   a.f = static_cast<const Real*>(f);
   a.S.n_pad_max = net->n_pad_max;
-  a.nb_deg_max = net->nb_deg_max;
   return a;
 }
 
-// persistent workgroups of the forward launch: the LDS-resident variant runs one per CU
+// persistent workgroups of the forward launches
 int net_fwd_grid(const npfem_net* net, int n_cells) {
-  const int g = net->fwd_lds ? net->plan->cu_count : 4 * net->plan->cu_count;
+  const int g = net->resident ? net_resident_per_cu(net->n_pad_max) * net->plan->cu_count : 4 * net->plan->cu_count;
   return std::max(1, std::min(g, n_cells));
 }
 
@@ -1807,19 +1889,20 @@ npfem_status net_infer_now(npfem_net* net, npfem_batch* b, const void* x, const 
   a.S.train = 0;
   a.n_cells = (int)b->n_cells;
   a.delta = static_cast<Real*>(delta);
-  if (net->inf_lds) {                       // resident inference: one workgroup per CU
+  const int grid = net_fwd_grid(net, (int)b->n_cells);
+  if (net->resident) {
     a.cframe = b->net_frames;
-    HIP_TRY(launch_net_infer<Real>(a, std::max(1, std::min(net->plan->cu_count, (int)b->n_cells)), net->inf_lds, s));
+    HIP_TRY(launch_net_resident<Real>(a, grid, 0, s));
     return NPFEM_OK;
   }
-  HIP_TRY(launch_net_forward<Real>(a, std::min(net->igrid, net_fwd_grid(net, (int)b->n_cells)), net->fwd_lds, s));
+  HIP_TRY(launch_net_forward<Real>(a, std::min(net->igrid, grid), s));
   return NPFEM_OK;
 }
 
 // the batch's frame buffer of the resident inference, allocated before any launch (and
 // so before a graph capture)
 npfem_status net_batch_frames(const npfem_net* net, npfem_batch* b) {
-  if (!net->inf_lds || b->net_frames) return NPFEM_OK;
+  if (!net->resident || b->net_frames) return NPFEM_OK;
   void* p;
   npfem_status s;
   if ((s = b->dbuf.alloc((size_t)b->n_cells * kNetFrame * sizeof(double), &p))) return s;
@@ -1860,12 +1943,16 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   a.S.feat = net->tfeat;
   a.S.H = net->tH;
   a.S.Z = net->tZ;
+  a.S.Am = net->tA;
+  a.S.mask = net->tmask;
   a.S.frame = net->tframe;
+  a.cframe = net->tframe;
   a.S.out = net->tout;
   a.S.train = 1;
   a.cells = cells;
   a.n_cells = n_cells;
-  HIP_TRY(launch_net_forward<Real>(a, net_fwd_grid(net, n_cells), net->fwd_lds, s));
+  if (net->resident_train) HIP_TRY(launch_net_resident<Real>(a, net_fwd_grid(net, n_cells), 1, s));
+  else HIP_TRY(launch_net_forward<Real>(a, std::min(n_cells, 4 * net->plan->cu_count), s));
   NetLossArgs<Real> la{};
   la.S = a.S;
   la.meshes = net->d_meshes;
@@ -1880,22 +1967,36 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   la.dout = net->tdout;
   la.cell_loss = net->tloss;
   HIP_TRY(launch_net_loss<Real>(la, s));
-  NetBwdArgs ba{};
-  ba.W = net->weights();
-  ba.S = a.S;
-  ba.meshes = net->d_meshes;
-  ba.cell_mesh = b->cell_mesh;
-  ba.cells = cells;
-  ba.n_cells = n_cells;
-  ba.dout = net->tdout;
-  ba.dH = net->dH;
-  ba.Q = net->Q;
-  ba.dZ = net->dZ;
-  ba.partial = net->partial;
   const int g = std::max(1, std::min(net->bgrid, n_cells));
-  HIP_TRY(launch_fill_zero(net->partial, (int64_t)g * net->lay.count, s));
-  HIP_TRY(launch_net_backward(ba, g, s));
-  HIP_TRY(launch_net_reduce(net->partial, g, net->lay.count, grad_out, s));
+  if (net->resident_train) {
+    NetChainArgs ca{};
+    ca.W = net->weights();
+    ca.S = a.S;
+    ca.meshes = net->d_meshes;
+    ca.cell_mesh = b->cell_mesh;
+    ca.cells = cells;
+    ca.n_cells = n_cells;
+    ca.dout = net->tdout;
+    ca.cellpart = net->cellpart;
+    ca.partial = net->partial;
+    HIP_TRY(launch_net_chain(ca, net_fwd_grid(net, n_cells), g, grad_out, s));
+  } else {
+    NetBwdArgs ba{};
+    ba.W = net->weights();
+    ba.S = a.S;
+    ba.meshes = net->d_meshes;
+    ba.cell_mesh = b->cell_mesh;
+    ba.cells = cells;
+    ba.n_cells = n_cells;
+    ba.dout = net->tdout;
+    ba.dH = net->dH;
+    ba.Q = net->Q;
+    ba.dZ = net->dZ;
+    ba.partial = net->partial;
+    HIP_TRY(launch_fill_zero(net->partial, (int64_t)g * net->lay.count, s));
+    HIP_TRY(launch_net_backward(ba, g, s));
+    HIP_TRY(launch_net_reduce(net->partial, g, net->lay.count, grad_out, s));
+  }
   if (loss_out) {
     std::vector<double> cl(n_cells);
     HIP_TRY(hipMemcpyAsync(cl.data(), net->tloss, n_cells * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1943,17 +2044,15 @@ npfem_status npfem_net_create(npfem_plan* p, const npfem_net_config* cfg, const 
     if ((s = net->buf.alloc(P * sizeof(float), &q))) return s;
     *dst = static_cast<float*>(q);
   }
-  const size_t nL = (size_t)cfg->layers * kNetH * kNetH;
-  if ((s = net->buf.alloc((size_t)kNetH * kNetFeatPad * 2, &q))) return s;
-  net->We = static_cast<uint16_t*>(q);
-  if ((s = net->buf.alloc(2 * nL * 2, &q))) return s;
-  net->Wl = static_cast<uint16_t*>(q);
-  if ((s = net->buf.alloc(nL * 2, &q))) return s;
-  net->WsT = static_cast<uint16_t*>(q);
-  if ((s = net->buf.alloc(nL * 2, &q))) return s;
-  net->WnT = static_cast<uint16_t*>(q);
-  if ((s = net->buf.alloc(3 * kNetH * 2, &q))) return s;
-  net->Wd = static_cast<uint16_t*>(q);
+  const size_t nL = (size_t)cfg->layers * kNetH * kNetH, nE = (size_t)kNetH * kNetFeatPad;
+  const std::pair<uint16_t**, size_t> blocks[] = {
+      {&net->packed.We, nE},   {&net->packed.Wl, 2 * nL},  {&net->packed.WsT, nL},  {&net->packed.WnT, nL},
+      {&net->packed.Wd, 3 * kNetH}, {&net->packed.WeA, nE}, {&net->packed.WlA, 2 * nL}, {&net->packed.WsTA, nL},
+      {&net->packed.WnTA, nL}, {&net->packed.WdA, 1024}};
+  for (const auto& [dst, count] : blocks) {
+    if ((s = net->buf.alloc(count * 2, &q))) return s;
+    *dst = static_cast<uint16_t*>(q);
+  }
   // per mesh type: rest positions about the mass-weighted centroid, masses, neighbours
   std::vector<NetMeshDev> md(p->meshes.size());
   for (size_t mi = 0; mi < p->meshes.size(); ++mi) {
@@ -1987,13 +2086,13 @@ npfem_status npfem_net_create(npfem_plan* p, const npfem_net_config* cfg, const 
     d.nb_idx = p->precision == NPFEM_FP64 ? mp.dev64.nb_idx : mp.dev32.nb_idx;
     d.nb_ell = p->precision == NPFEM_FP64 ? mp.dev64.nb_ell : mp.dev32.nb_ell;
     d.nb_deg = p->precision == NPFEM_FP64 ? mp.dev64.nb_deg : mp.dev32.nb_deg;
-    net->nb_deg_max = std::max(net->nb_deg_max, d.nb_deg);
     if ((s = net->buf.upload(Xc.data(), Xc.size(), &d.Xc))) return s;
     if ((s = net->buf.upload(mp.mass.data(), mp.mass.size(), &d.mass))) return s;
+    if ((s = net_upload_order(net.get(), m, mp, Xc, d))) return s;
   }
   if ((s = net->buf.upload(md.data(), md.size(), &net->d_meshes))) return s;
-  net->fwd_lds = std::getenv("NPFEM_NET_NO_LDS") ? 0 : net_forward_lds_bytes(net->n_pad_max, net->nb_deg_max);
-  net->inf_lds = std::getenv("NPFEM_NET_NO_LDS") ? 0 : net_infer_lds_bytes(net->n_pad_max, net->nb_deg_max);
+  net->resident = !std::getenv("NPFEM_NET_NO_LDS") && net_resident_lds_bytes(net->n_pad_max) > 0;
+  net->resident_train = net->resident && net_chain_lds_bytes(net->n_pad_max) > 0;
   if ((s = net_upload_params(net.get(), theta, nullptr))) return s;
   *out = net.release();
   return NPFEM_OK;
@@ -2081,7 +2180,7 @@ npfem_status npfem_net_adam_step(npfem_net* net, const float* grad, double lr, d
   net->adam_t += 1;
   HIP_TRY(launch_net_adam(net->theta, net->adam_m, net->adam_v, grad, net->lay.count, lr, b1, b2, eps,
                           net->adam_t, s));
-  HIP_TRY(launch_net_pack(net->weights(), net->We, net->Wl, net->WsT, net->WnT, net->Wd, s));
+  HIP_TRY(launch_net_pack(net->weights(), net->packed, s));
   return NPFEM_OK;
 }
 

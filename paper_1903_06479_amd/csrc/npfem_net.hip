@@ -1,21 +1,18 @@
 // gfx950 kernels of the learned warm start: per-cell frame and features, network
 // inference and training (forward, loss, backward, gradient reduction, Adam).
 //
-// One workgroup (4 wave64) carries one cell at a time.  Node-wise products with the
-// 64 x 64 (or 64 x 128) weight blocks run on the matrix cores
-// (v_mfma_f32_16x16x32_bf16): each wave takes 16-node row blocks; the A operand of a
-// layer is [h_i | mean_{j in N(i)} h_j] built on the fly from the activations in
-// memory (8 consecutive features per lane, gathered over the neighbour list), the B
-// operand is the weight block held in registers.  Weight gradients are sums over
-// nodes: 32-node chunks are staged transposed in LDS so that the node index becomes
-// the contiguous k dimension of the matrix instruction.  Every per-workgroup gradient
-// sum goes to its own slot and the slots are reduced in a fixed order, so training is
-// deterministic.
+// One workgroup carries one cell at a time; node-wise products with the 64 x 64 (or 64 x
+// 128) weight blocks run on the matrix cores (v_mfma_f32_16x16x32_bf16).  Meshes of up to
+// 768 rows run with their activations resident in LDS (net_resident_kernel, and for training
+// net_chain_kernel and net_wgrad_kernel); larger ones gather from memory
+// (net_forward_kernel, net_backward_kernel).  Every partial gradient sum goes to its own slot
+// and the slots are reduced in a fixed order, so training is deterministic.
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "npfem_internal.h"
 #include "npfem_net_internal.h"
@@ -166,7 +163,7 @@ __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, in
     fr[9] = s;
     if (A.S.frame) {
 #pragma unroll
-      for (int q = 0; q < 10; ++q) A.S.frame[(size_t)k * 12 + q] = fr[q];
+      for (int q = 0; q < 10; ++q) A.S.frame[(size_t)k * kNetFrame + q] = fr[q];
     }
   }
   __syncthreads();
@@ -412,81 +409,9 @@ __global__ void __launch_bounds__(kBlock) net_forward_kernel(NetFwdArgs<Real> A)
   }
 }
 
-// LDS-resident variant (meshes whose activations fit a compute unit): 512 threads; the
-// cell's activations live in LDS (row pitch kHP, so 16-byte operand reads of 8
-// consecutive rows fall in distinct banks) together with the mesh's neighbour lists;
-// each layer's output goes to memory (L2) and is copied back after a barrier.
-constexpr int kNetLdsBlock = 512;
-constexpr int kHP = 72;
-constexpr int kNetLdsHeader = 8 * kRS * 8 + 16 * 8;   // reduction, frame
-
-template <typename Real>
-__global__ void __launch_bounds__(kNetLdsBlock) net_forward_lds_kernel(NetFwdArgs<Real> A) {
-  const int np_max = A.S.n_pad_max, deg_max = A.nb_deg_max;
-  extern __shared__ __align__(16) unsigned char lds[];
-  double* red = reinterpret_cast<double*>(lds);
-  double* fr = red + 8 * kRS;
-  uint16_t* Hl = reinterpret_cast<uint16_t*>(lds + kNetLdsHeader);
-  uint16_t* Fl = Hl + (size_t)np_max * kHP;                    // features [np_max][32]
-  uint16_t* nbl = Fl + (size_t)np_max * kNetFeatPad;
-  uint8_t* degl = reinterpret_cast<uint8_t*>(nbl + (size_t)deg_max * np_max);
-  constexpr int NT = kNetLdsBlock, NWV = kNetLdsBlock / 64;
-  const NetLayout L = A.W.lay;
-  const bool train = A.S.train != 0;
-  const size_t plane = (size_t)A.S.n_pad_max * kNetH;
-  const int nh = train ? L.layers + 1 : 2;
-  int staged = -1;
-  for (int k = blockIdx.x; k < A.n_cells; k += gridDim.x) {
-    const int cell = A.cells ? A.cells[k] : k;
-    const int mi = A.cell_mesh[cell];
-    const NetMeshDev& M = A.meshes[mi];
-    const int n = M.n, np = M.n_pad;
-    const int64_t voff = A.cell_voff[cell];
-    if (mi != staged) {                       // neighbour lists of this mesh type into LDS
-      __syncthreads();
-      for (int e = tid(); e < M.nb_deg * np; e += NT) nbl[e] = (uint16_t)M.nb_ell[e];
-      for (int i = tid(); i < np; i += NT) degl[i] = (uint8_t)(i < n ? M.nb_ptr[i + 1] - M.nb_ptr[i] : 0);
-      staged = mi;
-    }
-    const size_t slot = train ? (size_t)k : (size_t)blockIdx.x;
-    uint16_t* feat = A.S.feat + slot * A.S.n_pad_max * kNetFeatPad;
-    uint16_t* Hs = A.S.H + slot * nh * plane;
-    uint16_t* Zs = train ? A.S.Z + slot * (L.layers + 1) * plane : nullptr;
-    cell_features<Real, NT>(A, M, k, A.x + 3 * voff, A.v + 3 * voff, A.f + 3 * voff, Fl, train ? feat : nullptr,
-                            red, fr);
-    encoder_rows<NWV>(A.W, Fl, n, np, Hl, kHP, train ? Hs : nullptr, Zs);
-    __syncthreads();
-    auto nbr = [&](int q, int i) { return (int)nbl[q * np + i]; };
-    auto deg = [&](int i) { return (int)degl[i]; };
-    for (int l = 0; l < L.layers; ++l) {
-      uint16_t* Hout = Hs + (size_t)(train ? l + 1 : 0) * plane;
-      layer_rows<NWV>(A.W, l, n, np, M.nb_deg, Hl, kHP, Hout, train ? Zs + (size_t)(l + 1) * plane : nullptr, nbr,
-                      deg);
-      __syncthreads();
-      const int chunks = np * (kNetH / 8);
-      for (int c0 = tid(); c0 < chunks; c0 += 4 * NT) {
-        bf16x8 t[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {                   // loads issued together (clamped, always valid)
-          const int c = min(c0 + u * NT, chunks - 1);
-          t[u] = ld8(Hout + (size_t)(c >> 3) * kNetH + 8 * (c & 7));
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = c0 + u * NT;
-          if (c < chunks) *reinterpret_cast<bf16x8*>(Hl + (size_t)(c >> 3) * kHP + 8 * (c & 7)) = t[u];
-        }
-      }
-      __syncthreads();
-    }
-    decoder_rows<Real, NWV>(A, k, voff, n, np, Hl, kHP, fr);
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------------------------
-// Inference: the frame of every cell first (one wave per cell), then the network with
-// the cell's activations resident in LDS and updated in place.
+// The frame of every cell (one wave per cell), then the network with the cell's
+// activations resident in LDS and updated in place (inference, and the training forward).
 // ---------------------------------------------------------------------------------
 
 __device__ inline double wave_sum(double x) {
@@ -551,239 +476,348 @@ __global__ void __launch_bounds__(256) net_frame_kernel(NetFwdArgs<Real> A) {
     if (lane == q) out[q] = fr[q];
 }
 
-constexpr int kInfBlock = 512;
-constexpr int kInfWaves = kInfBlock / 64;
-constexpr int kInfMaxRegRounds = 3;            // row-block rounds whose results stay in registers
+// The network with one cell per workgroup, its activations in LDS ([n_pad][kHP] BF16) and
+// the nodes taken in a reverse Cuthill-McKee order of the mesh, 16 positions per row block.
+// Every product has the node as the matrix instruction's column, z^T = W_s h^T + W_n mean^T.
+// Row 4 kq + i of result tile c stands for feature 32 (c / 2) + 8 kq + 4 (c % 2) + i, so that
+// a lane of group kq ends up with eight consecutive features per 32 of its node: its results
+// are the next product's operand, nothing is exchanged between lanes, and activations move
+// as 16-byte LDS accesses.  The neighbour sums run on the matrix unit too: a neighbour's row
+// is an operand as it is read, and a constant 0/1 operand picks a result tile's features from
+// it, so each instruction adds one neighbour per node in FP32, in the order of the mesh's list
+// (a row's neighbour positions stay in registers).
+//
+// Bound: the LDS.  A row block reads 14 rows of 128 bytes per node, the neighbours' from
+// arbitrary rows (about two lanes to a bank), 9 k of a layer's 15 k cycles at n = 642.
+// 100,000 cells: 15.5 ms; one row block per wave of the earlier layout (sums by dot2 on the
+// vector unit, 2-byte LDS results, 151 KB) took 33.0 ms, dot2 sums in this layout 15.9.  The
+// sums as a contraction with the adjacency over a window of nodes (transposing LDS reads, no
+// random rows) reach 13.0 ms, but add in another order: 40 cells of 100,000 then change in a
+// BF16 rounding, up to 4e-3 of a result.
+constexpr int kHP = 72;                        // LDS row pitch (BF16): 16 rows fall on distinct banks
 
-// LDS of the resident inference: h [n_pad][kHP] bf16, the neighbour lists, the degrees,
-// then the staging of the rounds beyond kInfMaxRegRounds (16 KB per round).
-__host__ __device__ inline size_t infer_lds_base(int n_pad, int nb_deg) {
-  return ((size_t)n_pad * kHP * 2 + (size_t)nb_deg * n_pad * 2 + (size_t)n_pad + 15) / 16 * 16;
+// A workgroup barrier that orders LDS accesses only: global loads and stores stay in flight.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// One message-passing layer of the resident variant.  Every wave computes h + relu(z)
-// for its row blocks rb = wave + kInfWaves r: the first RL rounds into the LDS staging
-// area Ob (per block, 8 packed dwords per lane), the last RR rounds into registers;
-// after a barrier all of them are written over h in LDS (the layer reads every
-// neighbour's old h before any row is overwritten).  The neighbour sums take one bf16
-// half of a dword per dot2 instruction (the other half weighted 0), so activations are
-// added in FP32 without being unpacked first.
-template <int RR>
-__device__ __attribute__((always_inline)) inline void infer_layer(const NetWeights& W, int l, int n, int np,
-                                                                  int width, uint16_t* H, const uint16_t* nbl,
-                                                                  const uint8_t* degl, uint32_t* Ob, int RL) {
+// Four rows x 16 columns of BF16 per 16-lane group, transposed: lane i passes the address of
+// row i / 4, columns 4 (i % 4) .. + 3, and receives column i of the four rows.
+typedef short short4_t __attribute__((ext_vector_type(4)));
+__device__ inline uint2 ld_tr(const uint16_t* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                       (__attribute__((address_space(3))) short4_t*)const_cast<uint16_t*>(p)));
+}
+__device__ inline bf16x8 join8(uint2 a, uint2 b) { return __builtin_bit_cast(bf16x8, uint4{a.x, a.y, b.x, b.y}); }
+__device__ inline uint2 ld4(const uint16_t* p) { return *reinterpret_cast<const uint2*>(p); }
+__device__ inline uint4 ldw(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+__device__ inline void stw(uint16_t* p, uint2 a, uint2 b) { *reinterpret_cast<uint4*>(p) = uint4{a.x, a.y, b.x, b.y}; }
+__device__ inline uint32_t pack2(float a, float b) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
-  const uint16_t* Wl = W.Wl + (size_t)l * kNetH * 2 * kNetH;
-  bf16x8 bq[4][4];
-  float bias[4];
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+__device__ inline float half_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ inline float half_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// The nodes of a k step as masks, 0xffff or 0 each: bits j and j + 16 of a lane's word
+// (shifted right by four per k step) are the nodes of dword j.
+__device__ inline uint4 adj_mask(uint32_t word) {
+  uint32_t d[4];
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) bq[s4][cb] = ld8(Wl + (size_t)(cb * 16 + l16) * 2 * kNetH + 32 * s4 + 8 * kq);
-    bias[cb] = W.theta[W.lay.b(l) + cb * 16 + l16];
-  }
-  const bf16x2 one_lo = {(__bf16)1.f, (__bf16)0.f}, one_hi = {(__bf16)0.f, (__bf16)1.f};
-  const bf16x2 zero2 = {(__bf16)0.f, (__bf16)0.f};
-  const int nrb = np >> 4;
-  // new h of row block rb: rows rb*16 + 4kq + i, column cb*16 + l16, as bf16 pairs over i
-  auto block = [&](int rb, uint32_t (&o)[8]) {
-    const int row = rb * 16 + l16;
-    bf16x8 aq[4];
-    aq[0] = ld8(H + (size_t)row * kHP + 8 * kq);
-    aq[1] = ld8(H + (size_t)row * kHP + 32 + 8 * kq);
-    float g[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) g[e] = 0.f;
-    const int dg = degl[row];                              // 0 for padding rows
-    auto add = [&](int j, bf16x2 wl, bf16x2 wh) {
-      const uint4 h0 = *reinterpret_cast<const uint4*>(H + (size_t)j * kHP + 8 * kq);
-      const uint4 h1 = *reinterpret_cast<const uint4*>(H + (size_t)j * kHP + 32 + 8 * kq);
-      const uint32_t w[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-#pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        const bf16x2 p = __builtin_bit_cast(bf16x2, w[d]);
-        g[2 * d] = __builtin_amdgcn_fdot2_f32_bf16(p, wl, g[2 * d], false);
-        g[2 * d + 1] = __builtin_amdgcn_fdot2_f32_bf16(p, wh, g[2 * d + 1], false);
-      }
-    };
-    // the first kNetUnrollDeg ELL columns are read unconditionally (ELL padding points
-    // at the row itself) and weighted by q < degree; wider meshes go on in a loop
-#pragma unroll
-    for (int q = 0; q < kNetUnrollDeg; ++q) {
-      const int j = q < width ? (int)nbl[q * np + row] : row;
-      const bool on = q < dg;
-      add(j, on ? one_lo : zero2, on ? one_hi : zero2);
-    }
-    for (int q = kNetUnrollDeg; q < dg; ++q) add((int)nbl[q * np + row], one_lo, one_hi);
-    const float inv = dg > 0 ? 1.0f / (float)dg : 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      aq[2][e] = (__bf16)(g[e] * inv);
-      aq[3][e] = (__bf16)(g[8 + e] * inv);
-    }
-    floatx4 acc[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[s4], bq[s4][cb], acc[cb], 0, 0, 0);
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      float hv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r2 = rb * 16 + 4 * kq + i;
-        const float z = acc[cb][i] + bias[cb];
-        hv[i] = r2 < n ? bf2f(H[(size_t)r2 * kHP + cb * 16 + l16]) + fmaxf(z, 0.f) : 0.f;
-      }
-      o[2 * cb] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)hv[0], (__bf16)hv[1]});
-      o[2 * cb + 1] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)hv[2], (__bf16)hv[3]});
-    }
-  };
-  auto put = [&](int rb, const uint32_t (&o)[8]) {
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r2 = rb * 16 + 4 * kq + i;
-        const uint32_t w = o[2 * cb + (i >> 1)];
-        H[(size_t)r2 * kHP + cb * 16 + l16] = (uint16_t)((i & 1) ? (w >> 16) : (w & 0xffffu));
-      }
-  };
-  uint32_t* ob = Ob + (size_t)wave * 8 * 64 + lane;        // this lane's dwords of round r: ob[r * kInfWaves * 512 + 64 d]
-  for (int r = 0; r < RL; ++r) {
-    const int rb = wave + kInfWaves * r;
-    if (rb >= nrb) break;                                  // uniform over the wave
-    uint32_t o[8];
-    block(rb, o);
-#pragma unroll
-    for (int d = 0; d < 8; ++d) ob[(size_t)r * kInfWaves * 512 + 64 * d] = o[d];
-  }
-  uint32_t out[RR][8];
-#pragma unroll
-  for (int r = 0; r < RR; ++r) {
-    const int rb = wave + kInfWaves * (RL + r);
-    if (rb >= nrb) break;
-    block(rb, out[r]);
-  }
-  __syncthreads();
-  for (int r = 0; r < RL; ++r) {
-    const int rb = wave + kInfWaves * r;
-    if (rb >= nrb) break;
-    uint32_t o[8];
-#pragma unroll
-    for (int d = 0; d < 8; ++d) o[d] = ob[(size_t)r * kInfWaves * 512 + 64 * d];
-    put(rb, o);
-  }
-#pragma unroll
-  for (int r = 0; r < RR; ++r) {
-    const int rb = wave + kInfWaves * (RL + r);
-    if (rb >= nrb) break;
-    put(rb, out[r]);
-  }
-  __syncthreads();
+  for (int j = 0; j < 4; ++j) d[j] = __umul24((word >> j) & 0x00010001u, 0xffffu);
+  return uint4{d[0], d[1], d[2], d[3]};
 }
 
-// Resident inference: one cell at a time per workgroup (512 threads), its activations
-// [n_pad][kHP] and its mesh's neighbour lists in LDS.  The encoder computes each row's
-// features from x_n, v_n, F_ext and the cell's frame as it forms its operand.
-template <typename Real, int RR>
-__global__ void __launch_bounds__(kInfBlock) net_infer_kernel(NetFwdArgs<Real> A, int RL) {
+// First feature of a lane's result tile c, and of its eight consecutive ones of 32-step s.
+__device__ inline int tile_feature(int c, int kq) { return 32 * (c >> 1) + 8 * kq + 4 * (c & 1); }
+
+// h^T operands (result tiles c) of the 32-node k step starting at row `row0`.
+__device__ inline void ld_nodes_t(const uint16_t* H, int row0, int l16, int kq, bf16x8 (&a)[4]) {
+  const uint16_t* p = H + (row0 + 8 * kq + (l16 >> 2)) * kHP + 8 * (l16 & 3);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int o = 32 * (c >> 1) + 4 * (c & 1);
+    a[c] = join8(ld_tr(p + o), ld_tr(p + o + 4 * kHP));
+  }
+}
+
+// One layer's [W_s | W_n] operands and biases, copied to LDS by the whole workgroup with
+// loads that bypass the registers.
+constexpr int kLayerOps = 16 * 512 + 2 * kNetH;    // in BF16 slots; the biases are FP32
+template <int NW>
+__device__ inline void stage_weights(const NetWeights& W, int l, uint16_t* dst) {
+  const uint16_t* src = W.WlA + (size_t)l * 16 * 512;
+  const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6), lane = tid() & 63;
+#pragma unroll
+  for (int q = 0; q < 16 / NW; ++q) {
+    const int f = wave + NW * q;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + f * 512 + lane * 8),
+                                     (__attribute__((address_space(3))) void*)(dst + f * 512), 16, 0, 0);
+  }
+  if (wave == 0)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(W.theta + W.lay.b(l) + lane),
+                                     (__attribute__((address_space(3))) void*)(dst + 16 * 512), 4, 0, 0);
+}
+__device__ inline void wait_staged() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
+
+// NW waves of up to RR row blocks each (n_pad <= 16 NW RR); a wave past the last one repeats
+// it without storing, so that the rounds are free of branches.  TRAIN keeps what the backward
+// pass reads: per layer the activations, the neighbour means and the signs of the
+// pre-activations, and the features, formed in FP64.
+template <typename Real, int NW, int RR, bool TRAIN>
+__global__ void __launch_bounds__(NW * 64, 2) net_resident_kernel(NetFwdArgs<Real> A) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int np_max = A.S.n_pad_max;
+  typedef typename std::conditional<TRAIN, double, float>::type F;
+  constexpr int kPairs = kNetUnrollDeg / 2;
+  const int zero_row = A.S.n_pad_max;          // a row of zeros: where a neighbour list has ended
   uint16_t* H = reinterpret_cast<uint16_t*>(lds);
-  uint16_t* nbl = H + (size_t)np_max * kHP;
-  uint8_t* degl = reinterpret_cast<uint8_t*>(nbl + (size_t)A.nb_deg_max * np_max);
-  uint32_t* Ob = reinterpret_cast<uint32_t*>(lds + infer_lds_base(np_max, A.nb_deg_max));
-  const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
+  // two layers' operands of [W_s | W_n]: a wave's copy comes from here, the next layer's is
+  // on its way meanwhile
+  uint16_t* Wb = H + (zero_row + 1) * kHP;
+  const int lane = tid() & 63, l16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
   const NetLayout L = A.W.lay;
-  int staged = -1;
+  const size_t plane = (size_t)A.S.n_pad_max * kNetH;
+  // picks a result tile's features from a 32-feature operand (even and odd tiles)
+  bf16x8 pick[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pick[t][e] = (__bf16)(kq == (l16 >> 2) && e == 4 * t + (l16 & 3) ? 1.f : 0.f);
+  if (tid() < kHP) H[zero_row * kHP + tid()] = 0;
+  // of this wave's rows, while the mesh stays the same: the vertex, the inverse degree and the
+  // first kNetUnrollDeg neighbours
+  int mesh = -1, vert[RR];
+  float inv[RR];
+  uint32_t nbr[RR][kPairs];
   for (int k = blockIdx.x; k < A.n_cells; k += gridDim.x) {
     const int cell = A.cells ? A.cells[k] : k;
     const int mi = A.cell_mesh[cell];
     const NetMeshDev& M = A.meshes[mi];
-    const int n = M.n, np = M.n_pad, nrb = np >> 4;
-    const int64_t voff = A.cell_voff[cell];
-    __syncthreads();                                       // the previous cell's decoder is done with H
-    if (mi != staged) {                                    // neighbour lists of this mesh type
-      for (int e = tid(); e < M.nb_deg * np; e += kInfBlock) nbl[e] = (uint16_t)M.nb_ell[e];
-      for (int i = tid(); i < np; i += kInfBlock) degl[i] = (uint8_t)(i < n ? M.nb_ptr[i + 1] - M.nb_ptr[i] : 0);
-      staged = mi;
-    }
-    const double* fr = A.cframe + (size_t)k * kNetFrame;
-    // ---- encoder: features of row l16 (lanes kq = 0, 1 hold features 0-7, 8-11) --------
-    {
-      bf16x8 be[4];
-      float bias_e[4];
+    const int n = M.n, np = M.n_pad, nrb = np >> 4, pairs = (M.nb_deg + 1) >> 1;
+    if (mi != mesh) {
+      mesh = mi;
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        be[cb] = ld8(A.W.We + (size_t)(cb * 16 + l16) * kNetFeatPad + 8 * kq);
-        bias_e[cb] = A.W.theta[L.off_be + cb * 16 + l16];
-      }
-      float R[9];
+      for (int r = 0; r < RR; ++r) {
+        const int row = min(wave + NW * r, nrb - 1) * 16 + l16;
+        vert[r] = row < n ? M.perm[row] : 0;
+        inv[r] = M.ideg[row];
 #pragma unroll
-      for (int q = 0; q < 9; ++q) R[q] = (float)fr[q];
-      const double s = fr[9];
-      const float hs = (float)(A.h / s), h2s = (float)(A.h * A.h / s), iq = (float)(1.0 / A.W.shape_scale);
-      const float irho = (float)M.inv_rho;
-      for (int rb = wave; rb < nrb; rb += kInfWaves) {
-        const int row = rb * 16 + l16;
-        float fv[kNetFeat];
-#pragma unroll
-        for (int q = 0; q < kNetFeat; ++q) fv[q] = 0.f;
-        if (row < n && kq < 2) {
-          const Real* xr = A.x + 3 * (voff + row);
-          const Real* vr = A.v + 3 * (voff + row);
-          const Real* fq = A.f + 3 * (voff + row);
-          const double m = M.mass[row];
-          float d[3], dv[3], df[3], Xa[3];
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            d[c] = (float)((double)xr[c] - fr[10 + c]);
-            dv[c] = (float)((double)vr[c] - fr[13 + c]);
-            df[c] = (float)((double)fq[c] - m * fr[16 + c]);
-            Xa[c] = (float)M.Xc[3 * row + c];
-          }
-          const float im = (float)(1.0 / m);
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            float rd = 0.f, rv = 0.f, rf = 0.f;            // (R^T w)_a = sum_b R[b][a] w_b
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-              rd += R[3 * b + a] * d[b];
-              rv += R[3 * b + a] * dv[b];
-              rf += R[3 * b + a] * df[b];
-            }
-            fv[a] = (rd - Xa[a]) * iq;
-            fv[3 + a] = rv * hs;
-            fv[6 + a] = rf * h2s * im;
-            fv[9 + a] = Xa[a] * irho;
-          }
+        for (int q = 0; q < kPairs; ++q) {
+          const uint32_t w = q < pairs ? M.nbp[q * np + row] : 0xffffffffu;
+          const uint32_t a = w & 0xffffu, b = w >> 16;
+          nbr[r][q] = (a == 0xffffu ? zero_row : a) | (b == 0xffffu ? zero_row : b) << 16;
         }
-        bf16x8 aq;
+      }
+    }
+    const int64_t voff = A.cell_voff[cell];
+    const double* fr = A.cframe + (size_t)k * kNetFrame;
+    uint16_t* Hs = TRAIN ? A.S.H + (size_t)k * (L.layers + 1) * plane : nullptr;
+    uint16_t* As = TRAIN ? A.S.Am + (size_t)k * L.layers * plane : nullptr;
+    uint16_t* Ms = TRAIN ? A.S.mask + (size_t)k * (L.layers + 1) * (plane / 16) : nullptr;
+    uint2 out[RR][4];                          // new activations of this wave's rows, BF16
+    // ---- encoder: lane group kq forms features 3 kq .. + 2 of its row -----------------
+    {
+      double cen[3];
+      F R[9];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) aq[e] = (__bf16)(kq == 0 ? fv[e] : (kq == 1 && e < 4 ? fv[8 + e] : 0.f));
+      for (int c = 0; c < 3; ++c) cen[c] = kq == 0 ? fr[10 + c] : (kq == 1 ? fr[13 + c] : fr[16 + c]);
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          const floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, be[cb], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      for (int q = 0; q < 9; ++q) R[q] = (F)fr[q];
+      const double s = fr[9];
+      const F scl = kq == 0 ? (F)(1.0 / A.W.shape_scale)
+                            : (kq == 1 ? (F)(A.h / s) : (kq == 2 ? (F)(A.h * A.h / s) : (F)M.inv_rho));
+      const Real* src = kq == 0 ? A.x : (kq == 1 ? A.v : A.f);
+      Real raw[RR][3];                         // every row is requested first
+#pragma unroll
+      for (int r = 0; r < RR; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) raw[r][c] = src[3 * (voff + vert[r]) + c];
+      stage_weights<NW>(A.W, 0, Wb);
+      bf16x8 we[4];
+      float4 bias[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        we[c] = ld8(A.W.WeA + c * 512 + lane * 8);
+        bias[c] = *reinterpret_cast<const float4*>(A.W.theta + L.off_be + tile_feature(c, kq));
+      }
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        if (NW * r >= nrb) continue;
+        const int rb = min(wave + NW * r, nrb - 1), row = rb * 16 + l16;
+        const bool own = wave + NW * r < nrb, tail = rb * 16 + 16 > n;   // uniform
+        __builtin_amdgcn_sched_barrier(0);     // one row block's registers at a time
+        // (R^T x - X) / shape, R^T v h / s, R^T f h^2 / (s m) or X / rho: one lane group each
+        F w[3], Xr[3];
+        float fv[3];
+        const double m = M.rest[4 * row + 3];
+        float im = 0.f;
+        if constexpr (TRAIN) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) Xr[a] = M.rest[4 * row + a];
+        } else {
+          const float4 q = *reinterpret_cast<const float4*>(M.restf + 4 * row);
+          Xr[0] = q.x, Xr[1] = q.y, Xr[2] = q.z, im = q.w;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) w[c] = (F)fma(kq == 2 ? -m : -1.0, cen[c], (double)raw[r][c]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const F Xa = Xr[a];
+          const F t = fma(R[6 + a], w[2], fma(R[3 + a], w[1], R[a] * w[0]));     // (R^T w)_a
+          F g = (kq == 3 ? Xa : t) - (kq == 0 ? Xa : F(0));
+          g *= scl;
+          if constexpr (TRAIN) g /= kq == 2 ? m : 1.0;
+          else g *= kq == 2 ? im : 1.f;
+          fv[a] = (float)g;
+          if (tail) fv[a] = row < n ? fv[a] : 0.f;
+        }
+        // features 0-7 to lane group 0, 8-11 to group 1: the operand's k slots
+        const uint32_t p0 = pack2(fv[0], fv[1]), p1 = pack2(fv[2], 0.f);
+        const uint32_t q0 = __shfl(p0, lane + 16, 64), q1 = __shfl(p1, lane + 16, 64);
+        const uint32_t r0 = __shfl(p0, lane + 32, 64), r1 = __shfl(p1, lane + 32, 64);
+        uint4 fw = {0u, 0u, 0u, 0u};
+        if (kq == 0) fw = uint4{p0, p1 | q0 << 16, q0 >> 16 | q1 << 16, r0};
+        if (kq == 1) fw = uint4{q1 | r0 << 16, r0 >> 16 | r1 << 16, 0u, 0u};
+        if (TRAIN && own) *reinterpret_cast<uint4*>(A.S.feat + ((size_t)k * A.S.n_pad_max + row) * kNetFeatPad + 8 * kq) = fw;
+        uint32_t bits = 0;
+        uint2 o[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(we[c], __builtin_bit_cast(bf16x8, fw),
+                                                                      floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          float z[4] = {acc[0] + bias[c].x, acc[1] + bias[c].y, acc[2] + bias[c].z, acc[3] + bias[c].w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int r2 = rb * 16 + 4 * kq + i;
-            const float z = r2 < n ? acc[i] + bias_e[cb] : 0.f;
-            H[(size_t)r2 * kHP + cb * 16 + l16] = f2bf(fmaxf(z, 0.f));
+            if (tail) z[i] = row < n ? z[i] : 0.f;
+            if (TRAIN) bits |= z[i] > 0.f ? 1u << (4 * c + i) : 0u;
+            z[i] = fmaxf(z[i], 0.f);
+          }
+          o[c] = uint2{pack2(z[0], z[1]), pack2(z[2], z[3])};
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          if (own) stw(H + row * kHP + 32 * s2 + 8 * kq, o[2 * s2], o[2 * s2 + 1]);
+          if (TRAIN && own) stw(Hs + (size_t)row * kNetH + 32 * s2 + 8 * kq, o[2 * s2], o[2 * s2 + 1]);
+        }
+        if (TRAIN && own) Ms[(size_t)rb * 64 + lane] = (uint16_t)bits;
+      }
+    }
+    wait_staged();
+    lds_barrier();
+    // ---- message-passing layers ---------------------------------------------------------
+    for (int l = 0; l < L.layers; ++l) {
+      bf16x8 wf[4][4];                         // [k step: W_s 0, 1, W_n 0, 1][output tile]
+      const uint16_t* Wl = Wb + (l & 1) * kLayerOps + lane * 8;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) wf[s][c] = ld8(Wl + (c * 4 + s) * 512);
+      if (l + 1 < L.layers) stage_weights<NW>(A.W, l + 1, Wb + ((l + 1) & 1) * kLayerOps);
+      const float* bias_l = reinterpret_cast<const float*>(Wb + (l & 1) * kLayerOps + 16 * 512) + 8 * kq;
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        if (NW * r >= nrb) continue;
+        const int rb = min(wave + NW * r, nrb - 1), row = rb * 16 + l16;
+        const bool own = wave + NW * r < nrb, tail = rb * 16 + 16 > n;
+        __builtin_amdgcn_sched_barrier(0);     // one row block's registers at a time
+        floatx4 ag[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ag[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto add = [&](int j) {
+          const bf16x8 h0 = ld8(H + j * kHP + 8 * kq), h1 = ld8(H + j * kHP + 32 + 8 * kq);
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            ag[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick[c & 1], c < 2 ? h0 : h1, ag[c], 0, 0, 0);
+        };
+#pragma unroll
+        for (int q = 0; q < kPairs; ++q) {
+          add((int)(nbr[r][q] & 0xffffu));
+          add((int)(nbr[r][q] >> 16));
+        }
+        for (int q = kPairs; q < pairs; ++q) {               // vertices of higher degree
+          const uint32_t w = M.nbp[q * np + row];
+          add((w & 0xffffu) == 0xffffu ? zero_row : (int)(w & 0xffffu));
+          add((w >> 16) == 0xffffu ? zero_row : (int)(w >> 16));
+        }
+        uint4 h[2], m[2];
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          h[s2] = ldw(H + row * kHP + 32 * s2 + 8 * kq);
+          const floatx4 u = ag[2 * s2] * inv[r], v = ag[2 * s2 + 1] * inv[r];
+          m[s2] = uint4{pack2(u[0], u[1]), pack2(u[2], u[3]), pack2(v[0], v[1]), pack2(v[2], v[3])};
+          if (TRAIN && own) *reinterpret_cast<uint4*>(As + (size_t)l * plane + (size_t)row * kNetH + 32 * s2 + 8 * kq) = m[s2];
+        }
+        const uint32_t hw[8] = {h[0].x, h[0].y, h[0].z, h[0].w, h[1].x, h[1].y, h[1].z, h[1].w};
+        const bf16x8 op[4] = {__builtin_bit_cast(bf16x8, h[0]), __builtin_bit_cast(bf16x8, h[1]),
+                              __builtin_bit_cast(bf16x8, m[0]), __builtin_bit_cast(bf16x8, m[1])};
+        uint32_t bits = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][c], op[s], acc, 0, 0, 0);
+          const float4 bv = *reinterpret_cast<const float4*>(bias_l + 32 * (c >> 1) + 4 * (c & 1));
+          const float z[4] = {acc[0] + bv.x, acc[1] + bv.y, acc[2] + bv.z, acc[3] + bv.w};
+          const float ho[4] = {half_lo(hw[2 * c]), half_hi(hw[2 * c]), half_lo(hw[2 * c + 1]), half_hi(hw[2 * c + 1])};
+          float hn[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            hn[i] = ho[i] + fmaxf(z[i], 0.f);
+            if (tail) hn[i] = row < n ? hn[i] : 0.f;
+            if (TRAIN) bits |= z[i] > 0.f ? 1u << (4 * c + i) : 0u;
+          }
+          out[r][c] = uint2{pack2(hn[0], hn[1]), pack2(hn[2], hn[3])};
+        }
+        if (TRAIN && own) {
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2)
+            stw(Hs + (size_t)(l + 1) * plane + (size_t)row * kNetH + 32 * s2 + 8 * kq, out[r][2 * s2], out[r][2 * s2 + 1]);
+          Ms[(size_t)(l + 1) * (plane / 16) + (size_t)rb * 64 + lane] = (uint16_t)bits;
+        }
+      }
+      lds_barrier();                           // every wave is done reading the old activations
+      if (l + 1 == L.layers) break;            // the decoder takes the last ones from registers
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        if (wave + NW * r >= nrb) continue;
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+          stw(H + ((wave + NW * r) * 16 + l16) * kHP + 32 * s2 + 8 * kq, out[r][2 * s2], out[r][2 * s2 + 1]);
+      }
+      wait_staged();
+      lds_barrier();
+    }
+    // ---- decoder: o = W_d h + b_d; lanes kq = 0 hold the three outputs of node l16 ------
+    {
+      const bf16x8 wd0 = ld8(A.W.WdA + lane * 8), wd1 = ld8(A.W.WdA + 512 + lane * 8);
+      const float* bd = A.W.theta + L.off_bd;
+      double R[9];
+#pragma unroll
+      for (int q = 0; q < 9; ++q) R[q] = fr[q];
+      const double s = fr[9];
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        if (wave + NW * r >= nrb) continue;
+        floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wd0, join8(out[r][0], out[r][1]),
+                                                              floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wd1, join8(out[r][2], out[r][3]), acc, 0, 0, 0);
+        if (kq == 0 && (wave + NW * r) * 16 + l16 < n) {
+          const int v = vert[r];
+          const float o[3] = {acc[0] + bd[0], acc[1] + bd[1], acc[2] + bd[2]};
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (A.delta) {
+              const double da = s * (R[3 * c] * o[0] + R[3 * c + 1] * o[1] + R[3 * c + 2] * o[2]);
+              A.delta[3 * (voff + v) + c] = (Real)da;
+            }
+            if (TRAIN) A.S.out[((size_t)k * A.S.n_pad_max + v) * 3 + c] = o[c];
           }
         }
       }
     }
-    __syncthreads();
-    for (int l = 0; l < L.layers; ++l) infer_layer<RR>(A.W, l, n, np, M.nb_deg, H, nbl, degl, Ob, RL);
-    // ---- decoder (the frame's R and s, read from memory) --------------------------------
-    double fr2[10];
-#pragma unroll
-    for (int q = 0; q < 10; ++q) fr2[q] = fr[q];
-    decoder_rows<Real, kInfWaves>(A, k, voff, n, np, H, kHP, fr2);
   }
 }
 
@@ -799,7 +833,7 @@ __global__ void __launch_bounds__(kBlock) net_loss_kernel(NetLossArgs<Real> A) {
     const NetMeshDev& M = A.meshes[A.cell_mesh[cell]];
     const int n = M.n, np = M.n_pad;
     const int64_t voff = A.cell_voff[cell];
-    const double* fr = A.S.frame + (size_t)k * 12;
+    const double* fr = A.S.frame + (size_t)k * kNetFrame;
     double R[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) R[q] = fr[q];
@@ -1001,6 +1035,342 @@ __global__ void __launch_bounds__(kBlock) net_backward_kernel(NetBwdArgs A) {
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Backward with the cell resident (meshes of n_pad <= 768), in the layout of
+// net_resident_kernel.  net_chain_kernel carries one cell's dLoss/dh through the layers in
+// registers (FP32) and leaves each layer's dz (BF16) in memory; net_wgrad_kernel forms the
+// weight gradients, sums over every node of the minibatch, from the stored planes.
+//
+// The chain is bound by one cell's latency (a minibatch of 256 cells has one workgroup per
+// CU): 114 us for 642 vertices, 4 layers; with the weight gradients (82 us), their sum (9) and
+// the forward (106) a minibatch takes 350 us, against 5.8 ms when one workgroup of four waves
+// went through a cell's layers in memory, sums over nodes running serially in 64 threads.  The neighbour term (mean_N)^T (W_n^T dz) = W_n^T sum_{i in N(j)} dz_i / deg_i is
+// formed with the sum first: dz_i and 1 / deg_i, split into three BF16 parts, in one
+// contraction over the window's nodes, then the FP32 sums, split likewise, against W_n; three
+// parts hold 24 bits, so both keep FP32 accuracy.
+// ---------------------------------------------------------------------------------
+__device__ inline float row16_sum(float x) {                // over the 16 lanes of a row
+  auto dpp = [](float y, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  x += dpp(x, std::integral_constant<int, 0xB1>{});         // quad_perm [1,0,3,2]
+  x += dpp(x, std::integral_constant<int, 0x4E>{});         // quad_perm [2,3,0,1]
+  x += dpp(x, std::integral_constant<int, 0x141>{});        // row_half_mirror
+  x += dpp(x, std::integral_constant<int, 0x140>{});        // row_mirror
+  return x;
+}
+
+template <int NW, int RR>
+__global__ void __launch_bounds__(NW * 64, 2) net_chain_kernel(NetChainArgs A) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int np_max = A.S.n_pad_max;
+  uint16_t* D = reinterpret_cast<uint16_t*>(lds);            // dz of the layer, [n_pad][kHP]
+  uint16_t* wdeg = D + (size_t)np_max * kHP;                 // [3][n_pad] parts of 1 / degree
+  float* red = reinterpret_cast<float*>(wdeg + (size_t)3 * np_max);    // [NW][256]
+  const int lane = tid() & 63, l16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
+  const NetLayout L = A.W.lay;
+  const size_t plane = (size_t)np_max * kNetH;
+  for (int k = blockIdx.x; k < A.n_cells; k += gridDim.x) {
+    const int cell = A.cells ? A.cells[k] : k;
+    const NetMeshDev& M = A.meshes[A.cell_mesh[cell]];
+    const int n = M.n, np = M.n_pad, nblk = np >> 5;
+    const uint16_t* Ms = A.S.mask + (size_t)k * (L.layers + 1) * (plane / 16);
+    uint16_t* Zs = A.S.Z + (size_t)k * (L.layers + 1) * plane;          // receives dz
+    float* part = A.cellpart + (size_t)k * net_cell_part(L.layers);
+    for (int e = tid(); e < 3 * np; e += NW * 64) wdeg[e] = M.wdeg[e];
+    // ---- decoder: dh = W_d^T dO, and the gradients of W_d and b_d ---------------------
+    floatx4 dh[RR][2][4];
+    {
+      const uint16_t* HL = A.S.H + ((size_t)k * (L.layers + 1) + L.layers) * plane;
+      float gw[3][16], gb[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) gw[c][q] = 0.f;
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const int blk = wave + NW * r;
+        if (blk >= nblk) break;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int row = blk * 32 + 16 * b + l16;
+          const float* o = A.dout + ((size_t)k * np_max + (row < n ? M.perm[row] : row)) * 3;   // zero on padding
+          const float d0 = o[0], d1 = o[1], d2 = o[2];
+          gb[0] += d0;
+          gb[1] += d1;
+          gb[2] += d2;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const int ft = tile_feature(c, kq);
+            const uint2 h = ld4(HL + (size_t)row * kNetH + ft);
+            const uint2 q0 = ld4(A.W.Wd + ft), q1 = ld4(A.W.Wd + kNetH + ft), q2 = ld4(A.W.Wd + 2 * kNetH + ft);
+            const float hv[4] = {half_lo(h.x), half_hi(h.x), half_lo(h.y), half_hi(h.y)};
+            const float v0[4] = {half_lo(q0.x), half_hi(q0.x), half_lo(q0.y), half_hi(q0.y)};
+            const float v1[4] = {half_lo(q1.x), half_hi(q1.x), half_lo(q1.y), half_hi(q1.y)};
+            const float v2[4] = {half_lo(q2.x), half_hi(q2.x), half_lo(q2.y), half_hi(q2.y)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              gw[0][4 * c + i] += d0 * hv[i];
+              gw[1][4 * c + i] += d1 * hv[i];
+              gw[2][4 * c + i] += d2 * hv[i];
+              dh[r][b][c][i] = d0 * v0[i] + d1 * v1[i] + d2 * v2[i];
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const float t = row16_sum(gw[c][q]);
+          if (l16 == 0) red[wave * 256 + c * kNetH + tile_feature(q >> 2, kq) + (q & 3)] = t;
+        }
+        const float t = row16_sum(gb[c]);
+        if (lane == 0) red[wave * 256 + 3 * kNetH + c] = t;
+      }
+      lds_barrier();
+      if (tid() < 3 * kNetH + 3) {
+        float t = 0.f;
+        for (int w = 0; w < NW; ++w) t += red[w * 256 + tid()];
+        part[(L.layers + 1) * kNetH + tid()] = t;
+      }
+      lds_barrier();
+    }
+    for (int l = L.layers - 1; l >= -1; --l) {               // l = -1: the encoder
+      // dz = dh * [z > 0] to LDS and memory, and the bias gradient
+      float bs[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) bs[q] = 0.f;
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const int blk = wave + NW * r;
+        if (blk >= nblk) break;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int row = blk * 32 + 16 * b + l16;
+          const uint32_t bits = Ms[(size_t)(l + 1) * (plane / 16) + (size_t)(blk * 2 + b) * 64 + lane];
+          uint2 w[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            float dz[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              dz[i] = (bits >> (4 * c + i)) & 1u ? dh[r][b][c][i] : 0.f;
+              bs[4 * c + i] += dz[i];
+            }
+            w[c] = uint2{pack2(dz[0], dz[1]), pack2(dz[2], dz[3])};
+          }
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) {
+            stw(D + row * kHP + 32 * s2 + 8 * kq, w[2 * s2], w[2 * s2 + 1]);
+            stw(Zs + (size_t)(l + 1) * plane + (size_t)row * kNetH + 32 * s2 + 8 * kq, w[2 * s2], w[2 * s2 + 1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const float t = row16_sum(bs[q]);
+        if (l16 == 0) red[wave * 256 + tile_feature(q >> 2, kq) + (q & 3)] = t;
+      }
+      lds_barrier();
+      if (tid() < kNetH) {
+        float t = 0.f;
+        for (int w = 0; w < NW; ++w) t += red[w * 256 + tid()];
+        part[(l + 1) * kNetH + tid()] = t;
+      }
+      if (l < 0) break;
+      // dh_prev = dh + W_s^T dz + W_n^T sum_{i in N} dz_i / deg_i
+      bf16x8 ws[2][4], wn[2][4];
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          ws[s][c] = ld8(A.W.WsTA + (size_t)((l * 4 + c) * 2 + s) * 512 + lane * 8);
+          wn[s][c] = ld8(A.W.WnTA + (size_t)((l * 4 + c) * 2 + s) * 512 + lane * 8);
+        }
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const int blk = wave + NW * r;
+        if (blk >= nblk) break;
+        __builtin_amdgcn_sched_barrier(0);     // one block's registers at a time
+        const int lo = M.blk[2 * blk], ks = M.blk[2 * blk + 1];
+        const uint32_t* adj = M.adj + (size_t)blk * M.adj_dw * 128 + lane;
+        floatx4 ag[2][4];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) ag[b][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        uint32_t w0 = 0, w1 = 0;
+#pragma unroll 1
+        for (int s = 0; s < ks; ++s) {
+          const int at = lo + 32 * s;
+          bf16x8 a[4];
+          ld_nodes_t(D, at, l16, kq, a);
+          if ((s & 3) == 0) {
+            w0 = adj[(size_t)(s >> 2) * 128];
+            w1 = adj[(size_t)(s >> 2) * 128 + 64];
+          }
+          const uint4 m0 = adj_mask(w0), m1 = adj_mask(w1);
+          w0 >>= 4;
+          w1 >>= 4;
+#pragma unroll
+          for (int p = 0; p < 3; ++p) {
+            const uint4 w = *reinterpret_cast<const uint4*>(wdeg + (size_t)p * np + at + 8 * kq);
+            const bf16x8 b0 = __builtin_bit_cast(bf16x8, uint4{m0.x & w.x, m0.y & w.y, m0.z & w.z, m0.w & w.w});
+            const bf16x8 b1 = __builtin_bit_cast(bf16x8, uint4{m1.x & w.x, m1.y & w.y, m1.z & w.z, m1.w & w.w});
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              ag[0][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b0, ag[0][c], 0, 0, 0);
+              ag[1][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b1, ag[1][c], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int row = blk * 32 + 16 * b + l16;
+          const bf16x8 z0 = ld8(D + row * kHP + 8 * kq), z1 = ld8(D + row * kHP + 32 + 8 * kq);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            dh[r][b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws[0][c], z0, dh[r][b][c], 0, 0, 0);
+            dh[r][b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws[1][c], z1, dh[r][b][c], 0, 0, 0);
+          }
+#pragma unroll
+          for (int p = 0; p < 3; ++p) {                      // the sums' leading, middle and last bits
+            uint2 t[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              t[c] = uint2{pack2(ag[b][c][0], ag[b][c][1]), pack2(ag[b][c][2], ag[b][c][3])};
+              ag[b][c][0] -= half_lo(t[c].x);
+              ag[b][c][1] -= half_hi(t[c].x);
+              ag[b][c][2] -= half_lo(t[c].y);
+              ag[b][c][3] -= half_hi(t[c].y);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              dh[r][b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wn[0][c], join8(t[0], t[1]), dh[r][b][c], 0, 0, 0);
+              dh[r][b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wn[1][c], join8(t[2], t[3]), dh[r][b][c], 0, 0, 0);
+            }
+          }
+        }
+      }
+      lds_barrier();                                         // every wave is done reading D
+    }
+    lds_barrier();                                           // and red, before the next cell
+  }
+}
+
+// Weight gradients dz^T h and dz^T mean (dz^T features for the encoder, plane 0): contractions
+// over the nodes of the cells k = blockIdx.x, + gridDim.x, ..., each wave taking every fourth
+// 32-node chunk.  A lane loads eight consecutive nodes x four columns (whole 128-byte rows
+// per 16 lanes) and picks its operands' node-contiguous halves with byte permutes, so a
+// tile's rows (columns) are 4 (row) + cc; nothing is transposed through LDS.  The four waves'
+// sums are added in LDS in a fixed order and written to this workgroup's slot.
+// Bound: memory, 385 MB for 256 cells of 642 vertices in 82 us (the copy rate).  Both products
+// of a layer in one workgroup read dz once (300 MB) but leave two waves per SIMD: 91 us.
+constexpr int kWgPitch = 68;
+__global__ void __launch_bounds__(256, 4) net_wgrad_kernel(NetChainArgs A) {
+  __shared__ __align__(16) float acc_s[kNetH * kWgPitch];
+  const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
+  const NetLayout L = A.W.lay;
+  // blockIdx.y: 0 the encoder, 2 l + 1 and 2 l + 2 the two products of layer l
+  const int np_max = A.S.n_pad_max, pl = (blockIdx.y + 1) >> 1, mean = pl > 0 && (blockIdx.y & 1) == 0;
+  const size_t plane = (size_t)np_max * kNetH;
+  const int pitch = pl == 0 ? kNetFeatPad : kNetH;
+  floatx4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto operand = [](const uint2 (&v)[8], int cc) {
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t a = cc < 2 ? v[2 * j].x : v[2 * j].y, b = cc < 2 ? v[2 * j + 1].x : v[2 * j + 1].y;
+      d[j] = __builtin_amdgcn_perm(b, a, (cc & 1) ? 0x07060302u : 0x05040100u);
+    }
+    return __builtin_bit_cast(bf16x8, uint4{d[0], d[1], d[2], d[3]});
+  };
+  for (int k = blockIdx.x; k < A.n_cells; k += gridDim.x) {
+    const int cell = A.cells ? A.cells[k] : k;
+    const int nch = A.meshes[A.cell_mesh[cell]].n_pad >> 5;
+    const uint16_t* Z = A.S.Z + ((size_t)k * (L.layers + 1) + pl) * plane + 4 * l16;
+    const uint16_t* B = pl == 0 ? A.S.feat + (size_t)k * np_max * kNetFeatPad + 4 * (l16 & 7)
+                                : (mean ? A.S.Am + ((size_t)k * L.layers + pl - 1) * plane
+                                        : A.S.H + ((size_t)k * (L.layers + 1) + pl - 1) * plane) + 4 * l16;
+    for (int c = wave; c < nch; c += 4) {
+      const int row = c * 32 + 8 * kq;
+      uint2 vz[8], vb[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        vz[j] = ld4(Z + (row + j) * kNetH);
+        vb[j] = ld4(B + (row + j) * pitch);
+      }
+      bf16x8 za[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) za[a] = operand(vz, a);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const bf16x8 o = operand(vb, b);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(za[a], o, acc[a][b], 0, 0, 0);
+      }
+    }
+  }
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float* p = acc_s + (4 * (4 * kq + i) + a) * kWgPitch + 4 * l16 + b;
+            *p = w == 0 ? acc[a][b][i] : *p + acc[a][b][i];
+          }
+    }
+    __syncthreads();
+  }
+  float* part = A.partial + (size_t)blockIdx.x * L.count;
+  if (pl == 0) {
+    for (int e = tid(); e < kNetH * kNetFeat; e += 256) part[L.off_We + e] = acc_s[e / kNetFeat * kWgPitch + e % kNetFeat];
+  } else {
+    float* o = part + (mean ? L.Wn(pl - 1) : L.Ws(pl - 1));
+    for (int e = tid(); e < kNetH * kNetH; e += 256) o[e] = acc_s[e / kNetH * kWgPitch + e % kNetH];
+  }
+}
+
+// The minibatch gradient: weights summed over the slots of net_wgrad_kernel, biases and the
+// decoder over the cells' sums of net_chain_kernel, in FP64, four strided partial sums per
+// parameter added in a fixed order.
+__global__ void __launch_bounds__(256) net_gather_kernel(NetChainArgs A, int slots, float* grad) {
+  __shared__ double sh[4][64];
+  const NetLayout L = A.W.lay;
+  const int g = tid() >> 6;
+  const int64_t p = (int64_t)blockIdx.x * 64 + (tid() & 63);
+  double t = 0.0;
+  if (p < L.count) {
+    const int np_ = net_cell_part(L.layers);
+    int at = -1;                                             // index into a cell's sums
+    if (p >= L.off_Wd) at = (L.layers + 1) * kNetH + (int)(p - L.off_Wd);
+    else if (p >= L.off_be && p < L.off_Ws0) at = (int)(p - L.off_be);
+    else if (p >= L.off_Ws0) {
+      const int64_t l = (p - L.off_Ws0) / L.layer_stride, q = (p - L.off_Ws0) % L.layer_stride - 2 * kNetH * kNetH;
+      if (q >= 0) at = (int)((l + 1) * kNetH + q);
+    }
+    if (at >= 0) {
+#pragma unroll 8
+      for (int k = g; k < A.n_cells; k += 4) t += (double)A.cellpart[(size_t)k * np_ + at];
+    } else {
+#pragma unroll 8
+      for (int s = g; s < slots; s += 4) t += (double)A.partial[(size_t)s * L.count + p];
+    }
+  }
+  sh[g][tid() & 63] = t;
+  __syncthreads();
+  if (g == 0 && p < L.count) grad[p] = (float)((sh[0][tid()] + sh[1][tid()]) + (sh[2][tid()] + sh[3][tid()]));
+}
+
 __global__ void net_reduce_kernel(const float* __restrict__ partial, int grid, int64_t count, float* grad) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= count) return;
@@ -1021,26 +1391,38 @@ __global__ void net_adam_kernel(float* theta, float* m, float* v, const float* g
   theta[p] -= lr * (mn / c1) / (sqrtf(vn / c2) + eps);
 }
 
-// BF16 copies of the weight blocks in the layouts the kernels read.
-__global__ void net_pack_kernel(NetWeights w, uint16_t* We, uint16_t* Wl, uint16_t* WsT, uint16_t* WnT,
-                                uint16_t* Wd) {
+// BF16 copies of the weight blocks in the layouts the kernels read: by rows for the
+// any-size kernels, and as operands of the resident ones ([..][lane][8], row l16 of tile c
+// standing for feature tile_feature(c, l16 / 4) + l16 % 4, eight consecutive k per lane).
+__global__ void net_pack_kernel(NetWeights w, NetPackDst d) {
   const NetLayout L = w.lay;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t nWe = (int64_t)kNetH * kNetFeatPad, nL = (int64_t)L.layers * kNetH * kNetH;
+  const int le = (int)(e & 511), l16 = (le >> 3) & 15, kk = 8 * (le >> 7) + (le & 7);
+  auto row = [&](int c) { return tile_feature(c, l16 >> 2) + (l16 & 3); };
   if (e < nWe) {
     const int o = (int)(e / kNetFeatPad), c = (int)(e % kNetFeatPad);
-    We[e] = c < kNetFeat ? f2bf(w.theta[L.off_We + o * kNetFeat + c]) : (uint16_t)0;
+    d.We[e] = c < kNetFeat ? f2bf(w.theta[L.off_We + o * kNetFeat + c]) : (uint16_t)0;
+    d.WeA[e] = kk < kNetFeat ? f2bf(w.theta[L.off_We + row((int)(e >> 9)) * kNetFeat + kk]) : (uint16_t)0;
   }
   if (e < nL) {
     const int l = (int)(e / (kNetH * kNetH)), r = (int)(e % (kNetH * kNetH));
     const int o = r / kNetH, q = r % kNetH;
     const float ws = w.theta[L.Ws(l) + r], wn = w.theta[L.Wn(l) + r];
-    Wl[(size_t)l * kNetH * 2 * kNetH + (size_t)o * 2 * kNetH + q] = f2bf(ws);
-    Wl[(size_t)l * kNetH * 2 * kNetH + (size_t)o * 2 * kNetH + kNetH + q] = f2bf(wn);
-    WsT[(size_t)l * kNetH * kNetH + (size_t)q * kNetH + o] = f2bf(ws);
-    WnT[(size_t)l * kNetH * kNetH + (size_t)q * kNetH + o] = f2bf(wn);
+    d.Wl[(size_t)l * kNetH * 2 * kNetH + (size_t)o * 2 * kNetH + q] = f2bf(ws);
+    d.Wl[(size_t)l * kNetH * 2 * kNetH + (size_t)o * 2 * kNetH + kNetH + q] = f2bf(wn);
+    d.WsT[(size_t)l * kNetH * kNetH + (size_t)q * kNetH + o] = f2bf(ws);
+    d.WnT[(size_t)l * kNetH * kNetH + (size_t)q * kNetH + o] = f2bf(wn);
+    const int f = (int)(e >> 9) & 7, in = row(f >> 1), k = 32 * (f & 1) + kk;   // [l][input tile][k step]
+    d.WsTA[e] = f2bf(w.theta[L.Ws(l) + k * kNetH + in]);
+    d.WnTA[e] = f2bf(w.theta[L.Wn(l) + k * kNetH + in]);
   }
-  if (e < 3 * kNetH) Wd[e] = f2bf(w.theta[L.off_Wd + e]);
+  if (e < 2 * nL) {
+    const int l = (int)(e / (2 * kNetH * kNetH)), f = (int)(e >> 9) & 15, s = f & 3;
+    d.WlA[e] = f2bf(w.theta[(s < 2 ? L.Ws(l) : L.Wn(l)) + row(f >> 2) * kNetH + 32 * (s & 1) + kk]);
+  }
+  if (e < 3 * kNetH) d.Wd[e] = f2bf(w.theta[L.off_Wd + e]);
+  if (e < 1024) d.WdA[e] = l16 < 3 ? f2bf(w.theta[L.off_Wd + l16 * kNetH + 32 * (int)(e >> 9) + kk]) : (uint16_t)0;
 }
 
 __global__ void fill_zero_kernel(float* p, int64_t count) {
@@ -1052,60 +1434,62 @@ inline int blocks_for(int64_t count, int threads) { return (int)((count + thread
 
 }  // namespace
 
-size_t net_forward_lds_bytes(int n_pad, int nb_deg) {
-  const size_t b = kNetLdsHeader + (size_t)n_pad * (kHP + kNetFeatPad) * 2 + (size_t)nb_deg * n_pad * 2 +
-                   (size_t)n_pad;
-  return (b + 15) / 16 * 16 <= 160 * 1024 && nb_deg <= 255 ? (b + 15) / 16 * 16 : 0;
-}
-
 template <typename Real>
-hipError_t launch_net_forward(const NetFwdArgs<Real>& a, int grid, size_t lds_bytes, hipStream_t s) {
+hipError_t launch_net_forward(const NetFwdArgs<Real>& a, int grid, hipStream_t s) {
   (void)hipGetLastError();
-  if (lds_bytes > 0) {
-    if (lds_bytes < net_forward_lds_bytes(a.S.n_pad_max, a.nb_deg_max)) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&net_forward_lds_kernel<Real>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(net_forward_lds_kernel<Real>, dim3(grid), dim3(kNetLdsBlock), lds_bytes, s, a);
-  } else {
-    hipLaunchKernelGGL(net_forward_kernel<Real>, dim3(grid), dim3(kBlock), 0, s, a);
-  }
+  hipLaunchKernelGGL(net_forward_kernel<Real>, dim3(grid), dim3(kBlock), 0, s, a);
   return hipGetLastError();
 }
 
-namespace {
-int infer_rounds(int n_pad) { return (n_pad / 16 + kInfWaves - 1) / kInfWaves; }
-}  // namespace
+// Waves per workgroup of the resident kernels: four, and two workgroups per CU, while the LDS
+// holds two (the 18 row blocks of a 258-vertex mesh would leave eight waves a third round of
+// two), else eight with at most six row blocks each.
+static int resident_waves(int n_pad) { return n_pad <= 320 ? 4 : 8; }
 
-size_t net_infer_lds_bytes(int n_pad, int nb_deg) {
-  const int lds_rounds = std::max(0, infer_rounds(n_pad) - kInfMaxRegRounds);
-  const size_t r = infer_lds_base(n_pad, nb_deg) + (size_t)lds_rounds * kInfWaves * 512 * 4;
-  return r <= 160 * 1024 && nb_deg <= 255 && n_pad <= 65535 ? r : 0;
+size_t net_resident_lds_bytes(int n_pad) {
+  return n_pad <= 768 ? (size_t)(n_pad + 1) * kHP * 2 + 2 * kLayerOps * 2 : 0;
 }
+size_t net_chain_lds_bytes(int n_pad) {
+  if (n_pad > 768) return 0;     // three blocks per wave
+  return ((size_t)n_pad * (kHP + 3) * 2 + (size_t)resident_waves(n_pad) * 256 * 4 + 15) / 16 * 16;
+}
+int net_resident_per_cu(int n_pad) { return resident_waves(n_pad) == 4 ? 2 : 1; }
 
-template <typename Real, int RR>
-hipError_t launch_infer_rr(const NetFwdArgs<Real>& a, int grid, size_t lds, int RL, hipStream_t s) {
-  const void* fn = reinterpret_cast<const void*>(&net_infer_kernel<Real, RR>);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+template <typename K, typename... Args>
+static hipError_t launch_lds(K kernel, dim3 grid, int threads, size_t lds, hipStream_t s, Args... args) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((net_infer_kernel<Real, RR>), dim3(grid), dim3(kInfBlock), lds, s, a, RL);
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, args...);
   return hipGetLastError();
 }
 
 template <typename Real>
-hipError_t launch_net_infer(const NetFwdArgs<Real>& a, int grid, size_t lds_bytes, hipStream_t s) {
+hipError_t launch_net_resident(const NetFwdArgs<Real>& a, int grid, int train, hipStream_t s) {
   (void)hipGetLastError();
-  if (!a.cframe || a.n_cells < 1 || grid < 1) return hipErrorInvalidValue;
-  const size_t need = net_infer_lds_bytes(a.S.n_pad_max, a.nb_deg_max);
-  if (need == 0 || lds_bytes < need) return hipErrorInvalidValue;
+  const int np = a.S.n_pad_max;
+  const size_t lds = net_resident_lds_bytes(np);
+  if (!a.cframe || a.n_cells < 1 || grid < 1 || lds == 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(net_frame_kernel<Real>, dim3((a.n_cells + 3) / 4), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int rounds = infer_rounds(a.S.n_pad_max);
-  const int RL = std::max(0, rounds - kInfMaxRegRounds);   // rounds staged in LDS
-  if (rounds <= 1) return launch_infer_rr<Real, 1>(a, grid, lds_bytes, 0, s);
-  if (rounds == 2) return launch_infer_rr<Real, 2>(a, grid, lds_bytes, 0, s);
-  return launch_infer_rr<Real, kInfMaxRegRounds>(a, grid, lds_bytes, RL, s);
+  if (resident_waves(np) == 4)
+    return train ? launch_lds(net_resident_kernel<Real, 4, 5, true>, dim3(grid), 256, lds, s, a)
+                 : launch_lds(net_resident_kernel<Real, 4, 5, false>, dim3(grid), 256, lds, s, a);
+  return train ? launch_lds(net_resident_kernel<Real, 8, 6, true>, dim3(grid), 512, lds, s, a)
+               : launch_lds(net_resident_kernel<Real, 8, 6, false>, dim3(grid), 512, lds, s, a);
+}
+
+hipError_t launch_net_chain(const NetChainArgs& a, int grid, int slots, float* grad, hipStream_t s) {
+  (void)hipGetLastError();
+  const size_t lds = net_chain_lds_bytes(a.S.n_pad_max);
+  if (a.n_cells < 1 || grid < 1 || slots < 1 || slots > a.n_cells || lds == 0) return hipErrorInvalidValue;
+  hipError_t e = resident_waves(a.S.n_pad_max) == 4 ? launch_lds(net_chain_kernel<4, 3>, dim3(grid), 256, lds, s, a)
+                                                    : launch_lds(net_chain_kernel<8, 3>, dim3(grid), 512, lds, s, a);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(net_wgrad_kernel, dim3(slots, 2 * a.W.lay.layers + 1), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(net_gather_kernel, dim3(blocks_for(a.W.lay.count, 64)), dim3(256), 0, s, a, slots, grad);
+  return hipGetLastError();
 }
 
 template <typename Real>
@@ -1136,11 +1520,10 @@ hipError_t launch_net_adam(float* theta, float* m, float* v, const float* grad, 
   return hipGetLastError();
 }
 
-hipError_t launch_net_pack(const NetWeights& w, uint16_t* We, uint16_t* Wl, uint16_t* WsT, uint16_t* WnT,
-                           uint16_t* Wd, hipStream_t s) {
+hipError_t launch_net_pack(const NetWeights& w, const NetPackDst& d, hipStream_t s) {
   (void)hipGetLastError();
-  const int64_t n = std::max<int64_t>((int64_t)w.lay.layers * kNetH * kNetH, (int64_t)kNetH * kNetFeatPad);
-  hipLaunchKernelGGL(net_pack_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, We, Wl, WsT, WnT, Wd);
+  const int64_t n = std::max<int64_t>((int64_t)w.lay.layers * kNetH * 2 * kNetH, (int64_t)kNetH * kNetFeatPad);
+  hipLaunchKernelGGL(net_pack_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, d);
   return hipGetLastError();
 }
 
@@ -1151,10 +1534,10 @@ hipError_t launch_fill_zero(float* p, int64_t count, hipStream_t s) {
   return hipGetLastError();
 }
 
-template hipError_t launch_net_forward<float>(const NetFwdArgs<float>&, int, size_t, hipStream_t);
-template hipError_t launch_net_forward<double>(const NetFwdArgs<double>&, int, size_t, hipStream_t);
-template hipError_t launch_net_infer<float>(const NetFwdArgs<float>&, int, size_t, hipStream_t);
-template hipError_t launch_net_infer<double>(const NetFwdArgs<double>&, int, size_t, hipStream_t);
+template hipError_t launch_net_forward<float>(const NetFwdArgs<float>&, int, hipStream_t);
+template hipError_t launch_net_forward<double>(const NetFwdArgs<double>&, int, hipStream_t);
+template hipError_t launch_net_resident<float>(const NetFwdArgs<float>&, int, int, hipStream_t);
+template hipError_t launch_net_resident<double>(const NetFwdArgs<double>&, int, int, hipStream_t);
 template hipError_t launch_net_loss<float>(const NetLossArgs<float>&, hipStream_t);
 template hipError_t launch_net_loss<double>(const NetLossArgs<double>&, hipStream_t);
 
