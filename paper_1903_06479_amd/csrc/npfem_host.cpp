@@ -679,6 +679,10 @@ npfem_status upload_mesh(npfem_plan* p, MeshPlan& mp, const std::vector<double>&
   if ((s = p->buf.upload(nbe.data(), nbe.size(), &d.nb_ell))) return s;
   if ((s = p->buf.upload(nbwe.data(), nbwe.size(), &d.nbw_ell))) return s;
   if ((s = p->buf.upload(vce.data(), vce.size(), &d.vc_ell))) return s;
+  std::vector<unsigned> vcp(vce.size());
+  for (size_t k = 0; k < vce.size(); ++k)
+    vcp[k] = vce[k] < 0 ? (unsigned)(9 * m->nt) << 2 : (unsigned)(9 * (vce[k] / 3)) << 2 | (unsigned)(vce[k] % 3);
+  if ((s = p->buf.upload(vcp.data(), vcp.size(), &d.vc_pk))) return s;
   if ((s = p->buf.upload(va.data(), va.size(), &d.vor_area))) return s;
   if ((s = p->buf.upload(e0.data(), e0.size(), &d.ell0))) return s;
   if ((s = p->buf.upload(ms.data(), ms.size(), &d.mass))) return s;
@@ -1107,13 +1111,13 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
   const int slots = p->cu_count * per_cu;
   b->grid = p->prm.grid_blocks > 0 ? p->prm.grid_blocks : slots;
   b->grid = std::max(1, std::min(b->grid, b->n_tiles));
-  // b, u, grad, d, q, the history, and a trial gradient if some mesh keeps it out of LDS
+  // x_n, b, u, grad, d, q, the history, and a trial gradient if some mesh keeps it out of LDS
   bool any_global = false, any_xu_global = false;
   for (int mi = 0; mi < nm; ++mi) {
     if (!b->by_mesh[mi].empty() && !p->meshes[mi].vec_lds) any_global = true;
     if (!b->by_mesh[mi].empty() && !p->meshes[mi].xu_lds) any_xu_global = true;
   }
-  b->n_vec = 5 + 2 * m + (any_global ? 1 : 0);
+  b->n_vec = 6 + 2 * m + (any_global ? 1 : 0);
   // per slot: the tile's vectors, then (if some mesh keeps them out of LDS) the current
   // cell's x_n and trial u
   b->slot_stride = ((int64_t)b->n_vec * T + (any_xu_global ? 2 : 0)) * 3 * b->n_pad_max;

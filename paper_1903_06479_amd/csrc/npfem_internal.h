@@ -33,6 +33,7 @@ struct MeshDev {
   const int* nb_ell;           // [nb_deg][n_pad] neighbour of vertex i (i itself as padding)
   const Real* nbw_ell;         // [nb_deg][n_pad] its cotangent weight (0 as padding)
   const int* vc_ell;           // [vc_deg][n_pad] incident corner 3t + k (-1 as padding)
+  const unsigned* vc_pk;       // [vc_deg][n_pad] the same as 9 t << 2 | k (9 nt << 2 as padding)
   const Real* vor_area;        // [n] mixed Voronoi area A_i
   const Real* ell0;            // [n] |l0_i|
   const Real* mass;            // [n]

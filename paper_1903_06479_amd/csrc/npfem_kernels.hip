@@ -34,15 +34,16 @@ template <typename Real> struct Eps;
 template <> struct Eps<float> { static constexpr double v = 1.1920928955078125e-07; };
 template <> struct Eps<double> { static constexpr double v = 2.220446049250313e-16; };
 
-// LDS: [red: 4 waves x 32 doubles][32 doubles, spare][ints: 32][mesh descriptor][cell vectors ...];
+// LDS: [red: 2 buffers x 4 waves x 16 doubles][ints: 32][mesh descriptor][cell vectors ...];
 // during the BF16 tile product the region from the cell vectors on holds the tile's rows
 // in BF16.  The current tile's mesh descriptor is copied to LDS so that reading its table
 // pointers waits on the LDS counter only, never on global loads in flight.
-constexpr int kRedStride = 32;
-constexpr int kRedDoubles = 4 * kRedStride;
+constexpr int kSumMax = 16;                     // values per workgroup sum
+constexpr int kRedDoubles = 4 * kSumMax;        // one buffer
 constexpr int kMeshLds = 256;
-constexpr int kLdsMesh = kRedDoubles * 8 + 32 * 8 + 32 * 4;
-constexpr int kLdsHeader = kLdsMesh + kMeshLds;   // reduction, 32 spare doubles, ints, mesh
+constexpr int kLdsInts = 2 * kRedDoubles * 8;
+constexpr int kLdsMesh = kLdsInts + 32 * 4;
+constexpr int kLdsHeader = kLdsMesh + kMeshLds;
 static_assert(sizeof(MeshDev<double>) <= kMeshLds && sizeof(MeshDev<float>) <= kMeshLds, "mesh descriptor");
 static_assert(sizeof(MeshDev<double>) % 4 == 0 && sizeof(MeshDev<float>) % 4 == 0, "mesh descriptor");
 
@@ -84,8 +85,8 @@ constexpr int kEllGroup = 6;
 template <int CTRL>
 __device__ inline double dpp_row(double x) {
   const long long v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 __device__ inline double read_lane(double x, int lane) {
@@ -93,40 +94,73 @@ __device__ inline double read_lane(double x, int lane) {
   const int lo = __builtin_amdgcn_readlane((int)v, lane), hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
-// Sum of a double over the wave: within each row of 16 lanes by DPP (pairs, quads, half
-// rows, rows), then the four row sums; the same on every lane, fixed order.
-__device__ inline double wave_sum(double x) {
-  x += dpp_row<0xB1>(x);    // quad_perm [1,0,3,2]
-  x += dpp_row<0x4E>(x);    // quad_perm [2,3,0,1]
-  x += dpp_row<0x141>(x);   // row_half_mirror
-  x += dpp_row<0x140>(x);   // row_mirror
-  return (read_lane(x, 0) + read_lane(x, 16)) + (read_lane(x, 32) + read_lane(x, 48));
+// Two values folded into one register: the lower 32 lanes (even rows of 16) get a's sums of
+// lanes l and l + 32 (l and l + 16), the upper (odd) ones b's.
+template <bool HALF>
+__device__ inline double fold(double a, double b) {
+  const long long va = __double_as_longlong(a), vb = __double_as_longlong(b);
+  const auto lo = HALF ? __builtin_amdgcn_permlane32_swap((unsigned)va, (unsigned)vb, false, false)
+                       : __builtin_amdgcn_permlane16_swap((unsigned)va, (unsigned)vb, false, false);
+  const auto hi = HALF ? __builtin_amdgcn_permlane32_swap((unsigned)(va >> 32), (unsigned)(vb >> 32), false, false)
+                       : __builtin_amdgcn_permlane16_swap((unsigned)(va >> 32), (unsigned)(vb >> 32), false, false);
+  return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
 }
 
-// Sum N (<= 32) doubles over the workgroup; fixed order, so deterministic.
-template <int N>
-__device__ inline void block_sum(double (&v)[N], double* red) {
-  static_assert(N <= kRedStride, "block_sum: too many values");
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) red[wave * kRedStride + i] = v[i];
+// A workgroup barrier that orders LDS accesses only: global loads and stores stay in flight.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The workgroup sums' LDS: two buffers in turn, so that a sum needs one barrier only (its
+// buffer's last readers are past the barrier of the sum in between).  GLOBAL: that barrier also
+// orders global memory (vectors of the current cell in the workspace).
+template <bool GLOBAL>
+struct Red {
+  double* buf;
+  int turn;
+  __device__ void barrier() const {
+    if (GLOBAL) __syncthreads();
+    else lds_barrier();
   }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    v[i] = (red[i] + red[kRedStride + i]) + (red[2 * kRedStride + i] + red[3 * kRedStride + i]);
-}
+};
 
-template <typename Real>
-__device__ inline double dot_vec(const Real* a, const Real* b, int len, double* red) {
-  double s[1] = {0.0};
-  for (int e = tid(); e < len; e += kBlock) s[0] += (double)a[e] * (double)b[e];
-  block_sum<1>(s, red);
-  return s[0];
+// Sum N doubles over the workgroup, the same uniform values on every lane; fixed order, so
+// deterministic.  Within a wave four values are folded into one register (halves, then rows
+// of 16 lanes), so that the steps within a row work on a quarter of the registers: about 5 N
+// instructions against 30 N for summing value by value (the 11 sums of an evaluation's end
+// took 530 of a wave's 5,100 instructions).  Lane i then adds value i of the four waves and
+// hands it out.
+template <int N, typename RED>
+__device__ inline void block_sum(double (&v)[N], RED& red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int n0 = 0; n0 < N; n0 += kSumMax) {
+    const int nn = N - n0 < kSumMax ? N - n0 : kSumMax, Q = (nn + 3) / 4;
+    double* buf = red.buf + red.turn * kRedDoubles;
+    red.turn ^= 1;
+    double w[kSumMax / 4];
+    auto val = [&](int i) { return i < nn ? v[n0 + i] : 0.0; };
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {               // row r of w[i]: value i + Q r
+      double x = fold<false>(fold<true>(val(i), val(i + 2 * Q)), fold<true>(val(i + Q), val(i + 3 * Q)));
+      x += dpp_row<0xB1>(x);                    // quad_perm [1,0,3,2]
+      x += dpp_row<0x4E>(x);                    // quad_perm [2,3,0,1]
+      x += dpp_row<0x141>(x);                   // row_half_mirror
+      x += dpp_row<0x140>(x);                   // row_mirror
+      w[i] = x;
+    }
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) buf[wave * kSumMax + i + Q * (lane >> 4)] = w[i];
+    }
+    red.barrier();
+    const double* p = buf + (lane & (kSumMax - 1));
+    const double t = (p[0] + p[kSumMax]) + (p[2 * kSumMax] + p[3 * kSumMax]);
+#pragma unroll
+    for (int i = 0; i < nn; ++i) v[n0 + i] = read_lane(t, i);
+  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -185,9 +219,9 @@ template <> __device__ inline float sqrt_<float>(float x) { return __builtin_amd
 // the area gradients of corners a and b, corner c taking minus their sum), then every
 // vertex gathers its corners into accV (and accA).
 // ---------------------------------------------------------------------------------
-template <typename Real>
+template <typename Real, typename RED>
 __device__ void normalisers(const MeshDev<Real>& M, const Real* xn, const Real* ut, Real* accV, Real* accA,
-                            Real* work, double* red, double& GV, double& GA) {
+                            Real* work, RED& red, double& GV, double& GA) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
   const bool area = accA != nullptr;
   for (int e = tid(); e < 3 * np; e += kBlock) {
@@ -272,7 +306,7 @@ __device__ void normalisers(const MeshDev<Real>& M, const Real* xn, const Real* 
     if (area)
       sm[1] += (double)accA[i] * accA[i] + (double)accA[np + i] * accA[np + i] + (double)accA[2 * np + i] * accA[2 * np + i];
   }
-  block_sum<2>(sm, red);
+  block_sum(sm, red);
   GV = sm[0];
   GA = area ? sm[1] : 1.0;
 }
@@ -321,12 +355,176 @@ __device__ inline Real sl2_tau(Real a1, Real a2, Real sig1, Real J) {
   return tau;
 }
 
+// In-plane terms of triangle t (area PD, modified Skalak, Rayleigh) and its share of the
+// volume: the gradient of corners a and b (corner c takes minus their sum) and e1 x e2 go to
+// out[0 .. 8 stride]; acc gains [0] 6 volume, [1] area, [4] area PD, [5] Skalak, [6] Rayleigh
+// energy, [7] collapsed triangles.
+template <typename Real, bool EXT>
+__device__ __attribute__((always_inline)) inline void triangle_terms(const MeshDev<Real>& M, Real Cst, Real Bsk, Real Dsk,
+                                                                     Real beta, bool area_on, Real ca, const Real* xn,
+                                                                     const Real* ut, int np, int t, double (&acc)[8],
+                                                                     Real* out, int stride) {
+  // The triangle's table entries are all requested before the first is used, then
+  // its corners' coordinates from LDS; scheduling barriers keep each group together.
+  const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
+  const double D00 = gld(M.dminv, 4 * t), D01 = gld(M.dminv, 4 * t + 1), D10 = gld(M.dminv, 4 * t + 2), D11 = gld(M.dminv, 4 * t + 3);
+  const double area_t = gld(M.area, t), i4a2_t = gld(M.inv4a2, t);
+  __builtin_amdgcn_sched_barrier(0);
+  const Real xa = xn[a], ya = xn[np + a], za = xn[2 * np + a];
+  const Real xb = xn[b], yb = xn[np + b], zb = xn[2 * np + b];
+  const Real xc = xn[c], yc = xn[np + c], zc = xn[2 * np + c];
+  const Real uax = ut[a], uay = ut[np + a], uaz = ut[2 * np + a];
+  const Real ubx = ut[b], uby = ut[np + b], ubz = ut[2 * np + b];
+  const Real ucx = ut[c], ucy = ut[np + c], ucz = ut[2 * np + c];
+  __builtin_amdgcn_sched_barrier(0);
+  const Real d00 = Real(D00), d01 = Real(D01), d10 = Real(D10), d11 = Real(D11);
+  const Real A0 = Real(area_t);
+  // The strain measures (sigma - 1, area ratio - 1) are small differences of O(1)
+  // quantities, so the edges, F = [e1 e2] D_m^-1, F^T F and |e1 x e2|^2 are formed
+  // in FP64 from the stored values (exact differences); everything after that works
+  // on the small differences and keeps its relative precision in FP32.
+  const double E1x = ((double)xa - (double)xc) + ((double)uax - (double)ucx);
+  const double E1y = ((double)ya - (double)yc) + ((double)uay - (double)ucy);
+  const double E1z = ((double)za - (double)zc) + ((double)uaz - (double)ucz);
+  const double E2x = ((double)xb - (double)xc) + ((double)ubx - (double)ucx);
+  const double E2y = ((double)yb - (double)yc) + ((double)uby - (double)ucy);
+  const double E2z = ((double)zb - (double)zc) + ((double)ubz - (double)ucz);
+  const double F0x = E1x * D00 + E2x * D10, F0y = E1y * D00 + E2y * D10, F0z = E1z * D00 + E2z * D10;
+  const double F1x = E1x * D01 + E2x * D11, F1y = E1y * D01 + E2y * D11, F1z = E1z * D01 + E2z * D11;
+  const double C00 = F0x * F0x + F0y * F0y + F0z * F0z;
+  const double C01 = F0x * F1x + F0y * F1y + F0z * F1z;
+  const double C11 = F1x * F1x + F1y * F1y + F1z * F1z;
+  const double Nx = E1y * E2z - E1z * E2y, Ny = E1z * E2x - E1x * E2z, Nz = E1x * E2y - E1y * E2x;
+  const double NN = Nx * Nx + Ny * Ny + Nz * Nz;
+  // displacement part of F for the Rayleigh term
+  const Real eu1x = uax - ucx, eu1y = uay - ucy, eu1z = uaz - ucz;
+  const Real eu2x = ubx - ucx, eu2y = uby - ucy, eu2z = ubz - ucz;
+  const Real f0x = Real(F0x), f0y = Real(F0y), f0z = Real(F0z);
+  const Real f1x = Real(F1x), f1y = Real(F1y), f1z = Real(F1z);
+  const Real g0x = eu1x * d00 + eu2x * d10, g0y = eu1y * d00 + eu2y * d10, g0z = eu1z * d00 + eu2z * d10;
+  const Real g1x = eu1x * d01 + eu2x * d11, g1y = eu1y * d01 + eu2y * d11, g1z = eu1z * d01 + eu2z * d11;
+  const Real c01 = Real(C01);
+  const Real nx = Real(Nx), ny = Real(Ny), nz = Real(Nz);
+  const Real nn = sqrt_(Real(NN));
+  // a collapsed triangle (area below 1e-6 of its rest area) has no second in-plane
+  // direction: u2 below is taken as zero, so that direction carries no force
+  const bool collapsed = NN * i4a2_t < 1e-12;
+  // area ratio J = sigma1 sigma2 = |e1 x e2| / (2 A0)
+  const Real Jsq_m1 = Real(NN * i4a2_t - 1.0);
+  const Real J = sqrt_(fmax(Real(1) + Jsq_m1, Real(0)));
+  const Real Jm1 = Jsq_m1 * rcp_(J + Real(1));
+  const Real half = Real(0.5 * (C00 - C11));
+  const Real disc = sqrt_(half * half + c01 * c01);
+  const Real s1m = Real(0.5 * ((C00 - 1.0) + (C11 - 1.0))) + disc;          // sigma1^2 - 1
+  const Real sig1 = sqrt_(fmax(Real(1) + s1m, Real(0)));
+  const Real a1 = s1m * rcp_(sig1 + Real(1));                              // sigma1 - 1
+  const Real inv_s1 = sig1 > Real(1e-30) ? rcp_(sig1) : Real(0);
+  const Real a2 = (Jm1 - a1) * inv_s1;                                     // sigma2 - 1
+  const Real sig2 = Real(1) + a2;
+  // right singular vectors v1, v2 = perp(v1); left u1 = F v1 / sigma1, u2 = nhat x u1
+  Real vx, vy;
+  if (half >= Real(0)) { vx = half + disc; vy = c01; } else { vx = c01; vy = disc - half; }
+  const Real vn = sqrt_(vx * vx + vy * vy);
+  if (vn > Real(0)) {
+    const Real ivn = rcp_(vn);
+    vx *= ivn;
+    vy *= ivn;
+  } else {
+    vx = Real(1);
+    vy = Real(0);
+  }
+  const Real u1x = (f0x * vx + f1x * vy) * inv_s1, u1y = (f0y * vx + f1y * vy) * inv_s1, u1z = (f0z * vx + f1z * vy) * inv_s1;
+  const Real inv_nn = nn > Real(1e-30) ? rcp_(nn) : Real(0);
+  const Real hx = collapsed ? Real(0) : nx * inv_nn, hy = collapsed ? Real(0) : ny * inv_nn,
+             hz = collapsed ? Real(0) : nz * inv_nn;
+  const Real u2x = hy * u1z - hz * u1y, u2y = hz * u1x - hx * u1z, u2z = hx * u1y - hy * u1x;
+  // area PD: closest SL(2) element diag(t, 1/t)
+  const Real tau = sl2_tau<Real>(a1, a2, sig1, J);
+  const Real dA1 = a1 - tau, dA2 = a2 + tau * rcp_(Real(1) + tau);
+  // modified Skalak: f'(s) = B/2 s (s^2 - 1) + D (s - 1)^3
+  const Real s2m = a2 * (Real(2) + a2);                                    // sigma2^2 - 1
+  const Real fp1 = Real(0.5) * Bsk * sig1 * s1m + Dsk * a1 * a1 * a1;
+  const Real fp2 = Real(0.5) * Bsk * sig2 * s2m + Dsk * a2 * a2 * a2;
+  const Real w1 = A0 * (Cst * dA1 + fp1), w2 = A0 * (Cst * dA2 + fp2), wr = beta * Cst * A0;
+  // dE/dF = w1 u1 v1^T + w2 u2 v2^T + wr F_u, with v2 = (-vy, vx)
+  const Real G0x = w1 * u1x * vx - w2 * u2x * vy + wr * g0x;
+  const Real G0y = w1 * u1y * vx - w2 * u2y * vy + wr * g0y;
+  const Real G0z = w1 * u1z * vx - w2 * u2z * vy + wr * g0z;
+  const Real G1x = w1 * u1x * vy + w2 * u2x * vx + wr * g1x;
+  const Real G1y = w1 * u1y * vy + w2 * u2y * vx + wr * g1y;
+  const Real G1z = w1 * u1z * vy + w2 * u2z * vx + wr * g1z;
+  // corner gradients [g_a g_b] = dE/dF D_m^-T, g_c = -g_a - g_b, plus the volume
+  // gradient k C / G_n * (e1 x e2) / 6 on each corner
+  Real gax = G0x * d00 + G1x * d01, gay = G0y * d00 + G1y * d01, gaz = G0z * d00 + G1z * d01;
+  Real gbx = G0x * d10 + G1x * d11, gby = G0y * d10 + G1y * d11, gbz = G0z * d10 + G1z * d11;
+  if (area_on) {
+    // global area: k_A (A - A0) / G_A times grad A_t, which is -(n/2) x e2 at corner a
+    // and (n/2) x e1 at corner b (n the unit normal, from the raw cross product)
+    const Real e1x = Real(E1x), e1y = Real(E1y), e1z = Real(E1z);
+    const Real e2x = Real(E2x), e2y = Real(E2y), e2z = Real(E2z);
+    const Real mx = ca * hx, my = ca * hy, mz = ca * hz;      // zero for a collapsed triangle
+    gax -= my * e2z - mz * e2y;
+    gay -= mz * e2x - mx * e2z;
+    gaz -= mx * e2y - my * e2x;
+    gbx += my * e1z - mz * e1y;
+    gby += mz * e1x - mx * e1z;
+    gbz += mx * e1y - my * e1x;
+  }
+  out[0] = gax;
+  out[stride] = gay;
+  out[2 * stride] = gaz;
+  out[3 * stride] = gbx;
+  out[4 * stride] = gby;
+  out[5 * stride] = gbz;
+  out[6 * stride] = nx;
+  out[7 * stride] = ny;
+  out[8 * stride] = nz;
+  // x_a . (x_b x x_c) = E1 . (E2 x x_c) with E1 = x_a - x_c, E2 = x_b - x_c (FP64)
+  const double cx = (double)xc + (double)ucx, cy = (double)yc + (double)ucy, cz = (double)zc + (double)ucz;
+  acc[0] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
+  acc[1] += (double)J * area_t;                         // deformed area = J A0
+  acc[7] += collapsed ? 1.0 : 0.0;
+  acc[4] += 0.5 * (double)(Cst * A0) * ((double)dA1 * dA1 + (double)dA2 * dA2);
+  acc[5] += (double)A0 * (0.125 * (double)Bsk * ((double)s1m * s1m + (double)s2m * s2m)
+                           + 0.25 * (double)Dsk * ((double)a1 * a1 * a1 * a1 + (double)a2 * a2 * a2 * a2));
+  acc[6] += 0.5 * (double)wr * ((double)g0x * g0x + (double)g0y * g0y + (double)g0z * g0z
+                                 + (double)g1x * g1x + (double)g1y * g1y + (double)g1z * g1z);
+}
+
+// An evaluation's result from its sums: the energies, the force norms |grad|^2, |M u/h^2|^2,
+// |b|^2 and |F_int|^2 of the residual, sum |u.b| of the rounding scale.
+template <typename Real>
+__device__ __attribute__((always_inline)) inline void finish_eval(const MeshDev<Real>& M, double inertial, double e_bend,
+                                                                  double e_pd, double e_sk, double e_tr, double e_vol,
+                                                                  double e_area, double e_col, double ub, double g2,
+                                                                  double mu2, double b2, double f2, double vol, double area,
+                                                                  double degen, EvalResult& res) {
+  res.vol = vol;
+  res.area = area;
+  res.degen = degen;
+  res.terms[0] = inertial;
+  res.terms[1] = e_pd;
+  res.terms[2] = e_sk;
+  res.terms[3] = e_bend;
+  res.terms[4] = e_vol;
+  res.terms[5] = e_tr;
+  res.terms[6] = e_area;
+  res.terms[7] = e_col;
+  res.E = inertial + e_pd + e_sk + e_bend + e_vol + e_tr + e_area + e_col;
+  // rounding scale of E: the sum of the magnitudes of its terms
+  res.noise = fabs(inertial) + 2.0 * ub + e_pd + e_sk + e_bend + e_vol + e_tr + e_area + e_col;
+  const double num = sqrt(g2);
+  const double den = sqrt(mu2) + sqrt(b2) + sqrt(f2) + M.floor_force;
+  res.resid = num == 0.0 ? 0.0 : num / den;
+  if (!isfinite(res.E) || !isfinite(num)) res.resid = INFINITY;
+}
+
 // EXT: the optional terms (global area, the literal volume normaliser, contacts) are
 // compiled in; without them the evaluation carries none of their code.
-template <typename Real, bool EXT>
+template <typename Real, bool EXT, typename RED>
 __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn,
                          double GA, const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec,
-                         Real* work, Real* gout, double* red, EvalResult& res) {
+                         Real* work, Real* gout, RED& red, EvalResult& res) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
   const Real inv_h2 = Real(1.0 / (h * h));
   const Real beta = Real(mat.beta), kb = Real(mat.k_bend);
@@ -413,14 +611,14 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   }
   double coefd = 0.0, vol = 0.0, area = 0.0, coefa = 0.0;
   if (pre) {
-    block_sum<4>(accA, red);
+    block_sum(accA, red);
     vol = accA[0] / 6.0;
     area = 0.5 * accA[3];
     coefd = mat.k_volume * (vol - M.V0) / Gn;               // k C / G_n
     coefa = area_on ? mat.k_area_global * (area - M.A0) / GA : 0.0;
   } else {
     double ab[2] = {accA[1], accA[2]};
-    block_sum<2>(ab, red);                                   // also the barrier before pass B
+    block_sum(ab, red);                                   // also the barrier before pass B
     accA[1] = ab[0];
     accA[2] = ab[1];
   }
@@ -480,145 +678,19 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   __syncthreads();   // work (R) is reused for the corner chunks below
 
   // ---- passes C/D: triangle in-plane terms + volume, per chunk --------------------
-  // area PD, Skalak, triangle Rayleigh, |u.b|, 6 volume, 2 area, collapsed triangles
-  double accC[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  double accT[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // as triangle_terms
+  double accU = 0.0;                               // |u.b|
   const Real ca = Real(0.5 * coefa);               // global area: k_A (A - A0) / G_A / 2
   double accD[4] = {0.0, 0.0, 0.0, 0.0};   // |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
   for (int t0 = 0; t0 < nt; t0 += ch) {
     const int tn = min(ch, nt - t0);
     for (int tt = tid(); tt < tn; tt += kBlock) {
       const int t = t0 + tt;
-      // The triangle's table entries are all requested before the first is used, then
-      // its corners' coordinates from LDS; scheduling barriers keep each group together.
-      const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
-      const double D00 = gld(M.dminv, 4 * t), D01 = gld(M.dminv, 4 * t + 1), D10 = gld(M.dminv, 4 * t + 2), D11 = gld(M.dminv, 4 * t + 3);
-      const double area_t = gld(M.area, t), i4a2_t = gld(M.inv4a2, t);
-      __builtin_amdgcn_sched_barrier(0);
-      const Real xa = xn[a], ya = xn[np + a], za = xn[2 * np + a];
-      const Real xb = xn[b], yb = xn[np + b], zb = xn[2 * np + b];
-      const Real xc = xn[c], yc = xn[np + c], zc = xn[2 * np + c];
-      const Real uax = ut[a], uay = ut[np + a], uaz = ut[2 * np + a];
-      const Real ubx = ut[b], uby = ut[np + b], ubz = ut[2 * np + b];
-      const Real ucx = ut[c], ucy = ut[np + c], ucz = ut[2 * np + c];
-      __builtin_amdgcn_sched_barrier(0);
-      const Real d00 = Real(D00), d01 = Real(D01), d10 = Real(D10), d11 = Real(D11);
-      const Real A0 = Real(area_t);
-      // The strain measures (sigma - 1, area ratio - 1) are small differences of O(1)
-      // quantities, so the edges, F = [e1 e2] D_m^-1, F^T F and |e1 x e2|^2 are formed
-      // in FP64 from the stored values (exact differences); everything after that works
-      // on the small differences and keeps its relative precision in FP32.
-      const double E1x = ((double)xa - (double)xc) + ((double)uax - (double)ucx);
-      const double E1y = ((double)ya - (double)yc) + ((double)uay - (double)ucy);
-      const double E1z = ((double)za - (double)zc) + ((double)uaz - (double)ucz);
-      const double E2x = ((double)xb - (double)xc) + ((double)ubx - (double)ucx);
-      const double E2y = ((double)yb - (double)yc) + ((double)uby - (double)ucy);
-      const double E2z = ((double)zb - (double)zc) + ((double)ubz - (double)ucz);
-      const double F0x = E1x * D00 + E2x * D10, F0y = E1y * D00 + E2y * D10, F0z = E1z * D00 + E2z * D10;
-      const double F1x = E1x * D01 + E2x * D11, F1y = E1y * D01 + E2y * D11, F1z = E1z * D01 + E2z * D11;
-      const double C00 = F0x * F0x + F0y * F0y + F0z * F0z;
-      const double C01 = F0x * F1x + F0y * F1y + F0z * F1z;
-      const double C11 = F1x * F1x + F1y * F1y + F1z * F1z;
-      const double Nx = E1y * E2z - E1z * E2y, Ny = E1z * E2x - E1x * E2z, Nz = E1x * E2y - E1y * E2x;
-      const double NN = Nx * Nx + Ny * Ny + Nz * Nz;
-      // displacement part of F for the Rayleigh term
-      const Real eu1x = uax - ucx, eu1y = uay - ucy, eu1z = uaz - ucz;
-      const Real eu2x = ubx - ucx, eu2y = uby - ucy, eu2z = ubz - ucz;
-      const Real f0x = Real(F0x), f0y = Real(F0y), f0z = Real(F0z);
-      const Real f1x = Real(F1x), f1y = Real(F1y), f1z = Real(F1z);
-      const Real g0x = eu1x * d00 + eu2x * d10, g0y = eu1y * d00 + eu2y * d10, g0z = eu1z * d00 + eu2z * d10;
-      const Real g1x = eu1x * d01 + eu2x * d11, g1y = eu1y * d01 + eu2y * d11, g1z = eu1z * d01 + eu2z * d11;
-      const Real c01 = Real(C01);
-      const Real nx = Real(Nx), ny = Real(Ny), nz = Real(Nz);
-      const Real nn = sqrt_(Real(NN));
-      // a collapsed triangle (area below 1e-6 of its rest area) has no second in-plane
-      // direction: u2 below is taken as zero, so that direction carries no force
-      const bool collapsed = NN * i4a2_t < 1e-12;
-      // area ratio J = sigma1 sigma2 = |e1 x e2| / (2 A0)
-      const Real Jsq_m1 = Real(NN * i4a2_t - 1.0);
-      const Real J = sqrt_(fmax(Real(1) + Jsq_m1, Real(0)));
-      const Real Jm1 = Jsq_m1 * rcp_(J + Real(1));
-      const Real half = Real(0.5 * (C00 - C11));
-      const Real disc = sqrt_(half * half + c01 * c01);
-      const Real s1m = Real(0.5 * ((C00 - 1.0) + (C11 - 1.0))) + disc;          // sigma1^2 - 1
-      const Real sig1 = sqrt_(fmax(Real(1) + s1m, Real(0)));
-      const Real a1 = s1m * rcp_(sig1 + Real(1));                              // sigma1 - 1
-      const Real inv_s1 = sig1 > Real(1e-30) ? rcp_(sig1) : Real(0);
-      const Real a2 = (Jm1 - a1) * inv_s1;                                     // sigma2 - 1
-      const Real sig2 = Real(1) + a2;
-      // right singular vectors v1, v2 = perp(v1); left u1 = F v1 / sigma1, u2 = nhat x u1
-      Real vx, vy;
-      if (half >= Real(0)) { vx = half + disc; vy = c01; } else { vx = c01; vy = disc - half; }
-      const Real vn = sqrt_(vx * vx + vy * vy);
-      if (vn > Real(0)) {
-        const Real ivn = rcp_(vn);
-        vx *= ivn;
-        vy *= ivn;
-      } else {
-        vx = Real(1);
-        vy = Real(0);
-      }
-      const Real u1x = (f0x * vx + f1x * vy) * inv_s1, u1y = (f0y * vx + f1y * vy) * inv_s1, u1z = (f0z * vx + f1z * vy) * inv_s1;
-      const Real inv_nn = nn > Real(1e-30) ? rcp_(nn) : Real(0);
-      const Real hx = collapsed ? Real(0) : nx * inv_nn, hy = collapsed ? Real(0) : ny * inv_nn,
-                 hz = collapsed ? Real(0) : nz * inv_nn;
-      const Real u2x = hy * u1z - hz * u1y, u2y = hz * u1x - hx * u1z, u2z = hx * u1y - hy * u1x;
-      // area PD: closest SL(2) element diag(t, 1/t)
-      const Real tau = sl2_tau<Real>(a1, a2, sig1, J);
-      const Real dA1 = a1 - tau, dA2 = a2 + tau * rcp_(Real(1) + tau);
-      // modified Skalak: f'(s) = B/2 s (s^2 - 1) + D (s - 1)^3
-      const Real s2m = a2 * (Real(2) + a2);                                    // sigma2^2 - 1
-      const Real fp1 = Real(0.5) * Bsk * sig1 * s1m + Dsk * a1 * a1 * a1;
-      const Real fp2 = Real(0.5) * Bsk * sig2 * s2m + Dsk * a2 * a2 * a2;
-      const Real w1 = A0 * (Cst * dA1 + fp1), w2 = A0 * (Cst * dA2 + fp2), wr = beta * Cst * A0;
-      // dE/dF = w1 u1 v1^T + w2 u2 v2^T + wr F_u, with v2 = (-vy, vx)
-      const Real G0x = w1 * u1x * vx - w2 * u2x * vy + wr * g0x;
-      const Real G0y = w1 * u1y * vx - w2 * u2y * vy + wr * g0y;
-      const Real G0z = w1 * u1z * vx - w2 * u2z * vy + wr * g0z;
-      const Real G1x = w1 * u1x * vy + w2 * u2x * vx + wr * g1x;
-      const Real G1y = w1 * u1y * vy + w2 * u2y * vx + wr * g1y;
-      const Real G1z = w1 * u1z * vy + w2 * u2z * vx + wr * g1z;
-      // corner gradients [g_a g_b] = dE/dF D_m^-T, g_c = -g_a - g_b, plus the volume
-      // gradient k C / G_n * (e1 x e2) / 6 on each corner
-      Real gax = G0x * d00 + G1x * d01, gay = G0y * d00 + G1y * d01, gaz = G0z * d00 + G1z * d01;
-      Real gbx = G0x * d10 + G1x * d11, gby = G0y * d10 + G1y * d11, gbz = G0z * d10 + G1z * d11;
-      if (area_on) {
-        // global area: k_A (A - A0) / G_A times grad A_t, which is -(n/2) x e2 at corner a
-        // and (n/2) x e1 at corner b (n the unit normal, from the raw cross product)
-        const Real e1x = Real(E1x), e1y = Real(E1y), e1z = Real(E1z);
-        const Real e2x = Real(E2x), e2y = Real(E2y), e2z = Real(E2z);
-        const Real mx = ca * hx, my = ca * hy, mz = ca * hz;      // zero for a collapsed triangle
-        gax -= my * e2z - mz * e2y;
-        gay -= mz * e2x - mx * e2z;
-        gaz -= mx * e2y - my * e2x;
-        gbx += my * e1z - mz * e1y;
-        gby += mz * e1x - mx * e1z;
-        gbz += mx * e1y - my * e1x;
-      }
-      work[0 * ch + tt] = gax;
-      work[1 * ch + tt] = gay;
-      work[2 * ch + tt] = gaz;
-      work[3 * ch + tt] = gbx;
-      work[4 * ch + tt] = gby;
-      work[5 * ch + tt] = gbz;
-      work[6 * ch + tt] = nx;
-      work[7 * ch + tt] = ny;
-      work[8 * ch + tt] = nz;
-      if (!pre) {
-        // x_a . (x_b x x_c) = E1 . (E2 x x_c) with E1 = x_a - x_c, E2 = x_b - x_c (FP64)
-        const double cx = (double)xc + (double)ucx, cy = (double)yc + (double)ucy, cz = (double)zc + (double)ucz;
-        accC[4] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
-        accC[5] += (double)J * area_t;                      // deformed area = J A0
-      }
-      accC[6] += collapsed ? 1.0 : 0.0;
-      accC[0] += 0.5 * (double)(Cst * A0) * ((double)dA1 * dA1 + (double)dA2 * dA2);
-      accC[1] += (double)A0 * (0.125 * (double)Bsk * ((double)s1m * s1m + (double)s2m * s2m)
-                               + 0.25 * (double)Dsk * ((double)a1 * a1 * a1 * a1 + (double)a2 * a2 * a2 * a2));
-      accC[2] += 0.5 * (double)wr * ((double)g0x * g0x + (double)g0y * g0y + (double)g0z * g0z
-                                     + (double)g1x * g1x + (double)g1y * g1y + (double)g1z * g1z);
+      triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accT, work + tt, ch);
     }
     if (!pre) {
-      double vv[2] = {accC[4], accC[5]};
-      block_sum<2>(vv, red);                  // also the barrier before the gather
+      double vv[2] = {accT[0], accT[1]};
+      block_sum(vv, red);                  // also the barrier before the gather
       vol = vv[0] / 6.0;
       area = vv[1];
       coefd = mat.k_volume * (vol - M.V0) / Gn;
@@ -677,7 +749,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
         accD[1] += mux * mux + muy * muy + muz * muz;
         accD[2] += (double)bx * bx + (double)by * by + (double)bz * bz;
         accD[3] += fx * fx + fy * fy + fz * fz;
-        accC[3] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+        accU += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
       }
     }
     __syncthreads();
@@ -685,28 +757,223 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   const double Cv = vol - M.V0, Ca = area - M.A0;
   const double e_vol = 0.5 * mat.k_volume * Cv * Cv / Gn;
   const double e_area = area_on ? 0.5 * mat.k_area_global * Ca * Ca / GA : 0.0;
-  double acc[11] = {accB[0], accC[0], accC[1], accC[2], accC[3], accD[0], accD[1], accD[2], accD[3], accC[6], accB[1]};
-  block_sum<11>(acc, red);
-  const double e_col = acc[10];
-  const double inertial = acc[0];
-  res.vol = vol;
-  res.area = area;
-  res.degen = acc[9];
-  res.terms[0] = inertial;
-  res.terms[1] = acc[1];
-  res.terms[2] = acc[2];
-  res.terms[3] = accA[1] + accA[2];
-  res.terms[4] = e_vol;
-  res.terms[5] = acc[3];
-  res.terms[6] = e_area;
-  res.terms[7] = e_col;
-  res.E = inertial + acc[1] + acc[2] + accA[1] + accA[2] + e_vol + acc[3] + e_area + e_col;
-  // rounding scale of E: the sum of the magnitudes of its terms
-  res.noise = fabs(inertial) + 2.0 * acc[4] + acc[1] + acc[2] + accA[1] + accA[2] + e_vol + acc[3] + e_area + e_col;
-  const double num = sqrt(acc[5]);
-  const double den = sqrt(acc[6]) + sqrt(acc[7]) + sqrt(acc[8]) + M.floor_force;
-  res.resid = num == 0.0 ? 0.0 : num / den;
-  if (!isfinite(res.E) || !isfinite(num)) res.resid = INFINITY;
+  double acc[11] = {accB[0], accB[1], accT[4], accT[5], accT[6], accT[7], accU, accD[0], accD[1], accD[2], accD[3]};
+  block_sum(acc, red);
+  finish_eval(M, acc[0], accA[1] + accA[2], acc[2], acc[3], acc[4], e_vol, e_area, acc[1], acc[6], acc[7], acc[8], acc[9],
+              acc[10], vol, area, acc[5], res);
+}
+
+// The same for a cell whose vectors and whole triangle list are in LDS (every mesh of the
+// batch: vec_lds and one chunk), in two passes with one workgroup sum between them: triangles
+// and bending residuals (into rb and the corner buffer, nothing they read is written), then
+// per vertex the bending, inertia and corner terms at once, so that the gradient is formed in
+// registers and written once.  The corner buffer holds nine values per triangle together
+// (the in-plane gradient of corners a and b, then e1 x e2), read at constant offsets from one
+// address per corner; vc_pk gives that address and how the corner combines a and b, and
+// padding points at nine zeros after the last triangle.
+// Bound: vector instructions and their latency at two waves per SIMD (LDS and registers).
+// One evaluation of a 642-vertex cell takes about 46 k cycles of its workgroup (of two per
+// CU).  Against five passes with three sums and nine barriers and the corner list decoded per
+// corner, a step of 1024 cells went from 790 to 725 us, of 100,000 from 77.1 to 69.8 ms and
+// of 2,000 with contacts from 8.75 to 7.37 ms.
+template <typename Real, bool EXT, typename RED>
+__device__ __attribute__((always_inline)) inline void evaluate_resident(
+    const MeshDev<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn, double GA,
+    const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec, Real* rb, Real* work, Real* gout,
+    RED& red, EvalResult& res) {
+  const int n = M.n, np = M.n_pad, nt = M.nt;
+  const Real inv_h2 = Real(1.0 / (h * h));
+  const Real beta = Real(mat.beta), kb = Real(mat.k_bend);
+  const Real Cst = Real(mat.C), Bsk = Real(mat.B), Dsk = Real(mat.D);
+  const bool area_on = EXT && mat.k_area_global > 0.0;
+  if (EXT && literal) {
+    double gv, ga;
+    normalisers(M, xn, ut, gout, static_cast<Real*>(nullptr), work, red, gv, ga);
+    Gn = gv;
+    red.barrier();
+  }
+  // global area (optional): the total area first
+  double coefa = 0.0;
+  if (area_on) {
+    double a2[1] = {0.0};
+    for (int t = tid(); t < nt; t += kBlock) {
+      const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
+      double N[3], E1[3], E2[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        E1[k] = ((double)xn[k * np + a] - (double)xn[k * np + c]) + ((double)ut[k * np + a] - (double)ut[k * np + c]);
+        E2[k] = ((double)xn[k * np + b] - (double)xn[k * np + c]) + ((double)ut[k * np + b] - (double)ut[k * np + c]);
+      }
+      N[0] = E1[1] * E2[2] - E1[2] * E2[1], N[1] = E1[2] * E2[0] - E1[0] * E2[2], N[2] = E1[0] * E2[1] - E1[1] * E2[0];
+      a2[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
+    }
+    block_sum(a2, red);
+    coefa = mat.k_area_global * (0.5 * a2[0] - M.A0) / GA;
+  }
+  const Real ca = Real(0.5 * coefa);               // k_A (A - A0) / G_A / 2
+
+  // ---- bending residuals -> rb ------------------------------------------------------
+  // first sum: 6 volume, 2 area, bending and its Rayleigh energy, area PD, Skalak, triangle
+  // Rayleigh energy, collapsed triangles
+  double accC[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int i = tid(); i < n; i += kBlock) {
+    Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
+    const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
+    const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
+    Real Ai = 0, l0 = 0;
+    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+      // a group's neighbours and weights (padding: the vertex itself, weight 0) are all
+      // requested before the first is used; the scheduling barrier keeps them together
+      int jj[kEllGroup];
+      Real ww[kEllGroup];
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u) {
+        const bool in = q0 + u < M.nb_deg;
+        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
+        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+      }
+      if (q0 == 0) {
+        Ai = gld(M.vor_area, i);
+        l0 = gld(M.ell0, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u) {
+        const int j = jj[u];
+        const Real w = ww[u];
+        const Real dux = ut[j] - uix, duy = ut[np + j] - uiy, duz = ut[2 * np + j] - uiz;
+        lx += w * ((xn[j] - xix) + dux);
+        ly += w * ((xn[np + j] - xiy) + duy);
+        lz += w * ((xn[2 * np + j] - xiz) + duz);
+        ux += w * dux;
+        uy += w * duy;
+        uz += w * duz;
+      }
+    }
+    const Real inv_A = rcp_(Ai);
+    lx *= inv_A; ly *= inv_A; lz *= inv_A;
+    ux *= inv_A; uy *= inv_A; uz *= inv_A;
+    const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
+    const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
+    const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
+    accC[2] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
+    accC[3] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
+    rb[i] = rx + beta * ux;
+    rb[np + i] = ry + beta * uy;
+    rb[2 * np + i] = rz + beta * uz;
+  }
+  // ---- triangles -> corner buffer -----------------------------------------------------
+  if (tid() < 9) work[9 * nt + tid()] = Real(0);
+  for (int t = tid(); t < nt; t += kBlock)
+    triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
+  block_sum(accC, red);
+  const double vol = accC[0] / 6.0, area = accC[1];
+  const double Cv = vol - M.V0;
+  const Real coef = Real(mat.k_volume * Cv / Gn / 6.0);      // per corner: k C / G_n * (e1 x e2) / 6
+
+  // ---- vertices: bending, inertia - b (+ collision), corners -> gout ---------------------
+  // second sum: inertial and collision energy, |u.b|, |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
+  double accD[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const Real wc = Real(col.w);
+  for (int i = tid(); i < n; i += kBlock) {
+    const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
+    const Real rix = rb[i], riy = rb[np + i], riz = rb[2 * np + i];
+    Real gx = 0, gy = 0, gz = 0, mass = 0;
+    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+      int jj[kEllGroup];
+      Real ww[kEllGroup];
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u) {
+        const bool in = q0 + u < M.nb_deg;
+        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
+        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+      }
+      if (q0 == 0) mass = gld(M.mass, i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u) {
+        const int j = jj[u];
+        const Real w = ww[u];
+        gx += w * (rb[j] - rix);
+        gy += w * (rb[np + j] - riy);
+        gz += w * (rb[2 * np + j] - riz);
+      }
+    }
+    const Real mi = mass * inv_h2;
+    const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
+    Real ox = kb * gx + (mi * ux - bx), oy = kb * gy + (mi * uy - by), oz = kb * gz + (mi * uz - bz);
+    if (EXT && col.n) {
+      // (w/2) min(d, 0)^2 with d = (x - q) . n: gradient w min(d, 0) n, zero once out
+      const Real cnx = gld(col.n, 3 * i), cny = gld(col.n, 3 * i + 1), cnz = gld(col.n, 3 * i + 2);
+      const Real cqx = gld(col.q, 3 * i), cqy = gld(col.q, 3 * i + 1), cqz = gld(col.q, 3 * i + 2);
+      const Real dd = ((xn[i] - cqx) + ux) * cnx + ((xn[np + i] - cqy) + uy) * cny + ((xn[2 * np + i] - cqz) + uz) * cnz;
+      const Real dm = dd < Real(0) ? dd : Real(0);
+      ox += wc * dm * cnx;
+      oy += wc * dm * cny;
+      oz += wc * dm * cnz;
+      accD[1] += 0.5 * col.w * (double)dm * dm;
+    }
+    accD[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
+               - ((double)ux * bx + (double)uy * by + (double)uz * bz);
+    // corners: k = 0 adds g_a, 1 g_b, 2 -(g_a + g_b), all of them the volume normal
+    Real cx = 0, cy = 0, cz = 0, vx = 0, vy = 0, vz = 0;
+    for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
+      unsigned cc[kEllGroup];
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u)
+        cc[u] = q0 + u < M.vc_deg ? gld(M.vc_pk, (q0 + u) * np + i) : (unsigned)(9 * nt) << 2;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kEllGroup; ++u) {
+        const Real* g = work + (cc[u] >> 2);
+        const unsigned k = cc[u] & 3u;
+        const Real wa = k == 0 ? Real(1) : (k == 1 ? Real(0) : Real(-1));
+        const Real wb = k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
+        cx += wa * g[0];
+        cy += wa * g[1];
+        cz += wa * g[2];
+        cx += wb * g[3];
+        cy += wb * g[4];
+        cz += wb * g[5];
+        vx += g[6];
+        vy += g[7];
+        vz += g[8];
+      }
+    }
+    cx += coef * vx;
+    cy += coef * vy;
+    cz += coef * vz;
+    const Real tx = cx + ox, ty = cy + oy, tz = cz + oz;
+    gout[i] = tx;
+    gout[np + i] = ty;
+    gout[2 * np + i] = tz;
+    const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
+    const double fx = tx - (mux - bx), fy = ty - (muy - by), fz = tz - (muz - bz);
+    accD[2] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+    accD[3] += (double)tx * tx + (double)ty * ty + (double)tz * tz;
+    accD[4] += mux * mux + muy * muy + muz * muz;
+    accD[5] += (double)bx * bx + (double)by * by + (double)bz * bz;
+    accD[6] += fx * fx + fy * fy + fz * fz;
+  }
+  for (int i = n + tid(); i < np; i += kBlock) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
+  block_sum(accD, red);                                      // also orders the gradient
+  const double Ca = area - M.A0;
+  const double e_vol = 0.5 * mat.k_volume * Cv * Cv / Gn;
+  const double e_area = area_on ? 0.5 * mat.k_area_global * Ca * Ca / GA : 0.0;
+  finish_eval(M, accD[0], accC[2] + accC[3], accC[4], accC[5], accC[6], e_vol, e_area, accD[1], accD[2], accD[3], accD[4],
+              accD[5], accD[6], vol, area, accC[7], res);
+}
+
+// One evaluation in the batch's vector layout (LAY as for step_kernel): with every vector in
+// LDS the fourth LDS vector holds the bending residuals (b is read from the workspace).
+template <typename Real, bool EXT, int LAY, typename RED>
+__device__ __attribute__((always_inline)) inline void evaluate_any(const MeshDev<Real>& M, const MaterialDev& mat,
+                                                                   bool literal, double h, double Gn, double GA,
+                                                                   const Contacts<Real>& col, const Real* xn, const Real* ut,
+                                                                   const Real* bvec, Real* rb, Real* work, Real* gout,
+                                                                   RED& red, EvalResult& res) {
+  if constexpr (LAY == 0) evaluate_resident<Real, EXT>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, rb, work, gout, red, res);
+  else evaluate<Real, EXT>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, work, gout, red, res);
 }
 
 // ---------------------------------------------------------------------------------
@@ -987,7 +1254,7 @@ __device__ __attribute__((noinline)) void tile_product(const MeshDev<Real>& M, c
 // ---------------------------------------------------------------------------------
 // The step
 // ---------------------------------------------------------------------------------
-enum { VB = 0, VU, VG, VD, VQ, VS0 };   // per-cell workspace vectors (history from VS0)
+enum { VX = 0, VB, VU, VG, VD, VQ, VS0 };   // per-cell workspace vectors (history from VS0)
 
 template <typename Real>
 struct Tile {
@@ -997,9 +1264,9 @@ struct Tile {
   __device__ Real* mat(int v) const { return W + (size_t)v * T * 3 * np; }
 };
 
-template <typename Real, typename CST>
+template <typename Real, typename CST, typename RED>
 __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, int cell, int64_t voff, CST& cs,
-                              const Real* xn, const Real* U, double* red, double* bc) {
+                              const Real* xn, const Real* U, RED& red, double* bc) {
   const int n = M.n, np = M.n_pad;
   const double h = A.sol.h;
   Real* xo = A.x_out + 3 * voff;
@@ -1023,7 +1290,7 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
         s1[4 + c] += m * ((double)U[c * np + i] / h);
       }
     }
-    block_sum<7>(s1, red);
+    block_sum(s1, red);
     const double xc[3] = {s1[1] / s1[0], s1[2] / s1[0], s1[3] / s1[0]};
     const double vc[3] = {s1[4] / s1[0], s1[5] / s1[0], s1[6] / s1[0]};
     double s2[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // L (3), I_xx I_yy I_zz I_xy I_xz I_yz
@@ -1043,7 +1310,7 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
       s2[7] -= m * rx * rz;
       s2[8] -= m * ry * rz;
     }
-    block_sum<9>(s2, red);
+    block_sum(s2, red);
     // omega = I^-1 L (3x3 symmetric, adjugate)
     const double Ixx = s2[3], Iyy = s2[4], Izz = s2[5], Ixy = s2[6], Ixz = s2[7], Iyz = s2[8];
     const double c00 = Iyy * Izz - Iyz * Iyz, c01 = Ixz * Iyz - Ixy * Izz, c02 = Ixy * Iyz - Ixz * Iyy;
@@ -1087,8 +1354,8 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
   }
 }
 
-template <typename Real, int H, bool EXT, int LAY, typename CST>
-__device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Real>& A, int tile, Real* W, CST* CS, double* red,
+template <typename Real, int H, bool EXT, int LAY, typename CST, typename RED>
+__device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Real>& A, int tile, Real* W, CST* CS, RED& red,
                          int* sint, unsigned char* lds) {
   const TileDesc td = A.tiles[tile];
   MeshDev<Real>* Ml = reinterpret_cast<MeshDev<Real>*>(lds + kLdsMesh);
@@ -1133,9 +1400,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     return EXT && A.col_n ? Contacts<Real>{A.col_q + 3 * s_voff[j], A.col_n + 3 * s_voff[j], A.w_col}
                    : Contacts<Real>{nullptr, nullptr, 0.0};
   };
-  // per cell: gradient and b in LDS, or (meshes too large for that) in the workspace
+  // per cell: gradient and b in LDS, or (meshes too large for that) in the workspace; with
+  // every mesh's vectors in LDS (LAY 0), b in the workspace and the bending residuals at bl
   auto gvec = [&](int j) { return vl ? gl : tl.vec(VS0 + 2 * m, j); };
-  auto bvec = [&](int j) { return vl ? bl : tl.vec(VB, j); };
+  const bool b_lds = LAY != 0 && vl;
+  auto bvec = [&](int j) { return b_lds ? bl : tl.vec(VB, j); };
 
   // ---- initial state: b = M v_n / h + F_ext, |grad V(x_n)|^2, first guess --------
   for (int j = 0; j < cnt; ++j) {
@@ -1149,6 +1418,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       aos_to_soa(tl.vec(VU, j), n, np, [&](int e) { return gs[e]; });
     }
     __syncthreads();
+    vcopy(tl.vec(VX, j), xn, len);                             // x_n in the vectors' layout from here on
     // normalisers at x_n (ut and, for the area term, the cell's gradient vector are free
     // until the first evaluation)
     double Gn, GA;
@@ -1184,12 +1454,13 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
   // goes on from y_n + delta only if that does not raise the objective; otherwise it
   // starts from y_n as the plain step does (status bit NPFEM_START_FALLBACK).
   for (int j = 0; j < cnt; ++j) {
-    stage_aos(xn, A.x + 3 * s_voff[j], n, np);
+    vcopy(xn, tl.vec(VX, j), len);
     vcopy(ut, tl.vec(VU, j), len);
-    if (vl) vcopy(bl, tl.vec(VB, j), len);
+    if (b_lds) vcopy(bl, tl.vec(VB, j), len);
     __syncthreads();
     EvalResult r;
-    evaluate<Real, EXT>(M, A.mat, literal, h, CS[j].Gn, CS[j].GA, contacts(j), xn, ut, bvec(j), work, gvec(j), red, r);
+    evaluate_any<Real, EXT, LAY>(M, A.mat, literal, h, CS[j].Gn, CS[j].GA, contacts(j), xn, ut, bvec(j), bl, work, gvec(j),
+                                 red, r);
     bool fallback = false;
     vcopy(tl.vec(VG, j), gvec(j), len);
     if (A.u_delta) {
@@ -1200,8 +1471,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       }
       __syncthreads();                                           // VG holds grad g(y_n); ut = u0 + delta
       EvalResult r1;
-      evaluate<Real, EXT>(M, A.mat, literal, h, CS[j].Gn, CS[j].GA, contacts(j), xn, ut, bvec(j), work, gvec(j), red,
-                          r1);
+      evaluate_any<Real, EXT, LAY>(M, A.mat, literal, h, CS[j].Gn, CS[j].GA, contacts(j), xn, ut, bvec(j), bl, work,
+                                   gvec(j), red, r1);
       if (isfinite(r1.E) && isfinite(r1.resid) && r1.E <= r.E) {
         r = r1;
         vcopy(tl.vec(VU, j), ut, len);
@@ -1291,8 +1562,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           }
         }
       }
-      stage_aos(xn, A.x + 3 * s_voff[j], n, np);
-      if (vl) vcopy(bl, tl.vec(VB, j), len);
+      vcopy(xn, tl.vec(VX, j), len);
+      if (b_lds) vcopy(bl, tl.vec(VB, j), len);
       // second half: y_p . r for every stored pair (one pass)
       double yr[H];
 #pragma unroll
@@ -1323,7 +1594,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
             }
           }
         }
-        block_sum<H>(yr, red);
+        block_sum(yr, red);
       }
       double cf[H];                                    // alpha_p - beta_p
 #pragma unroll
@@ -1371,7 +1642,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         for (int e = W * tid(); e < len; e += W * kBlock)
           d_slot(e, vload(D, e), vload(G, e), vload(U, e), [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), e) : zero; });
       }
-      block_sum<1>(gdv, red);
+      block_sum(gdv, red);
       const double gd = gdv[0];
       // line search: alpha = 1, 1/2, ... until sufficient decrease (Algorithm 1)
       double alpha = 1.0;
@@ -1388,7 +1659,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           }
           __syncthreads();
         }
-        evaluate<Real, EXT>(M, A.mat, literal, h, cs.Gn, cs.GA, contacts(j), xn, ut, bvec(j), work, GT, red, r);
+        evaluate_any<Real, EXT, LAY>(M, A.mat, literal, h, cs.Gn, cs.GA, contacts(j), xn, ut, bvec(j), bl, work, GT, red, r);
         const double slack = A.sol.noise * fmax(cs.noise, r.noise);
         accepted = isfinite(r.E) && (r.E <= cs.E + A.sol.c1 * alpha * gd + slack);
         if (accepted) break;
@@ -1465,7 +1736,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           vstore(G, e, vload(GT, e));
         }
       }
-      block_sum<4 + 3 * H>(acc, red);
+      block_sum(acc, red);
       // the reduced dot products (the same in every lane) picked by pair index o < H
       auto pick = [&](int base, int o) {
         double v = 0.0;
@@ -1559,7 +1830,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
 
   // ---- velocity update and dissipation --------------------------------------------
   for (int j = 0; j < cnt; ++j) {
-    stage_aos(xn, A.x + 3 * s_voff[j], n, np);
+    vcopy(xn, tl.vec(VX, j), len);
     vcopy(ut, tl.vec(VU, j), len);
     __syncthreads();
     double bc[2] = {s_vol[j], s_area[j]};
@@ -1580,8 +1851,10 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
 template <typename Real, int H, bool CSL, bool EXT, int LAY>
 __global__ void __launch_bounds__(kBlock, NPFEM_STEP_WAVES_PER_SIMD) step_kernel(StepArgs<Real> A) {
   extern __shared__ __align__(16) unsigned char lds[];
-  double* red = reinterpret_cast<double*>(lds);
-  int* sint = reinterpret_cast<int*>(lds + kRedDoubles * 8 + 32 * 8);
+  Red<LAY != 0> red;
+  red.buf = reinterpret_cast<double*>(lds);
+  red.turn = 0;
+  int* sint = reinterpret_cast<int*>(lds + kLdsInts);
   Real* W = A.work + (size_t)blockIdx.x * A.slot_stride;
   CellStateT<H>* CS = CSL ? reinterpret_cast<CellStateT<H>*>(lds + A.cs_lds)
                           : reinterpret_cast<CellStateT<H>*>(A.cstate) + (size_t)blockIdx.x * A.tile_cells_max;
@@ -1605,7 +1878,9 @@ template <typename Real, int LAY>
 __global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Real* u, Real* grad,
                                                       double* terms, Real* scratch) {
   extern __shared__ __align__(16) unsigned char lds[];
-  double* red = reinterpret_cast<double*>(lds);
+  Red<LAY != 0> red;
+  red.buf = reinterpret_cast<double*>(lds);
+  red.turn = 0;
   const int cell = blockIdx.x;
   const MeshDev<Real>& M = A.meshes[A.cell_mesh[cell]];
   const int n = M.n, np = M.n_pad, len = 3 * np;
@@ -1616,7 +1891,9 @@ __global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Re
   Real* xn = xl ? reinterpret_cast<Real*>(lds + kLdsHeader) : cs + 2 * 3 * A.n_pad_max;
   Real* ut = xl ? xn + 3 * np : cs + 3 * 3 * A.n_pad_max;
   Real* G = vl ? ut + 3 * np : cs;
-  Real* B = vl ? G + 3 * np : cs + 3 * A.n_pad_max;
+  // b: in LDS after the gradient, or (as in the step with every mesh's vectors in LDS) here
+  Real* rb = G + 3 * np;
+  Real* B = LAY != 0 && vl ? rb : cs + 3 * A.n_pad_max;
   Real* work = reinterpret_cast<Real*>(lds + kLdsHeader) + (xl ? (vl ? 12 : 6) * np : 0);
   stage_aos(xn, A.x + 3 * voff, n, np);
   const Real* vs = A.v + 3 * voff;
@@ -1630,8 +1907,8 @@ __global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Re
   stage_aos(ut, u + 3 * voff, n, np);
   __syncthreads();
   EvalResult r;
-  evaluate<Real, true>(M, A.mat, A.sol.literal != 0, A.sol.h, Gn, GA, Contacts<Real>{nullptr, nullptr, 0.0}, xn, ut, B, work, G,
-           red, r);
+  evaluate_any<Real, true, LAY>(M, A.mat, A.sol.literal != 0, A.sol.h, Gn, GA, Contacts<Real>{nullptr, nullptr, 0.0}, xn, ut, B,
+                                rb, work, G, red, r);
   for (int e = tid(); e < 3 * n; e += kBlock) {
     const int i = e / 3, c = e - 3 * i;
     grad[3 * voff + e] = G[c * np + i];
@@ -1803,10 +2080,10 @@ int stage_cols(size_t lds, int stage_rows, int n_pad) {
 
 template <typename Real>
 size_t lds_bytes(int n_pad, int chunk, int stage_rows, int vec_lds, int xu_lds) {
-  // x_n, trial u (and, with vec_lds, the gradient and b), 3 n_pad each, unless they live
-  // in the workspace, then the corner chunks (9 per triangle, at least 3 n_pad: the
-  // bending pass keeps its residuals there)
-  const size_t work = (size_t)(3 * n_pad > 9 * chunk ? 3 * n_pad : 9 * chunk);
+  // x_n, trial u (and, with vec_lds, the gradient and b or the bending residuals), 3 n_pad
+  // each, unless they live in the workspace, then the corner chunks (9 per triangle and 9
+  // zeros, at least 3 n_pad: the chunked evaluation keeps its bending residuals there)
+  const size_t work = (size_t)(3 * n_pad > 9 * chunk + 9 ? 3 * n_pad : 9 * chunk + 9);
   const size_t vecs = xu_lds ? (vec_lds ? 12 : 6) * (size_t)n_pad : 0;
   size_t region = sizeof(Real) * (vecs + work);
   if (stage_rows > 0 && n_pad <= kStageMaxPad) {
