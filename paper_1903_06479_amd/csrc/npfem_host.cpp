@@ -27,6 +27,7 @@ namespace {
 // LDS a step workgroup may use (the CU's 160 KB less the kernel's static arrays and a
 // margin).
 constexpr size_t kStepLdsCap = 160 * 1024 - 1024;
+constexpr size_t kTwoPerCu = 80 * 1024 - 512;    // two workgroups per compute unit
 
 thread_local std::string g_err;
 
@@ -692,63 +693,61 @@ npfem_status upload_mesh(npfem_plan* p, MeshPlan& mp, const std::vector<double>&
   if ((s = p->buf.upload(Mi.data(), Mi.size(), &d.minv))) return s;
   d.hinv_bf = d.minv_bf = nullptr;
   d.hinv_diag = d.minv_diag = nullptr;
-  d.bperm = d.bband = nullptr;
+  d.bperm = d.biperm = d.bband = nullptr;
   if (p->prm.inverse_bf16 && p->precision == NPFEM_FP32) {
     // exact FP32 diagonal + BF16 off-diagonal part (zero diagonal, zero padding); banded:
     // the off-diagonal part in the reverse Cuthill-McKee order, each 16-column block kept
     // over the k' range of its entries above kBandRel sqrt(A_ii A_jj)
     const bool banded = p->prm.inverse_bf16 == 2;
-    std::vector<int> perm(np);
+    std::vector<int> perm(np), iperm(np);
     for (int i = 0; i < np; ++i) perm[i] = i;
     if (banded) {
       const std::vector<int> ord = rcm_order(m);
       std::copy(ord.begin(), ord.end(), perm.begin());
     }
+    for (int i = 0; i < np; ++i) iperm[perm[i]] = i;
     const int ncb = np / 16;
-    std::vector<int> band((size_t)2 * ncb * 2, 0);
+    std::vector<int> band((size_t)2 * ncb * 4, 0);
     for (int which = 0; which < 2; ++which) {
       const std::vector<double>& A = which == 0 ? hinv : minv_h2;
-      std::vector<uint16_t> off((size_t)np * np, 0);
+      std::vector<uint16_t> off;                       // operands, block by block
       std::vector<float> dg(np, 0.0f);
       for (int i = 0; i < n; ++i) dg[i] = (float)A[(size_t)i * n + i];
-      if (!banded) {
-        for (int i = 0; i < n; ++i)
-          for (int j = 0; j < n; ++j)
-            if (j != i) off[(size_t)i * np + j] = to_bf16((float)A[(size_t)i * n + j]);
-      } else {
-        std::vector<double> sd(n);
-        for (int i = 0; i < n; ++i) sd[i] = std::sqrt(std::fabs(A[(size_t)i * n + i]));
-        for (int cb = 0; cb < ncb; ++cb) {
-          int lo = np, hi = 0;
-          for (int a = 16 * cb; a < 16 * cb + 16 && a < n; ++a)
-            for (int k = 0; k < n; ++k) {
-              const int i = perm[a], j = perm[k];
-              if (i != j && std::fabs(A[(size_t)i * n + j]) > kBandRel * sd[i] * sd[j]) {
-                lo = std::min(lo, k);
-                hi = std::max(hi, k + 1);
-              }
+      std::vector<double> sd(n);
+      for (int i = 0; i < n; ++i) sd[i] = std::sqrt(std::fabs(A[(size_t)i * n + i]));
+      for (int cb = 0; cb < ncb; ++cb) {
+        int lo = np, hi = 0;
+        for (int a = 16 * cb; a < 16 * cb + 16 && a < n && banded; ++a)
+          for (int k = 0; k < n; ++k) {
+            const int i = perm[a], j = perm[k];
+            if (i != j && std::fabs(A[(size_t)i * n + j]) > kBandRel * sd[i] * sd[j]) {
+              lo = std::min(lo, k);
+              hi = std::max(hi, k + 1);
             }
-          if (lo >= hi) lo = hi = 0;
-          lo = lo / 32 * 32;
-          hi = std::min(np, (hi + 31) / 32 * 32);
-          band[((size_t)which * ncb + cb) * 2] = lo;
-          band[((size_t)which * ncb + cb) * 2 + 1] = hi;
-          for (int a = 16 * cb; a < 16 * cb + 16 && a < n; ++a)
-            for (int k = lo; k < hi && k < n; ++k)
-              if (k != a) off[(size_t)a * np + k] = to_bf16((float)A[(size_t)perm[a] * n + perm[k]]);
-        }
+          }
+        if (!banded) lo = 0, hi = np;
+        if (lo >= hi) lo = hi = 0;
+        lo = lo / 32 * 32;
+        hi = std::min(np, (hi + 31) / 32 * 32);
+        int* bd = &band[((size_t)which * ncb + cb) * 4];
+        bd[0] = lo;
+        bd[1] = hi;
+        bd[2] = (int)(off.size() / 512);
+        off.resize(off.size() + (size_t)(hi - lo) * 16, 0);
+        for (int a = 16 * cb; a < 16 * cb + 16 && a < n; ++a)
+          for (int k = lo; k < hi && k < n; ++k)
+            if (k != a)
+              off[(size_t)bd[2] * 512 + (size_t)((k - lo) / 32) * 512 + (((k - lo) % 32) / 8 * 16 + a % 16) * 8 + k % 8] =
+                  to_bf16((float)A[(size_t)perm[a] * n + perm[k]]);
       }
+      if (off.empty()) off.resize(512, 0);             // a block without entries still names an operand
       const uint16_t** po = which == 0 ? &d.hinv_bf : &d.minv_bf;
       const float** pd = which == 0 ? &d.hinv_diag : &d.minv_diag;
       if ((s = p->buf.upload(off.data(), off.size(), po))) return s;
       if ((s = p->buf.upload(dg.data(), dg.size(), pd))) return s;
     }
-    if (!banded)                                   // the identity order, whole ranges
-      for (size_t k = 0; k < band.size(); k += 2) {
-        band[k] = 0;
-        band[k + 1] = np;
-      }
-    if (banded && (s = p->buf.upload(perm.data(), perm.size(), &d.bperm))) return s;   // null: identity
+    if ((s = p->buf.upload(perm.data(), perm.size(), &d.bperm))) return s;
+    if ((s = p->buf.upload(iperm.data(), iperm.size(), &d.biperm))) return s;
     if ((s = p->buf.upload(band.data(), band.size(), &d.bband))) return s;
   }
   d.V0 = m->V0;
@@ -846,7 +845,7 @@ npfem_status npfem_plan_create(int32_t device, const npfem_mesh* const* meshes, 
     const int n = m->n;
     mp.n_pad = round_up(n, 32);
     // two workgroups per CU when the whole triangle list fits in half the LDS
-    const size_t half = 80 * 1024 - 512;
+    const size_t half = kTwoPerCu;
     if (fp64)
       choose_layout<double>(mp.n_pad, m->nt, half, lds_cap, &mp.chunk, &mp.vec_lds, &mp.xu_lds);
     else
@@ -1085,8 +1084,17 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
       lds = std::max(lds, lds_bytes<Real>(p->meshes[mi].n_pad, p->meshes[mi].chunk, stage_rows,
                                           p->meshes[mi].vec_lds, p->meshes[mi].xu_lds));
   b->stage_k = stage_cols(lds, stage_rows, b->n_pad_max);   // the staging stays below the cell states
-  if (p->prm.inverse_bf16 == 2 && std::is_same<Real, float>::value && b->stage_k < 32)
-    return fail(NPFEM_E_UNSUPPORTED, "batch_schedule: banded products need an LDS staging area");
+  if (stage_rows > 0 && b->stage_k < 32)
+    return fail(NPFEM_E_UNSUPPORTED, "batch_schedule: BF16 products need an LDS staging area");
+  if (stage_rows == 0) {
+    // the rows of the other products, where that costs no workgroups per CU
+    const size_t cap = (lds > kTwoPerCu ? kStepLdsCap : kTwoPerCu) - (size_t)T * cell_state_bytes(m);
+    for (int mi = 0; mi < nm; ++mi) {
+      const size_t want = dense_stage_lds<Real>(p->meshes[mi].n_pad, 3 * T);
+      if (!b->by_mesh[mi].empty() && want <= cap) lds = std::max(lds, want);
+    }
+    b->stage_k = (int)(lds - lds_header());
+  }
   // the tile's cell states go to LDS (after everything else) when they fit the LDS a
   // workgroup may have and cost no workgroups per CU
   {
@@ -1594,16 +1602,11 @@ npfem_status npfem_apply_inverse(npfem_plan* p, int32_t mi, int32_t which, const
     const double* A = which == 0 ? mp.dev64.hinv : mp.dev64.minv;
     HIP_TRY(launch_apply_inverse<double>(A, mp.n_pad, static_cast<const double*>(in), static_cast<double*>(out),
                                          rows, s));
-  } else if (p->prm.inverse_bf16 == 2) {
-    const uint16_t* A = which == 0 ? mp.dev32.hinv_bf : mp.dev32.minv_bf;
-    const float* dg = which == 0 ? mp.dev32.hinv_diag : mp.dev32.minv_diag;
-    HIP_TRY(launch_apply_inverse_band(A, dg, mp.dev32.bperm, mp.dev32.bband + (size_t)which * 2 * (mp.n_pad / 16),
-                                      mp.n_pad, static_cast<const float*>(in), static_cast<float*>(out), rows, s));
   } else if (p->prm.inverse_bf16) {
-    const uint16_t* A = which == 0 ? mp.dev32.hinv_bf : mp.dev32.minv_bf;
-    const float* dg = which == 0 ? mp.dev32.hinv_diag : mp.dev32.minv_diag;
-    HIP_TRY(launch_apply_inverse_bf16(A, dg, mp.n_pad, static_cast<const float*>(in), static_cast<float*>(out),
-                                      rows, s));
+    const MeshDev<float>& d = mp.dev32;
+    HIP_TRY(launch_apply_inverse_band(which == 0 ? d.hinv_bf : d.minv_bf, which == 0 ? d.hinv_diag : d.minv_diag,
+                                      d.bperm, d.biperm, d.bband + (size_t)which * 4 * (mp.n_pad / 16), mp.n_pad,
+                                      static_cast<const float*>(in), static_cast<float*>(out), rows, s));
   } else {
     const float* A = which == 0 ? mp.dev32.hinv : mp.dev32.minv;
     HIP_TRY(launch_apply_inverse<float>(A, mp.n_pad, static_cast<const float*>(in), static_cast<float*>(out),

@@ -39,18 +39,18 @@ struct MeshDev {
   const Real* mass;            // [n]
   const Real* hinv;            // [n_pad][n_pad] H~^-1
   const Real* minv;            // [n_pad][n_pad] h^2 M~^-1
-  const uint16_t* hinv_bf;     // [n_pad][n_pad] off-diagonal part of H~^-1, BF16 bits (or null)
-  const uint16_t* minv_bf;     // [n_pad][n_pad] off-diagonal part of h^2 M~^-1, BF16 bits
+  const uint16_t* hinv_bf;     // off-diagonal part of H~^-1, BF16 bits, in operand order (or null)
+  const uint16_t* minv_bf;     // off-diagonal part of h^2 M~^-1 likewise
   const float* hinv_diag;      // [n_pad] diagonal of H~^-1
   const float* minv_diag;      // [n_pad] diagonal of h^2 M~^-1
-  // staged BF16 products: hinv_bf / minv_bf hold, in row n' and column k',
-  // A[perm[n']][perm[k']] within the band of n''s 16-column block, 0 outside (inverse_bf16
-  // = 2: a reverse Cuthill-McKee order and the significant entries' range; 1: the
-  // identity and the whole range)
-  const int* bperm;            // [n_pad] vertex at position k' of the order (identity on padding);
-                               // null for the identity order
-  const int* bband;            // [2][n_pad / 16][2] per matrix (H~^-1, h^2 M~^-1) and 16-column block:
-                               // k' range [lo, hi), multiples of 32
+  // BF16 products work in an order of the vertices (inverse_bf16 = 2: reverse Cuthill-McKee;
+  // 1: the identity).  Per 16-column block, hinv_bf / minv_bf hold A[perm[n']][perm[k']] over
+  // a range of k' (2: the significant entries'; 1: everything), 32 columns of k' per matrix
+  // instruction: 64 lanes x 8 values, lane l: n' = l & 15 of the block, k' = 8 (l >> 4) + e
+  const int* bperm;            // [n_pad] vertex at position k' of the order (identity on padding)
+  const int* biperm;           // [n_pad] its inverse
+  const int* bband;            // [2][n_pad / 16][4] per matrix (H~^-1, h^2 M~^-1) and column block: k' range
+                               // [lo, hi), multiples of 32, and its first operand; 0
   double V0;                   // rest volume
   double A0;                   // rest area
   double floor_force;          // B sqrt(A0): force floor of the residual
@@ -119,7 +119,7 @@ struct StepArgs {
   int n_pad_max;
   int layout;                  // largest over the batch's meshes: 0 current cell's vectors in LDS,
                                // 1 gradient and b in the workspace, 2 x_n and u there too
-  int stage_k;                 // k columns per LDS chunk of the BF16 tile product (0: unstaged)
+  int stage_k;                 // BF16 products: k columns staged per LDS chunk; else: bytes of LDS for the rows
   const Real* x;               // [V][3]
   const Real* v;
   const Real* f;
@@ -170,10 +170,9 @@ hipError_t launch_eval(const StepArgs<Real>& a, int n_cells, const Real* u, Real
 template <typename Real>
 hipError_t launch_apply_inverse(const Real* A, int n_pad, const Real* in, Real* out, int rows,
                                 hipStream_t s);
-hipError_t launch_apply_inverse_band(const uint16_t* A, const float* diag, const int* perm, const int* band,
-                                     int n_pad, const float* in, float* out, int rows, hipStream_t s);
-hipError_t launch_apply_inverse_bf16(const uint16_t* A, const float* diag, int n_pad, const float* in,
-                                     float* out, int rows, hipStream_t s);
+hipError_t launch_apply_inverse_band(const uint16_t* A, const float* diag, const int* perm, const int* iperm,
+                                     const int* band, int n_pad, const float* in, float* out, int rows,
+                                     hipStream_t s);
 template <typename Real>
 hipError_t launch_drag(const Real* x, const Real* v, const int64_t* cell_voff, const int* cell_mesh,
                        const int* mesh_n, int n_cells, const double* zeta, const double* rate,
@@ -191,6 +190,10 @@ hipError_t launch_stats_reset(npfem_stats_total* tot, hipStream_t s);
 template <typename Real>
 size_t lds_bytes(int n_pad, int chunk, int stage_rows, int vec_lds, int xu_lds);
 int stage_cols(size_t lds, int stage_rows, int n_pad);
+// LDS with which a dense product's rows are staged whole (its kernel's choice by stage_bytes)
+template <typename Real>
+size_t dense_stage_lds(int n_pad, int rows);
+int lds_header();
 template <typename Real>
 hipError_t set_lds_limit(size_t bytes);
 template <typename Real>

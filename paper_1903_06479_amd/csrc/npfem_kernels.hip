@@ -29,6 +29,7 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
 
 template <typename Real> struct Eps;
 template <> struct Eps<float> { static constexpr double v = 1.1920928955078125e-07; };
@@ -47,7 +48,13 @@ constexpr int kLdsHeader = kLdsMesh + kMeshLds;
 static_assert(sizeof(MeshDev<double>) <= kMeshLds && sizeof(MeshDev<float>) <= kMeshLds, "mesh descriptor");
 static_assert(sizeof(MeshDev<double>) % 4 == 0 && sizeof(MeshDev<float>) % 4 == 0, "mesh descriptor");
 
-__device__ inline int tid() { return threadIdx.x; }
+// Opaque, so that what is derived from it is formed where it is used and not kept in registers
+// over the whole step (and so over the tile products' calls, which it would make spill).
+__device__ inline int tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 
 // 16-byte vectors of the plan's precision for the per-cell vector passes (the SoA
 // vectors have 3 n_pad elements, a multiple of 96, so every pass is whole vectors).
@@ -977,278 +984,316 @@ __device__ __attribute__((always_inline)) inline void evaluate_any(const MeshDev
 }
 
 // ---------------------------------------------------------------------------------
-// Tile product Out^T = In^T A with A = A^T (n_pad x n_pad), In^T / Out^T (rows x n_pad)
-// on the matrix cores.  16x16 output blocks; each wave owns every fourth column block
-// and all (<= 4) row blocks, so an A fragment is loaded once per wave and reused.
-// Both operands are read as vectors along k (A is symmetric, so its column fragment is
-// a row fragment).  Operand lanes: lane l supplies row l%16, k-slot l/16 of A_op and
-// k-slot l/16, column l%16 of B_op; result slot i of lane l is row 4(l/16) + i (f32)
-// or row 4i + l/16 (f64), column l%16 (measured on gfx950).
+// Tile products Out^T = In^T A with A = A^T (n_pad x n_pad), In^T / Out^T (rows x n_pad),
+// rows <= 64, on the matrix cores in 16x16 output blocks.  Operand lanes: lane l supplies
+// row l%16 and k-slot l/16 of A_op, column l%16 and k-slot l/16 of B_op; result slot i of
+// lane l is row 4(l/16) + i (f32) or row 4i + l/16 (f64), column l%16 (measured on gfx950).
+//
+// Bound: the matrix comes from the L2 (0.4 MB banded, 0.3 MB FP32 at 258 and 3.6 MB FP64 at
+// 642 vertices per product), so what counts is how much of it is in flight.  Each wave takes
+// every fourth 16-column block and works through its blocks in batches of U operands with the
+// next batch, also across the end of a block, requested before the current one is used; the
+// rows come from LDS, two row blocks at a time (MB = 2: more would take the registers that the
+// step keeps over the call).  Pointers are in their address spaces and uniform values in scalar registers: this function is not
+// inlined, and flat loads would make every wait for LDS one for the matrix as well.
+// A banded product of 15 rows by 642 vertices takes 33 k cycles of two workgroups per CU (89 k
+// with row-major operands, no batch ahead and gathered staging; about 13 k at the L2's rate).
 // ---------------------------------------------------------------------------------
-__device__ inline void tile_gemm(const float* __restrict__ A, int np, const float* __restrict__ In,
-                                 float* __restrict__ Out, int rows) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int mb_n = (rows + 15) >> 4;
-  for (int nb = wave; nb < (np >> 4); nb += 4) {
-    const int n0 = nb << 4;
-    floatx4 acc[4];
+#define NPFEM_GLOBAL __attribute__((address_space(1)))
+#define NPFEM_CONST __attribute__((address_space(4)))
+#define NPFEM_LDS __attribute__((address_space(3)))
+
+// A pointer (or integer) that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ inline T* uniform(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
+}
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The wave's column blocks wave, wave + 4, ... of `ncb`.  P: block(cb) describes a block (ns
+// operand steps; past the end: none, with a valid address), fetch(b, s) requests operand s of
+// the matrix (the last one past the end), rows(b, s, mb) gives the rows' operand, mma
+// multiplies, pre / post load and store what the results need.
+template <int MB, int U, int UR, typename P>
+__device__ __attribute__((always_inline)) inline void stream_blocks(const P& p, int ncb) {
+  const int wave = uniform((int)(threadIdx.x >> 6));
+  typename P::Frag f0[U], f1[U];
+  typename P::Block b = p.block(wave);
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const float* arow = A + (size_t)(n0 + l16) * np + 4 * kq;
-    for (int k0 = 0; k0 < np; k0 += 16) {
-      const floatx4 bq = *reinterpret_cast<const floatx4*>(arow + k0);
+  for (int u = 0; u < U; ++u) f0[u] = p.fetch(b, u);
+  for (int cb = wave; cb < ncb; cb += 4) {
+    const typename P::Block nx = p.block(cb + 4);
+    typename P::Acc acc[MB];
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        if (mb < mb_n) {
-          const int r = mb * 16 + l16;
-          const floatx4 aq = r < rows ? *reinterpret_cast<const floatx4*>(In + (size_t)r * np + k0 + 4 * kq)
-                                      : floatx4{0.f, 0.f, 0.f, 0.f};
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.x, bq.x, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.y, bq.y, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.z, bq.z, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.w, bq.w, acc[mb], 0, 0, 0);
-        }
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = typename P::Acc{0, 0, 0, 0};
+    const typename P::Ends ends = p.pre(b);
+    int s0 = 0;
+    do {
+      const bool more = s0 + U < b.ns;
+      const typename P::Block src = more ? b : nx;
+      const int f = more ? s0 + U : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) f1[u] = p.fetch(src, f + u);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u0 = 0; u0 < U; u0 += UR) {
+        typename P::Frag r[UR][MB];
+#pragma unroll
+        for (int u = 0; u < UR; ++u)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) r[u][mb] = p.rows(b, s0 + u0 + u, mb);
+#pragma unroll
+        for (int u = 0; u < UR; ++u)
+          if (s0 + u0 + u < b.ns) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) p.mma(acc[mb], r[u][mb], f0[u0 + u]);
+          }
       }
-    }
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      if (mb < mb_n) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = mb * 16 + 4 * kq + i;
-          if (r < rows) Out[(size_t)r * np + n0 + l16] = acc[mb][i];
-        }
-      }
-    }
+      for (int u = 0; u < U; ++u) f0[u] = f1[u];
+      s0 += U;
+    } while (s0 < b.ns);
+    p.post(b, acc, ends);
+    b = nx;
   }
 }
 
-__device__ inline void tile_gemm(const double* __restrict__ A, int np, const double* __restrict__ In,
-                                 double* __restrict__ Out, int rows) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int mb_n = (rows + 15) >> 4;
-  for (int nb = wave; nb < (np >> 4); nb += 4) {
-    const int n0 = nb << 4;
-    doublex4 acc[4];
+// Dense product, the rows in LDS (STAGED, `ld` values apart) or read from memory where they
+// do not fit.
+template <typename Real, int MB, bool STAGED>
+struct DenseProduct {
+  static constexpr bool F32 = std::is_same<Real, float>::value;
+  typedef Real Frag __attribute__((ext_vector_type(4)));
+  typedef Real Frag16 __attribute__((ext_vector_type(4), aligned(16)));      // rows are 16-byte aligned
+  typedef Frag Acc;
+  struct Block { const NPFEM_GLOBAL Real* a; int cb, ns; };
+  struct Ends {};
+  const NPFEM_GLOBAL Real* A;
+  const NPFEM_GLOBAL Real* In;
+  NPFEM_GLOBAL Real* Out;
+  const NPFEM_LDS Real* stage;
+  int np, ld, n_rows, l16, kq;
+  __device__ Block block(int cb) const {
+    const bool in = cb < (np >> 4);
+    return Block{A + (size_t)(in ? cb : 0) * 16 * np, cb, in ? np >> 4 : 0};
+  }
+  __device__ Frag fetch(const Block& b, int s) const {
+    const int sc = max(min(s, b.ns - 1), 0);
+    return *reinterpret_cast<const NPFEM_GLOBAL Frag16*>(b.a + 16 * sc + (l16 * np + 4 * kq));
+  }
+  __device__ Frag rows(const Block& b, int s, int mb) const {
+    const int k = 16 * max(min(s, b.ns - 1), 0) + 4 * kq, r = mb * 16 + l16;
+    if constexpr (STAGED) return *reinterpret_cast<const NPFEM_LDS Frag16*>(stage + r * ld + k);
+    else return *reinterpret_cast<const NPFEM_GLOBAL Frag16*>(In + (min(r, n_rows - 1) * np + k));
+  }
+  __device__ Ends pre(const Block&) const { return Ends{}; }
+  __device__ void mma(Acc& c, const Frag& a, const Frag& b) const {
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acc[mb] = doublex4{0.0, 0.0, 0.0, 0.0};
-    const double* arow = A + (size_t)(n0 + l16) * np + 4 * kq;
-    for (int k0 = 0; k0 < np; k0 += 16) {
-      const doublex4 bq = *reinterpret_cast<const doublex4*>(arow + k0);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        if (mb < mb_n) {
-          const int r = mb * 16 + l16;
-          const doublex4 aq = r < rows ? *reinterpret_cast<const doublex4*>(In + (size_t)r * np + k0 + 4 * kq)
-                                       : doublex4{0.0, 0.0, 0.0, 0.0};
-          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.x, bq.x, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.y, bq.y, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.z, bq.z, acc[mb], 0, 0, 0);
-          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.w, bq.w, acc[mb], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      if (mb < mb_n) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = mb * 16 + 4 * i + kq;   // f64 result: slot i of lane l is row 4i + l/16
-          if (r < rows) Out[(size_t)r * np + n0 + l16] = acc[mb][i];
-        }
-      }
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (F32) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[k], c, 0, 0, 0);
+      else c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k], b[k], c, 0, 0, 0);
     }
   }
-}
+  __device__ void post(const Block& b, const Acc (&acc)[MB], const Ends&) const {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = mb * 16 + (F32 ? 4 * kq + i : 4 * i + kq);
+        if (r < n_rows) Out[(unsigned)(r * np + b.cb * 16 + l16)] = acc[mb][i];
+      }
+  }
+};
 
-// BF16 variant for FP32 plans: Out^T = In^T (diag(a) + A_off) with the off-diagonal part
-// A_off in BF16 on the matrix cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation) and
-// the diagonal applied exactly in FP32 in the epilogue.  In is rounded to BF16 on the
-// fly (8 consecutive k per lane, the same k order for both operands).
-__device__ inline void tile_gemm_bf16(const uint16_t* __restrict__ Abits, const float* __restrict__ diag,
-                                      int np, const float* __restrict__ In, float* __restrict__ Out,
-                                      int rows) {
-  const __bf16* A = reinterpret_cast<const __bf16*>(Abits);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int mb_n = (rows + 15) >> 4;
-  for (int nb = wave; nb < (np >> 4); nb += 4) {
-    const int n0 = nb << 4;
-    floatx4 acc[4];
+template <typename Real> constexpr int kDensePad = 16 / sizeof(Real);      // a row's LDS padding
+
+// Rows in LDS when `stage_bytes` hold them.
+template <typename Real>
+__device__ __attribute__((always_inline)) inline void dense_product(const Real* A, int np, const Real* In, Real* Out,
+                                                                    int rows, unsigned char* lds, int stage_bytes) {
+  const int mbn = (rows + 15) >> 4, ld = np + kDensePad<Real>;
+  const NPFEM_GLOBAL Real* Ig = (const NPFEM_GLOBAL Real*)In;
+  NPFEM_LDS Real* stage = (NPFEM_LDS Real*)(lds);
+  const bool staged = mbn * 16 * ld * (int)sizeof(Real) <= stage_bytes;
+  if (staged) {
+    typedef Real V __attribute__((ext_vector_type(kDensePad<Real>)));
+    constexpr int W = kDensePad<Real>, B = 4;
+    const int q = np / W, total = rows * q;
+    __syncthreads();
+    for (int e0 = tid(); e0 < total; e0 += B * kBlock) {
+      V v[B];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const __bf16* arow = A + (size_t)(n0 + l16) * np + 8 * kq;
-    for (int k0 = 0; k0 < np; k0 += 32) {
-      const bf16x8 bq = *reinterpret_cast<const bf16x8*>(arow + k0);
+      for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const NPFEM_GLOBAL V*>(Ig + W * min(e0 + u * kBlock, total - 1));
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        if (mb < mb_n) {
-          const int r = mb * 16 + l16;
-          bf16x8 aq;
-          if (r < rows) {
-            const floatx4 lo = *reinterpret_cast<const floatx4*>(In + (size_t)r * np + k0 + 8 * kq);
-            const floatx4 hi = *reinterpret_cast<const floatx4*>(In + (size_t)r * np + k0 + 8 * kq + 4);
-            aq = bf16x8{(__bf16)lo.x, (__bf16)lo.y, (__bf16)lo.z, (__bf16)lo.w,
-                        (__bf16)hi.x, (__bf16)hi.y, (__bf16)hi.z, (__bf16)hi.w};
-          } else {
-            aq = bf16x8{(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f,
-                        (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
-          }
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, bq, acc[mb], 0, 0, 0);
-        }
+      for (int u = 0; u < B; ++u) {
+        const int e = e0 + u * kBlock, r = e / q, c = e - r * q;
+        if (e < total) *reinterpret_cast<NPFEM_LDS V*>(stage + r * ld + W * c) = v[u];
       }
     }
-    const float dn = diag[n0 + l16];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      if (mb < mb_n) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = mb * 16 + 4 * kq + i;
-          if (r < rows) {
-            const size_t o = (size_t)r * np + n0 + l16;
-            Out[o] = acc[mb][i] + dn * In[o];
-          }
-        }
-      }
-    }
+    __syncthreads();
   }
+  const int lane = threadIdx.x & 63;
+  auto run = [&](auto mb, auto st, int r0) {
+    constexpr int MB = decltype(mb)::value;
+    const DenseProduct<Real, MB, decltype(st)::value> p{(const NPFEM_GLOBAL Real*)A, Ig + r0 * np, (NPFEM_GLOBAL Real*)Out + r0 * np,
+                                                        stage + r0 * ld, np, ld, rows - r0, lane & 15, lane >> 4};
+    stream_blocks<MB, sizeof(Real) == 4 ? 8 : 4, MB == 1 && sizeof(Real) == 4 ? 4 : 1>(p, np >> 4);
+  };
+  auto pairs = [&](auto st) {
+    for (int r0 = 0; r0 < rows; r0 += 32) {
+      if (rows - r0 > 16) run(std::integral_constant<int, 2>{}, st, r0);
+      else run(std::integral_constant<int, 1>{}, st, r0);
+    }
+  };
+  if (staged) pairs(std::true_type{});
+  else pairs(std::false_type{});
 }
 
 // n_pad up to which the whole k range of the staged BF16 product fits one chunk.
 constexpr int kStageMaxPad = 1024;
 
-// The same product with the tile's rows staged in LDS as BF16 (rows padded to 16), in
-// chunks of at most kc_max columns of k (one chunk when the rows fit the LDS region; a
-// chunk needs 16 ceil(rows/16) (kc + 8) BF16 of LDS at `stage`; the partial products of
-// later chunks are added to Out by the lane that wrote it), each wave carrying four
-// column blocks at a time, so that four independent B fragments are in flight per k step
-// and every A fragment read from LDS feeds four matrix instructions.
-// The off-diagonal part is stored in an order of the vertices (position k' holds vertex
-// perm[k']) and each 16-column block is applied over the k' range band[2 cb],
-// band[2 cb + 1] only: with inverse_bf16 = 2 a reverse Cuthill-McKee order, in which the
-// inverse's significant entries lie near the diagonal, and the range that holds them;
-// with inverse_bf16 = 1 the identity (perm null) and the whole range.  The input rows
-// are gathered through the permutation as they are staged, and each output column n' goes to vertex
-// perm[n'], with the exact FP32 diagonal of that vertex.  A wave's four column blocks
-// are consecutive, so their ranges nearly coincide; it runs over their union (the stored
-// matrix is zero outside each block's own range).
-__device__ inline void tile_gemm_bf16_band(const uint16_t* __restrict__ Abits, const float* __restrict__ diag,
-                                           const int* __restrict__ perm, const int* __restrict__ band, int np,
-                                           const float* __restrict__ In, float* __restrict__ Out, int rows,
-                                           __bf16* stage, int kc_max) {
-  const __bf16* A = reinterpret_cast<const __bf16*>(Abits);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int mb_n = (rows + 15) >> 4;
-  constexpr int NB = 4;
-  const int ncb = np >> 4;
+// BF16 product of FP32 plans: Out^T = In^T (diag(a) + A_off) with the off-diagonal part in
+// BF16 (v_mfma_f32_16x16x32_bf16, FP32 accumulation), stored operand by operand in an order of
+// the vertices (position k' holds vertex perm[k']) over each 16-column block's range of k'
+// (see MeshDev), and the diagonal applied exactly in FP32 in the epilogue.
+template <int MB>
+struct BandProduct {
+  typedef bf16x8 Frag;
+  typedef floatx4 Acc;
+  struct Block { const NPFEM_GLOBAL bf16x8* a; int ns, k, n; };   // n: the lane's vertex (column)
+  struct Ends { float d, in[MB][4]; };
+  const NPFEM_GLOBAL bf16x8* A;
+  const NPFEM_GLOBAL float* diag;
+  const NPFEM_GLOBAL int* perm;
+  const NPFEM_CONST intx4* band;
+  const NPFEM_GLOBAL float* In;
+  NPFEM_GLOBAL float* Out;
+  const NPFEM_LDS __bf16* stage;
+  int np, kb0, kc, n_rows, lane;
+  __device__ Block block(int cb) const {
+    Block b{A, 0, 0, 0};
+    if (cb < (np >> 4)) {
+      const intx4 r = band[cb];
+      const int lo = max(r.x, kb0), hi = min(r.y, kb0 + kc);       // this chunk's part
+      if (lo < hi) {
+        b.a = A + (size_t)(r.z + ((lo - r.x) >> 5)) * 64;
+        b.ns = (hi - lo) >> 5;
+        b.k = lo - kb0;
+      }
+      b.n = perm[(unsigned)(cb * 16 + (lane & 15))];
+    }
+    return b;
+  }
+  __device__ Frag fetch(const Block& b, int s) const { return b.a[max(min(s, b.ns - 1), 0) * 64 + lane]; }
+  __device__ Frag rows(const Block& b, int s, int mb) const {
+    const int k = b.k + 32 * max(min(s, b.ns - 1), 0) + 8 * (lane >> 4);
+    return *reinterpret_cast<const NPFEM_LDS bf16x8*>(stage + (mb * 16 + (lane & 15)) * (kc + 8) + k);
+  }
+  __device__ void mma(Acc& c, const Frag& a, const Frag& b) const {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+  __device__ Ends pre(const Block& b) const {
+    Ends e;
+    e.d = kb0 == 0 ? diag[(unsigned)b.n] : 1.f;                              // later chunks add to Out
+    const NPFEM_GLOBAL float* src = kb0 == 0 ? In : (const NPFEM_GLOBAL float*)Out;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e.in[mb][i] = src[(unsigned)(min(mb * 16 + 4 * (lane >> 4) + i, n_rows - 1) * np + b.n)];
+    return e;
+  }
+  __device__ void post(const Block& b, const Acc (&acc)[MB], const Ends& e) const {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = mb * 16 + 4 * (lane >> 4) + i;
+        if (r < n_rows) Out[(unsigned)(r * np + b.n)] = acc[mb][i] + e.d * e.in[mb][i];
+      }
+  }
+};
+
+// The rows are staged in LDS as BF16 (padded to 16 ceil(rows/16) with zeros), in chunks of at
+// most kc_max columns of k' (one chunk when they fit; a chunk needs 16 ceil(rows/16) (kc + 8)
+// BF16): read in the vectors' order and scattered into the product's, four vertices of four
+// rows per thread and turn (gathered in the product's order, each row's 4-byte reads took a
+// cache line per lane).
+__device__ __attribute__((always_inline)) inline void band_product(const uint16_t* A, const float* diag, const int* perm,
+                                                                   const int* iperm, const int* band, int np,
+                                                                   const float* In, float* Out, int rows,
+                                                                   unsigned char* lds, int kc_max) {
+  NPFEM_LDS __bf16* stage = (NPFEM_LDS __bf16*)(lds);
+  const NPFEM_GLOBAL float* Ig = (const NPFEM_GLOBAL float*)In;
+  const NPFEM_GLOBAL int* ip = (const NPFEM_GLOBAL int*)iperm;
+  const int mbn = (rows + 15) >> 4, lane = threadIdx.x & 63;
   for (int kb0 = 0; kb0 < np; kb0 += kc_max) {
     const int kc = min(kc_max, np - kb0);               // a multiple of 32
     const int ldk = kc + 8;
-    const int k8n = kc >> 3;
+    const int ng = np >> 2, total = ng * 4 * mbn;
+    constexpr int B = 3;
     __syncthreads();
-    if (perm) {                                         // gathered through the order
-#pragma unroll 4
-      for (int e = tid(); e < mb_n * 16 * k8n; e += kBlock) {
-        const int r = e / k8n, k8 = (e - r * k8n) << 3;
-        const int4 p0 = *reinterpret_cast<const int4*>(perm + kb0 + k8);
-        const int4 p1 = *reinterpret_cast<const int4*>(perm + kb0 + k8 + 4);
-        const float* row = In + (size_t)(r < rows ? r : 0) * np;
-        const float z = r < rows ? 1.f : 0.f;
-        const bf16x8 v = {(__bf16)(z * row[p0.x]), (__bf16)(z * row[p0.y]), (__bf16)(z * row[p0.z]),
-                          (__bf16)(z * row[p0.w]), (__bf16)(z * row[p1.x]), (__bf16)(z * row[p1.y]),
-                          (__bf16)(z * row[p1.z]), (__bf16)(z * row[p1.w])};
-        *reinterpret_cast<bf16x8*>(stage + r * ldk + k8) = v;
+    for (int e0 = tid(); e0 < total; e0 += B * kBlock) {
+      floatx4 v[B][4];
+      intx4 pos[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int e = min(e0 + u * kBlock, total - 1), rq = e / ng, g = e - rq * ng;
+        pos[u] = *reinterpret_cast<const NPFEM_GLOBAL intx4*>(ip + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          v[u][i] = *reinterpret_cast<const NPFEM_GLOBAL floatx4*>(Ig + (min(4 * rq + i, rows - 1) * np + 4 * g));
       }
-    } else {                                            // the identity order: 16-byte loads
-      for (int e = tid(); e < mb_n * 16 * k8n; e += kBlock) {
-        const int r = e / k8n, k8 = (e - r * k8n) << 3;
-        bf16x8 v;
-        if (r < rows) {
-          const floatx4 lo = *reinterpret_cast<const floatx4*>(In + (size_t)r * np + kb0 + k8);
-          const floatx4 hi = *reinterpret_cast<const floatx4*>(In + (size_t)r * np + kb0 + k8 + 4);
-          v = bf16x8{(__bf16)lo.x, (__bf16)lo.y, (__bf16)lo.z, (__bf16)lo.w,
-                     (__bf16)hi.x, (__bf16)hi.y, (__bf16)hi.z, (__bf16)hi.w};
-        } else {
-          v = bf16x8{(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f,
-                     (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int e = e0 + u * kBlock, rq = e / ng;
+        if (e >= total) continue;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int k = pos[u][w] - kb0;
+          if ((unsigned)k >= (unsigned)kc) continue;    // another chunk's
+#pragma unroll
+          for (int i = 0; i < 4; ++i) stage[(4 * rq + i) * ldk + k] = (__bf16)(4 * rq + i < rows ? v[u][i][w] : 0.f);
         }
-        *reinterpret_cast<bf16x8*>(stage + r * ldk + k8) = v;
       }
     }
     __syncthreads();
-    // one 16-row block of the tile at a time (a 5-cell tile has one): the accumulators of
-    // one row block by NB column blocks stay small next to the step's other live values
-    for (int mb = 0; mb < mb_n; ++mb) {
-      for (int g0 = NB * wave; g0 < ncb; g0 += 4 * NB) {
-        floatx4 acc[NB];
-        const __bf16* arow[NB];
-        bool valid[NB];
-        int lo = np, hi = 0;
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          const int cb = g0 + q;
-          valid[q] = cb < ncb;
-          arow[q] = A + (size_t)((valid[q] ? cb : 0) * 16 + l16) * np + kb0 + 8 * kq;
-          if (valid[q]) {
-            lo = min(lo, band[2 * cb]);
-            hi = max(hi, band[2 * cb + 1]);
-          }
-          acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-        const int k_lo = max(lo, kb0) - kb0, k_hi = min(hi, kb0 + kc) - kb0;   // this chunk's part
-        const __bf16* srow = stage + (mb * 16 + l16) * ldk + 8 * kq;
-        for (int k0 = k_lo; k0 < k_hi; k0 += 32) {
-          bf16x8 bq[NB];
-#pragma unroll
-          for (int q = 0; q < NB; ++q) bq[q] = *reinterpret_cast<const bf16x8*>(arow[q] + k0);
-          const bf16x8 aq = *reinterpret_cast<const bf16x8*>(srow + k0);
-#pragma unroll
-          for (int q = 0; q < NB; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, bq[q], acc[q], 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          if (!valid[q]) continue;
-          const int n = perm ? perm[(g0 + q) * 16 + l16] : (g0 + q) * 16 + l16;
-          const float dn = diag[n];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int r = mb * 16 + 4 * kq + i;
-            if (r < rows) {
-              const size_t o = (size_t)r * np + n;
-              Out[o] = acc[q][i] + (kb0 == 0 ? dn * In[o] : Out[o]);
-            }
-          }
-        }
-      }
+    auto run = [&](auto mb, int r0) {
+      constexpr int MB = decltype(mb)::value;
+      const BandProduct<MB> p{(const NPFEM_GLOBAL bf16x8*)A, (const NPFEM_GLOBAL float*)diag, (const NPFEM_GLOBAL int*)perm,
+                              (const NPFEM_CONST intx4*)band, Ig + r0 * np, (NPFEM_GLOBAL float*)Out + r0 * np,
+                              stage + r0 * ldk, np, kb0, kc, rows - r0, lane};
+      stream_blocks<MB, 8, MB == 1 ? 2 : 1>(p, np >> 4);
+    };
+    for (int r0 = 0; r0 < rows; r0 += 32) {
+      if (rows - r0 > 16) run(std::integral_constant<int, 2>{}, r0);
+      else run(std::integral_constant<int, 1>{}, r0);
     }
   }
 }
 
-// The tile's product with H~^-1 (which 0) or h^2 M~^-1 (which 1) in the plan's format.
+// The tile's product with H~^-1 (which 0) or h^2 M~^-1 (which 1) in the plan's format; M in
+// LDS; stage: the LDS from the cell vectors on; stage_k: see StepArgs.
 // Kept out of line: inlined into the step, its accumulators and staging add to the
 // register pressure of the whole iteration loop and the step kernel spills more.
 template <typename Real>
-__device__ __attribute__((noinline)) void tile_product(const MeshDev<Real>& M, const SolverDev& sol, int which, const Real* In,
-                                    Real* Out, int rows, unsigned char* stage, int stage_k) {
+__device__ __attribute__((noinline)) void tile_product(const MeshDev<Real>* mesh, int bf16, int which, const Real* In_,
+                                                       Real* Out_, int rows_, unsigned char* stage, int stage_k_) {
+  const NPFEM_LDS MeshDev<Real>* M = (const NPFEM_LDS MeshDev<Real>*)mesh;
+  const Real* In = uniform(In_);
+  Real* Out = uniform(Out_);
+  const int rows = uniform(rows_), stage_k = uniform(stage_k_), np = uniform(M->n_pad);
+  which = uniform(which);
   if constexpr (std::is_same<Real, float>::value) {
-    if (sol.bf16) {
-      const uint16_t* Ab = which == 0 ? M.hinv_bf : M.minv_bf;
-      const float* dg = which == 0 ? M.hinv_diag : M.minv_diag;
-      // staged (banded, or dense with the identity order); unstaged only for dense storage
-      // (the host guarantees stage_k >= 32 for banded storage)
-      if (stage_k >= 32)
-        tile_gemm_bf16_band(Ab, dg, M.bperm, M.bband + which * 2 * (M.n_pad >> 4), M.n_pad, In, Out, rows,
-                            reinterpret_cast<__bf16*>(stage), stage_k);
-      else
-        tile_gemm_bf16(Ab, dg, M.n_pad, In, Out, rows);
+    if (uniform(bf16)) {
+      band_product(uniform(which == 0 ? M->hinv_bf : M->minv_bf), uniform(which == 0 ? M->hinv_diag : M->minv_diag),
+                   uniform(M->bperm), uniform(M->biperm), uniform(M->bband) + which * 4 * (np >> 4), np, In, Out, rows,
+                   stage, stage_k);
       return;
     }
   }
-  tile_gemm(which == 0 ? M.hinv : M.minv, M.n_pad, In, Out, rows);
+  dense_product<Real>(uniform(which == 0 ? M->hinv : M->minv), np, In, Out, rows, stage, stage_k);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1385,7 +1430,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
   // and b in the workspace, 2 x_n and u too; below it the placement is known at compile
   // time and every access to these vectors is an LDS instruction)
   const bool vl = LAY == 0 || M.vec_lds != 0, xl = LAY < 2 || M.xu_lds != 0;
-  unsigned char* stage = lds + kLdsHeader;                   // BF16 staging of the tile product
+  unsigned char* stage = lds + kLdsHeader;                   // the tile products' rows
   Real* xn = xl ? reinterpret_cast<Real*>(lds + kLdsHeader) : W + (size_t)A.n_vec_slot * A.tile_cells_max * 3 * np;
   Real* ut = xn + 3 * np;
   Real* gl = ut + 3 * np;
@@ -1434,7 +1479,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     __syncthreads();
   }
   if (!A.u_guess) {
-    tile_product(M, A.sol, 1, tl.mat(VB), tl.mat(VU), 3 * cnt, stage, A.stage_k);                                              // u = h^2 M~^-1 b
+    tile_product(Ml, A.sol.bf16, 1, tl.mat(VB), tl.mat(VU), 3 * cnt, stage, A.stage_k);                                              // u = h^2 M~^-1 b
     __syncthreads();
     if (A.guess_only) {
       for (int j = 0; j < cnt; ++j) {
@@ -1527,7 +1572,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     }
     __syncthreads();
     if (sint[1] == 0) break;
-    tile_product(M, A.sol, 0, tl.mat(VQ), tl.mat(VD), 3 * cnt, stage, A.stage_k);                                              // r = H~^-1 q
+    tile_product(Ml, A.sol.bf16, 0, tl.mat(VQ), tl.mat(VD), 3 * cnt, stage, A.stage_k);                                              // r = H~^-1 q
     __syncthreads();
     for (int j = 0; j < cnt; ++j) {
       auto& cs = CS[j];
@@ -1928,23 +1973,17 @@ template <typename Real>
 __global__ void __launch_bounds__(kBlock) apply_inverse_kernel(const Real* A, int np, const Real* in,
                                                                Real* out, int rows) {
   const int r0 = blockIdx.x * 48;
-  tile_gemm(A, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0));
+  dense_product<Real>(A, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0), nullptr, 0);
 }
 
 // 48 rows per workgroup, staged in LDS in chunks of kc columns (48 (kc + 8) BF16).
 __global__ void __launch_bounds__(kBlock) apply_inverse_band_kernel(const uint16_t* A, const float* diag,
-                                                                    const int* perm, const int* band, int np,
-                                                                    const float* in, float* out, int rows, int kc) {
+                                                                    const int* perm, const int* iperm, const int* band,
+                                                                    int np, const float* in, float* out, int rows,
+                                                                    int kc) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int r0 = blockIdx.x * 48;
-  tile_gemm_bf16_band(A, diag, perm, band, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0),
-                      reinterpret_cast<__bf16*>(lds), kc);
-}
-
-__global__ void __launch_bounds__(kBlock) apply_inverse_bf16_kernel(const uint16_t* A, const float* diag, int np,
-                                                                    const float* in, float* out, int rows) {
-  const int r0 = blockIdx.x * 48;
-  tile_gemm_bf16(A, diag, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0));
+  band_product(A, diag, perm, iperm, band, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0), lds, kc);
 }
 
 template <typename Real>
@@ -2068,6 +2107,8 @@ hipError_t launch_stats_reset(npfem_stats_total* tot, hipStream_t s) {
   return hipGetLastError();
 }
 
+int lds_header() { return kLdsHeader; }
+
 // k columns of the BF16 tile product staged per chunk: what the LDS region of `lds`
 // bytes holds for stage_rows rows (a multiple of 32, capped at n_pad; 0: not staged).
 int stage_cols(size_t lds, int stage_rows, int n_pad) {
@@ -2077,6 +2118,11 @@ int stage_cols(size_t lds, int stage_rows, int n_pad) {
   return (int)(k32 >= n_pad ? n_pad : (k32 >= 32 ? k32 : 0));
 }
 #endif
+
+template <typename Real>
+size_t dense_stage_lds(int n_pad, int rows) {
+  return kLdsHeader + (size_t)(rows + 15) / 16 * 16 * (n_pad + kDensePad<Real>) * sizeof(Real);
+}
 
 template <typename Real>
 size_t lds_bytes(int n_pad, int chunk, int stage_rows, int vec_lds, int xu_lds) {
@@ -2189,21 +2235,14 @@ hipError_t launch_apply_inverse(const Real* A, int n_pad, const Real* in, Real* 
 }
 
 #if !defined(NPFEM_PART) || NPFEM_PART == 1
-hipError_t launch_apply_inverse_band(const uint16_t* A, const float* diag, const int* perm, const int* band,
-                                     int n_pad, const float* in, float* out, int rows, hipStream_t s) {
+hipError_t launch_apply_inverse_band(const uint16_t* A, const float* diag, const int* perm, const int* iperm,
+                                     const int* band, int n_pad, const float* in, float* out, int rows,
+                                     hipStream_t s) {
   (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
   const int kc = std::min(n_pad, (65536 / (2 * 48) - 8) / 32 * 32);
   const size_t lds = (size_t)48 * (kc + 8) * 2;
-  hipLaunchKernelGGL(apply_inverse_band_kernel, dim3((rows + 47) / 48), dim3(kBlock), lds, s, A, diag, perm, band,
+  hipLaunchKernelGGL(apply_inverse_band_kernel, dim3((rows + 47) / 48), dim3(kBlock), lds, s, A, diag, perm, iperm, band,
                      n_pad, in, out, rows, kc);
-  return hipGetLastError();
-}
-
-hipError_t launch_apply_inverse_bf16(const uint16_t* A, const float* diag, int n_pad, const float* in,
-                                     float* out, int rows, hipStream_t s) {
-  (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
-  hipLaunchKernelGGL(apply_inverse_bf16_kernel, dim3((rows + 47) / 48), dim3(kBlock), 0, s, A, diag, n_pad, in,
-                     out, rows);
   return hipGetLastError();
 }
 #endif
@@ -2220,7 +2259,8 @@ hipError_t launch_drag(const Real* x, const Real* v, const int64_t* cell_voff, c
 }
 
 #define NPFEM_INSTANTIATE(R)                                                                       \
-  template size_t lds_bytes<R>(int, int, int, int, int);                                                     \
+  template size_t lds_bytes<R>(int, int, int, int, int);                                           \
+  template size_t dense_stage_lds<R>(int, int);                                                    \
   template hipError_t set_lds_limit<R>(size_t);                                                    \
   template hipError_t occupancy<R>(int*, size_t);                                                  \
   template hipError_t launch_step<R>(const StepArgs<R>&, int, size_t, hipStream_t, int*);          \
