@@ -208,8 +208,8 @@ npfem_status npfem_batch_create(npfem_plan *plan, int64_t n_cells, const int32_t
 void npfem_batch_destroy(npfem_batch *batch);
 
 /*
- * Schedule of a batch: cells_per_tile (1..21) cells share one product with H~^-1 on the
- * matrix cores and one workgroup; lbfgs_m (0..8) is the L-BFGS history length used by
+ * Schedule of a batch: up to cells_per_tile (1..21) cells share one product with H~^-1 on
+ * the matrix cores and one workgroup; lbfgs_m (0..8) is the L-BFGS history length used by
  * this batch (the solution does not depend on either, only the time to reach it).
  * npfem_batch_schedule rebuilds the tile queue and workspace (synchronously; no step of
  * this batch may be in flight); npfem_batch_get_schedule reports the current one
@@ -222,8 +222,8 @@ npfem_status npfem_batch_get_schedule(const npfem_batch *batch, int32_t *cells_p
 /*
  * Autotuner: times one step of the batch on the caller's inputs for each candidate
  * schedule (cells_per_tile in {5, 10, 16, 21}, and also 2 and 3 when the batch has fewer
- * than 10 cells per compute unit, so that its tiles can occupy every workgroup slot;
- * lbfgs_m in {2, 3, 5, 8} up to max_lbfgs_m) and keeps the fastest.  x, v, f_ext: device inputs as for npfem_step;
+ * than 10 cells per compute unit; where fewer cells per tile than that keep more workgroups
+ * busy, the tiles are cut accordingly, which n_tiles shows; lbfgs_m in {2, 3, 5, 8} up to max_lbfgs_m) and keeps the fastest.  x, v, f_ext: device inputs as for npfem_step;
  * x_scratch, v_scratch: device [V_total][3] outputs it may overwrite.  Synchronous.
  * best_ms (may be NULL) receives the best step time in milliseconds.
  */
@@ -308,12 +308,12 @@ npfem_status npfem_step_contacts(npfem_batch *batch, const void *x, const void *
  * forbid hipMalloc.  Same arguments, results and per-cell statistics as npfem_step
  * (bit for bit), launched directly on `stream` (never through the batch's graphs).
  * The tile counter, the cell states and the persistent workgroups' workspace live in a
- * static device array of 64 MiB per GPU, allocated when the library's code is loaded on
+ * static device array of 67 MiB per GPU, allocated when the library's code is loaded on
  * that GPU and held until the process ends; its address is looked up when the first
  * plan on the GPU is created.  The persistent grid is reduced to the workgroups whose
  * workspace fits the array (a 642-vertex FP32 batch at 5 cells per tile and history 2
- * keeps about 180 workgroups).  NPFEM_E_UNSUPPORTED if a single workgroup's workspace
- * exceeds 64 MiB.  Every call on a GPU shares that GPU's array: calls that overlap on
+ * keeps about 170 workgroups).  NPFEM_E_UNSUPPORTED if a single workgroup's workspace
+ * exceeds 67 MiB.  Every call on a GPU shares that GPU's array: calls that overlap on
  * one GPU (on different streams, or from several threads) race and must not be issued.
  */
 npfem_status npfem_step_noalloc(npfem_batch *batch, const void *x, const void *v, const void *f_ext,

@@ -13,6 +13,7 @@
 #include <thread>
 #include <type_traits>
 #include <unordered_map>
+#include <queue>
 #include <vector>
 
 #include "npfem.h"
@@ -966,7 +967,9 @@ struct npfem_batch {
   const int* mesh_n = nullptr;
   void* eval_scratch = nullptr;
   // schedule: tiling, history length and workspace (rebuilt by the autotuner)
-  int T = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1;
+  // T: cells per tile; T_set: as asked for or chosen, which T falls short of where the cells are
+  // spread over idle workgroups (spread: chosen by the library)
+  int T = 0, T_set = 0, spread = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1;
   size_t lds = 0;
   int64_t slot_stride = 0;
   DeviceBuffers sched;
@@ -1141,16 +1144,75 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
   return NPFEM_OK;
 }
 
-npfem_status schedule(npfem_batch* b, int T, int m) {
-  return b->plan->precision == NPFEM_FP64 ? batch_schedule<double>(b, T, m) : batch_schedule<float>(b, T, m);
+// Cells per tile (at most T_max) for which the batch's tiles are expected to be done first.
+// A tile's cells run one after the other on its workgroup, so few large tiles leave workgroups
+// idle and a last part-filled round of them costs a whole one, while small tiles share a product
+// among fewer cells.  The tile queue is played through with a tile's time taken as its cells'
+// (in proportion to the vertices) plus its product's: measured at 642 vertices, a product of up
+// to 16 rows takes 0.4 of a cell's round in FP32 and about 0.9 in FP64 (where the matrix
+// cores bound it, so every further 16 rows take as much again; in FP32 0.4 of it).  From four
+// rounds on the tail weighs little and the sharing decides: such sizes are not looked at.
+// Against at least five per tile (two for a tuned batch): 37 cells of 642 vertices 386 -> 256 us
+// (one per tile), 2000 with contacts 6.46 -> 5.66 ms (four), 1024 in FP64 6.8 -> 5.2 ms (four),
+// 3000 of 258 vertices 1585 -> 1242 us (six).
+int spread_tile(const npfem_batch* b, int T_max) {
+  const npfem_plan* p = b->plan;
+  const bool fp64 = p->precision == NPFEM_FP64;
+  const int nm = (int)p->meshes.size();
+  std::vector<int> order;
+  for (int i = 0; i < nm; ++i)
+    if (!b->by_mesh[i].empty()) order.push_back(i);
+  std::sort(order.begin(), order.end(), [&](int a, int c) { return p->meshes[a].mesh->n > p->meshes[c].mesh->n; });
+  auto slots_of = [&](int T) {
+    if (p->prm.grid_blocks > 0) return p->prm.grid_blocks;
+    size_t lds = 0;
+    for (int mi : order) {
+      const MeshPlan& mp = p->meshes[mi];
+      const int rows = p->prm.inverse_bf16 && !fp64 ? (3 * T + 15) / 16 * 16 : 0;
+      lds = std::max(lds, fp64 ? lds_bytes<double>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds)
+                               : lds_bytes<float>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds));
+    }
+    return p->cu_count * (lds <= kTwoPerCu ? 2 : 1);
+  };
+  int best = T_max;
+  double best_t = 1e300;
+  for (int T = T_max; T >= 1; --T) {
+    const int slots = slots_of(T);
+    if (b->n_cells > (int64_t)4 * slots * T) break;
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    double end = 0.0;
+    for (int mi : order) {
+      const int64_t nc = (int64_t)b->by_mesh[mi].size();
+      for (int64_t c0 = 0; c0 < nc; c0 += T) {
+        const int cnt = (int)std::min<int64_t>(T, nc - c0), blocks = (3 * cnt + 15) / 16;
+        const double t = p->meshes[mi].n_pad * (cnt + (fp64 ? 0.9 * blocks : 0.4 + 0.16 * (blocks - 1)));
+        double start = 0.0;
+        if ((int)free_at.size() == slots) {
+          start = free_at.top();
+          free_at.pop();
+        }
+        free_at.push(start + t);
+        end = std::max(end, start + t);
+      }
+    }
+    if (end < best_t) {
+      best_t = end;
+      best = T;
+    }
+  }
+  return best;
 }
 
-int default_tile(const npfem_batch* b) {
-  // as many cells per tile as keep every compute unit busy (the matrix product runs 3T
-  // rows; T = 5, 10, 16 fill 16, 32, 48 rows)
-  const int64_t want = 2 * (int64_t)b->plan->cu_count;
-  return b->n_cells / 16 >= want ? 16 : (b->n_cells / 10 >= want ? 10 : 5);
+npfem_status schedule(npfem_batch* b, int T, int m, int spread) {
+  const int Tt = spread ? spread_tile(b, T) : T;
+  const npfem_status s = b->plan->precision == NPFEM_FP64 ? batch_schedule<double>(b, Tt, m) : batch_schedule<float>(b, Tt, m);
+  b->T_set = T;
+  b->spread = spread;
+  return s;
 }
+
+// Tiles of up to 16 cells (48 rows of a product) where they keep every workgroup busy.
+constexpr int kTileDefault = 16;
 
 }  // namespace
 
@@ -1189,8 +1251,8 @@ npfem_status npfem_batch_create(npfem_plan* p, int64_t n_cells, const int32_t* c
   if ((s = b->buf.upload(voff.data(), voff.size(), &b->cell_voff))) return s;
   if ((s = b->buf.upload(cm.data(), cm.size(), &b->cell_mesh))) return s;
   if ((s = b->buf.upload(mesh_n.data(), mesh_n.size(), &b->mesh_n))) return s;
-  const int T = p->prm.cells_per_tile > 0 ? p->prm.cells_per_tile : default_tile(b.get());
-  if ((s = schedule(b.get(), T, p->prm.lbfgs_m))) return s;
+  const int T = p->prm.cells_per_tile > 0 ? p->prm.cells_per_tile : spread_tile(b.get(), kTileDefault);
+  if ((s = schedule(b.get(), T, p->prm.lbfgs_m, 0))) return s;
   if (n_vert_out) *n_vert_out = v;
   *out = b.release();
   return NPFEM_OK;
@@ -1474,13 +1536,13 @@ npfem_status npfem_batch_schedule(npfem_batch* b, int32_t cells_per_tile, int32_
   if (cells_per_tile < 1 || cells_per_tile > kMaxTile) return fail(NPFEM_E_INVALID, "batch_schedule: cells_per_tile must be in [1, 21]");
   if (lbfgs_m < 0 || lbfgs_m > kMaxHistory) return fail(NPFEM_E_INVALID, "batch_schedule: lbfgs_m must be in [0, 8]");
   HIP_TRY(hipSetDevice(b->plan->device));
-  return schedule(b, cells_per_tile, lbfgs_m);
+  return schedule(b, cells_per_tile, lbfgs_m, b->spread && cells_per_tile == b->T_set);
 }
 
 npfem_status npfem_batch_get_schedule(const npfem_batch* b, int32_t* cells_per_tile, int32_t* lbfgs_m,
                                       int32_t* grid_blocks, int32_t* n_tiles) {
   if (!b) return fail(NPFEM_E_INVALID, "batch_get_schedule: NULL batch");
-  if (cells_per_tile) *cells_per_tile = b->T;
+  if (cells_per_tile) *cells_per_tile = b->T_set;
   if (lbfgs_m) *lbfgs_m = b->m;
   if (grid_blocks) *grid_blocks = b->grid;
   if (n_tiles) *n_tiles = b->n_tiles;
@@ -1499,34 +1561,42 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   double best = 1e300;
-  const int T0 = b->T, m0 = b->m;
-  int bT = T0, bm = m0;
-  // tiles of 2 or 3 cells only for batches that leave workgroups idle at 5 cells per tile
+  const int T0 = b->T_set, m0 = b->m, spread0 = b->spread;
+  int bT = T0, bm = m0, bs = spread0;
+  // tiles of 2 or 3 cells only for batches that leave workgroups idle at 5 cells per tile; each
+  // size spread over idle workgroups and as it is, every resulting tile size once
   const int Ts[] = {2, 3, 5, 10, 16, 21};
   const int ms[] = {2, 3, 5, 8};
   const bool small = b->n_cells < 5 * 2 * (int64_t)b->plan->cu_count;
   npfem_status st = NPFEM_OK;
+  std::vector<int> tried;
   for (int T : Ts) {
     if (T < 5 && !small) continue;
     if ((int64_t)T > b->n_cells && T != 5) continue;
-    for (int m : ms) {
-      if (m > max_lbfgs_m && !(m == 2 && max_lbfgs_m < 2)) continue;
-      const int mm = std::min(m, max_lbfgs_m);
-      if ((st = schedule(b, T, mm))) break;
-      // one step to warm up, one timed
-      if ((st = launch_step_now(b, x, v, f, x_scratch, v_scratch, nullptr, nullptr, s))) break;
-      (void)hipEventRecord(e0, s);
-      if ((st = launch_step_now(b, x, v, f, x_scratch, v_scratch, nullptr, nullptr, s))) break;
-      (void)hipEventRecord(e1, s);
-      if (hipEventSynchronize(e1) != hipSuccess) { st = fail(NPFEM_E_HIP, "batch_autotune: event sync failed"); break; }
-      float ms_ = 0.f;
-      (void)hipEventElapsedTime(&ms_, e0, e1);
-      if (ms_ < best) {
-        best = ms_;
-        bT = T;
-        bm = mm;
+    for (int sp = 1; sp >= 0 && !st; --sp) {
+      const int Tt = sp ? spread_tile(b, T) : T;
+      if (std::find(tried.begin(), tried.end(), Tt) != tried.end()) continue;
+      tried.push_back(Tt);
+      for (int m : ms) {
+        if (m > max_lbfgs_m && !(m == 2 && max_lbfgs_m < 2)) continue;
+        const int mm = std::min(m, max_lbfgs_m);
+        if ((st = schedule(b, T, mm, sp))) break;
+        // one step to warm up, one timed
+        if ((st = launch_step_now(b, x, v, f, x_scratch, v_scratch, nullptr, nullptr, s))) break;
+        (void)hipEventRecord(e0, s);
+        if ((st = launch_step_now(b, x, v, f, x_scratch, v_scratch, nullptr, nullptr, s))) break;
+        (void)hipEventRecord(e1, s);
+        if (hipEventSynchronize(e1) != hipSuccess) { st = fail(NPFEM_E_HIP, "batch_autotune: event sync failed"); break; }
+        float ms_ = 0.f;
+        (void)hipEventElapsedTime(&ms_, e0, e1);
+        if (ms_ < best) {
+          best = ms_;
+          bT = T;
+          bm = mm;
+          bs = sp;
+        }
+        if (mm != m) break;
       }
-      if (mm != m) break;
     }
     if (st) break;
   }
@@ -1535,12 +1605,12 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
   b->use_graph = use_graph;
   if (st) {
     const std::string msg = g_err;
-    (void)schedule(b, T0, m0);               // leave the batch on the schedule it had
+    (void)schedule(b, T0, m0, spread0);      // leave the batch on the schedule it had
     g_err = msg;
     return st;
   }
   if (best_ms) *best_ms = best;
-  return schedule(b, bT, bm);
+  return schedule(b, bT, bm, bs);
 }
 
 npfem_status npfem_stats_accumulate(const npfem_cell_stats* st, int64_t n, npfem_stats_total* tot, void* stream) {

@@ -60,3 +60,15 @@ def test_step_is_the_same_for_every_tile_size(mesh, precision, bf16):
         if ref is not None:
             assert torch.equal(xo, ref[0]) and torch.equal(vo, ref[1]), tile
         ref = (xo, vo)
+
+
+@pytest.mark.parametrize("precision,cells,tile,tiles", [("fp32", 3, 1, 3), ("fp64", 3, 1, 3), ("fp32", 1100, 3, 367),
+                                                        ("fp64", 1000, 4, 250)])
+def test_default_tiles_fill_the_workgroups(precision, cells, tile, tiles):
+    """Few cells are spread over the workgroups (two per compute unit in FP32, one for an
+    FP64 batch of 642 vertices; 256 units); an explicit size is kept."""
+    from paper_1903_06479_amd import Batch
+    X, Tr = mesh_of("642")
+    batch = Batch(make([(X, Tr)], precision, inverse_bf16=2 if precision == "fp32" else 0), np.zeros(cells, np.int32))
+    assert batch.schedule()["cells_per_tile"] == tile and batch.schedule()["n_tiles"] == tiles
+    assert batch.schedule(cells_per_tile=5)["n_tiles"] == (cells + 4) // 5
