@@ -18,6 +18,7 @@ SOURCES = ["npfem_host.cpp", "npfem_kernels.hip", "npfem_net.hip", "npfem_collid
 UNITS = [
     ("kernels64", "npfem_kernels.hip", ["-DNPFEM_PART=2"]),
     ("kernels32", "npfem_kernels.hip", ["-DNPFEM_PART=1"]),
+    ("kernels32w", "npfem_kernels.hip", ["-DNPFEM_PART=3"]),
     ("net", "npfem_net.hip", []),
     ("collide", "npfem_collide.hip", []),
     ("factor", "npfem_factor.hip", []),

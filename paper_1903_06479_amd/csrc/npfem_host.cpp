@@ -664,10 +664,11 @@ npfem_status upload_mesh(npfem_plan* p, MeshPlan& mp, const std::vector<double>&
     nbd = std::max(nbd, m->nb_ptr[i + 1] - m->nb_ptr[i]);
     vcd = std::max(vcd, m->vc_ptr[i + 1] - m->vc_ptr[i]);
   }
-  std::vector<int> nbe((size_t)nbd * np), vce((size_t)vcd * np, -1);
-  std::vector<Real> nbwe((size_t)nbd * np, Real(0));
+  const int nbs = round_up(nbd, kEllGroup), vcs = round_up(vcd, kEllGroup);
+  std::vector<int> nbe((size_t)nbs * np), vce((size_t)vcs * np, -1);
+  std::vector<Real> nbwe((size_t)nbs * np, Real(0));
   for (int i = 0; i < np; ++i)
-    for (int q = 0; q < nbd; ++q) nbe[(size_t)q * np + i] = i < n ? i : 0;
+    for (int q = 0; q < nbs; ++q) nbe[(size_t)q * np + i] = i < n ? i : 0;
   for (int i = 0; i < n; ++i) {
     for (int q = m->nb_ptr[i]; q < m->nb_ptr[i + 1]; ++q) {
       const size_t o = (size_t)(q - m->nb_ptr[i]) * np + i;
@@ -969,7 +970,7 @@ struct npfem_batch {
   // schedule: tiling, history length and workspace (rebuilt by the autotuner)
   // T: cells per tile; T_set: as asked for or chosen, which T falls short of where the cells are
   // spread over idle workgroups (spread: chosen by the library)
-  int T = 0, T_set = 0, spread = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1;
+  int T = 0, T_set = 0, spread = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1, wide = 0;
   size_t lds = 0;
   int64_t slot_stride = 0;
   DeviceBuffers sched;
@@ -1048,6 +1049,26 @@ StepArgs<Real> make_args(npfem_batch* b) {
   return a;
 }
 
+// The step's kernels by workgroup size: FP32 plans have both, FP64 plans the wide one.
+template <typename Real>
+hipError_t step_occupancy(int wide, int* per_cu, size_t lds) {
+  if constexpr (std::is_same<Real, float>::value)
+    if (!wide) return occupancy<Real, kNarrow>(per_cu, lds);
+  return occupancy<Real, kWide>(per_cu, lds);
+}
+template <typename Real>
+hipError_t step_lds_limit(size_t lds) {
+  if constexpr (std::is_same<Real, float>::value)
+    if (hipError_t e = set_lds_limit<Real, kNarrow>(lds)) return e;
+  return set_lds_limit<Real, kWide>(lds);
+}
+template <typename Real>
+hipError_t step_launch(const StepArgs<Real>& a, int wide, int grid, size_t lds, hipStream_t s, int* counter) {
+  if constexpr (std::is_same<Real, float>::value)
+    if (!wide) return launch_step<Real, kNarrow>(a, grid, lds, s, counter);
+  return launch_step<Real, kWide>(a, grid, lds, s, counter);
+}
+
 // (Re)build the schedule for T cells per tile and history length m: the tile list
 // (cells of one mesh type, largest meshes first since the cost grows like n^2), the
 // LDS size, the persistent grid and the workspace.
@@ -1098,16 +1119,23 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
     }
     b->stage_k = (int)(lds - lds_header());
   }
+  // eight waves for a workgroup that has a CU to itself
+  {
+    HIP_TRY(step_lds_limit<Real>(lds));
+    int per = 0;
+    HIP_TRY(step_occupancy<Real>(0, &per, lds));
+    b->wide = std::is_same<Real, double>::value || per < 2 || b->n_tiles <= p->cu_count;
+  }
   // the tile's cell states go to LDS (after everything else) when they fit the LDS a
   // workgroup may have and cost no workgroups per CU
   {
     const size_t base = (lds + 15) / 16 * 16, with_cs = base + (size_t)T * cell_state_bytes(m);
     b->cs_lds = -1;
     if (with_cs <= kStepLdsCap) {
-      HIP_TRY(set_lds_limit<Real>(with_cs));
+      HIP_TRY(step_lds_limit<Real>(with_cs));
       int per_base = 0, per_cs = 0;
-      HIP_TRY(occupancy<Real>(&per_base, lds));
-      HIP_TRY(occupancy<Real>(&per_cs, with_cs));
+      HIP_TRY(step_occupancy<Real>(b->wide, &per_base, lds));
+      HIP_TRY(step_occupancy<Real>(b->wide, &per_cs, with_cs));
       if (per_cs >= per_base && per_cs > 0) {
         b->cs_lds = (int)base;
         lds = with_cs;
@@ -1115,9 +1143,9 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
     }
   }
   b->lds = lds;
-  HIP_TRY(set_lds_limit<Real>(lds));
+  HIP_TRY(step_lds_limit<Real>(lds));
   int per_cu = 0;
-  HIP_TRY(occupancy<Real>(&per_cu, lds));
+  HIP_TRY(step_occupancy<Real>(b->wide, &per_cu, lds));
   if (per_cu < 1) return fail(NPFEM_E_UNSUPPORTED, "batch: step kernel does not fit on a compute unit");
   const int slots = p->cu_count * per_cu;
   b->grid = p->prm.grid_blocks > 0 ? p->prm.grid_blocks : slots;
@@ -1172,7 +1200,7 @@ int spread_tile(const npfem_batch* b, int T_max) {
       lds = std::max(lds, fp64 ? lds_bytes<double>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds)
                                : lds_bytes<float>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds));
     }
-    return p->cu_count * (lds <= kTwoPerCu ? 2 : 1);
+    return p->cu_count * (!fp64 && lds <= kTwoPerCu ? 2 : 1);
   };
   int best = T_max;
   double best_t = 1e300;
@@ -1286,7 +1314,7 @@ npfem_status launch_step_now(npfem_batch* b, const void* x, const void* v, const
     a.x_out = static_cast<double*>(x_out);
     a.v_out = static_cast<double*>(v_out);
     a.stats = stats;
-    HIP_TRY(launch_step<double>(a, b->grid, b->lds, s, b->counter));
+    HIP_TRY(step_launch<double>(a, b->wide, b->grid, b->lds, s, b->counter));
   } else {
     auto a = make_args<float>(b);
     a.col_q = static_cast<const float*>(col_q);
@@ -1301,7 +1329,7 @@ npfem_status launch_step_now(npfem_batch* b, const void* x, const void* v, const
     a.x_out = static_cast<float*>(x_out);
     a.v_out = static_cast<float*>(v_out);
     a.stats = stats;
-    HIP_TRY(launch_step<float>(a, b->grid, b->lds, s, b->counter));
+    HIP_TRY(step_launch<float>(a, b->wide, b->grid, b->lds, s, b->counter));
   }
   return NPFEM_OK;
 }
@@ -1492,7 +1520,7 @@ npfem_status npfem_step_noalloc(npfem_batch* b, const void* x, const void* v, co
     a.x_out = static_cast<double*>(x_out);
     a.v_out = static_cast<double*>(v_out);
     a.stats = stats;
-    HIP_TRY(launch_step<double>(a, grid, b->lds, s, counter));
+    HIP_TRY(step_launch<double>(a, b->wide, grid, b->lds, s, counter));
   } else {
     auto a = make_args<float>(b);
     a.tile_counter = counter;
@@ -1505,7 +1533,7 @@ npfem_status npfem_step_noalloc(npfem_batch* b, const void* x, const void* v, co
     a.x_out = static_cast<float*>(x_out);
     a.v_out = static_cast<float*>(v_out);
     a.stats = stats;
-    HIP_TRY(launch_step<float>(a, grid, b->lds, s, counter));
+    HIP_TRY(step_launch<float>(a, b->wide, grid, b->lds, s, counter));
   }
   return NPFEM_OK;
 }

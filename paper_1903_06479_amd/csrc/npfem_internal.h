@@ -8,8 +8,10 @@
 namespace npfem {
 
 constexpr int kBlock = 256;        // threads per workgroup (4 wave64)
+constexpr int kNarrow = 256, kWide = 512;   // threads of a step workgroup: two or one per CU
 constexpr int kMaxHistory = 8;     // L-BFGS pairs
 constexpr int kMaxTile = 21;       // cells per tile: 3*21 = 63 rows <= 4 MFMA row blocks
+constexpr int kEllGroup = 6;       // entries of a vertex's ELL lists fetched together
 constexpr int kTerms = 11;         // objective terms reported by npfem_eval
 
 // Rest data of one mesh type on the device (precision Real).
@@ -29,7 +31,8 @@ struct MeshDev {
   const int* nb_ptr;           // [n+1] vertex -> neighbours
   const int* nb_idx;
   const Real* nb_w;            // cotangent weight (cot a + cot b)/2 of each neighbour edge
-  int nb_deg, vc_deg;          // padded widths of the ELL lists below (max degree / valence)
+  int nb_deg, vc_deg;          // widths of the ELL lists below (max degree / valence); they are stored
+                               // up to the next multiple of kEllGroup, filled with padding
   const int* nb_ell;           // [nb_deg][n_pad] neighbour of vertex i (i itself as padding)
   const Real* nbw_ell;         // [nb_deg][n_pad] its cotangent weight (0 as padding)
   const int* vc_ell;           // [vc_deg][n_pad] incident corner 3t + k (-1 as padding)
@@ -162,7 +165,7 @@ hipError_t launch_collide(const CollideArgs<Real>& a, int n_cells, int64_t n_ver
 int collide_scan_blocks(int64_t table);
 
 // Launch wrappers (npfem_kernels.hip).
-template <typename Real>
+template <typename Real, int NT>
 hipError_t launch_step(const StepArgs<Real>& a, int grid, size_t lds, hipStream_t s, int* counter);
 template <typename Real>
 hipError_t launch_eval(const StepArgs<Real>& a, int n_cells, const Real* u, Real* grad,
@@ -194,9 +197,9 @@ int stage_cols(size_t lds, int stage_rows, int n_pad);
 template <typename Real>
 size_t dense_stage_lds(int n_pad, int rows);
 int lds_header();
-template <typename Real>
+template <typename Real, int NT>
 hipError_t set_lds_limit(size_t bytes);
-template <typename Real>
+template <typename Real, int NT>
 hipError_t occupancy(int* blocks_per_cu, size_t lds);
 
 }  // namespace npfem

@@ -35,18 +35,27 @@ template <typename Real> struct Eps;
 template <> struct Eps<float> { static constexpr double v = 1.1920928955078125e-07; };
 template <> struct Eps<double> { static constexpr double v = 2.220446049250313e-16; };
 
-// LDS: [red: 2 buffers x 4 waves x 16 doubles][ints: 32][mesh descriptor][cell vectors ...];
-// during the BF16 tile product the region from the cell vectors on holds the tile's rows
-// in BF16.  The current tile's mesh descriptor is copied to LDS so that reading its table
-// pointers waits on the LDS counter only, never on global loads in flight.
-constexpr int kSumMax = 16;                     // values per workgroup sum
-constexpr int kRedDoubles = 4 * kSumMax;        // one buffer
-constexpr int kMeshLds = 256;
+// Threads of a step workgroup.  The step runs at two waves per SIMD (256 registers; at 128 it
+// spills, and the evaluation is bound by instructions issued, not by latency): four waves where
+// the LDS holds two workgroups per CU (FP32 meshes to about 650 vertices), eight where one has
+// the CU to itself, because of its LDS, in FP64 or because there are no more tiles than CUs.
+// Eight against four waves where one workgroup has the CU: a batch of 258-, 642- and
+// 2562-vertex cells 35.5 -> 25.2 ms, 37 cells 249 -> 203 us, one FP64 cell 333 -> 305 us;
+// eight waves at 128 registers, two workgroups per CU: 100,000 cells 58 -> 67 ms.
+// This file is compiled for one of them (see NPFEM_PART below).
+#if NPFEM_PART == 1
+constexpr int kThreads = kNarrow;
+#else
+constexpr int kThreads = kWide;
+#endif
+constexpr int kWaves = kThreads / 64;
+
+// LDS: [red: 2 buffers x up to 8 waves x 12 doubles][ints: 32][cell vectors ...]; during a tile
+// product the region from the cell vectors on holds the tile's rows.
+constexpr int kSumMax = 12;                     // values per workgroup sum
+constexpr int kRedDoubles = kWide / 64 * kSumMax;   // one buffer
 constexpr int kLdsInts = 2 * kRedDoubles * 8;
-constexpr int kLdsMesh = kLdsInts + 32 * 4;
-constexpr int kLdsHeader = kLdsMesh + kMeshLds;
-static_assert(sizeof(MeshDev<double>) <= kMeshLds && sizeof(MeshDev<float>) <= kMeshLds, "mesh descriptor");
-static_assert(sizeof(MeshDev<double>) % 4 == 0 && sizeof(MeshDev<float>) % 4 == 0, "mesh descriptor");
+constexpr int kLdsHeader = kLdsInts + 32 * 4;
 
 // Opaque, so that what is derived from it is formed where it is used and not kept in registers
 // over the whole step (and so over the tile products' calls, which it would make spill).
@@ -63,30 +72,45 @@ template <> struct Vec16<float> { typedef float type __attribute__((ext_vector_t
 template <> struct Vec16<double> { typedef double type __attribute__((ext_vector_type(2))); static constexpr int W = 2; };
 template <typename Real>
 __device__ inline typename Vec16<Real>::type vload(const Real* p, int e) {
-  return *reinterpret_cast<const typename Vec16<Real>::type*>(p + e);
+  return *reinterpret_cast<const typename Vec16<Real>::type*>(reinterpret_cast<const char*>(p) + (unsigned)(e * (int)sizeof(Real)));
 }
 template <typename Real>
 __device__ inline void vstore(Real* p, int e, typename Vec16<Real>::type v) {
-  *reinterpret_cast<typename Vec16<Real>::type*>(p + e) = v;
+  *reinterpret_cast<typename Vec16<Real>::type*>(reinterpret_cast<char*>(p) + (unsigned)(e * (int)sizeof(Real))) = v;
 }
 template <typename Real>
 __device__ inline void vcopy(Real* dst, const Real* src, int len) {
   constexpr int W = Vec16<Real>::W;
 #pragma unroll 2
-  for (int e = W * tid(); e < len; e += W * kBlock) vstore(dst, e, vload(src, e));
+  for (int e = W * tid(); e < len; e += W * kThreads) vstore(dst, e, vload(src, e));
 }
 
-// Reads of the per-mesh tables (global memory shared by every cell): with the address
-// space explicit the compiler emits global loads with a scalar base and a 32-bit offset,
-// not flat loads, which would also hold up every wait on the LDS.
+#define NPFEM_GLOBAL __attribute__((address_space(1)))
+#define NPFEM_CONST __attribute__((address_space(4)))
+#define NPFEM_LDS __attribute__((address_space(3)))
+
+// A pointer (or integer) that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ inline T* uniform(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
+}
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A mesh descriptor in constant memory: its table pointers come by scalar loads into scalar
+// registers, so a table read needs a 32-bit offset only (from LDS they were vectors, and every
+// read took 64-bit address arithmetic).
+template <typename Real> using MeshC = NPFEM_CONST MeshDev<Real>;
+
+// Reads of the per-mesh tables (global memory shared by every cell): with the address space
+// explicit and the offset in 32-bit bytes the compiler emits global loads with a scalar base
+// and a vector offset, without 64-bit address arithmetic, and not flat loads, which would
+// also hold up every wait on the LDS.
 template <typename T>
 __device__ inline T gld(const T* p, int i) {
-  typedef const T __attribute__((address_space(1))) GT;
-  return ((GT*)p)[(unsigned)i];
+  return *(const NPFEM_GLOBAL T*)((const NPFEM_GLOBAL char*)p + (unsigned)(i * (int)sizeof(T)));
 }
-
-// Entries of a vertex's ELL lists (neighbours, incident corners) fetched per group.
-constexpr int kEllGroup = 6;
 
 // Lane permutation of a double within rows of 16 lanes (DPP, on the vector ALU).
 template <int CTRL>
@@ -137,7 +161,7 @@ struct Red {
 // deterministic.  Within a wave four values are folded into one register (halves, then rows
 // of 16 lanes), so that the steps within a row work on a quarter of the registers: about 5 N
 // instructions against 30 N for summing value by value (the 11 sums of an evaluation's end
-// took 530 of a wave's 5,100 instructions).  Lane i then adds value i of the four waves and
+// took 530 of a wave's 5,100 instructions).  Lane i then adds value i of the waves and
 // hands it out.
 template <int N, typename RED>
 __device__ inline void block_sum(double (&v)[N], RED& red) {
@@ -163,8 +187,9 @@ __device__ inline void block_sum(double (&v)[N], RED& red) {
       for (int i = 0; i < Q; ++i) buf[wave * kSumMax + i + Q * (lane >> 4)] = w[i];
     }
     red.barrier();
-    const double* p = buf + (lane & (kSumMax - 1));
-    const double t = (p[0] + p[kSumMax]) + (p[2 * kSumMax] + p[3 * kSumMax]);
+    const double* p = buf + (lane < kSumMax ? lane : 0);
+    double t = (p[0] + p[kSumMax]) + (p[2 * kSumMax] + p[3 * kSumMax]);
+    if constexpr (kWaves == 8) t += (p[4 * kSumMax] + p[5 * kSumMax]) + (p[6 * kSumMax] + p[7 * kSumMax]);
 #pragma unroll
     for (int i = 0; i < nn; ++i) v[n0 + i] = read_lane(t, i);
   }
@@ -181,16 +206,16 @@ constexpr int kStageBatch = 8;
 template <typename Real, typename Load>
 __device__ inline void aos_to_soa(Real* dst, int n, int np, Load load) {
   const int len = 3 * n;
-  for (int base = 0; base < len; base += kStageBatch * kBlock) {
+  for (int base = 0; base < len; base += kStageBatch * kThreads) {
     Real v[kStageBatch];
 #pragma unroll
     for (int k = 0; k < kStageBatch; ++k) {
-      const int e = base + k * kBlock + tid();
+      const int e = base + k * kThreads + tid();
       v[k] = e < len ? load(e) : Real(0);
     }
 #pragma unroll
     for (int k = 0; k < kStageBatch; ++k) {
-      const int e = base + k * kBlock + tid();
+      const int e = base + k * kThreads + tid();
       if (e < len) {
         const int i = e / 3, c = e - 3 * i;
         dst[c * np + i] = v[k];
@@ -198,7 +223,7 @@ __device__ inline void aos_to_soa(Real* dst, int n, int np, Load load) {
     }
   }
   const int pad = np - n;
-  for (int e = tid(); e < 3 * pad; e += kBlock) {
+  for (int e = tid(); e < 3 * pad; e += kThreads) {
     const int c = e / pad, i = n + (e - c * pad);
     dst[c * np + i] = Real(0);
   }
@@ -227,18 +252,18 @@ template <> __device__ inline float sqrt_<float>(float x) { return __builtin_amd
 // vertex gathers its corners into accV (and accA).
 // ---------------------------------------------------------------------------------
 template <typename Real, typename RED>
-__device__ void normalisers(const MeshDev<Real>& M, const Real* xn, const Real* ut, Real* accV, Real* accA,
+__device__ void normalisers(const MeshC<Real>& M, const Real* xn, const Real* ut, Real* accV, Real* accA,
                             Real* work, RED& red, double& GV, double& GA) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
   const bool area = accA != nullptr;
-  for (int e = tid(); e < 3 * np; e += kBlock) {
+  for (int e = tid(); e < 3 * np; e += kThreads) {
     accV[e] = Real(0);
     if (area) accA[e] = Real(0);
   }
   for (int t0 = 0; t0 < nt; t0 += ch) {
     __syncthreads();
     const int tn = min(ch, nt - t0);
-    for (int tt = tid(); tt < tn; tt += kBlock) {
+    for (int tt = tid(); tt < tn; tt += kThreads) {
       const int t = t0 + tt;
       const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
       Real e1x = xn[a] - xn[c], e1y = xn[np + a] - xn[np + c], e1z = xn[2 * np + a] - xn[2 * np + c];
@@ -268,14 +293,14 @@ __device__ void normalisers(const MeshDev<Real>& M, const Real* xn, const Real* 
       }
     }
     __syncthreads();
-    for (int i = tid(); i < n; i += kBlock) {
+    for (int i = tid(); i < n; i += kThreads) {
       Real gx = 0, gy = 0, gz = 0, ax = 0, ay = 0, az = 0;
       // incident corners from the ELL list, a group of indices in flight together;
       // padding and corners outside this chunk add zero
       for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
         int cc[kEllGroup];
 #pragma unroll
-        for (int u = 0; u < kEllGroup; ++u) cc[u] = q0 + u < M.vc_deg ? gld(M.vc_ell, (q0 + u) * np + i) : -1;
+        for (int u = 0; u < kEllGroup; ++u) cc[u] = gld(M.vc_ell + (q0 + u) * np, i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kEllGroup; ++u) {
@@ -308,7 +333,7 @@ __device__ void normalisers(const MeshDev<Real>& M, const Real* xn, const Real* 
   }
   __syncthreads();
   double sm[2] = {0.0, 0.0};
-  for (int i = tid(); i < n; i += kBlock) {
+  for (int i = tid(); i < n; i += kThreads) {
     sm[0] += (double)accV[i] * accV[i] + (double)accV[np + i] * accV[np + i] + (double)accV[2 * np + i] * accV[2 * np + i];
     if (area)
       sm[1] += (double)accA[i] * accA[i] + (double)accA[np + i] * accA[np + i] + (double)accA[2 * np + i] * accA[2 * np + i];
@@ -367,7 +392,7 @@ __device__ inline Real sl2_tau(Real a1, Real a2, Real sig1, Real J) {
 // out[0 .. 8 stride]; acc gains [0] 6 volume, [1] area, [4] area PD, [5] Skalak, [6] Rayleigh
 // energy, [7] collapsed triangles.
 template <typename Real, bool EXT>
-__device__ __attribute__((always_inline)) inline void triangle_terms(const MeshDev<Real>& M, Real Cst, Real Bsk, Real Dsk,
+__device__ __attribute__((always_inline)) inline void triangle_terms(const MeshC<Real>& M, Real Cst, Real Bsk, Real Dsk,
                                                                      Real beta, bool area_on, Real ca, const Real* xn,
                                                                      const Real* ut, int np, int t, double (&acc)[8],
                                                                      Real* out, int stride) {
@@ -501,7 +526,7 @@ __device__ __attribute__((always_inline)) inline void triangle_terms(const MeshD
 // An evaluation's result from its sums: the energies, the force norms |grad|^2, |M u/h^2|^2,
 // |b|^2 and |F_int|^2 of the residual, sum |u.b| of the rounding scale.
 template <typename Real>
-__device__ __attribute__((always_inline)) inline void finish_eval(const MeshDev<Real>& M, double inertial, double e_bend,
+__device__ __attribute__((always_inline)) inline void finish_eval(const MeshC<Real>& M, double inertial, double e_bend,
                                                                   double e_pd, double e_sk, double e_tr, double e_vol,
                                                                   double e_area, double e_col, double ub, double g2,
                                                                   double mu2, double b2, double f2, double vol, double area,
@@ -529,7 +554,7 @@ __device__ __attribute__((always_inline)) inline void finish_eval(const MeshDev<
 // EXT: the optional terms (global area, the literal volume normaliser, contacts) are
 // compiled in; without them the evaluation carries none of their code.
 template <typename Real, bool EXT, typename RED>
-__device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn,
+__device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn,
                          double GA, const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec,
                          Real* work, Real* gout, RED& red, EvalResult& res) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
@@ -556,7 +581,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   // ---- pass A: (volume and area when needed first) and bending residuals -> work ----
   double accA[4] = {0.0, 0.0, 0.0, 0.0};   // 6 volume, bending energy, bending Rayleigh energy, 2 area
   if (pre) {
-    for (int t = tid(); t < nt; t += kBlock) {
+    for (int t = tid(); t < nt; t += kThreads) {
       const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
       const double E1x = ((double)xn[a] - (double)xn[c]) + ((double)ut[a] - (double)ut[c]);
       const double E1y = ((double)xn[np + a] - (double)xn[np + c]) + ((double)ut[np + a] - (double)ut[np + c]);
@@ -570,7 +595,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
       accA[3] += sqrt(Nx * Nx + Ny * Ny + Nz * Nz);
     }
   }
-  for (int i = tid(); i < n; i += kBlock) {
+  for (int i = tid(); i < n; i += kThreads) {
     Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
     const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
     const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
@@ -582,9 +607,8 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
       Real ww[kEllGroup];
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u) {
-        const bool in = q0 + u < M.nb_deg;
-        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
-        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
       }
       if (q0 == 0) {
         Ai = gld(M.vor_area, i);
@@ -635,7 +659,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   // the term drops out wherever the vertex no longer penetrates
   double accB[2] = {0.0, 0.0};
   const Real wc = Real(col.w);
-  for (int i = tid(); i < n; i += kBlock) {
+  for (int i = tid(); i < n; i += kThreads) {
     Real gx = 0, gy = 0, gz = 0;
     const Real rix = work[i], riy = work[np + i], riz = work[2 * np + i];
     Real mass = 0;
@@ -646,9 +670,8 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
       Real ww[kEllGroup];
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u) {
-        const bool in = q0 + u < M.nb_deg;
-        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
-        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
       }
       if (q0 == 0) mass = gld(M.mass, i);
       __builtin_amdgcn_sched_barrier(0);
@@ -681,7 +704,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
     accB[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
                - ((double)ux * bx + (double)uy * by + (double)uz * bz);
   }
-  for (int i = n + tid(); i < np; i += kBlock) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
+  for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
   __syncthreads();   // work (R) is reused for the corner chunks below
 
   // ---- passes C/D: triangle in-plane terms + volume, per chunk --------------------
@@ -691,7 +714,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
   double accD[4] = {0.0, 0.0, 0.0, 0.0};   // |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
   for (int t0 = 0; t0 < nt; t0 += ch) {
     const int tn = min(ch, nt - t0);
-    for (int tt = tid(); tt < tn; tt += kBlock) {
+    for (int tt = tid(); tt < tn; tt += kThreads) {
       const int t = t0 + tt;
       triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accT, work + tt, ch);
     }
@@ -706,7 +729,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
     }
     const Real coef = Real(coefd / 6.0);         // per corner: k C / G_n * (e1 x e2) / 6
     const bool last = t0 + ch >= nt;
-    for (int i = tid(); i < n; i += kBlock) {
+    for (int i = tid(); i < n; i += kThreads) {
       Real gx = 0, gy = 0, gz = 0, vx = 0, vy = 0, vz = 0;
       // Branch-free, so that the reads of all corners are in flight together: a padding
       // entry, or a corner outside this chunk, reads the chunk's first triangle and adds
@@ -716,7 +739,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
       for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
         int cc[kEllGroup];
 #pragma unroll
-        for (int u = 0; u < kEllGroup; ++u) cc[u] = q0 + u < M.vc_deg ? gld(M.vc_ell, (q0 + u) * np + i) : -1;
+        for (int u = 0; u < kEllGroup; ++u) cc[u] = gld(M.vc_ell + (q0 + u) * np, i);
         if (q0 == 0 && last) mass = gld(M.mass, i);      // with the first group
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -785,7 +808,7 @@ __device__ void evaluate(const MeshDev<Real>& M, const MaterialDev& mat, bool li
 // of 2,000 with contacts from 8.75 to 7.37 ms.
 template <typename Real, bool EXT, typename RED>
 __device__ __attribute__((always_inline)) inline void evaluate_resident(
-    const MeshDev<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn, double GA,
+    const MeshC<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn, double GA,
     const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec, Real* rb, Real* work, Real* gout,
     RED& red, EvalResult& res) {
   const int n = M.n, np = M.n_pad, nt = M.nt;
@@ -803,7 +826,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   double coefa = 0.0;
   if (area_on) {
     double a2[1] = {0.0};
-    for (int t = tid(); t < nt; t += kBlock) {
+    for (int t = tid(); t < nt; t += kThreads) {
       const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
       double N[3], E1[3], E2[3];
 #pragma unroll
@@ -823,7 +846,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   // first sum: 6 volume, 2 area, bending and its Rayleigh energy, area PD, Skalak, triangle
   // Rayleigh energy, collapsed triangles
   double accC[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = tid(); i < n; i += kBlock) {
+  for (int i = tid(); i < n; i += kThreads) {
     Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
     const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
     const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
@@ -835,9 +858,8 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
       Real ww[kEllGroup];
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u) {
-        const bool in = q0 + u < M.nb_deg;
-        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
-        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
       }
       if (q0 == 0) {
         Ai = gld(M.vor_area, i);
@@ -871,7 +893,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   }
   // ---- triangles -> corner buffer -----------------------------------------------------
   if (tid() < 9) work[9 * nt + tid()] = Real(0);
-  for (int t = tid(); t < nt; t += kBlock)
+  for (int t = tid(); t < nt; t += kThreads)
     triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
   block_sum(accC, red);
   const double vol = accC[0] / 6.0, area = accC[1];
@@ -882,7 +904,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   // second sum: inertial and collision energy, |u.b|, |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
   double accD[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const Real wc = Real(col.w);
-  for (int i = tid(); i < n; i += kBlock) {
+  for (int i = tid(); i < n; i += kThreads) {
     const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
     const Real rix = rb[i], riy = rb[np + i], riz = rb[2 * np + i];
     Real gx = 0, gy = 0, gz = 0, mass = 0;
@@ -891,9 +913,8 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
       Real ww[kEllGroup];
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u) {
-        const bool in = q0 + u < M.nb_deg;
-        jj[u] = in ? gld(M.nb_ell, (q0 + u) * np + i) : i;
-        ww[u] = in ? gld(M.nbw_ell, (q0 + u) * np + i) : Real(0);
+        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
       }
       if (q0 == 0) mass = gld(M.mass, i);
       __builtin_amdgcn_sched_barrier(0);
@@ -928,7 +949,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
       unsigned cc[kEllGroup];
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u)
-        cc[u] = q0 + u < M.vc_deg ? gld(M.vc_pk, (q0 + u) * np + i) : (unsigned)(9 * nt) << 2;
+        cc[u] = gld(M.vc_pk + (q0 + u) * np, i);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < kEllGroup; ++u) {
@@ -962,7 +983,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
     accD[5] += (double)bx * bx + (double)by * by + (double)bz * bz;
     accD[6] += fx * fx + fy * fy + fz * fz;
   }
-  for (int i = n + tid(); i < np; i += kBlock) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
+  for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
   block_sum(accD, red);                                      // also orders the gradient
   const double Ca = area - M.A0;
   const double e_vol = 0.5 * mat.k_volume * Cv * Cv / Gn;
@@ -974,7 +995,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
 // One evaluation in the batch's vector layout (LAY as for step_kernel): with every vector in
 // LDS the fourth LDS vector holds the bending residuals (b is read from the workspace).
 template <typename Real, bool EXT, int LAY, typename RED>
-__device__ __attribute__((always_inline)) inline void evaluate_any(const MeshDev<Real>& M, const MaterialDev& mat,
+__device__ __attribute__((always_inline)) inline void evaluate_any(const MeshC<Real>& M, const MaterialDev& mat,
                                                                    bool literal, double h, double Gn, double GA,
                                                                    const Contacts<Real>& col, const Real* xn, const Real* ut,
                                                                    const Real* bvec, Real* rb, Real* work, Real* gout,
@@ -991,7 +1012,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_any(const MeshDev
 //
 // Bound: the matrix comes from the L2 (0.4 MB banded, 0.3 MB FP32 at 258 and 3.6 MB FP64 at
 // 642 vertices per product), so what counts is how much of it is in flight.  Each wave takes
-// every fourth 16-column block and works through its blocks in batches of U operands with the
+// every kWaves-th 16-column block and works through its blocks in batches of U operands with the
 // next batch, also across the end of a block, requested before the current one is used; the
 // rows come from LDS, two row blocks at a time (MB = 2: more would take the registers that the
 // step keeps over the call).  Pointers are in their address spaces and uniform values in scalar registers: this function is not
@@ -999,20 +1020,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_any(const MeshDev
 // A banded product of 15 rows by 642 vertices takes 33 k cycles of two workgroups per CU (89 k
 // with row-major operands, no batch ahead and gathered staging; about 13 k at the L2's rate).
 // ---------------------------------------------------------------------------------
-#define NPFEM_GLOBAL __attribute__((address_space(1)))
-#define NPFEM_CONST __attribute__((address_space(4)))
-#define NPFEM_LDS __attribute__((address_space(3)))
-
-// A pointer (or integer) that is the same in every lane, in scalar registers.
-template <typename T>
-__device__ inline T* uniform(T* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
-}
-__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// The wave's column blocks wave, wave + 4, ... of `ncb`.  P: block(cb) describes a block (ns
+// The wave's column blocks wave, wave + kWaves, ... of `ncb`.  P: block(cb) describes a block (ns
 // operand steps; past the end: none, with a valid address), fetch(b, s) requests operand s of
 // the matrix (the last one past the end), rows(b, s, mb) gives the rows' operand, mma
 // multiplies, pre / post load and store what the results need.
@@ -1023,8 +1031,8 @@ __device__ __attribute__((always_inline)) inline void stream_blocks(const P& p, 
   typename P::Block b = p.block(wave);
 #pragma unroll
   for (int u = 0; u < U; ++u) f0[u] = p.fetch(b, u);
-  for (int cb = wave; cb < ncb; cb += 4) {
-    const typename P::Block nx = p.block(cb + 4);
+  for (int cb = wave; cb < ncb; cb += kWaves) {
+    const typename P::Block nx = p.block(cb + kWaves);
     typename P::Acc acc[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[mb] = typename P::Acc{0, 0, 0, 0};
@@ -1122,13 +1130,13 @@ __device__ __attribute__((always_inline)) inline void dense_product(const Real* 
     constexpr int W = kDensePad<Real>, B = 4;
     const int q = np / W, total = rows * q;
     __syncthreads();
-    for (int e0 = tid(); e0 < total; e0 += B * kBlock) {
+    for (int e0 = tid(); e0 < total; e0 += B * kThreads) {
       V v[B];
 #pragma unroll
-      for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const NPFEM_GLOBAL V*>(Ig + W * min(e0 + u * kBlock, total - 1));
+      for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const NPFEM_GLOBAL V*>(Ig + W * min(e0 + u * kThreads, total - 1));
 #pragma unroll
       for (int u = 0; u < B; ++u) {
-        const int e = e0 + u * kBlock, r = e / q, c = e - r * q;
+        const int e = e0 + u * kThreads, r = e / q, c = e - r * q;
         if (e < total) *reinterpret_cast<NPFEM_LDS V*>(stage + r * ld + W * c) = v[u];
       }
     }
@@ -1232,14 +1240,14 @@ __device__ __attribute__((always_inline)) inline void band_product(const uint16_
     const int kc = min(kc_max, np - kb0);               // a multiple of 32
     const int ldk = kc + 8;
     const int ng = np >> 2, total = ng * 4 * mbn;
-    constexpr int B = 3;
+    constexpr int B = kWaves == 8 ? 2 : 3;
     __syncthreads();
-    for (int e0 = tid(); e0 < total; e0 += B * kBlock) {
+    for (int e0 = tid(); e0 < total; e0 += B * kThreads) {
       floatx4 v[B][4];
       intx4 pos[B];
 #pragma unroll
       for (int u = 0; u < B; ++u) {
-        const int e = min(e0 + u * kBlock, total - 1), rq = e / ng, g = e - rq * ng;
+        const int e = min(e0 + u * kThreads, total - 1), rq = e / ng, g = e - rq * ng;
         pos[u] = *reinterpret_cast<const NPFEM_GLOBAL intx4*>(ip + 4 * g);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -1247,7 +1255,7 @@ __device__ __attribute__((always_inline)) inline void band_product(const uint16_
       }
 #pragma unroll
       for (int u = 0; u < B; ++u) {
-        const int e = e0 + u * kBlock, rq = e / ng;
+        const int e = e0 + u * kThreads, rq = e / ng;
         if (e >= total) continue;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -1273,27 +1281,25 @@ __device__ __attribute__((always_inline)) inline void band_product(const uint16_
   }
 }
 
-// The tile's product with H~^-1 (which 0) or h^2 M~^-1 (which 1) in the plan's format; M in
-// LDS; stage: the LDS from the cell vectors on; stage_k: see StepArgs.
+// The tile's product with H~^-1 (which 0) or h^2 M~^-1 (which 1) in the plan's format; stage: the LDS from the cell vectors on; stage_k: see StepArgs.
 // Kept out of line: inlined into the step, its accumulators and staging add to the
 // register pressure of the whole iteration loop and the step kernel spills more.
 template <typename Real>
 __device__ __attribute__((noinline)) void tile_product(const MeshDev<Real>* mesh, int bf16, int which, const Real* In_,
                                                        Real* Out_, int rows_, unsigned char* stage, int stage_k_) {
-  const NPFEM_LDS MeshDev<Real>* M = (const NPFEM_LDS MeshDev<Real>*)mesh;
+  const MeshC<Real>* M = (const MeshC<Real>*)uniform(mesh);
   const Real* In = uniform(In_);
   Real* Out = uniform(Out_);
-  const int rows = uniform(rows_), stage_k = uniform(stage_k_), np = uniform(M->n_pad);
+  const int rows = uniform(rows_), stage_k = uniform(stage_k_), np = M->n_pad;
   which = uniform(which);
   if constexpr (std::is_same<Real, float>::value) {
     if (uniform(bf16)) {
-      band_product(uniform(which == 0 ? M->hinv_bf : M->minv_bf), uniform(which == 0 ? M->hinv_diag : M->minv_diag),
-                   uniform(M->bperm), uniform(M->biperm), uniform(M->bband) + which * 4 * (np >> 4), np, In, Out, rows,
-                   stage, stage_k);
+      band_product(which == 0 ? M->hinv_bf : M->minv_bf, which == 0 ? M->hinv_diag : M->minv_diag, M->bperm, M->biperm,
+                   M->bband + which * 4 * (np >> 4), np, In, Out, rows, stage, stage_k);
       return;
     }
   }
-  dense_product<Real>(uniform(which == 0 ? M->hinv : M->minv), np, In, Out, rows, stage, stage_k);
+  dense_product<Real>(which == 0 ? M->hinv : M->minv, np, In, Out, rows, stage, stage_k);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1310,14 +1316,14 @@ struct Tile {
 };
 
 template <typename Real, typename CST, typename RED>
-__device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, int cell, int64_t voff, CST& cs,
+__device__ void finalize_cell(const StepArgs<Real>& A, const MeshC<Real>& M, int cell, int64_t voff, CST& cs,
                               const Real* xn, const Real* U, RED& red, double* bc) {
   const int n = M.n, np = M.n_pad;
   const double h = A.sol.h;
   Real* xo = A.x_out + 3 * voff;
   Real* vo = A.v_out + 3 * voff;
   if (cs.status & NPFEM_NONFINITE) {
-    for (int e = tid(); e < 3 * n; e += kBlock) {
+    for (int e = tid(); e < 3 * n; e += kThreads) {
       const int i = e / 3, c = e - 3 * i;
       xo[e] = xn[c * np + i];
       vo[e] = A.v[3 * voff + e];
@@ -1325,7 +1331,7 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
   } else {
     // v = u / h, then damp its departure from the best-fit rigid motion (section 2.1.4)
     double s1[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int i = tid(); i < n; i += kBlock) {
+    for (int i = tid(); i < n; i += kThreads) {
       const double m = gld(M.mass, i);
       s1[0] += m;
 #pragma unroll
@@ -1339,7 +1345,7 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
     const double xc[3] = {s1[1] / s1[0], s1[2] / s1[0], s1[3] / s1[0]};
     const double vc[3] = {s1[4] / s1[0], s1[5] / s1[0], s1[6] / s1[0]};
     double s2[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // L (3), I_xx I_yy I_zz I_xy I_xz I_yz
-    for (int i = tid(); i < n; i += kBlock) {
+    for (int i = tid(); i < n; i += kThreads) {
       const double m = gld(M.mass, i);
       const double rx = (double)xn[i] + (double)U[i] - xc[0];
       const double ry = (double)xn[np + i] + (double)U[np + i] - xc[1];
@@ -1368,7 +1374,7 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshDev<Real>& M, i
       w[2] = (c02 * s2[0] + c12 * s2[1] + c22 * s2[2]) / det;
     }
     const double kap = A.mat.kappa;
-    for (int i = tid(); i < n; i += kBlock) {
+    for (int i = tid(); i < n; i += kThreads) {
       const double rx = (double)xn[i] + (double)U[i] - xc[0];
       const double ry = (double)xn[np + i] + (double)U[np + i] - xc[1];
       const double rz = (double)xn[2 * np + i] + (double)U[2 * np + i] - xc[2];
@@ -1403,25 +1409,20 @@ template <typename Real, int H, bool EXT, int LAY, typename CST, typename RED>
 __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Real>& A, int tile, Real* W, CST* CS, RED& red,
                          int* sint, unsigned char* lds) {
   const TileDesc td = A.tiles[tile];
-  MeshDev<Real>* Ml = reinterpret_cast<MeshDev<Real>*>(lds + kLdsMesh);
   // the tile's cells and their vertex offsets, looked up once per tile
   __shared__ int s_cell[kMaxTile];
   __shared__ int64_t s_voff[kMaxTile];
   {
-    constexpr int nw = sizeof(MeshDev<Real>) / 4;
-    static_assert(nw <= 128, "mesh descriptor copy");
-    const int* src = reinterpret_cast<const int*>(A.meshes + td.mesh);
-    if (tid() < nw) reinterpret_cast<int*>(Ml)[tid()] = src[tid()];
-    const int jt = tid() - 128;
-    if (jt >= 0 && jt < td.count) {
+    const int jt = tid();
+    if (jt < td.count) {
       const int c = A.tile_cells[td.first + jt];
       s_cell[jt] = c;
       s_voff[jt] = A.cell_voff[c];
     }
     __syncthreads();
   }
-  const MeshDev<Real>& M = *Ml;
-  const int n = M.n, np = M.n_pad, cnt = td.count, len = 3 * np;
+  const MeshC<Real>& M = *(const MeshC<Real>*)(A.meshes + uniform(td.mesh));
+  const int n = M.n, np = M.n_pad, cnt = uniform(td.count), len = 3 * np;
   Tile<Real> tl{W, np, A.tile_cells_max};
   // the current cell's x_n and trial u (and gradient and b) in LDS, then the corner
   // chunks; for meshes too large for that, x_n and u follow the tile's vectors in the
@@ -1479,13 +1480,13 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     __syncthreads();
   }
   if (!A.u_guess) {
-    tile_product(Ml, A.sol.bf16, 1, tl.mat(VB), tl.mat(VU), 3 * cnt, stage, A.stage_k);                                              // u = h^2 M~^-1 b
+    tile_product<Real>(A.meshes + td.mesh, A.sol.bf16, 1, tl.mat(VB), tl.mat(VU), 3 * cnt, stage, A.stage_k);                                              // u = h^2 M~^-1 b
     __syncthreads();
     if (A.guess_only) {
       for (int j = 0; j < cnt; ++j) {
         const int64_t voff = s_voff[j];
         const Real* U = tl.vec(VU, j);
-        for (int e = tid(); e < len; e += kBlock) {
+        for (int e = tid(); e < len; e += kThreads) {
           const int c = e / np, i = e - c * np;
           if (i < n) A.x_out[3 * (voff + i) + c] = U[e];
         }
@@ -1510,7 +1511,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     vcopy(tl.vec(VG, j), gvec(j), len);
     if (A.u_delta) {
       const int64_t voff = s_voff[j];
-      for (int e = tid(); e < len; e += kBlock) {
+      for (int e = tid(); e < len; e += kThreads) {
         const int c = e / np, i = e - c * np;
         if (i < n) ut[e] += A.u_delta[3 * (voff + i) + c];
       }
@@ -1572,7 +1573,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
     }
     __syncthreads();
     if (sint[1] == 0) break;
-    tile_product(Ml, A.sol.bf16, 0, tl.mat(VQ), tl.mat(VD), 3 * cnt, stage, A.stage_k);                                              // r = H~^-1 q
+    tile_product<Real>(A.meshes + td.mesh, A.sol.bf16, 0, tl.mat(VQ), tl.mat(VD), 3 * cnt, stage, A.stage_k);                                              // r = H~^-1 q
     __syncthreads();
     for (int j = 0; j < cnt; ++j) {
       auto& cs = CS[j];
@@ -1592,10 +1593,10 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       // loaded in one batch together with the staging of x_n and b and kept in registers
       // until the direction is formed, so the two halves below cost two memory round
       // trips instead of four.  The sums run in the same order either way.
-      const bool fused = len <= 2 * W * kBlock;
+      const bool fused = len <= 2 * W * kThreads;
       const V zero = {};
       V rr[2], ys[H][2];
-      const int ek[2] = {W * tid(), W * tid() + W * kBlock};
+      const int ek[2] = {W * tid(), W * tid() + W * kThreads};
       if (fused) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -1627,7 +1628,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           }
         } else {
 #pragma unroll 2
-          for (int e = W * tid(); e < len; e += W * kBlock) {
+          for (int e = W * tid(); e < len; e += W * kThreads) {
             const auto rv = vload(D, e);
 #pragma unroll
             for (int p = 0; p < H; ++p) {
@@ -1684,7 +1685,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
                    [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero; });
       } else {
 #pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kBlock)
+        for (int e = W * tid(); e < len; e += W * kThreads)
           d_slot(e, vload(D, e), vload(G, e), vload(U, e), [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), e) : zero; });
       }
       block_sum(gdv, red);
@@ -1698,7 +1699,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         if (hv > 0) {
           const Real al = Real(alpha);
 #pragma unroll 2
-          for (int e = W * tid(); e < len; e += W * kBlock) {
+          for (int e = W * tid(); e < len; e += W * kThreads) {
             const auto uv = vload(U, e), dv = vload(D, e);
             vstore(ut, e, uv + al * dv);
           }
@@ -1743,7 +1744,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         Real* Sn = tl.vec(VS0 + ns, j);
         Real* Yn = tl.vec(VS0 + m + ns, j);
 #pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kBlock) {
+        for (int e = W * tid(); e < len; e += W * kThreads) {
           const auto gt = vload(GT, e), gv = vload(G, e), dv = vload(D, e), uv = vload(U, e);
           const auto sv = al * dv;
           const auto yv = gt - gv;
@@ -1776,7 +1777,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         }
       } else {
 #pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kBlock) {
+        for (int e = W * tid(); e < len; e += W * kThreads) {
           vstore(U, e, vload(U, e) + al * vload(D, e));
           vstore(G, e, vload(GT, e));
         }
@@ -1852,7 +1853,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       if (conv || out_of_iters) { __syncthreads(); continue; }
       // q = g - sum_p alpha_p y_p (one pass)
 #pragma unroll 2
-      for (int e = W * tid(); e < len; e += W * kBlock) {
+      for (int e = W * tid(); e < len; e += W * kThreads) {
         const auto gv = vload(G, e);
         double qv[W];
 #pragma unroll
@@ -1885,16 +1886,13 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
   }
 }
 
-#ifndef NPFEM_STEP_WAVES_PER_SIMD
-#define NPFEM_STEP_WAVES_PER_SIMD 2
-#endif
 // H: compile-time bound on the L-BFGS history (the loops over pairs are unrolled to H);
 // CSL: the tile's cell states live in LDS at byte offset A.cs_lds (else in the workspace);
 // EXT: the optional terms of the objective are compiled in; LAY: the batch's vector
 // layout (0: every mesh keeps the current cell's vectors in LDS, 1: some mesh keeps the
 // gradient and b in the workspace, 2: some mesh keeps x_n and u there too).
 template <typename Real, int H, bool CSL, bool EXT, int LAY>
-__global__ void __launch_bounds__(kBlock, NPFEM_STEP_WAVES_PER_SIMD) step_kernel(StepArgs<Real> A) {
+__global__ void __launch_bounds__(kThreads, 2) step_kernel(StepArgs<Real> A) {
   extern __shared__ __align__(16) unsigned char lds[];
   Red<LAY != 0> red;
   red.buf = reinterpret_cast<double*>(lds);
@@ -1920,14 +1918,14 @@ __global__ void reset_counter(int* c) {
 
 // One workgroup per cell: objective and gradient at x_n + u (no iteration).
 template <typename Real, int LAY>
-__global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Real* u, Real* grad,
+__global__ void __launch_bounds__(kThreads) eval_kernel(StepArgs<Real> A, const Real* u, Real* grad,
                                                       double* terms, Real* scratch) {
   extern __shared__ __align__(16) unsigned char lds[];
   Red<LAY != 0> red;
   red.buf = reinterpret_cast<double*>(lds);
   red.turn = 0;
   const int cell = blockIdx.x;
-  const MeshDev<Real>& M = A.meshes[A.cell_mesh[cell]];
+  const MeshC<Real>& M = *(const MeshC<Real>*)(A.meshes + uniform(A.cell_mesh[cell]));
   const int n = M.n, np = M.n_pad, len = 3 * np;
   const int64_t voff = A.cell_voff[cell];
   // per cell in the scratch: gradient, b, x_n, u (3 n_pad_max each), where not in LDS
@@ -1954,7 +1952,7 @@ __global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Re
   EvalResult r;
   evaluate_any<Real, true, LAY>(M, A.mat, A.sol.literal != 0, A.sol.h, Gn, GA, Contacts<Real>{nullptr, nullptr, 0.0}, xn, ut, B,
                                 rb, work, G, red, r);
-  for (int e = tid(); e < 3 * n; e += kBlock) {
+  for (int e = tid(); e < 3 * n; e += kThreads) {
     const int i = e / 3, c = e - 3 * i;
     grad[3 * voff + e] = G[c * np + i];
   }
@@ -1970,14 +1968,14 @@ __global__ void __launch_bounds__(kBlock) eval_kernel(StepArgs<Real> A, const Re
 }
 
 template <typename Real>
-__global__ void __launch_bounds__(kBlock) apply_inverse_kernel(const Real* A, int np, const Real* in,
+__global__ void __launch_bounds__(kThreads) apply_inverse_kernel(const Real* A, int np, const Real* in,
                                                                Real* out, int rows) {
   const int r0 = blockIdx.x * 48;
   dense_product<Real>(A, np, in + (size_t)r0 * np, out + (size_t)r0 * np, min(48, rows - r0), nullptr, 0);
 }
 
 // 48 rows per workgroup, staged in LDS in chunks of kc columns (48 (kc + 8) BF16).
-__global__ void __launch_bounds__(kBlock) apply_inverse_band_kernel(const uint16_t* A, const float* diag,
+__global__ void __launch_bounds__(kThreads) apply_inverse_band_kernel(const uint16_t* A, const float* diag,
                                                                     const int* perm, const int* iperm, const int* band,
                                                                     int np, const float* in, float* out, int rows,
                                                                     int kc) {
@@ -2081,10 +2079,10 @@ __global__ void stats_reset_kernel(npfem_stats_total* tot) {
 
 }  // namespace
 
-// The library builds this file as two objects, NPFEM_PART 1 (the FP32 instantiations and
-// everything that is not a template) and NPFEM_PART 2 (the FP64 instantiations), so that
-// they compile in parallel; without NPFEM_PART it holds both.
-#if !defined(NPFEM_PART) || NPFEM_PART == 1
+// The library builds this file as three objects, which compile in parallel: NPFEM_PART 1 (the
+// FP32 instantiations with kNarrow threads and everything that is not a template), 2 (FP64, kWide
+// threads) and 3 (the FP32 step with kWide threads).
+#if NPFEM_PART == 1
 // Device scratch of the allocation-free step (npfem_step_noalloc): the tile counter,
 // the cell states and the workspace of the persistent workgroups.  One copy per device,
 // held until the process ends.  Host code never uses this name as an address: it takes
@@ -2139,6 +2137,9 @@ size_t lds_bytes(int n_pad, int chunk, int stage_rows, int vec_lds, int xu_lds) 
   return kLdsHeader + region;
 }
 
+// (Local to each object: the kernels they name have the same names in all of them.)
+namespace {
+
 // Layout 2 (x_n and u in the workspace) exists for FP64 plans only: FP32 plans of the
 // supported meshes always keep them in LDS (the host refuses an FP32 mesh that would not).
 template <typename Real> constexpr int kMaxLayout = std::is_same<Real, double>::value ? 2 : 1;
@@ -2157,11 +2158,16 @@ void step_kernel_ptrs(std::vector<const void*>& out) {
   out.push_back(reinterpret_cast<const void*>(&step_kernel<Real, 2, true, true, LAY>));
   out.push_back(reinterpret_cast<const void*>(&step_kernel<Real, 5, true, true, LAY>));
   out.push_back(reinterpret_cast<const void*>(&step_kernel<Real, kMaxHistory, true, true, LAY>));
+#if NPFEM_PART != 3
   out.push_back(reinterpret_cast<const void*>(&eval_kernel<Real, LAY>));
+#endif
 }
 
-template <typename Real>
+}  // namespace
+
+template <typename Real, int NT>
 hipError_t set_lds_limit(size_t bytes) {
+  static_assert(NT == kThreads, "compiled elsewhere");
   std::vector<const void*> fns;
   step_kernel_ptrs<Real, 0>(fns);
   step_kernel_ptrs<Real, 1>(fns);
@@ -2173,16 +2179,18 @@ hipError_t set_lds_limit(size_t bytes) {
   return hipSuccess;
 }
 
-template <typename Real>
+template <typename Real, int NT>
 hipError_t occupancy(int* blocks_per_cu, size_t lds) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      blocks_per_cu, step_kernel<Real, kMaxHistory, false, true, kMaxLayout<Real>>, kBlock, lds);
+      blocks_per_cu, step_kernel<Real, kMaxHistory, false, true, kMaxLayout<Real>>, kThreads, lds);
 }
+
+namespace {
 
 template <typename Real, int H, bool EXT, int LAY>
 void launch_step_h(const StepArgs<Real>& a, int grid, size_t lds, hipStream_t s) {
-  if (a.cs_lds >= 0) hipLaunchKernelGGL((step_kernel<Real, H, true, EXT, LAY>), dim3(grid), dim3(kBlock), lds, s, a);
-  else hipLaunchKernelGGL((step_kernel<Real, H, false, EXT, LAY>), dim3(grid), dim3(kBlock), lds, s, a);
+  if (a.cs_lds >= 0) hipLaunchKernelGGL((step_kernel<Real, H, true, EXT, LAY>), dim3(grid), dim3(kThreads), lds, s, a);
+  else hipLaunchKernelGGL((step_kernel<Real, H, false, EXT, LAY>), dim3(grid), dim3(kThreads), lds, s, a);
 }
 
 template <typename Real, bool EXT, int LAY>
@@ -2200,7 +2208,9 @@ void launch_step_x(const StepArgs<Real>& a, int grid, size_t lds, hipStream_t s)
   else launch_step_e<Real, false, LAY>(a, grid, lds, s);
 }
 
-template <typename Real>
+}  // namespace
+
+template <typename Real, int NT>
 hipError_t launch_step(const StepArgs<Real>& a, int grid, size_t lds, hipStream_t s, int* counter) {
   (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
   if (a.layout < 0 || a.layout > kMaxLayout<Real>) return hipErrorInvalidValue;
@@ -2217,11 +2227,11 @@ hipError_t launch_eval(const StepArgs<Real>& a, int n_cells, const Real* u, Real
   (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
   if (a.layout < 0 || a.layout > kMaxLayout<Real>) return hipErrorInvalidValue;
   if (a.layout == 0)
-    hipLaunchKernelGGL((eval_kernel<Real, 0>), dim3(n_cells), dim3(kBlock), lds, s, a, u, grad, terms, a.work);
+    hipLaunchKernelGGL((eval_kernel<Real, 0>), dim3(n_cells), dim3(kThreads), lds, s, a, u, grad, terms, a.work);
   else if (a.layout == 1)
-    hipLaunchKernelGGL((eval_kernel<Real, 1>), dim3(n_cells), dim3(kBlock), lds, s, a, u, grad, terms, a.work);
+    hipLaunchKernelGGL((eval_kernel<Real, 1>), dim3(n_cells), dim3(kThreads), lds, s, a, u, grad, terms, a.work);
   else if constexpr (kMaxLayout<Real> >= 2)
-    hipLaunchKernelGGL((eval_kernel<Real, kMaxLayout<Real>>), dim3(n_cells), dim3(kBlock), lds, s, a, u, grad, terms, a.work);
+    hipLaunchKernelGGL((eval_kernel<Real, kMaxLayout<Real>>), dim3(n_cells), dim3(kThreads), lds, s, a, u, grad, terms, a.work);
   return hipGetLastError();
 }
 
@@ -2229,19 +2239,19 @@ template <typename Real>
 hipError_t launch_apply_inverse(const Real* A, int n_pad, const Real* in, Real* out, int rows,
                                 hipStream_t s) {
   (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
-  hipLaunchKernelGGL(apply_inverse_kernel<Real>, dim3((rows + 47) / 48), dim3(kBlock), 0, s, A, n_pad,
+  hipLaunchKernelGGL(apply_inverse_kernel<Real>, dim3((rows + 47) / 48), dim3(kThreads), 0, s, A, n_pad,
                      in, out, rows);
   return hipGetLastError();
 }
 
-#if !defined(NPFEM_PART) || NPFEM_PART == 1
+#if NPFEM_PART == 1
 hipError_t launch_apply_inverse_band(const uint16_t* A, const float* diag, const int* perm, const int* iperm,
                                      const int* band, int n_pad, const float* in, float* out, int rows,
                                      hipStream_t s) {
   (void)hipGetLastError();   // drop an error left behind by unrelated earlier calls
   const int kc = std::min(n_pad, (65536 / (2 * 48) - 8) / 32 * 32);
   const size_t lds = (size_t)48 * (kc + 8) * 2;
-  hipLaunchKernelGGL(apply_inverse_band_kernel, dim3((rows + 47) / 48), dim3(kBlock), lds, s, A, diag, perm, iperm, band,
+  hipLaunchKernelGGL(apply_inverse_band_kernel, dim3((rows + 47) / 48), dim3(kThreads), lds, s, A, diag, perm, iperm, band,
                      n_pad, in, out, rows, kc);
   return hipGetLastError();
 }
@@ -2258,23 +2268,25 @@ hipError_t launch_drag(const Real* x, const Real* v, const int64_t* cell_voff, c
   return hipGetLastError();
 }
 
-#define NPFEM_INSTANTIATE(R)                                                                       \
-  template size_t lds_bytes<R>(int, int, int, int, int);                                           \
-  template size_t dense_stage_lds<R>(int, int);                                                    \
-  template hipError_t set_lds_limit<R>(size_t);                                                    \
-  template hipError_t occupancy<R>(int*, size_t);                                                  \
-  template hipError_t launch_step<R>(const StepArgs<R>&, int, size_t, hipStream_t, int*);          \
-  template hipError_t launch_eval<R>(const StepArgs<R>&, int, const R*, R*, double*, size_t,       \
-                                     hipStream_t);                                                 \
-  template hipError_t launch_apply_inverse<R>(const R*, int, const R*, R*, int, hipStream_t);      \
-  template hipError_t launch_drag<R>(const R*, const R*, const int64_t*, const int*, const int*,   \
-                                     int, const double*, const double*, const double*, double,     \
-                                     double, double, double, R*, hipStream_t);
-#if !defined(NPFEM_PART) || NPFEM_PART == 1
+#define NPFEM_INSTANTIATE_STEP(R)                                                                          \
+  template hipError_t set_lds_limit<R, kThreads>(size_t);                                                  \
+  template hipError_t occupancy<R, kThreads>(int*, size_t);                                                \
+  template hipError_t launch_step<R, kThreads>(const StepArgs<R>&, int, size_t, hipStream_t, int*);
+#define NPFEM_INSTANTIATE(R)                                                                               \
+  NPFEM_INSTANTIATE_STEP(R)                                                                                \
+  template size_t lds_bytes<R>(int, int, int, int, int);                                                   \
+  template size_t dense_stage_lds<R>(int, int);                                                            \
+  template hipError_t launch_eval<R>(const StepArgs<R>&, int, const R*, R*, double*, size_t, hipStream_t); \
+  template hipError_t launch_apply_inverse<R>(const R*, int, const R*, R*, int, hipStream_t);              \
+  template hipError_t launch_drag<R>(const R*, const R*, const int64_t*, const int*, const int*, int,      \
+                                     const double*, const double*, const double*, double, double, double,  \
+                                     double, R*, hipStream_t);
+#if NPFEM_PART == 1
 NPFEM_INSTANTIATE(float)
-#endif
-#if !defined(NPFEM_PART) || NPFEM_PART == 2
+#elif NPFEM_PART == 2
 NPFEM_INSTANTIATE(double)
+#else
+NPFEM_INSTANTIATE_STEP(float)
 #endif
 
 }  // namespace npfem
