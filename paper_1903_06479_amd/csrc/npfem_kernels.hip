@@ -1589,22 +1589,29 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       auto slot = [&](int p) { return m > 0 ? (head - hn + p + m) % m : 0; };
       constexpr int W = Vec16<Real>::W;
       typedef typename Vec16<Real>::type V;
-      // When a vector takes at most two 16-byte slots per thread, r and the stored y_p are
-      // loaded in one batch together with the staging of x_n and b and kept in registers
-      // until the direction is formed, so the two halves below cost two memory round
-      // trips instead of four.  The sums run in the same order either way.
-      const bool fused = len <= 2 * W * kThreads;
+      // When a vector takes at most two 16-byte slots per thread (`fused`), r and the stored
+      // y_p are loaded in one batch together with the staging of x_n and kept in registers
+      // until the direction is formed; with a history of at most two pairs (`keep`) the
+      // gradient, u and the s_p too, and all of it until the next q is formed, so that an
+      // iteration costs one memory round trip instead of five (longer histories would
+      // spill).  The sums run in the same order either way.
+      const bool fused = len <= 2 * W * kThreads, keep = H <= 2 && fused;
       const V zero = {};
-      V rr[2], ys[H][2];
+      V rr[2], gg[2], uu[2], dd[2], ys[H][2], ss[H][2];
       const int ek[2] = {W * tid(), W * tid() + W * kThreads};
       if (fused) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
           const bool in = ek[k] < len;
           rr[k] = in ? vload(D, ek[k]) : zero;
+          if (H <= 2) {
+            gg[k] = in ? vload(G, ek[k]) : zero;
+            uu[k] = in ? vload(U, ek[k]) : zero;
+          }
 #pragma unroll
           for (int p = 0; p < H; ++p) {
-            ys[p][k] = in && hn > 0 ? vload(tl.vec(VS0 + m + slot(p), j), ek[k]) : zero;
+            ys[p][k] = in && p < hn ? vload(tl.vec(VS0 + m + slot(p), j), ek[k]) : zero;
+            if (H <= 2) ss[p][k] = in && p < hn ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero;
           }
         }
       }
@@ -1622,7 +1629,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
 #pragma unroll
               for (int p = 0; p < H; ++p) {
 #pragma unroll
-                for (int w = 0; w < W; ++w) yr[p] += (double)(p < hn ? ys[p][k][w] : Real(0)) * rr[k][w];
+                for (int w = 0; w < W; ++w) yr[p] += (double)ys[p][k][w] * rr[k][w];
               }
             }
           }
@@ -1676,13 +1683,18 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         }
         vstore(D, e, dv);
         vstore(ut, e, tv);
+        return dv;
       };
       if (fused) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-          if (ek[k] < len)
-            d_slot(ek[k], rr[k], vload(G, ek[k]), vload(U, ek[k]),
-                   [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero; });
+          if (ek[k] < len) {
+            if (H <= 2)
+              dd[k] = d_slot(ek[k], rr[k], gg[k], uu[k], [&](int p) { return ss[p][k]; });
+            else
+              d_slot(ek[k], rr[k], vload(G, ek[k]), vload(U, ek[k]),
+                     [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero; });
+          }
       } else {
 #pragma unroll 2
         for (int e = W * tid(); e < len; e += W * kThreads)
@@ -1740,21 +1752,20 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       double acc[4 + 3 * H];
 #pragma unroll
       for (int k = 0; k < 4 + 3 * H; ++k) acc[k] = 0.0;
+      V gt2[2], yn2[2];                                          // keep: the new gradient and y
       if (m > 0) {
         Real* Sn = tl.vec(VS0 + ns, j);
         Real* Yn = tl.vec(VS0 + m + ns, j);
-#pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kThreads) {
-          const auto gt = vload(GT, e), gv = vload(G, e), dv = vload(D, e), uv = vload(U, e);
-          const auto sv = al * dv;
-          const auto yv = gt - gv;
+        auto a_slot = [&](int e, const V& gt, const V& gv, const V& dv, const V& uv, auto&& s_of, auto&& y_of) {
+          const V sv = al * dv;
+          const V yv = gt - gv;
 #pragma unroll
           for (int p = 0; p < H; ++p) {
             // every slot is read (its index is always inside the ring) and the terms of
             // pairs not in use are switched off, so that all reads are in flight together;
             // p = 0 is the slot being replaced when the ring is full
             const bool use = p < hn && !(full && p == 0);
-            const auto so = vload(tl.vec(VS0 + slot(p), j), e), yo = vload(tl.vec(VS0 + m + slot(p), j), e);
+            const V so = s_of(p), yo = y_of(p);
 #pragma unroll
             for (int w = 0; w < W; ++w) {
               const double sw = use ? (double)so[w] : 0.0, yw = use ? (double)yo[w] : 0.0;
@@ -1774,6 +1785,21 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
             acc[2] += (double)yv[w] * yv[w];
             acc[3] += (double)sv[w] * gt[w];
           }
+          return yv;
+        };
+        if (keep) {
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            if (ek[k] < len) {
+              gt2[k] = vload(GT, ek[k]);
+              yn2[k] = a_slot(ek[k], gt2[k], gg[k], dd[k], uu[k], [&](int p) { return ss[p][k]; }, [&](int p) { return ys[p][k]; });
+            }
+          }
+        } else {
+#pragma unroll 2
+          for (int e = W * tid(); e < len; e += W * kThreads)
+            a_slot(e, vload(GT, e), vload(G, e), vload(D, e), vload(U, e), [&](int p) { return vload(tl.vec(VS0 + slot(p), j), e); },
+                   [&](int p) { return vload(tl.vec(VS0 + m + slot(p), j), e); });
         }
       } else {
 #pragma unroll 2
@@ -1851,7 +1877,33 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         else if (out_of_iters) { cs.status = NPFEM_MAXITER; cs.active = 0; }
       }
       if (conv || out_of_iters) { __syncthreads(); continue; }
-      // q = g - sum_p alpha_p y_p (one pass)
+      // q = g - sum_p alpha_p y_p (one pass; oldest pair first, the new one last)
+      if (keep && m > 0) {
+        double a_new = 0.0;
+#pragma unroll
+        for (int p = 0; p < H; ++p)
+          if (p == n_kept && store) a_new = al_new[p];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (ek[k] < len) {
+            double qv[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) qv[w] = gt2[k][w];
+#pragma unroll
+            for (int o = 0; o < H; ++o) {
+              const double ao = o >= hn || (full && o == 0) ? 0.0 : (full ? al_new[o > 0 ? o - 1 : 0] : al_new[o]);
+#pragma unroll
+              for (int w = 0; w < W; ++w) qv[w] -= ao * (double)ys[o][k][w];
+            }
+            V q;
+#pragma unroll
+            for (int w = 0; w < W; ++w) q[w] = Real(qv[w] - a_new * (double)yn2[k][w]);
+            vstore(Q, ek[k], q);
+          }
+        }
+        __syncthreads();
+        continue;
+      }
 #pragma unroll 2
       for (int e = W * tid(); e < len; e += W * kThreads) {
         const auto gv = vload(G, e);
