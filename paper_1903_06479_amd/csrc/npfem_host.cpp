@@ -1000,9 +1000,8 @@ struct npfem_batch {
   // contact search: hashed grid buffers (allocated on first use)
   DeviceBuffers cbuf;
   int64_t c_table = 0;
-  unsigned *c_count = nullptr, *c_start = nullptr, *c_fill = nullptr, *c_bsum = nullptr, *c_vkey = nullptr,
-           *c_sorted = nullptr;
-  int* c_vcell = nullptr;
+  unsigned *c_count = nullptr, *c_start = nullptr, *c_bsum = nullptr, *c_vkey = nullptr, *c_vrank = nullptr;
+  GridVertex* c_sorted = nullptr;
   double* c_normals = nullptr;
   unsigned long long* c_ncontacts = nullptr;
   void drop_graph() {
@@ -1426,16 +1425,15 @@ npfem_status collide_now(npfem_batch* b, const double* origin, const void* x, do
   a.mask = (unsigned)(b->c_table - 1);
   a.count = b->c_count;
   a.start = b->c_start;
-  a.fill = b->c_fill;
   a.bsum = b->c_bsum;
   a.vkey = b->c_vkey;
-  a.vcell = b->c_vcell;
+  a.vrank = b->c_vrank;
   a.sorted = b->c_sorted;
   a.normals = b->c_normals;
   a.q = static_cast<Real*>(q);
   a.n = static_cast<Real*>(n);
   a.n_contacts = b->c_ncontacts;
-  HIP_TRY(launch_collide<Real>(a, (int)b->n_cells, b->n_vert, s));
+  HIP_TRY(launch_collide<Real>(a, (int)b->n_cells, s));
   return NPFEM_OK;
 }
 
@@ -1459,16 +1457,14 @@ npfem_status npfem_collisions_detect(npfem_batch* b, const double* cell_origin, 
     b->c_count = static_cast<unsigned*>(p);
     if ((st = b->cbuf.alloc(table * sizeof(unsigned), &p))) return st;
     b->c_start = static_cast<unsigned*>(p);
-    if ((st = b->cbuf.alloc(table * sizeof(unsigned), &p))) return st;
-    b->c_fill = static_cast<unsigned*>(p);
     if ((st = b->cbuf.alloc((size_t)nb * sizeof(unsigned), &p))) return st;
     b->c_bsum = static_cast<unsigned*>(p);
     if ((st = b->cbuf.alloc(b->n_vert * sizeof(unsigned), &p))) return st;
     b->c_vkey = static_cast<unsigned*>(p);
+    if ((st = b->cbuf.alloc(b->n_vert * sizeof(GridVertex), &p))) return st;
+    b->c_sorted = static_cast<GridVertex*>(p);
     if ((st = b->cbuf.alloc(b->n_vert * sizeof(unsigned), &p))) return st;
-    b->c_sorted = static_cast<unsigned*>(p);
-    if ((st = b->cbuf.alloc(b->n_vert * sizeof(int), &p))) return st;
-    b->c_vcell = static_cast<int*>(p);
+    b->c_vrank = static_cast<unsigned*>(p);
     if ((st = b->cbuf.alloc(b->n_vert * 3 * sizeof(double), &p))) return st;
     b->c_normals = static_cast<double*>(p);
     if ((st = b->cbuf.alloc(sizeof(unsigned long long), &p))) return st;

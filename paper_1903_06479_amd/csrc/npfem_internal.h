@@ -138,6 +138,11 @@ struct StepArgs {
 };
 
 // Contact search between cells (npfem_collide.hip).
+struct alignas(16) GridVertex {
+  double x, y, z;              // world position
+  int cell;
+  unsigned v;
+};
 template <typename Real>
 struct CollideArgs {
   const MeshDev<Real>* meshes;
@@ -150,18 +155,17 @@ struct CollideArgs {
   unsigned mask;               // hash table size - 1 (a power of two)
   unsigned* count;             // [table] vertices per bucket
   unsigned* start;             // [table] first slot of each bucket
-  unsigned* fill;              // [table] slots filled so far
   unsigned* bsum;              // [scan blocks] block sums of the scan
   unsigned* vkey;              // [V] bucket of each vertex
-  int* vcell;                  // [V] cell of each vertex
-  unsigned* sorted;            // [V] vertices ordered by bucket
+  unsigned* vrank;             // [V] its rank in the bucket
+  GridVertex* sorted;          // [V] vertices ordered by bucket
   double* normals;             // [V][3] unit area-weighted vertex normals
   Real* q;                     // [V][3] out: partner position in the vertex's cell frame
   Real* n;                     // [V][3] out: partner normal (zero: no contact)
   unsigned long long* n_contacts;  // out: number of vertices with a contact
 };
 template <typename Real>
-hipError_t launch_collide(const CollideArgs<Real>& a, int n_cells, int64_t n_vert, hipStream_t s);
+hipError_t launch_collide(const CollideArgs<Real>& a, int n_cells, hipStream_t s);
 int collide_scan_blocks(int64_t table);
 
 // Launch wrappers (npfem_kernels.hip).

@@ -50,10 +50,10 @@ constexpr int kThreads = kWide;
 #endif
 constexpr int kWaves = kThreads / 64;
 
-// LDS: [red: 2 buffers x up to 8 waves x 12 doubles][ints: 32][cell vectors ...]; during a tile
+// LDS: [red: 2 buffers x 4 waves x 16 or 8 waves x 8 doubles][ints: 32][cell vectors ...]; during a tile
 // product the region from the cell vectors on holds the tile's rows.
-constexpr int kSumMax = 12;                     // values per workgroup sum
-constexpr int kRedDoubles = kWide / 64 * kSumMax;   // one buffer
+constexpr int kSumMax = 64 / kWaves;            // values per workgroup sum
+constexpr int kRedDoubles = kWaves * kSumMax;   // one buffer
 constexpr int kLdsInts = 2 * kRedDoubles * 8;
 constexpr int kLdsHeader = kLdsInts + 32 * 4;
 
@@ -1610,8 +1610,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           }
 #pragma unroll
           for (int p = 0; p < H; ++p) {
-            ys[p][k] = in && p < hn ? vload(tl.vec(VS0 + m + slot(p), j), ek[k]) : zero;
-            if (H <= 2) ss[p][k] = in && p < hn ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero;
+            ys[p][k] = in && (H <= 2 ? hn > 0 : p < hn) ? vload(tl.vec(VS0 + m + slot(p), j), ek[k]) : zero;
+            if (H <= 2) ss[p][k] = in && hn > 0 ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero;
           }
         }
       }
@@ -1629,7 +1629,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
 #pragma unroll
               for (int p = 0; p < H; ++p) {
 #pragma unroll
-                for (int w = 0; w < W; ++w) yr[p] += (double)ys[p][k][w] * rr[k][w];
+                for (int w = 0; w < W; ++w) yr[p] += (double)(p < hn ? ys[p][k][w] : Real(0)) * rr[k][w];
               }
             }
           }
@@ -1893,7 +1893,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
             for (int o = 0; o < H; ++o) {
               const double ao = o >= hn || (full && o == 0) ? 0.0 : (full ? al_new[o > 0 ? o - 1 : 0] : al_new[o]);
 #pragma unroll
-              for (int w = 0; w < W; ++w) qv[w] -= ao * (double)ys[o][k][w];
+              for (int w = 0; w < W; ++w) qv[w] -= ao * (double)(o < hn ? ys[o][k][w] : Real(0));
             }
             V q;
 #pragma unroll
