@@ -18,10 +18,11 @@ namespace npfem {
 // with B the half bandwidth b rounded up to a multiple of 16; padding positions carry
 // the identity.
 //
-// Matrix-core layouts (FP32): blocks of kFactorMfmaRows = 16 positions i0 .. i0+15, k steps
-// of 4 positions, one entry per lane l (row r = l & 15, k index q = l >> 4):
-//   FA[st][l] = -L[i0+r][i0-B+4st+q]     GA[st][l] = -L[i0+16+4st+q][i0+r]
-//   DA[st][l] = (L_D^-1)[r][4st+q]       DB[st][l] = (L_D^-1)[4st+q][r]
+// Matrix-core layouts (FP32): blocks of kFactorMfmaRows = 16 positions i0 .. i0+15, groups g of
+// 16 positions in four k steps e of 4, the four entries of lane l (row r = l & 15, k index
+// q = l >> 4) together:
+//   FA[g][l][e] = -L[i0+r][i0-B+16g+4e+q]     GA[g][l][e] = -L[i0+16+16g+4e+q][i0+r]
+//   DA[l][e] = (L_D^-1)[r][4e+q]              DB[l][e] = (L_D^-1)[4e+q][r]
 // with L_D the block's 16 x 16 diagonal block.
 constexpr int kFactorRows = 8;
 constexpr int kFactorMfmaRows = 16;
@@ -34,9 +35,9 @@ struct BandFactorDev {
   const Real* F[2];
   const Real* G[2];
   const Real* T[2];
-  const Real* FA[2];           // [n_pad / 16][B / 4][64]
+  const Real* FA[2];           // [n_pad / 16][B / 16][64][4]
   const Real* GA[2];
-  const Real* DA[2];           // [n_pad / 16][4][64]
+  const Real* DA[2];           // [n_pad / 16][64][4]
   const Real* DB[2];
 };
 template <typename Real>

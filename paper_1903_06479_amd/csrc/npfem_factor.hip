@@ -4,11 +4,11 @@
 // reverse Cuthill-McKee order of the mesh, so that L is banded (half bandwidth b); each
 // right-hand side q then needs L y = P q and L^T z = y, out = P^T z.
 //
-// Both kernels give one wave 64 right-hand sides.  The right-hand sides are brought into
-// the order and transposed to [position][right-hand side] once, through an LDS tile, into
-// the caller's workspace, which then holds y and z; the result goes back the same way.
-// The solved positions still inside the band sit in an LDS ring (one row of 64 values per
-// position).
+// A wave takes 16 (FP32) or 64 (FP64) right-hand sides.  They are brought into the order and
+// transposed to [position][right-hand side] once, through an LDS tile, into the caller's
+// workspace, which then holds y and z; the result goes back the same way.  The solved
+// positions still inside the band sit in an LDS ring (one value per position and right-hand
+// side).
 //   FP32: the matrix cores, blocks of 16 positions (band_solve_mfma_kernel).
 //   FP64: the vector units, one lane per right-hand side, blocks of 8 positions; the
 //         factor entries are uniform across the wave and are read through the scalar
@@ -24,7 +24,7 @@
 namespace npfem {
 namespace {
 
-constexpr int kRhs = 64;        // right-hand sides per wave (one per lane)
+constexpr int kRhs = 64;        // right-hand sides per wave in FP64 (one per lane)
 constexpr int kTileRow = 65;    // padded row of the 64 x 64 transpose tile
 
 // acc[k] += sum over jj < B of C[jj][k] * ring[(base + jj) mod W] (the factor entries are
@@ -188,137 +188,150 @@ __global__ __launch_bounds__(kRhs) void band_solve_kernel(const Real* __restrict
   store_solution(Y, lds, iperm, out, np, rows, r0, lane);
 }
 
-// FP32 substitution on the matrix cores (v_mfma_f32_16x16x4_f32), blocks of 16 positions.
-// A block's update from the solved window, acc -= L[block][window] x[window], is a 16 x B
-// by B x 64 product: A operand the factor (one entry per lane, so no broadcast), B operand
-// the ring (position x right-hand side), four accumulator tiles of 16 right-hand sides
-// (lane l holds rows 4 (l >> 4) .. +3 of column l & 15).  The 16 x 16 diagonal block is
-// applied as its inverse, 16 more matrix instructions; the right-hand sides reach the B
-// layout through the ring slots the block is about to fill.  The factor stream runs one
-// 16-position group ahead across blocks, the ring values one group ahead within a block;
-// Y rows and the diagonal inverse one block ahead.
+// FP32 substitution on the matrix cores (v_mfma_f32_16x16x4_f32), blocks of 16 positions and
+// 16 right-hand sides per wave.  A block's update from the solved window,
+// acc -= L[block][window] x[window], is a 16 x B by B x 16 product: A operand the factor,
+// B operand the ring, both with four steps per 16-byte read; lane l holds rows
+// 4 (l >> 4) .. +3 of column l & 15 of the result.  The 16 x 16 diagonal block is applied as
+// its inverse, 4 more matrix instructions; the right-hand sides reach the B layout through the
+// ring slots of the block's 16 positions (the oldest of the window, which nothing needs after
+// the update).
+// Bound: one wave's chain of dependent matrix instructions and LDS turns per block, so what
+// counts is the number of waves: with 64 right-hand sides per wave a ring of 48 KB left three
+// waves per CU, a quarter of whose SIMDs idled (60,000 rows of 2562 vertices: 5.44 ms); 16 of
+// them need 11 KB, 14 waves per CU, and share the factor through the caches.  The factor stream
+// runs kAhead 16-position groups ahead across blocks, the ring one group, Y and the diagonal
+// inverse one block.
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
+constexpr int kRhsM = 16;       // right-hand sides per wave
+constexpr int kAhead = 4;
 
 template <bool kFwd>
-__device__ __forceinline__ void mfma_pass(const float* __restrict__ A, const float* __restrict__ D,
-                                          float* __restrict__ Y, float* win, int np, int B, int W, int lane) {
+__device__ __forceinline__ void mfma_pass(const floatx4_t* __restrict__ A, const floatx4_t* __restrict__ D,
+                                          float* __restrict__ Y, floatx4_t* win, int np, int B, int lane) {
   const int l16 = lane & 15, kq = lane >> 4;
-  const int nb = np / kFactorMfmaRows, ks = B / 4, ng = B / 16;
-  for (int s = 0; s < W; ++s) win[s * kRhs + lane] = 0.f;
+  const int nb = np / kFactorMfmaRows, ng = B / 16;
+  for (int s = 0; s < ng; ++s) win[s * 64 + lane] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // the factor's groups in the order of use
+  int left = nb * ng - 1, pg = 0;
+  size_t po = kFwd ? 0 : (size_t)(nb - 1) * ng * 64;
+  auto fetch = [&]() {
+    const floatx4_t v = A[po + lane];
+    if (left > 0) {                                   // past the last: the last again
+      --left;
+      const bool wrap = ++pg == ng;
+      pg = wrap ? 0 : pg;
+      po = kFwd || !wrap ? po + 64 : po - (size_t)(2 * ng - 1) * 64;
+    }
+    return v;
+  };
+  floatx4_t a[kAhead];
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k) a[k] = fetch();
+  auto rows = [&](int bi) {
+    floatx4_t v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = Y[(bi * 16 + 4 * kq + r) * kRhsM + l16];
+    return v;
+  };
+  auto put = [&](int slot, const floatx4_t& v) {       // rows 4 kq + r -> operand layout
+    float* w = reinterpret_cast<float*>(win);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[(slot * 64 + r * 16 + l16) * 4 + kq] = v[r];
+  };
   const int b_first = kFwd ? 0 : nb - 1;
-  floatx4_t nxt[4];
-  float an[4], dn[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) nxt[t][r] = Y[(size_t)(b_first * 16 + 4 * kq + r) * kRhs + t * 16 + l16];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    an[q] = A[((size_t)b_first * ks + q) * 64 + lane];
-    dn[q] = D[((size_t)b_first * 4 + q) * 64 + lane];
-  }
-  // ring values of a 16-position group starting at slot sb (a multiple of 16, as are B
-  // and W, so the group does not wrap), in the B-operand layout
-  auto ring_group = [&](int sb, float (&bv)[4][4]) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) bv[q][t] = win[(sb + 4 * q + kq) * kRhs + t * 16 + l16];
-  };
-  auto first_slot = [&](int i0) {
-    const int base = kFwd ? i0 - B : i0 + kFactorMfmaRows;
-    return ((base % W) + W) % W;
-  };
-  float bn_[4][4];
-  ring_group(first_slot(b_first * kFactorMfmaRows), bn_);
+  floatx4_t nxt = rows(b_first), dn = D[b_first * 64 + lane];
+  int own = kFwd ? 0 : b_first % ng;                   // ring slot (of 16 positions) of the block
+  // the window's slots in the order of the factor's steps (ascending positions): forward from
+  // the oldest, which is the block's own slot; backward from the block's successor
+  auto next_slot = [&](int s) { return s + 1 == ng ? 0 : s + 1; };
+  floatx4_t bn = win[(kFwd ? own : next_slot(own)) * 64 + lane];
   for (int it = 0; it < nb; ++it) {
     const int bi = kFwd ? it : nb - 1 - it;
-    const bool more = it + 1 < nb;
-    const int bn = kFwd ? bi + 1 : bi - 1;
-    const int i0 = bi * kFactorMfmaRows;
-    floatx4_t acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = nxt[t];
-    if (more) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) nxt[t][r] = Y[(size_t)(bn * 16 + 4 * kq + r) * kRhs + t * 16 + l16];
-    }
-    const float* __restrict__ Ab = A + (size_t)bi * ks * 64;
-    const float* __restrict__ An = more ? A + (size_t)bn * ks * 64 : nullptr;
-    int sb = first_slot(i0);
+    const int bnx = it + 1 < nb ? (kFwd ? bi + 1 : bi - 1) : bi;
+    floatx4_t acc = nxt;
+    const floatx4_t d = dn;
+    nxt = rows(bnx);
+    dn = D[bnx * 64 + lane];
+    int sb = kFwd ? own : next_slot(own);
     for (int g = 0; g < ng; ++g) {
-      float a[4], bv[4][4];
+      const floatx4_t av = a[0], bv = bn;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = an[q];
+      for (int k = 0; k + 1 < kAhead; ++k) a[k] = a[k + 1];
+      a[kAhead - 1] = fetch();
+      sb = next_slot(sb);
+      bn = win[sb * 64 + lane];                        // past the last group: not used
 #pragma unroll
-        for (int t = 0; t < 4; ++t) bv[q][t] = bn_[q][t];
-      }
-      const float* __restrict__ src = g + 1 < ng ? Ab + (g + 1) * 256 : An;
-      if (src) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) an[q] = src[q * 64 + lane];
-      }
-      sb = sb + 16 == W ? 0 : sb + 16;
-      if (g + 1 < ng) ring_group(sb, bn_);           // the next group: solved positions only
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], bv[q][t], acc[t], 0, 0, 0);
+      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], acc, 0, 0, 0);
     }
     // the diagonal block: x = L_D^-1 acc (forward) or L_D^-T acc (backward)
-    float d[4];
+    put(own, acc);
+    const floatx4_t yv = win[own * 64 + lane];
+    floatx4_t x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) d[q] = dn[q];
-    if (more) {
+    for (int q = 0; q < 4; ++q) x = __builtin_amdgcn_mfma_f32_16x16x4f32(d[q], yv[q], x, 0, 0, 0);
+    put(own, x);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) dn[q] = D[((size_t)bn * 4 + q) * 64 + lane];
-    }
-    const int sd = i0 % W;                           // multiples of 16: no wrap inside the block
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) win[(sd + 4 * kq + r) * kRhs + t * 16 + l16] = acc[t][r];
-    floatx4_t x[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) x[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        x[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[q], win[(sd + 4 * q + kq) * kRhs + t * 16 + l16], x[t], 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        win[(sd + 4 * kq + r) * kRhs + t * 16 + l16] = x[t][r];
-        Y[(size_t)(i0 + 4 * kq + r) * kRhs + t * 16 + l16] = x[t][r];
-      }
+    for (int r = 0; r < 4; ++r) Y[(bi * 16 + 4 * kq + r) * kRhsM + l16] = x[r];
+    own = kFwd ? next_slot(own) : (own == 0 ? ng - 1 : own - 1);
     // the next block's first group, which may hold the positions just solved
-    if (more) ring_group(first_slot(bn * kFactorMfmaRows), bn_);
+    bn = win[(kFwd ? own : next_slot(own)) * 64 + lane];
   }
 }
 
-__global__ __launch_bounds__(kRhs) void band_solve_mfma_kernel(const float* __restrict__ FA,
-                                                               const float* __restrict__ GA,
-                                                               const float* __restrict__ DA,
-                                                               const float* __restrict__ DB,
-                                                               const int* __restrict__ iperm,
-                                                               const float* __restrict__ in, float* __restrict__ out,
-                                                               float* __restrict__ work, int np, int B, int W,
-                                                               int rows) {
+__global__ __launch_bounds__(64) void band_solve_mfma_kernel(const floatx4_t* __restrict__ FA,
+                                                             const floatx4_t* __restrict__ GA,
+                                                             const floatx4_t* __restrict__ DA,
+                                                             const floatx4_t* __restrict__ DB,
+                                                             const int* __restrict__ iperm,
+                                                             const float* __restrict__ in, float* __restrict__ out,
+                                                             float* __restrict__ work, int np, int B, int rows) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* lds = reinterpret_cast<float*>(smem);
-  const int lane = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * kRhs;
-  float* __restrict__ Y = work + (size_t)blockIdx.x * np * kRhs;
-  load_rhs(in, Y, lds, iperm, np, rows, r0, lane);       // ends with a barrier: Y visible to all lanes
-  mfma_pass<true>(FA, DA, Y, lds, np, B, W, lane);
-  mfma_pass<false>(GA, DB, Y, lds, np, B, W, lane);
+  const int lane = threadIdx.x, l16 = lane & 15, kq = lane >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * kRhsM;
+  float* __restrict__ Y = work + (size_t)blockIdx.x * np * kRhsM;
+  const int rn = (int)min((int64_t)kRhsM, rows - r0);
+  const float* __restrict__ src = in + r0 * np;
+  // in[r][k] -> Y[iperm[k]][r - r0] through a [16][65] tile; the next 64 columns are on their
+  // way while these are written (rows past the end repeat the last, and are zero in Y)
+  float v[kRhsM];
+  auto request = [&](int k0) {
+    const int k = min(k0 + lane, np - 1);
+#pragma unroll
+    for (int r = 0; r < kRhsM; ++r) v[r] = src[min(r, rn - 1) * np + k];
+  };
+  request(0);
+  for (int k0 = 0; k0 < np; k0 += 64) {
+    const int ip = iperm[min(k0 + lane, np - 1)];
+#pragma unroll
+    for (int r = 0; r < kRhsM; ++r) lds[r * kTileRow + lane] = r < rn ? v[r] : 0.f;
+    if (k0 + 64 < np) request(k0 + 64);
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < 64; kk += 4) {
+      const int pos = __shfl(ip, kk + kq);
+      if (k0 + kk + kq < np) Y[pos * kRhsM + l16] = lds[l16 * kTileRow + kk + kq];
+    }
+    __syncthreads();
+  }
+  mfma_pass<true>(FA, DA, Y, reinterpret_cast<floatx4_t*>(lds), np, B, lane);
+  mfma_pass<false>(GA, DB, Y, reinterpret_cast<floatx4_t*>(lds), np, B, lane);
   __syncthreads();
-  store_solution(Y, lds, iperm, out, np, rows, r0, lane);
+  // and back
+  float* __restrict__ dst = out + r0 * np;
+  for (int k0 = 0; k0 < np; k0 += 64) {
+    const int ip = iperm[min(k0 + lane, np - 1)];
+#pragma unroll
+    for (int kk = 0; kk < 64; kk += 4) lds[l16 * kTileRow + kk + kq] = Y[__shfl(ip, kk + kq) * kRhsM + l16];
+    __syncthreads();
+    if (k0 + lane < np) {
+#pragma unroll
+      for (int r = 0; r < kRhsM; ++r)
+        if (r < rn) dst[r * np + k0 + lane] = lds[r * kTileRow + lane];
+    }
+    __syncthreads();
+  }
 }
 
 }  // namespace
@@ -336,19 +349,26 @@ template <typename Real>
 hipError_t launch_band_solve(const BandFactorDev<Real>& f, int which, int n_pad, const Real* in, Real* out,
                              Real* work, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  const size_t lds = band_solve_lds_bytes<Real>(f.ring);
+  size_t lds = band_solve_lds_bytes<Real>(f.ring);
   if (lds > kBandSolveMaxLds) return hipErrorInvalidValue;
-  const int grid = (rows + kRhs - 1) / kRhs;
+  const int rhs = std::is_same<Real, float>::value ? kRhsM : kRhs;
+  const int grid = (rows + rhs - 1) / rhs;
   const void* fn;
-  if constexpr (std::is_same<Real, float>::value) fn = reinterpret_cast<const void*>(&band_solve_mfma_kernel);
-  else fn = reinterpret_cast<const void*>(&band_solve_kernel<double>);
+  if constexpr (std::is_same<Real, float>::value) {
+    fn = reinterpret_cast<const void*>(&band_solve_mfma_kernel);
+    lds = (size_t)std::max(f.B, kTileRow) * kRhsM * sizeof(float);
+  } else {
+    fn = reinterpret_cast<const void*>(&band_solve_kernel<double>);
+  }
   if (lds > 64 * 1024) {          // above the default dynamic LDS limit (set on the current device)
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   if constexpr (std::is_same<Real, float>::value)
-    hipLaunchKernelGGL(band_solve_mfma_kernel, dim3(grid), dim3(kRhs), lds, s, f.FA[which], f.GA[which],
-                       f.DA[which], f.DB[which], f.iperm, in, out, work, n_pad, f.B, f.ring, rows);
+    hipLaunchKernelGGL(band_solve_mfma_kernel, dim3(grid), dim3(64), lds, s,
+                       reinterpret_cast<const floatx4_t*>(f.FA[which]), reinterpret_cast<const floatx4_t*>(f.GA[which]),
+                       reinterpret_cast<const floatx4_t*>(f.DA[which]), reinterpret_cast<const floatx4_t*>(f.DB[which]),
+                       f.iperm, in, out, work, n_pad, f.B, rows);
   else
     hipLaunchKernelGGL(band_solve_kernel<double>, dim3(grid), dim3(kRhs), lds, s, f.F[which], f.G[which],
                        f.T[which], f.iperm, in, out, work, n_pad, f.B, f.ring, rows);

@@ -565,8 +565,8 @@ void factor_layouts(const BandFactorHost& f, int np, int B, std::vector<Real>& F
       for (int l = 0; l < k; ++l) Tb[R + k * R + l] = Real(f.at(i0 + k, i0 + l));
     }
   }
-  // matrix-core layouts: blocks of 16 positions, k steps of 4, one entry per lane
-  // (lane l: row l & 15, k index l >> 4)
+  // matrix-core layouts: blocks of 16 positions, k steps of 4, four steps' entries of a lane
+  // together (lane l: row l & 15, k index l >> 4)
   const int M = kFactorMfmaRows, nb = np / M, ks = B / 4;
   FA.assign((size_t)nb * ks * 64, Real(0));
   GA.assign((size_t)nb * ks * 64, Real(0));
@@ -578,8 +578,8 @@ void factor_layouts(const BandFactorHost& f, int np, int B, std::vector<Real>& F
       for (int l = 0; l < 64; ++l) {
         const int row = i0 + (l & 15), kq = l >> 4;
         const int jf = i0 - B + 4 * st + kq, jg = i0 + M + 4 * st + kq;
-        if (jf >= 0) FA[((size_t)bi * ks + st) * 64 + l] = Real(-f.at(row, jf));
-        if (jg < np) GA[((size_t)bi * ks + st) * 64 + l] = Real(-f.at(jg, row));
+        if (jf >= 0) FA[((size_t)bi * ks + st / 4 * 4) * 64 + 4 * l + st % 4] = Real(-f.at(row, jf));
+        if (jg < np) GA[((size_t)bi * ks + st / 4 * 4) * 64 + 4 * l + st % 4] = Real(-f.at(jg, row));
       }
     // inverse of the 16 x 16 lower-triangular diagonal block, by forward substitution
     double Dinv[16][16] = {};
@@ -592,8 +592,8 @@ void factor_layouts(const BandFactorHost& f, int np, int B, std::vector<Real>& F
     for (int st = 0; st < 4; ++st)
       for (int l = 0; l < 64; ++l) {
         const int r = l & 15, k = 4 * st + (l >> 4);
-        DA[((size_t)bi * 4 + st) * 64 + l] = Real(Dinv[r][k]);     // L_D^-1
-        DB[((size_t)bi * 4 + st) * 64 + l] = Real(Dinv[k][r]);     // L_D^-T
+        DA[(size_t)bi * 256 + 4 * l + st] = Real(Dinv[r][k]);     // L_D^-1
+        DB[(size_t)bi * 256 + 4 * l + st] = Real(Dinv[k][r]);     // L_D^-T
       }
   }
 }
