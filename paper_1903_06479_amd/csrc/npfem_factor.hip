@@ -199,12 +199,13 @@ __global__ __launch_bounds__(kRhs) void band_solve_kernel(const Real* __restrict
 // Bound: one wave's chain of dependent matrix instructions and LDS turns per block, so what
 // counts is the number of waves: with 64 right-hand sides per wave a ring of 48 KB left three
 // waves per CU, a quarter of whose SIMDs idled (60,000 rows of 2562 vertices: 5.44 ms); 16 of
-// them need 11 KB, 14 waves per CU, and share the factor through the caches.  The factor stream
+// them need 11 KB, 14 waves per CU, and share the factor through the caches (2.49 ms; 2.86 with
+// four groups of the factor in flight, 3.98 with one).  The factor stream
 // runs kAhead 16-position groups ahead across blocks, the ring one group, Y and the diagonal
 // inverse one block.
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int kRhsM = 16;       // right-hand sides per wave
-constexpr int kAhead = 4;
+constexpr int kAhead = 8;
 
 template <bool kFwd>
 __device__ __forceinline__ void mfma_pass(const floatx4_t* __restrict__ A, const floatx4_t* __restrict__ D,
@@ -212,22 +213,11 @@ __device__ __forceinline__ void mfma_pass(const floatx4_t* __restrict__ A, const
   const int l16 = lane & 15, kq = lane >> 4;
   const int nb = np / kFactorMfmaRows, ng = B / 16;
   for (int s = 0; s < ng; ++s) win[s * 64 + lane] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  // the factor's groups in the order of use
-  int left = nb * ng - 1, pg = 0;
-  size_t po = kFwd ? 0 : (size_t)(nb - 1) * ng * 64;
-  auto fetch = [&]() {
-    const floatx4_t v = A[po + lane];
-    if (left > 0) {                                   // past the last: the last again
-      --left;
-      const bool wrap = ++pg == ng;
-      pg = wrap ? 0 : pg;
-      po = kFwd || !wrap ? po + 64 : po - (size_t)(2 * ng - 1) * 64;
-    }
-    return v;
-  };
+  // kAhead groups of the factor in flight, group g of a block in a[g % kAhead] (registers that
+  // wait for a load are never copied: a copy would wait for it)
   floatx4_t a[kAhead];
 #pragma unroll
-  for (int k = 0; k < kAhead; ++k) a[k] = fetch();
+  for (int k = 0; k < kAhead; ++k) a[k] = A[((size_t)(kFwd ? 0 : nb - 1) * ng + min(k, ng - 1)) * 64 + lane];
   auto rows = [&](int bi) {
     floatx4_t v;
 #pragma unroll
@@ -254,15 +244,20 @@ __device__ __forceinline__ void mfma_pass(const floatx4_t* __restrict__ A, const
     nxt = rows(bnx);
     dn = D[bnx * 64 + lane];
     int sb = kFwd ? own : next_slot(own);
-    for (int g = 0; g < ng; ++g) {
-      const floatx4_t av = a[0], bv = bn;
+    for (int g0 = 0; g0 < ng; g0 += kAhead) {
 #pragma unroll
-      for (int k = 0; k + 1 < kAhead; ++k) a[k] = a[k + 1];
-      a[kAhead - 1] = fetch();
-      sb = next_slot(sb);
-      bn = win[sb * 64 + lane];                        // past the last group: not used
+      for (int u = 0; u < kAhead; ++u) {
+        const int g = g0 + u;
+        if (g >= ng) break;
+        const floatx4_t bv = bn;
+        sb = next_slot(sb);
+        bn = win[sb * 64 + lane];                      // past the last group: not used
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], acc, 0, 0, 0);
+        for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][q], bv[q], acc, 0, 0, 0);
+        // in its place the group kAhead on, or the next block's
+        const bool in = g + kAhead < ng;
+        a[u] = A[((size_t)(in ? bi : bnx) * ng + (in ? g + kAhead : u)) * 64 + lane];
+      }
     }
     // the diagonal block: x = L_D^-1 acc (forward) or L_D^-T acc (backward)
     put(own, acc);
