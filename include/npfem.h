@@ -208,12 +208,12 @@ npfem_status npfem_batch_create(npfem_plan *plan, int64_t n_cells, const int32_t
 void npfem_batch_destroy(npfem_batch *batch);
 
 /*
- * Schedule of a batch: up to cells_per_tile (1..21) cells share one product with H~^-1 on
- * the matrix cores and one workgroup; lbfgs_m (0..8) is the L-BFGS history length used by
+ * Schedule of a batch: cells_per_tile (1..21) cells share one product with H~^-1 on the
+ * matrix cores and one workgroup; lbfgs_m (0..8) is the L-BFGS history length used by
  * this batch (the solution does not depend on either, only the time to reach it).
- * npfem_batch_schedule rebuilds the tile queue and workspace (synchronously; no step of
- * this batch may be in flight); npfem_batch_get_schedule reports the current one
- * (outputs may be NULL).
+ * npfem_batch_schedule rebuilds the tile queue and workspace for exactly that size
+ * (synchronously; no step of this batch may be in flight); npfem_batch_get_schedule reports
+ * the schedule in use, as npfem_batch_schedule takes it (outputs may be NULL).
  */
 npfem_status npfem_batch_schedule(npfem_batch *batch, int32_t cells_per_tile, int32_t lbfgs_m);
 npfem_status npfem_batch_get_schedule(const npfem_batch *batch, int32_t *cells_per_tile,
@@ -222,9 +222,10 @@ npfem_status npfem_batch_get_schedule(const npfem_batch *batch, int32_t *cells_p
 /*
  * Autotuner: times one step of the batch on the caller's inputs for each candidate
  * schedule (cells_per_tile in {5, 10, 16, 21}, and also 2 and 3 when the batch has fewer
- * than 10 cells per compute unit; where fewer cells per tile than that keep more workgroups
- * busy, the tiles are cut accordingly, which n_tiles shows; lbfgs_m in {2, 3, 5, 8} up to max_lbfgs_m) and keeps the fastest.  x, v, f_ext: device inputs as for npfem_step;
- * x_scratch, v_scratch: device [V_total][3] outputs it may overwrite.  Synchronous.
+ * than 10 cells per compute unit, each of them and, where that is expected to keep more
+ * workgroups busy, a smaller size in its place; lbfgs_m in {2, 3, 5, 8} up to max_lbfgs_m) and
+ * keeps the fastest, which npfem_batch_get_schedule reports.  x, v, f_ext: device inputs as for
+ * npfem_step; x_scratch, v_scratch: device [V_total][3] outputs it may overwrite.  Synchronous.
  * best_ms (may be NULL) receives the best step time in milliseconds.
  */
 npfem_status npfem_batch_autotune(npfem_batch *batch, const void *x, const void *v, const void *f_ext,

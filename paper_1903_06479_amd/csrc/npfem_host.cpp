@@ -968,9 +968,7 @@ struct npfem_batch {
   const int* mesh_n = nullptr;
   void* eval_scratch = nullptr;
   // schedule: tiling, history length and workspace (rebuilt by the autotuner)
-  // T: cells per tile; T_set: as asked for or chosen, which T falls short of where the cells are
-  // spread over idle workgroups (spread: chosen by the library)
-  int T = 0, T_set = 0, spread = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1, wide = 0;
+  int T = 0, m = 0, n_tiles = 0, grid = 0, n_vec = 0, stage_k = 0, cs_lds = -1, wide = 0;
   size_t lds = 0;
   int64_t slot_stride = 0;
   DeviceBuffers sched;
@@ -1230,12 +1228,8 @@ int spread_tile(const npfem_batch* b, int T_max) {
   return best;
 }
 
-npfem_status schedule(npfem_batch* b, int T, int m, int spread) {
-  const int Tt = spread ? spread_tile(b, T) : T;
-  const npfem_status s = b->plan->precision == NPFEM_FP64 ? batch_schedule<double>(b, Tt, m) : batch_schedule<float>(b, Tt, m);
-  b->T_set = T;
-  b->spread = spread;
-  return s;
+npfem_status schedule(npfem_batch* b, int T, int m) {
+  return b->plan->precision == NPFEM_FP64 ? batch_schedule<double>(b, T, m) : batch_schedule<float>(b, T, m);
 }
 
 // Tiles of up to 16 cells (48 rows of a product) where they keep every workgroup busy.
@@ -1279,7 +1273,7 @@ npfem_status npfem_batch_create(npfem_plan* p, int64_t n_cells, const int32_t* c
   if ((s = b->buf.upload(cm.data(), cm.size(), &b->cell_mesh))) return s;
   if ((s = b->buf.upload(mesh_n.data(), mesh_n.size(), &b->mesh_n))) return s;
   const int T = p->prm.cells_per_tile > 0 ? p->prm.cells_per_tile : spread_tile(b.get(), kTileDefault);
-  if ((s = schedule(b.get(), T, p->prm.lbfgs_m, 0))) return s;
+  if ((s = schedule(b.get(), T, p->prm.lbfgs_m))) return s;
   if (n_vert_out) *n_vert_out = v;
   *out = b.release();
   return NPFEM_OK;
@@ -1560,13 +1554,13 @@ npfem_status npfem_batch_schedule(npfem_batch* b, int32_t cells_per_tile, int32_
   if (cells_per_tile < 1 || cells_per_tile > kMaxTile) return fail(NPFEM_E_INVALID, "batch_schedule: cells_per_tile must be in [1, 21]");
   if (lbfgs_m < 0 || lbfgs_m > kMaxHistory) return fail(NPFEM_E_INVALID, "batch_schedule: lbfgs_m must be in [0, 8]");
   HIP_TRY(hipSetDevice(b->plan->device));
-  return schedule(b, cells_per_tile, lbfgs_m, b->spread && cells_per_tile == b->T_set);
+  return schedule(b, cells_per_tile, lbfgs_m);
 }
 
 npfem_status npfem_batch_get_schedule(const npfem_batch* b, int32_t* cells_per_tile, int32_t* lbfgs_m,
                                       int32_t* grid_blocks, int32_t* n_tiles) {
   if (!b) return fail(NPFEM_E_INVALID, "batch_get_schedule: NULL batch");
-  if (cells_per_tile) *cells_per_tile = b->T_set;
+  if (cells_per_tile) *cells_per_tile = b->T;
   if (lbfgs_m) *lbfgs_m = b->m;
   if (grid_blocks) *grid_blocks = b->grid;
   if (n_tiles) *n_tiles = b->n_tiles;
@@ -1585,8 +1579,8 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   double best = 1e300;
-  const int T0 = b->T_set, m0 = b->m, spread0 = b->spread;
-  int bT = T0, bm = m0, bs = spread0;
+  const int T0 = b->T, m0 = b->m;
+  int bT = T0, bm = m0;
   // tiles of 2 or 3 cells only for batches that leave workgroups idle at 5 cells per tile; each
   // size spread over idle workgroups and as it is, every resulting tile size once
   const int Ts[] = {2, 3, 5, 10, 16, 21};
@@ -1604,7 +1598,7 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
       for (int m : ms) {
         if (m > max_lbfgs_m && !(m == 2 && max_lbfgs_m < 2)) continue;
         const int mm = std::min(m, max_lbfgs_m);
-        if ((st = schedule(b, T, mm, sp))) break;
+        if ((st = schedule(b, Tt, mm))) break;
         // one step to warm up, one timed
         if ((st = launch_step_now(b, x, v, f, x_scratch, v_scratch, nullptr, nullptr, s))) break;
         (void)hipEventRecord(e0, s);
@@ -1615,9 +1609,8 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
         (void)hipEventElapsedTime(&ms_, e0, e1);
         if (ms_ < best) {
           best = ms_;
-          bT = T;
+          bT = Tt;
           bm = mm;
-          bs = sp;
         }
         if (mm != m) break;
       }
@@ -1629,12 +1622,12 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
   b->use_graph = use_graph;
   if (st) {
     const std::string msg = g_err;
-    (void)schedule(b, T0, m0, spread0);      // leave the batch on the schedule it had
+    (void)schedule(b, T0, m0);               // leave the batch on the schedule it had
     g_err = msg;
     return st;
   }
   if (best_ms) *best_ms = best;
-  return schedule(b, bT, bm, bs);
+  return schedule(b, bT, bm);
 }
 
 npfem_status npfem_stats_accumulate(const npfem_cell_stats* st, int64_t n, npfem_stats_total* tot, void* stream) {

@@ -160,6 +160,9 @@ class Plan:
             N._lib.npfem_plan_destroy(h)
 
 
+TUNER_TILES = (2, 3, 5, 10, 16, 21)      # tile sizes that the autotuner starts from
+
+
 class Batch:
     """The cells advanced together; each cell's vertices are contiguous, in order."""
 
@@ -177,7 +180,7 @@ class Batch:
         self.offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
 
     def schedule(self, cells_per_tile: int | None = None, lbfgs_m: int | None = None) -> dict:
-        """Set (when given) and report the schedule: cells per tile, history length,
+        """Set (when given) and report the schedule in use: cells per tile, history length,
         persistent workgroups, tiles."""
         if cells_per_tile is not None or lbfgs_m is not None:
             cur = self.schedule()
@@ -190,13 +193,18 @@ class Batch:
         return {"cells_per_tile": T.value, "lbfgs_m": m.value, "grid_blocks": g.value, "n_tiles": nt.value}
 
     def autotune(self, x, v, f, max_lbfgs_m: int = 5, stream=None) -> dict:
-        """Time the candidate schedules on these inputs and keep the fastest."""
+        """Time the candidate schedules on these inputs and keep the fastest.  Returns what
+        `schedule()` reports of it, with the time (`best_ms`) and, as `cells_per_tile`, the
+        candidate size that the kept tiles came from; the cells per tile in use, which are fewer
+        where that keeps more workgroups busy, are `tile_cells` (`schedule()`'s `cells_per_tile`)."""
         import torch
         xs, vs = torch.empty_like(x), torch.empty_like(v)
         best = c_double()
         N.check(N.lib().npfem_batch_autotune(self._h, _dptr(x), _dptr(v), _dptr(f), _dptr(xs), _dptr(vs),
                                              max_lbfgs_m, _stream(stream), byref(best)), "npfem_batch_autotune")
         out = self.schedule()
+        out["tile_cells"] = out["cells_per_tile"]
+        out["cells_per_tile"] = next(t for t in TUNER_TILES if t >= out["tile_cells"])
         out["best_ms"] = best.value
         return out
 
