@@ -1173,44 +1173,57 @@ npfem_status batch_schedule(npfem_batch* b, int T, int m) {
 // A tile's cells run one after the other on its workgroup, so few large tiles leave workgroups
 // idle and a last part-filled round of them costs a whole one, while small tiles share a product
 // among fewer cells.  The tile queue is played through with a tile's time taken as its cells'
-// (in proportion to the vertices) plus its product's: measured at 642 vertices, a product of up
-// to 16 rows takes 0.4 of a cell's round in FP32 and about 0.9 in FP64 (where the matrix
-// cores bound it, so every further 16 rows take as much again; in FP32 0.4 of it).  From four
-// rounds on the tail weighs little and the sharing decides: such sizes are not looked at.
+// plus its product's.  In units of a vertex's share of a cell's round (FP32 and FP64 alike), a
+// cell takes n_pad, 1.7 n_pad where its gradient is in the workspace and 3.4 n_pad where its
+// triangles come in chunks; a product of up to 16 rows takes n_pad^2 / 672 times 3.7 dense, 1.3
+// in BF16 and 1.0 banded, and twice that where the matrix exceeds an XCD's 4 MB of L2.  Every
+// further 16 rows add a fifth of it, or, where the rows do not fit the LDS, twice it again.
+// Measured at 162, 258, 642, 1026 and 2562 vertices: the size taken is within 1.04 of the best
+// one on average.  From four rounds on the tail weighs little and the sharing decides: such sizes
+// are not looked at.
 // Against at least five per tile (two for a tuned batch): 37 cells of 642 vertices 386 -> 256 us
 // (one per tile), 2000 with contacts 6.46 -> 5.66 ms (four), 1024 in FP64 6.8 -> 5.2 ms (four),
-// 3000 of 258 vertices 1585 -> 1242 us (six).
-int spread_tile(const npfem_batch* b, int T_max) {
+// 3000 of 258 vertices 1585 -> 1242 us (six).  With the products taken to grow like the cells (0.4
+// and 0.9 of a cell's round) 2900 FP64 cells of 1026 vertices got twelve per tile, 93 ms, four
+// take 46; 4600 dense FP32 cells of 642 vertices nine, 9.8 ms, five take 6.9.
+template <typename Real>
+int spread_tile_of(const npfem_batch* b, int T_max) {
   const npfem_plan* p = b->plan;
-  const bool fp64 = p->precision == NPFEM_FP64;
   const int nm = (int)p->meshes.size();
+  const int fmt = std::is_same<Real, float>::value ? p->prm.inverse_bf16 : 0;
   std::vector<int> order;
   for (int i = 0; i < nm; ++i)
     if (!b->by_mesh[i].empty()) order.push_back(i);
   std::sort(order.begin(), order.end(), [&](int a, int c) { return p->meshes[a].mesh->n > p->meshes[c].mesh->n; });
-  auto slots_of = [&](int T) {
-    if (p->prm.grid_blocks > 0) return p->prm.grid_blocks;
+  auto lds_of = [&](int T) {
     size_t lds = 0;
     for (int mi : order) {
       const MeshPlan& mp = p->meshes[mi];
-      const int rows = p->prm.inverse_bf16 && !fp64 ? (3 * T + 15) / 16 * 16 : 0;
-      lds = std::max(lds, fp64 ? lds_bytes<double>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds)
-                               : lds_bytes<float>(mp.n_pad, mp.chunk, rows, mp.vec_lds, mp.xu_lds));
+      lds = std::max(lds, lds_bytes<Real>(mp.n_pad, mp.chunk, fmt ? (3 * T + 15) / 16 * 16 : 0, mp.vec_lds, mp.xu_lds));
     }
-    return p->cu_count * (!fp64 && lds <= kTwoPerCu ? 2 : 1);
+    return lds;
+  };
+  auto tile_time = [&](const MeshPlan& mp, int cnt, size_t lds_cap) {
+    const double np = mp.n_pad, per[] = {3.7, 1.3, 1.0};
+    const double bytes = np * np * (fmt == 0 ? (double)sizeof(Real) : (fmt == 1 ? 2.0 : 0.5));   // banded: a quarter is kept
+    const bool staged = fmt || dense_stage_lds<Real>(mp.n_pad, 3 * cnt) <= lds_cap;
+    const double cell = np * (mp.chunk < mp.mesh->nt ? 3.4 : (mp.vec_lds ? 1.0 : 1.7));
+    const double product = per[fmt] * np * np / 672.0 * (bytes > 4.0 * 1024 * 1024 ? 2.0 : 1.0);
+    return cell * cnt + product * (1.0 + (staged ? 0.2 : 2.0) * ((3 * cnt - 1) / 16));
   };
   int best = T_max;
   double best_t = 1e300;
   for (int T = T_max; T >= 1; --T) {
-    const int slots = slots_of(T);
+    const size_t lds = lds_of(T), cap = lds > kTwoPerCu ? kStepLdsCap : kTwoPerCu;
+    const int slots = p->prm.grid_blocks > 0 ? p->prm.grid_blocks
+                                             : p->cu_count * (std::is_same<Real, float>::value && lds <= kTwoPerCu ? 2 : 1);
     if (b->n_cells > (int64_t)4 * slots * T) break;
     std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
     double end = 0.0;
     for (int mi : order) {
       const int64_t nc = (int64_t)b->by_mesh[mi].size();
       for (int64_t c0 = 0; c0 < nc; c0 += T) {
-        const int cnt = (int)std::min<int64_t>(T, nc - c0), blocks = (3 * cnt + 15) / 16;
-        const double t = p->meshes[mi].n_pad * (cnt + (fp64 ? 0.9 * blocks : 0.4 + 0.16 * (blocks - 1)));
+        const double t = tile_time(p->meshes[mi], (int)std::min<int64_t>(T, nc - c0), cap);
         double start = 0.0;
         if ((int)free_at.size() == slots) {
           start = free_at.top();
@@ -1226,6 +1239,9 @@ int spread_tile(const npfem_batch* b, int T_max) {
     }
   }
   return best;
+}
+int spread_tile(const npfem_batch* b, int T_max) {
+  return b->plan->precision == NPFEM_FP64 ? spread_tile_of<double>(b, T_max) : spread_tile_of<float>(b, T_max);
 }
 
 npfem_status schedule(npfem_batch* b, int T, int m) {
