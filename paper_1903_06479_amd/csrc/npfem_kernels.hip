@@ -823,7 +823,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
     red.barrier();
   }
   // global area (optional): the total area first
-  double coefa = 0.0;
+  double coefa = 0.0, area64 = 0.0;
   if (area_on) {
     double a2[1] = {0.0};
     for (int t = tid(); t < nt; t += kThreads) {
@@ -838,7 +838,8 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
       a2[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
     }
     block_sum(a2, red);
-    coefa = mat.k_area_global * (0.5 * a2[0] - M.A0) / GA;
+    area64 = 0.5 * a2[0];
+    coefa = mat.k_area_global * (area64 - M.A0) / GA;
   }
   const Real ca = Real(0.5 * coefa);               // k_A (A - A0) / G_A / 2
 
@@ -896,7 +897,7 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   for (int t = tid(); t < nt; t += kThreads)
     triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
   block_sum(accC, red);
-  const double vol = accC[0] / 6.0, area = accC[1];
+  const double vol = accC[0] / 6.0, area = area_on ? area64 : accC[1];   // the area whose gradient is taken
   const double Cv = vol - M.V0;
   const Real coef = Real(mat.k_volume * Cv / Gn / 6.0);      // per corner: k C / G_n * (e1 x e2) / 6
 
