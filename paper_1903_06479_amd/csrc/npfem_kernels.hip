@@ -49,11 +49,16 @@ constexpr int kThreads = kNarrow;
 constexpr int kThreads = kWide;
 #endif
 constexpr int kWaves = kThreads / 64;
+// Every sum over a workgroup runs as kWide threads form it, so that a cell's bits do not depend on
+// the workgroup it gets (and so not on its batch): thread t of a narrower one goes through
+// the elements of threads t, t + kThreads, ... one set after the other, and their sums meet where
+// the waves' do.  (Half sums for 256 threads cost throughput 0.8 %: a second fold per sum.)
+constexpr int kSets = kWide / kThreads;
 
-// LDS: [red: 2 buffers x 4 waves x 16 or 8 waves x 8 doubles][ints: 32][cell vectors ...]; during a tile
+// LDS: [red: 2 buffers x 8 waves x 8 doubles][ints: 32][cell vectors ...]; during a tile
 // product the region from the cell vectors on holds the tile's rows.
-constexpr int kSumMax = 64 / kWaves;            // values per workgroup sum
-constexpr int kRedDoubles = kWaves * kSumMax;   // one buffer
+constexpr int kSumMax = 8;                              // values per exchange
+constexpr int kRedDoubles = kSets * kWaves * kSumMax;   // one buffer
 constexpr int kLdsInts = 2 * kRedDoubles * 8;
 constexpr int kLdsHeader = kLdsInts + 32 * 4;
 
@@ -144,9 +149,16 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// The workgroup sums' LDS: two buffers in turn, so that a sum needs one barrier only (its
-// buffer's last readers are past the barrier of the sum in between).  GLOBAL: that barrier also
-// orders global memory (vectors of the current cell in the workspace).
+// The workgroup sums: N values over all threads, the same on every lane; fixed order, so
+// deterministic.  put folds the lanes' values of one set and stores the wave's; finish, one barrier
+// later, adds the waves' of all sets.  There are two buffers in turn, so a sum needs one barrier only:
+// its buffer's last readers are past the barrier of the sum in between.  GLOBAL: that barrier
+// also orders global memory (vectors of the current cell in the workspace).
+// Within a wave four values are folded into one register (halves, then rows of 16 lanes),
+// so that the steps within a row work on a quarter of the registers: about 5 N
+// instructions against 30 N for summing value by value (the 11 sums of an evaluation's end
+// took 530 of a wave's 5,100 instructions).  Lane i then adds value i of the waves and hands
+// it out.
 template <bool GLOBAL>
 struct Red {
   double* buf;
@@ -155,24 +167,11 @@ struct Red {
     if (GLOBAL) __syncthreads();
     else lds_barrier();
   }
-};
-
-// Sum N doubles over the workgroup, the same uniform values on every lane; fixed order, so
-// deterministic.  Within a wave four values are folded into one register (halves, then rows
-// of 16 lanes), so that the steps within a row work on a quarter of the registers: about 5 N
-// instructions against 30 N for summing value by value (the 11 sums of an evaluation's end
-// took 530 of a wave's 5,100 instructions).  Lane i then adds value i of the waves and
-// hands it out.
-template <int N, typename RED>
-__device__ inline void block_sum(double (&v)[N], RED& red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int n0 = 0; n0 < N; n0 += kSumMax) {
-    const int nn = N - n0 < kSumMax ? N - n0 : kSumMax, Q = (nn + 3) / 4;
-    double* buf = red.buf + red.turn * kRedDoubles;
-    red.turn ^= 1;
-    double w[kSumMax / 4];
-    auto val = [&](int i) { return i < nn ? v[n0 + i] : 0.0; };
+  // values N0 .. N0 + NN - 1 of v in (NN + 3) / 4 registers
+  template <int N0, int NN, int N>
+  static __device__ void fold_range(const double (&v)[N], double* w) {
+    constexpr int Q = (NN + 3) / 4;
+    auto val = [&](int i) { return i < NN ? v[N0 + i] : 0.0; };
 #pragma unroll
     for (int i = 0; i < Q; ++i) {               // row r of w[i]: value i + Q r
       double x = fold<false>(fold<true>(val(i), val(i + 2 * Q)), fold<true>(val(i + Q), val(i + 3 * Q)));
@@ -182,18 +181,144 @@ __device__ inline void block_sum(double (&v)[N], RED& red) {
       x += dpp_row<0x140>(x);                   // row_mirror
       w[i] = x;
     }
+  }
+  template <int NN>
+  __device__ void store(int set, const double* w) const {
+    constexpr int Q = (NN + 3) / 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double* out = buf + turn * kRedDoubles + (set * kWaves + wave) * kSumMax;
     if ((lane & 15) == 0) {
 #pragma unroll
-      for (int i = 0; i < Q; ++i) buf[wave * kSumMax + i + Q * (lane >> 4)] = w[i];
+      for (int i = 0; i < Q; ++i) out[i + Q * (lane >> 4)] = w[i];
     }
-    red.barrier();
-    const double* p = buf + (lane < kSumMax ? lane : 0);
-    double t = (p[0] + p[kSumMax]) + (p[2 * kSumMax] + p[3 * kSumMax]);
-    if constexpr (kWaves == 8) t += (p[4 * kSumMax] + p[5 * kSumMax]) + (p[6 * kSumMax] + p[7 * kSumMax]);
-#pragma unroll
-    for (int i = 0; i < nn; ++i) v[n0 + i] = read_lane(t, i);
   }
-}
+  template <int N>
+  __device__ void put(int set, const double (&v)[N]) const {
+    double w[(N + 3) / 4];
+    fold_range<0, N>(v, w);
+    store<N>(set, w);
+  }
+  // For every set in turn, N values: of two sets, those past the fourth are folded together
+  // (held: the first set's), so that no register of four is left half empty twice.
+  template <int N>
+  __device__ void put_sets(int set, const double (&v)[N], double (&held)[N > 4 ? N - 4 : 1]) const {
+    if constexpr (kSets == 1 || N <= 4) {
+      put(set, v);
+    } else {
+      constexpr int K = N - 4, Q = (2 * K + 3) / 4;
+      const int row = (threadIdx.x & 63) >> 4, wave = threadIdx.x >> 6;
+      double w[1];
+      fold_range<0, 4>(v, w);
+      store<4>(set, w);
+      if (set == 0) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) held[i] = v[4 + i];
+      } else {
+        double t[2 * K], x[Q];
+#pragma unroll
+        for (int i = 0; i < K; ++i) t[i] = held[i], t[K + i] = v[4 + i];
+        fold_range<0, 2 * K>(t, x);
+        double* out = buf + turn * kRedDoubles + wave * kSumMax + 4;
+        if ((threadIdx.x & 15) == 0) {
+#pragma unroll
+          for (int i = 0; i < Q; ++i) {
+            const int q = i + Q * row;
+            if (q < 2 * K) out[q < K ? q : kWaves * kSumMax + q - K] = x[i];
+          }
+        }
+      }
+    }
+  }
+  // Sum of one set, the other one (if there is one) being zero: its slots hold twice as many values.
+  template <int N0 = 0, int N>
+  __device__ void sum_one(double (&v)[N]) {
+    if constexpr (N0 < N) {
+      constexpr int most = kSets * kSumMax, NN = N - N0 < most ? N - N0 : most, Q = (NN + 3) / 4;
+      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+      double w[Q];
+      fold_range<N0, NN>(v, w);
+      double* out = buf + turn * kRedDoubles + wave * most;
+      if ((lane & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) out[i + Q * (lane >> 4)] = w[i];
+      }
+      barrier();
+      const double* p = buf + turn * kRedDoubles + (lane < most ? lane : 0);
+      turn ^= 1;
+      double t = (p[0] + p[most]) + (p[2 * most] + p[3 * most]);
+      if constexpr (kSets == 1) t += (p[4 * most] + p[5 * most]) + (p[6 * most] + p[7 * most]);
+#pragma unroll
+      for (int i = 0; i < NN; ++i) v[N0 + i] = read_lane(t, i);
+      sum_one<N0 + NN>(v);
+    }
+  }
+  template <int N>
+  __device__ void finish(double (&v)[N]) { finish_range<0, N>(v); }
+  template <int N0, int NN, int N>
+  __device__ void finish_range(double (&v)[N]) {
+    const int lane = threadIdx.x & 63;
+    barrier();
+    const double* p = buf + turn * kRedDoubles + (lane < kSumMax ? lane : 0);
+    turn ^= 1;
+    static_assert(kSets * kWaves == 8, "the waves' sums");
+    double t = (p[0] + p[kSumMax]) + (p[2 * kSumMax] + p[3 * kSumMax]);
+    t += (p[4 * kSumMax] + p[5 * kSumMax]) + (p[6 * kSumMax] + p[7 * kSumMax]);
+#pragma unroll
+    for (int i = 0; i < NN; ++i) v[N0 + i] = read_lane(t, i);
+  }
+};
+
+// Sums of more values than one exchange holds.
+template <int N>
+struct Folded {
+  static constexpr int R = (N + 3) / 4;
+  double w[kSets][R] = {};
+  template <int N0 = 0>
+  static __device__ void fold_all(const double (&v)[N], double (&x)[R]) {
+    if constexpr (N0 < N) {
+      Red<false>::fold_range<N0, (N - N0 < kSumMax ? N - N0 : kSumMax)>(v, x + N0 / 4);
+      fold_all<N0 + kSumMax>(v, x);
+    }
+  }
+  __device__ void fold(int set, const double (&v)[N]) {
+    double x[R];
+    fold_all(v, x);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (kSets == 1 || set == 0) w[0][i] = x[i];
+      else w[kSets - 1][i] = x[i];
+    }
+  }
+  template <int N0 = 0, typename RED>
+  __device__ void sum(double (&v)[N], RED& red) const {
+    if constexpr (N0 < N) {
+      constexpr int NN = N - N0 < kSumMax ? N - N0 : kSumMax;
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) red.template store<NN>(s, w[s] + N0 / 4);
+      red.template finish_range<N0, NN>(v);
+      sum<N0 + kSumMax>(v, red);
+    }
+  }
+};
+
+// Sums that go on from loop to loop: get and set a set's values around a loop over its elements.
+template <int N>
+struct Sums {
+  double v[kSets][N] = {};
+  __device__ void get(int set, double (&x)[N]) const {
+#pragma unroll
+    for (int k = 0; k < N; ++k) x[k] = kSets == 1 || set == 0 ? v[0][k] : v[kSets - 1][k];
+  }
+  __device__ void set(int set, const double (&x)[N]) {
+    if (kSets == 1 || set == 0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[0][k] = x[k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[kSets - 1][k] = x[k];
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------------
 // LDS staging
@@ -252,7 +377,7 @@ template <> __device__ inline float sqrt_<float>(float x) { return __builtin_amd
 // vertex gathers its corners into accV (and accA).
 // ---------------------------------------------------------------------------------
 template <typename Real, typename RED>
-__device__ void normalisers(const MeshC<Real>& M, const Real* xn, const Real* ut, Real* accV, Real* accA,
+__device__ __attribute__((always_inline)) inline void normalisers(const MeshC<Real>& M, const Real* xn, const Real* ut, Real* accV, Real* accA,
                             Real* work, RED& red, double& GV, double& GA) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
   const bool area = accA != nullptr;
@@ -332,13 +457,18 @@ __device__ void normalisers(const MeshC<Real>& M, const Real* xn, const Real* ut
     }
   }
   __syncthreads();
-  double sm[2] = {0.0, 0.0};
-  for (int i = tid(); i < n; i += kThreads) {
-    sm[0] += (double)accV[i] * accV[i] + (double)accV[np + i] * accV[np + i] + (double)accV[2 * np + i] * accV[2 * np + i];
-    if (area)
-      sm[1] += (double)accA[i] * accA[i] + (double)accA[np + i] * accA[np + i] + (double)accA[2 * np + i] * accA[2 * np + i];
+  double sm[2];
+#pragma unroll 1
+  for (int set = 0; set < kSets; ++set) {
+    double sv[2] = {0.0, 0.0};
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
+      sv[0] += (double)accV[i] * accV[i] + (double)accV[np + i] * accV[np + i] + (double)accV[2 * np + i] * accV[2 * np + i];
+      if (area)
+        sv[1] += (double)accA[i] * accA[i] + (double)accA[np + i] * accA[np + i] + (double)accA[2 * np + i] * accA[2 * np + i];
+    }
+    red.put(set, sv);
   }
-  block_sum(sm, red);
+  red.finish(sm);
   GV = sm[0];
   GA = area ? sm[1] : 1.0;
 }
@@ -389,12 +519,23 @@ __device__ inline Real sl2_tau(Real a1, Real a2, Real sig1, Real J) {
 
 // In-plane terms of triangle t (area PD, modified Skalak, Rayleigh) and its share of the
 // volume: the gradient of corners a and b (corner c takes minus their sum) and e1 x e2 go to
-// out[0 .. 8 stride]; acc gains [0] 6 volume, [1] area, [4] area PD, [5] Skalak, [6] Rayleigh
-// energy, [7] collapsed triangles.
-template <typename Real, bool EXT>
+// out[0 .. 8 stride]; acc gains the triangle's part of an evaluation's first sum.
+// That sum holds 6 volume, area, the internal energies and the collapsed triangles; with TERMS
+// (for reports) the energies one by one (bending, its Rayleigh part, area PD, Skalak, triangle
+// Rayleigh), else their sum, which is a register less to fold per set.
+template <bool TERMS>
+struct SumC {
+  static constexpr int N = TERMS ? 8 : 4, V = 0, A = 1, B = 2, BR = TERMS ? 3 : 2, PD = TERMS ? 4 : 2, SK = TERMS ? 5 : 2,
+                       TR = TERMS ? 6 : 2, DEG = TERMS ? 7 : 3;
+};
+// The second: inertial energy, |u.b|, |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2, collision energy.
+enum { D_IN = 0, D_UB, D_G2, D_MU2, D_B2, D_F2, D_COL };
+template <bool EXT> constexpr int kSumD = EXT ? 7 : 6;
+
+template <typename Real, bool EXT, bool TERMS>
 __device__ __attribute__((always_inline)) inline void triangle_terms(const MeshC<Real>& M, Real Cst, Real Bsk, Real Dsk,
                                                                      Real beta, bool area_on, Real ca, const Real* xn,
-                                                                     const Real* ut, int np, int t, double (&acc)[8],
+                                                                     const Real* ut, int np, int t, double (&acc)[SumC<TERMS>::N],
                                                                      Real* out, int stride) {
   // The triangle's table entries are all requested before the first is used, then
   // its corners' coordinates from LDS; scheduling barriers keep each group together.
@@ -513,48 +654,54 @@ __device__ __attribute__((always_inline)) inline void triangle_terms(const MeshC
   out[8 * stride] = nz;
   // x_a . (x_b x x_c) = E1 . (E2 x x_c) with E1 = x_a - x_c, E2 = x_b - x_c (FP64)
   const double cx = (double)xc + (double)ucx, cy = (double)yc + (double)ucy, cz = (double)zc + (double)ucz;
-  acc[0] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
-  acc[1] += (double)J * area_t;                         // deformed area = J A0
-  acc[7] += collapsed ? 1.0 : 0.0;
-  acc[4] += 0.5 * (double)(Cst * A0) * ((double)dA1 * dA1 + (double)dA2 * dA2);
-  acc[5] += (double)A0 * (0.125 * (double)Bsk * ((double)s1m * s1m + (double)s2m * s2m)
+  typedef SumC<TERMS> C;
+  acc[C::V] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
+  acc[C::A] += (double)J * area_t;                         // deformed area = J A0
+  acc[C::DEG] += collapsed ? 1.0 : 0.0;
+  acc[C::PD] += 0.5 * (double)(Cst * A0) * ((double)dA1 * dA1 + (double)dA2 * dA2);
+  acc[C::SK] += (double)A0 * (0.125 * (double)Bsk * ((double)s1m * s1m + (double)s2m * s2m)
                            + 0.25 * (double)Dsk * ((double)a1 * a1 * a1 * a1 + (double)a2 * a2 * a2 * a2));
-  acc[6] += 0.5 * (double)wr * ((double)g0x * g0x + (double)g0y * g0y + (double)g0z * g0z
+  acc[C::TR] += 0.5 * (double)wr * ((double)g0x * g0x + (double)g0y * g0y + (double)g0z * g0z
                                  + (double)g1x * g1x + (double)g1y * g1y + (double)g1z * g1z);
 }
 
-// An evaluation's result from its sums: the energies, the force norms |grad|^2, |M u/h^2|^2,
-// |b|^2 and |F_int|^2 of the residual, sum |u.b| of the rounding scale.
-template <typename Real>
-__device__ __attribute__((always_inline)) inline void finish_eval(const MeshC<Real>& M, double inertial, double e_bend,
-                                                                  double e_pd, double e_sk, double e_tr, double e_vol,
-                                                                  double e_area, double e_col, double ub, double g2,
-                                                                  double mu2, double b2, double f2, double vol, double area,
-                                                                  double degen, EvalResult& res) {
+// An evaluation's result from its two sums: the energies, the force norms |grad|^2,
+// |M u/h^2|^2, |b|^2 and |F_int|^2 of the residual, sum |u.b| of the rounding scale.
+template <typename Real, bool EXT, bool TERMS>
+__device__ __attribute__((always_inline)) inline void finish_eval(const MeshC<Real>& M, const double (&c)[SumC<TERMS>::N],
+                                                                  const double (&d)[kSumD<EXT>], double e_vol,
+                                                                  double e_area, double vol, double area,
+                                                                  EvalResult& res) {
+  typedef SumC<TERMS> C;
+  const double inertial = d[D_IN], ub = d[D_UB], e_col = EXT ? d[kSumD<EXT> - 1] : 0.0;
+  const double e_bend = TERMS ? c[C::B] + c[C::BR] : c[C::B];      // without TERMS: all internal energies
+  const double e_pd = TERMS ? c[C::PD] : 0.0, e_sk = TERMS ? c[C::SK] : 0.0, e_tr = TERMS ? c[C::TR] : 0.0;
   res.vol = vol;
   res.area = area;
-  res.degen = degen;
-  res.terms[0] = inertial;
-  res.terms[1] = e_pd;
-  res.terms[2] = e_sk;
-  res.terms[3] = e_bend;
-  res.terms[4] = e_vol;
-  res.terms[5] = e_tr;
-  res.terms[6] = e_area;
-  res.terms[7] = e_col;
+  res.degen = c[C::DEG];
+  if constexpr (TERMS) {
+    res.terms[0] = inertial;
+    res.terms[1] = e_pd;
+    res.terms[2] = e_sk;
+    res.terms[3] = e_bend;
+    res.terms[4] = e_vol;
+    res.terms[5] = e_tr;
+    res.terms[6] = e_area;
+    res.terms[7] = e_col;
+  }
   res.E = inertial + e_pd + e_sk + e_bend + e_vol + e_tr + e_area + e_col;
   // rounding scale of E: the sum of the magnitudes of its terms
   res.noise = fabs(inertial) + 2.0 * ub + e_pd + e_sk + e_bend + e_vol + e_tr + e_area + e_col;
-  const double num = sqrt(g2);
-  const double den = sqrt(mu2) + sqrt(b2) + sqrt(f2) + M.floor_force;
+  const double num = sqrt(d[D_G2]);
+  const double den = sqrt(d[D_MU2]) + sqrt(d[D_B2]) + sqrt(d[D_F2]) + M.floor_force;
   res.resid = num == 0.0 ? 0.0 : num / den;
   if (!isfinite(res.E) || !isfinite(num)) res.resid = INFINITY;
 }
 
 // EXT: the optional terms (global area, the literal volume normaliser, contacts) are
 // compiled in; without them the evaluation carries none of their code.
-template <typename Real, bool EXT, typename RED>
-__device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn,
+template <typename Real, bool EXT, bool TERMS, typename RED>
+__device__ __attribute__((always_inline)) inline void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn,
                          double GA, const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec,
                          Real* work, Real* gout, RED& red, EvalResult& res) {
   const int n = M.n, np = M.n_pad, nt = M.nt, ch = M.chunk;
@@ -579,9 +726,14 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
     Gn = gv;
   }
   // ---- pass A: (volume and area when needed first) and bending residuals -> work ----
-  double accA[4] = {0.0, 0.0, 0.0, 0.0};   // 6 volume, bending energy, bending Rayleigh energy, 2 area
+  typedef SumC<TERMS> C;
+  Sums<C::N> sumT;
+  double sumA[2] = {0.0, 0.0};             // 6 volume, 2 area
+#pragma unroll 1
+  for (int set = 0; set < kSets; ++set) {
   if (pre) {
-    for (int t = tid(); t < nt; t += kThreads) {
+    double accA[2] = {0.0, 0.0};
+    for (int t = tid() + set * kThreads; t < nt; t += kWide) {
       const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
       const double E1x = ((double)xn[a] - (double)xn[c]) + ((double)ut[a] - (double)ut[c]);
       const double E1y = ((double)xn[np + a] - (double)xn[np + c]) + ((double)ut[np + a] - (double)ut[np + c]);
@@ -592,10 +744,13 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
       const double cx = (double)xn[c] + ut[c], cy = (double)xn[np + c] + ut[np + c], cz = (double)xn[2 * np + c] + ut[2 * np + c];
       accA[0] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
       const double Nx = E1y * E2z - E1z * E2y, Ny = E1z * E2x - E1x * E2z, Nz = E1x * E2y - E1y * E2x;
-      accA[3] += sqrt(Nx * Nx + Ny * Ny + Nz * Nz);
+      accA[1] += sqrt(Nx * Nx + Ny * Ny + Nz * Nz);
     }
+    red.put(set, accA);
   }
-  for (int i = tid(); i < n; i += kThreads) {
+  double accT[C::N];
+  sumT.get(set, accT);
+  for (int i = tid() + set * kThreads; i < n; i += kWide) {
     Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
     const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
     const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
@@ -634,32 +789,33 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
     const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
     const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
     const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
-    accA[1] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
-    accA[2] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
+    accT[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
+    accT[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
     work[i] = rx + beta * ux;
     work[np + i] = ry + beta * uy;
     work[2 * np + i] = rz + beta * uz;
   }
+  sumT.set(set, accT);
+  }
+  if (pre) red.finish(sumA);                   // also the barrier before pass B
+  else red.barrier();
   double coefd = 0.0, vol = 0.0, area = 0.0, coefa = 0.0;
   if (pre) {
-    block_sum(accA, red);
-    vol = accA[0] / 6.0;
-    area = 0.5 * accA[3];
+    vol = sumA[0] / 6.0;
+    area = 0.5 * sumA[1];
     coefd = mat.k_volume * (vol - M.V0) / Gn;               // k C / G_n
     coefa = area_on ? mat.k_area_global * (area - M.A0) / GA : 0.0;
-  } else {
-    double ab[2] = {accA[1], accA[2]};
-    block_sum(ab, red);                                   // also the barrier before pass B
-    accA[1] = ab[0];
-    accA[2] = ab[1];
   }
 
   // ---- pass B: bending gradient + inertia - b (+ collision) -> gout -----------------
   // collision: (w/2) min(d, 0)^2 per vertex with d = (x - q) . n, gradient w min(d, 0) n;
   // the term drops out wherever the vertex no longer penetrates
-  double accB[2] = {0.0, 0.0};
+  Sums<2> sumB;
   const Real wc = Real(col.w);
-  for (int i = tid(); i < n; i += kThreads) {
+#pragma unroll 1
+  for (int set = 0; set < kSets; ++set) {
+  double accB[2] = {0.0, 0.0};
+  for (int i = tid() + set * kThreads; i < n; i += kWide) {
     Real gx = 0, gy = 0, gz = 0;
     const Real rix = work[i], riy = work[np + i], riz = work[2 * np + i];
     Real mass = 0;
@@ -704,23 +860,32 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
     accB[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
                - ((double)ux * bx + (double)uy * by + (double)uz * bz);
   }
+  sumB.set(set, accB);
+  }
   for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
   __syncthreads();   // work (R) is reused for the corner chunks below
 
   // ---- passes C/D: triangle in-plane terms + volume, per chunk --------------------
-  double accT[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // as triangle_terms
-  double accU = 0.0;                               // |u.b|
   const Real ca = Real(0.5 * coefa);               // global area: k_A (A - A0) / G_A / 2
-  double accD[4] = {0.0, 0.0, 0.0, 0.0};   // |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
+  Sums<5> sumD;                                    // D_UB .. D_F2
   for (int t0 = 0; t0 < nt; t0 += ch) {
     const int tn = min(ch, nt - t0);
-    for (int tt = tid(); tt < tn; tt += kThreads) {
-      const int t = t0 + tt;
-      triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accT, work + tt, ch);
+#pragma unroll 1
+    for (int set = 0; set < kSets; ++set) {
+      double accT[C::N];
+      sumT.get(set, accT);
+      for (int tt = tid() + set * kThreads; tt < tn; tt += kWide)
+        triangle_terms<Real, EXT, TERMS>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t0 + tt, accT, work + tt, ch);
+      sumT.set(set, accT);
     }
     if (!pre) {
-      double vv[2] = {accT[0], accT[1]};
-      block_sum(vv, red);                  // also the barrier before the gather
+      double vv[2];
+#pragma unroll
+      for (int set = 0; set < kSets; ++set) {
+        const double v2[2] = {sumT.v[set][C::V], sumT.v[set][C::A]};
+        red.put(set, v2);
+      }
+      red.finish(vv);                      // also the barrier before the gather
       vol = vv[0] / 6.0;
       area = vv[1];
       coefd = mat.k_volume * (vol - M.V0) / Gn;
@@ -729,12 +894,16 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
     }
     const Real coef = Real(coefd / 6.0);         // per corner: k C / G_n * (e1 x e2) / 6
     const bool last = t0 + ch >= nt;
-    for (int i = tid(); i < n; i += kThreads) {
+#pragma unroll 1
+    for (int set = 0; set < kSets; ++set) {
+    double accD[5];
+    sumD.get(set, accD);
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
       Real gx = 0, gy = 0, gz = 0, vx = 0, vy = 0, vz = 0;
       // Branch-free, so that the reads of all corners are in flight together: a padding
       // entry, or a corner outside this chunk, reads the chunk's first triangle and adds
-      // zero; corner k adds g_a, g_b or -(g_a + g_b) (the same roundings as adding each
-      // case on its own).
+      // zero; corner k adds g_a, g_b or -g_a and -g_b, in the order and with the roundings of
+      // evaluate_resident (a cell's bits do not depend on the other meshes of its batch).
       Real mass = 0;
       for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
         int cc[kEllGroup];
@@ -751,10 +920,14 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
           const Real ax = work[tc], ay = work[ch + tc], az = work[2 * ch + tc];
           const Real bx = work[3 * ch + tc], by = work[4 * ch + tc], bz = work[5 * ch + tc];
           const Real nx = work[6 * ch + tc], ny = work[7 * ch + tc], nz = work[8 * ch + tc];
-          const Real sg = ok ? (k == 2 ? Real(-1) : Real(1)) : Real(0);
-          gx += sg * (k == 0 ? ax : (k == 1 ? bx : ax + bx));
-          gy += sg * (k == 0 ? ay : (k == 1 ? by : ay + by));
-          gz += sg * (k == 0 ? az : (k == 1 ? bz : az + bz));
+          const Real wa = !ok || k == 1 ? Real(0) : (k == 0 ? Real(1) : Real(-1));
+          const Real wb = !ok || k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
+          gx += wa * ax;
+          gy += wa * ay;
+          gz += wa * az;
+          gx += wb * bx;
+          gy += wb * by;
+          gz += wb * bz;
           vx += ok ? nx : Real(0);
           vy += ok ? ny : Real(0);
           vz += ok ? nz : Real(0);
@@ -775,22 +948,34 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
         const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
         const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
         const double fx = gx - (mux - bx), fy = gy - (muy - by), fz = gz - (muz - bz);
-        accD[0] += (double)gx * gx + (double)gy * gy + (double)gz * gz;
-        accD[1] += mux * mux + muy * muy + muz * muz;
-        accD[2] += (double)bx * bx + (double)by * by + (double)bz * bz;
-        accD[3] += fx * fx + fy * fy + fz * fz;
-        accU += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+        accD[0] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+        accD[1] += (double)gx * gx + (double)gy * gy + (double)gz * gz;
+        accD[2] += mux * mux + muy * muy + muz * muz;
+        accD[3] += (double)bx * bx + (double)by * by + (double)bz * bz;
+        accD[4] += fx * fx + fy * fy + fz * fz;
       }
+    }
+    sumD.set(set, accD);
     }
     __syncthreads();
   }
   const double Cv = vol - M.V0, Ca = area - M.A0;
   const double e_vol = 0.5 * mat.k_volume * Cv * Cv / Gn;
   const double e_area = area_on ? 0.5 * mat.k_area_global * Ca * Ca / GA : 0.0;
-  double acc[11] = {accB[0], accB[1], accT[4], accT[5], accT[6], accT[7], accU, accD[0], accD[1], accD[2], accD[3]};
-  block_sum(acc, red);
-  finish_eval(M, acc[0], accA[1] + accA[2], acc[2], acc[3], acc[4], e_vol, e_area, acc[1], acc[6], acc[7], acc[8], acc[9],
-              acc[10], vol, area, acc[5], res);
+  constexpr int ND = kSumD<EXT>;
+  double sc[C::N], sd[ND];
+#pragma unroll
+  for (int set = 0; set < kSets; ++set) red.put(set, sumT.v[set]);
+  red.finish(sc);
+#pragma unroll
+  for (int set = 0; set < kSets; ++set) {
+    double v[ND];
+#pragma unroll
+    for (int q = 0; q < ND; ++q) v[q] = q == D_IN ? sumB.v[set][0] : (q == D_COL ? sumB.v[set][1] : sumD.v[set][q - 1]);
+    red.put(set, v);
+  }
+  red.finish(sd);
+  finish_eval<Real, EXT, TERMS>(M, sc, sd, e_vol, e_area, vol, area, res);
 }
 
 // The same for a cell whose vectors and whole triangle list are in LDS (every mesh of the
@@ -806,7 +991,7 @@ __device__ void evaluate(const MeshC<Real>& M, const MaterialDev& mat, bool lite
 // CU).  Against five passes with three sums and nine barriers and the corner list decoded per
 // corner, a step of 1024 cells went from 790 to 725 us, of 100,000 from 77.1 to 69.8 ms and
 // of 2,000 with contacts from 8.75 to 7.37 ms.
-template <typename Real, bool EXT, typename RED>
+template <typename Real, bool EXT, bool TERMS, typename RED>
 __device__ __attribute__((always_inline)) inline void evaluate_resident(
     const MeshC<Real>& M, const MaterialDev& mat, bool literal, double h, double Gn, double GA,
     const Contacts<Real>& col, const Real* xn, const Real* ut, const Real* bvec, Real* rb, Real* work, Real* gout,
@@ -825,8 +1010,11 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   // global area (optional): the total area first
   double coefa = 0.0, area64 = 0.0;
   if (area_on) {
-    double a2[1] = {0.0};
-    for (int t = tid(); t < nt; t += kThreads) {
+    double a2[1];
+#pragma unroll 1
+    for (int set = 0; set < kSets; ++set) {
+    double as[1] = {0.0};
+    for (int t = tid() + set * kThreads; t < nt; t += kWide) {
       const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
       double N[3], E1[3], E2[3];
 #pragma unroll
@@ -835,19 +1023,24 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
         E2[k] = ((double)xn[k * np + b] - (double)xn[k * np + c]) + ((double)ut[k * np + b] - (double)ut[k * np + c]);
       }
       N[0] = E1[1] * E2[2] - E1[2] * E2[1], N[1] = E1[2] * E2[0] - E1[0] * E2[2], N[2] = E1[0] * E2[1] - E1[1] * E2[0];
-      a2[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
+      as[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
     }
-    block_sum(a2, red);
+    red.put(set, as);
+    }
+    red.finish(a2);
     area64 = 0.5 * a2[0];
     coefa = mat.k_area_global * (area64 - M.A0) / GA;
   }
   const Real ca = Real(0.5 * coefa);               // k_A (A - A0) / G_A / 2
 
   // ---- bending residuals -> rb ------------------------------------------------------
-  // first sum: 6 volume, 2 area, bending and its Rayleigh energy, area PD, Skalak, triangle
-  // Rayleigh energy, collapsed triangles
-  double accC[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = tid(); i < n; i += kThreads) {
+  typedef SumC<TERMS> C;
+  double sumC[C::N];
+  if (tid() < 9) work[9 * nt + tid()] = Real(0);
+#pragma unroll 1
+  for (int set = 0; set < kSets; ++set) {
+  double accC[C::N] = {};
+  for (int i = tid() + set * kThreads; i < n; i += kWide) {
     Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
     const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
     const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
@@ -886,26 +1079,30 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
     const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
     const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
     const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
-    accC[2] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
-    accC[3] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
+    accC[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
+    accC[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
     rb[i] = rx + beta * ux;
     rb[np + i] = ry + beta * uy;
     rb[2 * np + i] = rz + beta * uz;
   }
   // ---- triangles -> corner buffer -----------------------------------------------------
-  if (tid() < 9) work[9 * nt + tid()] = Real(0);
-  for (int t = tid(); t < nt; t += kThreads)
-    triangle_terms<Real, EXT>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
-  block_sum(accC, red);
-  const double vol = accC[0] / 6.0, area = area_on ? area64 : accC[1];   // the area whose gradient is taken
+  for (int t = tid() + set * kThreads; t < nt; t += kWide)
+    triangle_terms<Real, EXT, TERMS>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
+  red.put(set, accC);
+  }
+  red.finish(sumC);
+  const double vol = sumC[C::V] / 6.0, area = area_on ? area64 : sumC[C::A];   // the area whose gradient is taken
   const double Cv = vol - M.V0;
   const Real coef = Real(mat.k_volume * Cv / Gn / 6.0);      // per corner: k C / G_n * (e1 x e2) / 6
 
   // ---- vertices: bending, inertia - b (+ collision), corners -> gout ---------------------
-  // second sum: inertial and collision energy, |u.b|, |grad|^2, |M u/h^2|^2, |b|^2, |F_int|^2
-  double accD[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  constexpr int ND = kSumD<EXT>;
+  double sumD[ND], held[ND - 4];
   const Real wc = Real(col.w);
-  for (int i = tid(); i < n; i += kThreads) {
+#pragma unroll 1
+  for (int set = 0; set < kSets; ++set) {
+  double accD[ND] = {};
+  for (int i = tid() + set * kThreads; i < n; i += kWide) {
     const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
     const Real rix = rb[i], riy = rb[np + i], riz = rb[2 * np + i];
     Real gx = 0, gy = 0, gz = 0, mass = 0;
@@ -940,9 +1137,9 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
       ox += wc * dm * cnx;
       oy += wc * dm * cny;
       oz += wc * dm * cnz;
-      accD[1] += 0.5 * col.w * (double)dm * dm;
+      if constexpr (EXT) accD[D_COL] += 0.5 * col.w * (double)dm * dm;
     }
-    accD[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
+    accD[D_IN] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
                - ((double)ux * bx + (double)uy * by + (double)uz * bz);
     // corners: k = 0 adds g_a, 1 g_b, 2 -(g_a + g_b), all of them the volume normal
     Real cx = 0, cy = 0, cz = 0, vx = 0, vy = 0, vz = 0;
@@ -978,31 +1175,33 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
     gout[2 * np + i] = tz;
     const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
     const double fx = tx - (mux - bx), fy = ty - (muy - by), fz = tz - (muz - bz);
-    accD[2] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
-    accD[3] += (double)tx * tx + (double)ty * ty + (double)tz * tz;
-    accD[4] += mux * mux + muy * muy + muz * muz;
-    accD[5] += (double)bx * bx + (double)by * by + (double)bz * bz;
-    accD[6] += fx * fx + fy * fy + fz * fz;
+    accD[D_UB] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+    accD[D_G2] += (double)tx * tx + (double)ty * ty + (double)tz * tz;
+    accD[D_MU2] += mux * mux + muy * muy + muz * muz;
+    accD[D_B2] += (double)bx * bx + (double)by * by + (double)bz * bz;
+    accD[D_F2] += fx * fx + fy * fy + fz * fz;
+  }
+  red.put_sets(set, accD, held);
   }
   for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
-  block_sum(accD, red);                                      // also orders the gradient
+  red.finish(sumD);                                          // also orders the gradient
   const double Ca = area - M.A0;
   const double e_vol = 0.5 * mat.k_volume * Cv * Cv / Gn;
   const double e_area = area_on ? 0.5 * mat.k_area_global * Ca * Ca / GA : 0.0;
-  finish_eval(M, accD[0], accC[2] + accC[3], accC[4], accC[5], accC[6], e_vol, e_area, accD[1], accD[2], accD[3], accD[4],
-              accD[5], accD[6], vol, area, accC[7], res);
+  finish_eval<Real, EXT, TERMS>(M, sumC, sumD, e_vol, e_area, vol, area, res);
+
 }
 
 // One evaluation in the batch's vector layout (LAY as for step_kernel): with every vector in
 // LDS the fourth LDS vector holds the bending residuals (b is read from the workspace).
-template <typename Real, bool EXT, int LAY, typename RED>
+template <typename Real, bool EXT, int LAY, bool TERMS = false, typename RED>
 __device__ __attribute__((always_inline)) inline void evaluate_any(const MeshC<Real>& M, const MaterialDev& mat,
                                                                    bool literal, double h, double Gn, double GA,
                                                                    const Contacts<Real>& col, const Real* xn, const Real* ut,
                                                                    const Real* bvec, Real* rb, Real* work, Real* gout,
                                                                    RED& red, EvalResult& res) {
-  if constexpr (LAY == 0) evaluate_resident<Real, EXT>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, rb, work, gout, red, res);
-  else evaluate<Real, EXT>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, work, gout, red, res);
+  if constexpr (LAY == 0) evaluate_resident<Real, EXT, TERMS>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, rb, work, gout, red, res);
+  else evaluate<Real, EXT, TERMS>(M, mat, literal, h, Gn, GA, col, xn, ut, bvec, work, gout, red, res);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1319,7 +1518,7 @@ struct Tile {
 };
 
 template <typename Real, typename CST, typename RED>
-__device__ void finalize_cell(const StepArgs<Real>& A, const MeshC<Real>& M, int cell, int64_t voff, CST& cs,
+__device__ __attribute__((always_inline)) inline void finalize_cell(const StepArgs<Real>& A, const MeshC<Real>& M, int cell, int64_t voff, CST& cs,
                               const Real* xn, const Real* U, RED& red, double* bc) {
   const int n = M.n, np = M.n_pad;
   const double h = A.sol.h;
@@ -1333,22 +1532,30 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshC<Real>& M, int
     }
   } else {
     // v = u / h, then damp its departure from the best-fit rigid motion (section 2.1.4)
-    double s1[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int i = tid(); i < n; i += kThreads) {
+    double s1[7];
+#pragma unroll 1
+    for (int set = 0; set < kSets; ++set) {
+    double sv[7] = {0, 0, 0, 0, 0, 0, 0};
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
       const double m = gld(M.mass, i);
-      s1[0] += m;
+      sv[0] += m;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         const double x = (double)xn[c * np + i] + (double)U[c * np + i];
-        s1[1 + c] += m * x;
-        s1[4 + c] += m * ((double)U[c * np + i] / h);
+        sv[1 + c] += m * x;
+        sv[4 + c] += m * ((double)U[c * np + i] / h);
       }
     }
-    block_sum(s1, red);
+    red.put(set, sv);
+    }
+    red.finish(s1);
     const double xc[3] = {s1[1] / s1[0], s1[2] / s1[0], s1[3] / s1[0]};
     const double vc[3] = {s1[4] / s1[0], s1[5] / s1[0], s1[6] / s1[0]};
+    Folded<9> fold2;
+#pragma unroll 1
+    for (int set = 0; set < kSets; ++set) {
     double s2[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // L (3), I_xx I_yy I_zz I_xy I_xz I_yz
-    for (int i = tid(); i < n; i += kThreads) {
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
       const double m = gld(M.mass, i);
       const double rx = (double)xn[i] + (double)U[i] - xc[0];
       const double ry = (double)xn[np + i] + (double)U[np + i] - xc[1];
@@ -1364,7 +1571,10 @@ __device__ void finalize_cell(const StepArgs<Real>& A, const MeshC<Real>& M, int
       s2[7] -= m * rx * rz;
       s2[8] -= m * ry * rz;
     }
-    block_sum(s2, red);
+    fold2.fold(set, s2);
+    }
+    double s2[9];
+    fold2.sum(s2, red);
     // omega = I^-1 L (3x3 symmetric, adjugate)
     const double Ixx = s2[3], Iyy = s2[4], Izz = s2[5], Ixy = s2[6], Ixz = s2[7], Iyz = s2[8];
     const double c00 = Iyy * Izz - Iyz * Iyz, c01 = Ixz * Iyz - Ixy * Izz, c02 = Ixy * Iyz - Ixz * Iyy;
@@ -1598,10 +1808,14 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       // gradient, u and the s_p too, and all of it until the next q is formed, so that an
       // iteration costs one memory round trip instead of five (longer histories would
       // spill).  The sums run in the same order either way.
-      const bool fused = len <= 2 * W * kThreads, keep = H <= 2 && fused;
+      // With both workgroup sizes compiled (FP32), vectors of at most two slots for kNarrow threads
+      // are taken by that many threads of either, so that the sums run alike.
+      const bool small = std::is_same<Real, float>::value && len <= 2 * W * kNarrow;
+      const int e0 = kThreads > kNarrow && small && tid() >= kNarrow ? len : W * tid(), es = W * (small ? kNarrow : kThreads);
+      const bool fused = small || len <= 2 * W * kThreads, keep = H <= 2 && fused;
       const V zero = {};
       V rr[2], gg[2], uu[2], dd[2], ys[H][2], ss[H][2];
-      const int ek[2] = {W * tid(), W * tid() + W * kThreads};
+      const int ek[2] = {e0, e0 + es};
       if (fused) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -1621,9 +1835,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       vcopy(xn, tl.vec(VX, j), len);
       if (b_lds) vcopy(bl, tl.vec(VB, j), len);
       // second half: y_p . r for every stored pair (one pass)
-      double yr[H];
-#pragma unroll
-      for (int p = 0; p < H; ++p) yr[p] = 0.0;
+      double yr[H] = {};
       if (hn > 0) {
         if (fused) {
 #pragma unroll
@@ -1636,21 +1848,28 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
               }
             }
           }
+          red.sum_one(yr);
         } else {
+          Folded<H> fold;
+#pragma unroll 1
+          for (int set = 0; set < kSets; ++set) {
+            double y1[H] = {};
 #pragma unroll 2
-          for (int e = W * tid(); e < len; e += W * kThreads) {
-            const auto rv = vload(D, e);
+            for (int e = W * (tid() + set * kThreads); e < len; e += W * kWide) {
+              const auto rv = vload(D, e);
 #pragma unroll
-            for (int p = 0; p < H; ++p) {
-              if (p < hn) {
-                const auto yv = vload(tl.vec(VS0 + m + slot(p), j), e);
+              for (int p = 0; p < H; ++p) {
+                if (p < hn) {
+                  const auto yv = vload(tl.vec(VS0 + m + slot(p), j), e);
 #pragma unroll
-                for (int w = 0; w < W; ++w) yr[p] += (double)yv[w] * rv[w];
+                  for (int w = 0; w < W; ++w) y1[p] += (double)yv[w] * rv[w];
+                }
               }
             }
+            fold.fold(set, y1);
           }
+          fold.sum(yr, red);
         }
-        block_sum(yr, red);
       }
       double cf[H];                                    // alpha_p - beta_p
 #pragma unroll
@@ -1698,12 +1917,20 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
               d_slot(ek[k], rr[k], vload(G, ek[k]), vload(U, ek[k]),
                      [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), ek[k]) : zero; });
           }
+        red.sum_one(gdv);
       } else {
+        Folded<1> fold;
+#pragma unroll 1
+        for (int set = 0; set < kSets; ++set) {
 #pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kThreads)
-          d_slot(e, vload(D, e), vload(G, e), vload(U, e), [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), e) : zero; });
+          for (int e = W * (tid() + set * kThreads); e < len; e += W * kWide)
+            d_slot(e, vload(D, e), vload(G, e), vload(U, e),
+                   [&](int p) { return hn > 0 ? vload(tl.vec(VS0 + slot(p), j), e) : zero; });
+          fold.fold(set, gdv);
+          gdv[0] = 0.0;
+        }
+        fold.sum(gdv, red);
       }
-      block_sum(gdv, red);
       const double gd = gdv[0];
       // line search: alpha = 1, 1/2, ... until sufficient decrease (Algorithm 1)
       double alpha = 1.0;
@@ -1714,7 +1941,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
         if (hv > 0) {
           const Real al = Real(alpha);
 #pragma unroll 2
-          for (int e = W * tid(); e < len; e += W * kThreads) {
+          for (int e = e0; e < len; e += es) {                     // each thread's own elements of D
             const auto uv = vload(U, e), dv = vload(D, e);
             vstore(ut, e, uv + al * dv);
           }
@@ -1752,9 +1979,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
       const bool full = m > 0 && hn == m;
       const int ns = head;                                       // slot written
       // acc: [0] s.y  [1] s.s  [2] y.y  [3] s.g'  [4+p] s_p.g'  [4+H+p] s.y_p  [4+2H+p] y.s_p
-      double acc[4 + 3 * H];
-#pragma unroll
-      for (int k = 0; k < 4 + 3 * H; ++k) acc[k] = 0.0;
+      constexpr int NA = 4 + 3 * H;
+      double acc[NA] = {};
       V gt2[2], yn2[2];                                          // keep: the new gradient and y
       if (m > 0) {
         Real* Sn = tl.vec(VS0 + ns, j);
@@ -1790,7 +2016,23 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
           }
           return yv;
         };
-        if (keep) {
+        auto a_loop = [&](int e, int step) {
+#pragma unroll 2
+          for (; e < len; e += step)
+            a_slot(e, vload(GT, e), vload(G, e), vload(D, e), vload(U, e), [&](int p) { return vload(tl.vec(VS0 + slot(p), j), e); },
+                   [&](int p) { return vload(tl.vec(VS0 + m + slot(p), j), e); });
+        };
+        if (kSets > 1 && !fused) {
+          Folded<NA> fold;
+#pragma unroll 1
+          for (int set = 0; set < kSets; ++set) {
+            a_loop(e0 + W * set * kThreads, W * kWide);
+            fold.fold(set, acc);
+#pragma unroll
+            for (int q = 0; q < NA; ++q) acc[q] = 0.0;
+          }
+          fold.sum(acc, red);
+        } else if (keep) {
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
             if (ek[k] < len) {
@@ -1798,20 +2040,19 @@ __device__ __attribute__((always_inline)) inline void run_tile(const StepArgs<Re
               yn2[k] = a_slot(ek[k], gt2[k], gg[k], dd[k], uu[k], [&](int p) { return ss[p][k]; }, [&](int p) { return ys[p][k]; });
             }
           }
+          red.sum_one(acc);
         } else {
-#pragma unroll 2
-          for (int e = W * tid(); e < len; e += W * kThreads)
-            a_slot(e, vload(GT, e), vload(G, e), vload(D, e), vload(U, e), [&](int p) { return vload(tl.vec(VS0 + slot(p), j), e); },
-                   [&](int p) { return vload(tl.vec(VS0 + m + slot(p), j), e); });
+          a_loop(e0, es);
+          red.sum_one(acc);
         }
       } else {
 #pragma unroll 2
-        for (int e = W * tid(); e < len; e += W * kThreads) {
+        for (int e = e0; e < len; e += es) {
           vstore(U, e, vload(U, e) + al * vload(D, e));
           vstore(G, e, vload(GT, e));
         }
+        red.barrier();
       }
-      block_sum(acc, red);
       // the reduced dot products (the same in every lane) picked by pair index o < H
       auto pick = [&](int base, int o) {
         double v = 0.0;
@@ -2005,7 +2246,7 @@ __global__ void __launch_bounds__(kThreads) eval_kernel(StepArgs<Real> A, const 
   stage_aos(ut, u + 3 * voff, n, np);
   __syncthreads();
   EvalResult r;
-  evaluate_any<Real, true, LAY>(M, A.mat, A.sol.literal != 0, A.sol.h, Gn, GA, Contacts<Real>{nullptr, nullptr, 0.0}, xn, ut, B,
+  evaluate_any<Real, true, LAY, true>(M, A.mat, A.sol.literal != 0, A.sol.h, Gn, GA, Contacts<Real>{nullptr, nullptr, 0.0}, xn, ut, B,
                                 rb, work, G, red, r);
   for (int e = tid(); e < 3 * n; e += kThreads) {
     const int i = e / 3, c = e - 3 * i;
