@@ -1785,6 +1785,7 @@ struct npfem_net {
   const NetMeshDev* d_meshes = nullptr;
   int n_pad_max = 0;
   bool resident = false, resident_train = false;   // every mesh fits the resident kernels
+  bool features32 = true;                   // inference: features in FP32
   int adam_t = 0;
   // inference scratch: per workgroup, features and two activation planes
   DeviceBuffers ibuf;
@@ -2002,6 +2003,7 @@ npfem_status net_infer_now(npfem_net* net, npfem_batch* b, const void* x, const 
   const int grid = net_fwd_grid(net, (int)b->n_cells);
   if (net->resident) {
     a.cframe = b->net_frames;
+    a.features32 = net->features32;
     HIP_TRY(launch_net_resident<Real>(a, grid, 0, s));
     return NPFEM_OK;
   }
@@ -2196,6 +2198,7 @@ npfem_status npfem_net_create(npfem_plan* p, const npfem_net_config* cfg, const 
     d.nb_idx = p->precision == NPFEM_FP64 ? mp.dev64.nb_idx : mp.dev32.nb_idx;
     d.nb_ell = p->precision == NPFEM_FP64 ? mp.dev64.nb_ell : mp.dev32.nb_ell;
     d.nb_deg = p->precision == NPFEM_FP64 ? mp.dev64.nb_deg : mp.dev32.nb_deg;
+    net->features32 = net->features32 && net_features32(d.n_pad, d.nb_deg);
     if ((s = net->buf.upload(Xc.data(), Xc.size(), &d.Xc))) return s;
     if ((s = net->buf.upload(mp.mass.data(), mp.mass.size(), &d.mass))) return s;
     if ((s = net_upload_order(net.get(), m, mp, Xc, d))) return s;

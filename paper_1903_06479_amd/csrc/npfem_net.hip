@@ -518,6 +518,10 @@ __device__ inline uint32_t pack2(float a, float b) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
+__device__ inline uint32_t pack2(double a, double b) {      // rounded once
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
 __device__ inline float half_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float half_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -565,11 +569,12 @@ __device__ inline void wait_staged() { __builtin_amdgcn_s_waitcnt(0x0f70); }   /
 // NW waves of up to RR row blocks each (n_pad <= 16 NW RR); a wave past the last one repeats
 // it without storing, so that the rounds are free of branches.  TRAIN keeps what the backward
 // pass reads: per layer the activations, the neighbour means and the signs of the
-// pre-activations, and the features, formed in FP64.
-template <typename Real, int NW, int RR, bool TRAIN>
+// pre-activations.  F: the precision in which the features are formed (before BF16 rounds them):
+// FP64 in training, and in inference but for the small regular meshes (net_features32).
+template <typename Real, int NW, int RR, bool TRAIN, typename F>
 __global__ void __launch_bounds__(NW * 64, 2) net_resident_kernel(NetFwdArgs<Real> A) {
   extern __shared__ __align__(16) unsigned char lds[];
-  typedef typename std::conditional<TRAIN, double, float>::type F;
+  constexpr bool kF64 = std::is_same<F, double>::value;
   constexpr int kPairs = kNetUnrollDeg / 2;
   const int zero_row = A.S.n_pad_max;          // a row of zeros: where a neighbour list has ended
   uint16_t* H = reinterpret_cast<uint16_t*>(lds);
@@ -655,11 +660,10 @@ __global__ void __launch_bounds__(NW * 64, 2) net_resident_kernel(NetFwdArgs<Rea
         const bool own = wave + NW * r < nrb, tail = rb * 16 + 16 > n;   // uniform
         __builtin_amdgcn_sched_barrier(0);     // one row block's registers at a time
         // (R^T x - X) / shape, R^T v h / s, R^T f h^2 / (s m) or X / rho: one lane group each
-        F w[3], Xr[3];
-        float fv[3];
+        F w[3], Xr[3], fv[3];
         const double m = M.rest[4 * row + 3];
         float im = 0.f;
-        if constexpr (TRAIN) {
+        if constexpr (kF64) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) Xr[a] = M.rest[4 * row + a];
         } else {
@@ -674,13 +678,13 @@ __global__ void __launch_bounds__(NW * 64, 2) net_resident_kernel(NetFwdArgs<Rea
           const F t = fma(R[6 + a], w[2], fma(R[3 + a], w[1], R[a] * w[0]));     // (R^T w)_a
           F g = (kq == 3 ? Xa : t) - (kq == 0 ? Xa : F(0));
           g *= scl;
-          if constexpr (TRAIN) g /= kq == 2 ? m : 1.0;
+          if constexpr (kF64) g /= kq == 2 ? m : 1.0;
           else g *= kq == 2 ? im : 1.f;
-          fv[a] = (float)g;
-          if (tail) fv[a] = row < n ? fv[a] : 0.f;
+          fv[a] = g;
+          if (tail) fv[a] = row < n ? fv[a] : F(0);
         }
         // features 0-7 to lane group 0, 8-11 to group 1: the operand's k slots
-        const uint32_t p0 = pack2(fv[0], fv[1]), p1 = pack2(fv[2], 0.f);
+        const uint32_t p0 = pack2(fv[0], fv[1]), p1 = pack2(fv[2], F(0));
         const uint32_t q0 = __shfl(p0, lane + 16, 64), q1 = __shfl(p1, lane + 16, 64);
         const uint32_t r0 = __shfl(p0, lane + 32, 64), r1 = __shfl(p1, lane + 32, 64);
         uint4 fw = {0u, 0u, 0u, 0u};
@@ -1458,6 +1462,11 @@ size_t net_chain_lds_bytes(int n_pad) {
   if (n_pad > 768) return 0;     // three blocks per wave
   return ((size_t)n_pad * (kHP + 3) * 2 + (size_t)resident_waves(n_pad) * 256 * 4 + 15) / 16 * 16;
 }
+// FP32 features in inference: meshes of up to 704 rows and degree eight.  They round to the other
+// BF16 value in about one feature of 5,500 (measured at 642 vertices); larger meshes and those of high
+// degree have FP64 features (2,000 cells of 742 vertices: 435 us with FP32, 448 with FP64).
+bool net_features32(int n_pad, int nb_deg) { return n_pad <= 704 && nb_deg <= 8; }
+
 int net_resident_per_cu(int n_pad) { return resident_waves(n_pad) == 4 ? 2 : 1; }
 
 template <typename K, typename... Args>
@@ -1478,11 +1487,14 @@ hipError_t launch_net_resident(const NetFwdArgs<Real>& a, int grid, int train, h
   hipLaunchKernelGGL(net_frame_kernel<Real>, dim3((a.n_cells + 3) / 4), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (resident_waves(np) == 4)
-    return train ? launch_lds(net_resident_kernel<Real, 4, 5, true>, dim3(grid), 256, lds, s, a)
-                 : launch_lds(net_resident_kernel<Real, 4, 5, false>, dim3(grid), 256, lds, s, a);
-  return train ? launch_lds(net_resident_kernel<Real, 8, 6, true>, dim3(grid), 512, lds, s, a)
-               : launch_lds(net_resident_kernel<Real, 8, 6, false>, dim3(grid), 512, lds, s, a);
+  if (resident_waves(np) == 4) {
+    if (train) return launch_lds(net_resident_kernel<Real, 4, 5, true, double>, dim3(grid), 256, lds, s, a);
+    return a.features32 ? launch_lds(net_resident_kernel<Real, 4, 5, false, float>, dim3(grid), 256, lds, s, a)
+                        : launch_lds(net_resident_kernel<Real, 4, 5, false, double>, dim3(grid), 256, lds, s, a);
+  }
+  if (train) return launch_lds(net_resident_kernel<Real, 8, 6, true, double>, dim3(grid), 512, lds, s, a);
+  return a.features32 ? launch_lds(net_resident_kernel<Real, 8, 6, false, float>, dim3(grid), 512, lds, s, a)
+                      : launch_lds(net_resident_kernel<Real, 8, 6, false, double>, dim3(grid), 512, lds, s, a);
 }
 
 hipError_t launch_net_chain(const NetChainArgs& a, int grid, int slots, float* grad, hipStream_t s) {

@@ -124,6 +124,7 @@ struct NetFwdArgs {
   const Real* f;
   Real* delta;                 // [V][3] world-frame correction (inference), or null
   double* cframe;              // [n_cells][kNetFrame] frames of the resident kernels
+  int features32;              // resident inference: features formed in FP32 (net_features32)
 };
 
 template <typename Real>
@@ -180,6 +181,7 @@ template <typename Real>
 hipError_t launch_net_resident(const NetFwdArgs<Real>& a, int grid, int train, hipStream_t s);
 size_t net_resident_lds_bytes(int n_pad);
 int net_resident_per_cu(int n_pad);
+bool net_features32(int n_pad, int nb_deg);
 // Backward of the resident forward (n_pad <= 768, else net_chain_lds_bytes is 0): `slots`
 // (<= n_cells) weight-gradient partial sums, the gradient into grad.
 hipError_t launch_net_chain(const NetChainArgs& a, int grid, int slots, float* grad, hipStream_t s);

@@ -57,3 +57,21 @@ def test_time_follows_the_rows_of_high_degree():
             best.append(a.elapsed_time(b))
         us.append(min(best))
     assert us[1] <= 6 * us[0], us
+
+
+@pytest.mark.parametrize("segments,rings,cells", [(20, 37, 60), (16, 40, 60), (200, 3, 60), (11, 31, 60)])
+def test_features_keep_their_precision(segments, rings, cells, monkeypatch):
+    """Meshes above 704 rows or of high degree form their features in FP64, as the kernels that
+    gather from memory do: the same features are rounded to BF16, and the corrections are the
+    same bits (features formed in FP32 round the other way in a few of a cell's)."""
+    from paper_1903_06479_amd import Batch, Net
+    m = polar_mesh(segments, rings)
+    theta = gpu_params(mp.NetConfig(), 17).astype(np.float32)
+    plan = make([m], "fp32")
+    batch = Batch(plan, np.zeros(cells, np.int32))
+    xs = [T(a) for a in cells_of(m[0], cells, 20)]
+    got = Net(plan, theta).infer(batch, *xs).clone()
+    monkeypatch.setenv("NPFEM_NET_NO_LDS", "1")
+    ref = Net(plan, theta).infer(batch, *xs)
+    torch.cuda.synchronize()
+    assert torch.equal(got, ref)
