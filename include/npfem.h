@@ -309,12 +309,12 @@ npfem_status npfem_step_contacts(npfem_batch *batch, const void *x, const void *
  * forbid hipMalloc.  Same arguments, results and per-cell statistics as npfem_step
  * (bit for bit), launched directly on `stream` (never through the batch's graphs).
  * The tile counter, the cell states and the persistent workgroups' workspace live in a
- * static device array of 67 MiB per GPU, allocated when the library's code is loaded on
+ * static device array of 77 MiB per GPU, allocated when the library's code is loaded on
  * that GPU and held until the process ends; its address is looked up when the first
  * plan on the GPU is created.  The persistent grid is reduced to the workgroups whose
  * workspace fits the array (a 642-vertex FP32 batch at 5 cells per tile and history 2
- * keeps about 170 workgroups).  NPFEM_E_UNSUPPORTED if a single workgroup's workspace
- * exceeds 67 MiB.  Every call on a GPU shares that GPU's array: calls that overlap on
+ * keeps about 200 workgroups).  NPFEM_E_UNSUPPORTED if a single workgroup's workspace
+ * exceeds 77 MiB.  Every call on a GPU shares that GPU's array: calls that overlap on
  * one GPU (on different streams, or from several threads) race and must not be issued.
  */
 npfem_status npfem_step_noalloc(npfem_batch *batch, const void *x, const void *v, const void *f_ext,

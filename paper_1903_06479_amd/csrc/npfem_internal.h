@@ -187,7 +187,7 @@ hipError_t launch_drag(const Real* x, const Real* v, const int64_t* cell_voff, c
                        Real* f, hipStream_t s);
 // Allocation-free step: size of the per-device scratch array and its device address
 // (the address must be looked up with the device current).
-constexpr size_t kScratchBytes = size_t(67) << 20;
+constexpr size_t kScratchBytes = size_t(77) << 20;
 hipError_t scratch_address(void** ptr);
 hipError_t launch_stats_accumulate(const npfem_cell_stats* st, int64_t n, npfem_stats_total* tot, hipStream_t s);
 hipError_t launch_stats_reset(npfem_stats_total* tot, hipStream_t s);
