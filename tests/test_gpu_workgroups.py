@@ -52,3 +52,47 @@ def test_bits_do_not_depend_on_the_workgroup(mesh, bf16, lbfgs_m, optional):
         mixed = run(plan_of([m, big], optional, inverse_bf16=bf16, lbfgs_m=lbfgs_m), [0] * 7 + [1],
                     torch.cat([x[:7 * n], xb]), torch.cat([v[:7 * n], vb]), torch.cat([f[:7 * n], fb]), 3)
         assert torch.equal(mixed[1][:7 * n], few[1]) and torch.equal(mixed[2][:7 * n], few[2])
+
+
+@pytest.mark.parametrize("mesh,bf16,lbfgs_m,terms", [("162", 0, 5, ""), ("162", 1, 2, ""), ("162", 2, 8, ""), ("42", 2, 5, ""),
+                                                     ("pass", 0, 2, ""), ("162", 2, 5, "area"), ("162", 0, 2, "literal"),
+                                                     ("162", 2, 2, "contacts"), ("162", 0, 8, "contacts")])
+def test_four_waves_match_oracle(mesh, bf16, lbfgs_m, terms):
+    """More tiles than CUs, so that workgroups have four waves: a few of the cells against the
+    oracle, 1e-5 of the diameter as for the other FP32 steps."""
+    import oracle.model as om
+    import oracle.step as ostep
+    from paper_1903_06479_amd import Batch, Mesh, Plan, default_material, default_params
+    X, Tr = mesh_of(mesh)
+    n, cells, ka = len(X), 300, 60.0 if terms == "area" else 0.0
+    x, v, f = (a.astype(np.float32).astype(np.float64) for a in cells_of(X, cells, 51))
+    plan = Plan([Mesh(X, Tr)], DT, material=default_material(k_area_global=ka),
+                params=default_params(precision="fp32", inverse_bf16=bf16, lbfgs_m=lbfgs_m, max_iter=200,
+                                      volume_normaliser=int(terms == "literal")))
+    batch = Batch(plan, np.zeros(cells, np.int32))
+    s = batch.schedule(cells_per_tile=1)
+    assert s["grid_blocks"] == s["n_tiles"] == cells > torch.cuda.get_device_properties(0).multi_processor_count
+    ts = [T(a, torch.float32) for a in (x, v, f)]
+    contacts = None
+    if terms == "contacts":          # tangent planes through and just above some of the vertices
+        rng = np.random.default_rng(52)
+        nn = rng.standard_normal(x.shape)
+        nn /= np.linalg.norm(nn, axis=1, keepdims=True)
+        nn[rng.random(len(x)) > 0.2] = 0.0
+        q = (x + 0.05 * nn * rng.random((len(x), 1))).astype(np.float32).astype(np.float64)
+        nn = nn.astype(np.float32).astype(np.float64)
+        contacts, w = (q, nn), 2.0e4
+        xo, _, _ = batch.step_contacts(*ts, T(q, torch.float32), T(nn, torch.float32), w)
+        batch.schedule(cells_per_tile=3)
+        eight, _, _ = batch.step_contacts(*ts, T(q, torch.float32), T(nn, torch.float32), w)
+        assert torch.equal(eight, xo)
+    else:
+        xo, _, _ = batch.step(*ts)
+    torch.cuda.synchronize()
+    xo = xo.cpu().numpy().astype(np.float64)
+    m = om.Model(X, Tr, om.Material(k_area_global=ka), DT)
+    for c in (0, 151, 299):
+        k = slice(c * n, (c + 1) * n)
+        extra = {"contacts": (contacts[0][k], contacts[1][k], w)} if contacts else {}
+        xr, _, _ = ostep.step(m, x[k], v[k], f[k], ostep.Params(tol=1e-12, polish=True), literal=terms == "literal", **extra)
+        assert np.abs(xo[k] - xr).max() <= 1e-5 * np.ptp(X[:, 0]), c
