@@ -1,5 +1,6 @@
 """Compile the gfx950 library libnpfem.so in-tree with hipcc: one object per source (the
-step kernels as two, FP32 and FP64), compiled in parallel, then linked."""
+step kernels as three: FP64, and FP32 with workgroups of 256 and of 512 threads), compiled
+in parallel, then linked."""
 from __future__ import annotations
 
 import os

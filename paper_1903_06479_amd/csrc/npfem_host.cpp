@@ -600,8 +600,9 @@ void factor_layouts(const BandFactorHost& f, int np, int B, std::vector<Real>& F
 
 // Uploads both factors (H~ and M~/h^2) in precision Real, in one band width B (the wider
 // of the two), with the order's inverse permutation, in the layout of the plan's kernel
-// (FP32: FA, GA, DA, DB; FP64: F, G, T); leaves them null when the kernel's LDS ring
-// would not fit a compute unit.
+// (FP32: FA, GA, DA, DB; FP64: F, G, T); leaves them null when the band is too wide: when a
+// ring of 64 right-hand sides per position would not fit a compute unit (what the FP64
+// kernel keeps; the same limit holds in FP32, whose kernel keeps 16).
 template <typename Real>
 npfem_status upload_factor(npfem_plan* p, int np, const std::vector<int>& perm, const BandFactorHost (&fh)[2],
                            BandFactorDev<Real>& f) {
@@ -1784,7 +1785,7 @@ struct npfem_net {
   NetPackDst packed{};
   const NetMeshDev* d_meshes = nullptr;
   int n_pad_max = 0;
-  bool resident = false, resident_train = false;   // every mesh fits the resident kernels
+  bool resident = false;                    // every mesh fits the resident kernels
   bool features32 = true;                   // inference: features in FP32
   int adam_t = 0;
   // inference scratch: per workgroup, features and two activation planes
@@ -1946,7 +1947,7 @@ npfem_status net_training_scratch(npfem_net* net, int cells) {
   get(C * sizeof(double), &net->tloss);
   get(C * np * 3 * sizeof(float), &net->tout);
   get(C * np * 3 * sizeof(float), &net->tdout);
-  if (net->resident_train) {
+  if (net->resident) {
     // weight-gradient slots: enough workgroups per layer to keep the memory busy, few enough
     // that summing them stays cheap
     net->bgrid = std::max(1, std::min(cells, kNetGradSlots));
@@ -2063,7 +2064,7 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   a.S.train = 1;
   a.cells = cells;
   a.n_cells = n_cells;
-  if (net->resident_train) HIP_TRY(launch_net_resident<Real>(a, net_fwd_grid(net, n_cells), 1, s));
+  if (net->resident) HIP_TRY(launch_net_resident<Real>(a, net_fwd_grid(net, n_cells), 1, s));
   else HIP_TRY(launch_net_forward<Real>(a, std::min(n_cells, 4 * net->plan->cu_count), s));
   NetLossArgs<Real> la{};
   la.S = a.S;
@@ -2080,7 +2081,7 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   la.cell_loss = net->tloss;
   HIP_TRY(launch_net_loss<Real>(la, s));
   const int g = std::max(1, std::min(net->bgrid, n_cells));
-  if (net->resident_train) {
+  if (net->resident) {
     NetChainArgs ca{};
     ca.W = net->weights();
     ca.S = a.S;
@@ -2204,8 +2205,8 @@ npfem_status npfem_net_create(npfem_plan* p, const npfem_net_config* cfg, const 
     if ((s = net_upload_order(net.get(), m, mp, Xc, d))) return s;
   }
   if ((s = net->buf.upload(md.data(), md.size(), &net->d_meshes))) return s;
-  net->resident = !std::getenv("NPFEM_NET_NO_LDS") && net_resident_lds_bytes(net->n_pad_max) > 0;
-  net->resident_train = net->resident && net_chain_lds_bytes(net->n_pad_max) > 0;
+  net->resident = !std::getenv("NPFEM_NET_NO_LDS") && net_resident_lds_bytes(net->n_pad_max) > 0 &&
+                  net_chain_lds_bytes(net->n_pad_max) > 0;
   if ((s = net_upload_params(net.get(), theta, nullptr))) return s;
   *out = net.release();
   return NPFEM_OK;

@@ -1,6 +1,6 @@
 // gfx950 kernels of the batched npFEM step.
 //
-// One workgroup (4 wave64) owns a tile of up to kMaxTile cells of one mesh type and
+// One workgroup (four or eight wave64) owns a tile of up to kMaxTile cells of one mesh type and
 // carries them through a whole time step (Algorithm 1 of the paper): first guess,
 // quasi-Newton iterations with line search, velocity update and dissipation.  Cells
 // are worked on one at a time by the whole workgroup, with the cell's rest positions
@@ -52,7 +52,7 @@ constexpr int kWaves = kThreads / 64;
 // Every sum over a workgroup runs as kWide threads form it, so that a cell's bits do not depend on
 // the workgroup it gets (and so not on its batch): thread t of a narrower one goes through
 // the elements of threads t, t + kThreads, ... one set after the other, and their sums meet where
-// the waves' do.  (Half sums for 256 threads cost throughput 0.8 %: a second fold per sum.)
+// the waves' do.  The second fold per sum takes 2.5 % of the step of 100,000 cells (53.8 -> 55.2 ms).
 constexpr int kSets = kWide / kThreads;
 
 // LDS: [red: 2 buffers x 8 waves x 8 doubles][ints: 32][cell vectors ...]; during a tile
@@ -731,71 +731,71 @@ __device__ __attribute__((always_inline)) inline void evaluate(const MeshC<Real>
   double sumA[2] = {0.0, 0.0};             // 6 volume, 2 area
 #pragma unroll 1
   for (int set = 0; set < kSets; ++set) {
-  if (pre) {
-    double accA[2] = {0.0, 0.0};
-    for (int t = tid() + set * kThreads; t < nt; t += kWide) {
-      const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
-      const double E1x = ((double)xn[a] - (double)xn[c]) + ((double)ut[a] - (double)ut[c]);
-      const double E1y = ((double)xn[np + a] - (double)xn[np + c]) + ((double)ut[np + a] - (double)ut[np + c]);
-      const double E1z = ((double)xn[2 * np + a] - (double)xn[2 * np + c]) + ((double)ut[2 * np + a] - (double)ut[2 * np + c]);
-      const double E2x = ((double)xn[b] - (double)xn[c]) + ((double)ut[b] - (double)ut[c]);
-      const double E2y = ((double)xn[np + b] - (double)xn[np + c]) + ((double)ut[np + b] - (double)ut[np + c]);
-      const double E2z = ((double)xn[2 * np + b] - (double)xn[2 * np + c]) + ((double)ut[2 * np + b] - (double)ut[2 * np + c]);
-      const double cx = (double)xn[c] + ut[c], cy = (double)xn[np + c] + ut[np + c], cz = (double)xn[2 * np + c] + ut[2 * np + c];
-      accA[0] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
-      const double Nx = E1y * E2z - E1z * E2y, Ny = E1z * E2x - E1x * E2z, Nz = E1x * E2y - E1y * E2x;
-      accA[1] += sqrt(Nx * Nx + Ny * Ny + Nz * Nz);
+    if (pre) {
+      double accA[2] = {0.0, 0.0};
+      for (int t = tid() + set * kThreads; t < nt; t += kWide) {
+        const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
+        const double E1x = ((double)xn[a] - (double)xn[c]) + ((double)ut[a] - (double)ut[c]);
+        const double E1y = ((double)xn[np + a] - (double)xn[np + c]) + ((double)ut[np + a] - (double)ut[np + c]);
+        const double E1z = ((double)xn[2 * np + a] - (double)xn[2 * np + c]) + ((double)ut[2 * np + a] - (double)ut[2 * np + c]);
+        const double E2x = ((double)xn[b] - (double)xn[c]) + ((double)ut[b] - (double)ut[c]);
+        const double E2y = ((double)xn[np + b] - (double)xn[np + c]) + ((double)ut[np + b] - (double)ut[np + c]);
+        const double E2z = ((double)xn[2 * np + b] - (double)xn[2 * np + c]) + ((double)ut[2 * np + b] - (double)ut[2 * np + c]);
+        const double cx = (double)xn[c] + ut[c], cy = (double)xn[np + c] + ut[np + c], cz = (double)xn[2 * np + c] + ut[2 * np + c];
+        accA[0] += E1x * (E2y * cz - E2z * cy) + E1y * (E2z * cx - E2x * cz) + E1z * (E2x * cy - E2y * cx);
+        const double Nx = E1y * E2z - E1z * E2y, Ny = E1z * E2x - E1x * E2z, Nz = E1x * E2y - E1y * E2x;
+        accA[1] += sqrt(Nx * Nx + Ny * Ny + Nz * Nz);
+      }
+      red.put(set, accA);
     }
-    red.put(set, accA);
-  }
-  double accT[C::N];
-  sumT.get(set, accT);
-  for (int i = tid() + set * kThreads; i < n; i += kWide) {
-    Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
-    const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
-    const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
-    Real Ai = 0, l0 = 0;
-    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
-      // a group's neighbours and weights (padding: the vertex itself, weight 0) are all
-      // requested before the first is used; the scheduling barrier keeps them together
-      int jj[kEllGroup];
-      Real ww[kEllGroup];
+    double accT[C::N];
+    sumT.get(set, accT);
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
+      Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
+      const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
+      const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
+      Real Ai = 0, l0 = 0;
+      for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+        // a group's neighbours and weights (padding: the vertex itself, weight 0) are all
+        // requested before the first is used; the scheduling barrier keeps them together
+        int jj[kEllGroup];
+        Real ww[kEllGroup];
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
-        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
-      }
-      if (q0 == 0) {
-        Ai = gld(M.vor_area, i);
-        l0 = gld(M.ell0, i);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < kEllGroup; ++u) {
+          jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+          ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
+        }
+        if (q0 == 0) {
+          Ai = gld(M.vor_area, i);
+          l0 = gld(M.ell0, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        const int j = jj[u];
-        const Real w = ww[u];
-        const Real dux = ut[j] - uix, duy = ut[np + j] - uiy, duz = ut[2 * np + j] - uiz;
-        lx += w * ((xn[j] - xix) + dux);
-        ly += w * ((xn[np + j] - xiy) + duy);
-        lz += w * ((xn[2 * np + j] - xiz) + duz);
-        ux += w * dux;
-        uy += w * duy;
-        uz += w * duz;
+        for (int u = 0; u < kEllGroup; ++u) {
+          const int j = jj[u];
+          const Real w = ww[u];
+          const Real dux = ut[j] - uix, duy = ut[np + j] - uiy, duz = ut[2 * np + j] - uiz;
+          lx += w * ((xn[j] - xix) + dux);
+          ly += w * ((xn[np + j] - xiy) + duy);
+          lz += w * ((xn[2 * np + j] - xiz) + duz);
+          ux += w * dux;
+          uy += w * duy;
+          uz += w * duz;
+        }
       }
+      const Real inv_A = rcp_(Ai);
+      lx *= inv_A; ly *= inv_A; lz *= inv_A;
+      ux *= inv_A; uy *= inv_A; uz *= inv_A;
+      const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
+      const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
+      const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
+      accT[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
+      accT[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
+      work[i] = rx + beta * ux;
+      work[np + i] = ry + beta * uy;
+      work[2 * np + i] = rz + beta * uz;
     }
-    const Real inv_A = rcp_(Ai);
-    lx *= inv_A; ly *= inv_A; lz *= inv_A;
-    ux *= inv_A; uy *= inv_A; uz *= inv_A;
-    const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
-    const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
-    const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
-    accT[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
-    accT[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
-    work[i] = rx + beta * ux;
-    work[np + i] = ry + beta * uy;
-    work[2 * np + i] = rz + beta * uz;
-  }
-  sumT.set(set, accT);
+    sumT.set(set, accT);
   }
   if (pre) red.finish(sumA);                   // also the barrier before pass B
   else red.barrier();
@@ -814,53 +814,53 @@ __device__ __attribute__((always_inline)) inline void evaluate(const MeshC<Real>
   const Real wc = Real(col.w);
 #pragma unroll 1
   for (int set = 0; set < kSets; ++set) {
-  double accB[2] = {0.0, 0.0};
-  for (int i = tid() + set * kThreads; i < n; i += kWide) {
-    Real gx = 0, gy = 0, gz = 0;
-    const Real rix = work[i], riy = work[np + i], riz = work[2 * np + i];
-    Real mass = 0;
-    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
-      // as in pass A: the group's neighbours and weights (and the mass) are requested
-      // before the first is used
-      int jj[kEllGroup];
-      Real ww[kEllGroup];
+    double accB[2] = {0.0, 0.0};
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
+      Real gx = 0, gy = 0, gz = 0;
+      const Real rix = work[i], riy = work[np + i], riz = work[2 * np + i];
+      Real mass = 0;
+      for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+        // as in pass A: the group's neighbours and weights (and the mass) are requested
+        // before the first is used
+        int jj[kEllGroup];
+        Real ww[kEllGroup];
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
-        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
-      }
-      if (q0 == 0) mass = gld(M.mass, i);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < kEllGroup; ++u) {
+          jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+          ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
+        }
+        if (q0 == 0) mass = gld(M.mass, i);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        const int j = jj[u];
-        const Real w = ww[u];
-        gx += w * (work[j] - rix);
-        gy += w * (work[np + j] - riy);
-        gz += w * (work[2 * np + j] - riz);
+        for (int u = 0; u < kEllGroup; ++u) {
+          const int j = jj[u];
+          const Real w = ww[u];
+          gx += w * (work[j] - rix);
+          gy += w * (work[np + j] - riy);
+          gz += w * (work[2 * np + j] - riz);
+        }
       }
+      const Real mi = mass * inv_h2;
+      const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
+      const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
+      Real ox = kb * gx + (mi * ux - bx), oy = kb * gy + (mi * uy - by), oz = kb * gz + (mi * uz - bz);
+      if (EXT && col.n) {
+        const Real cnx = gld(col.n, 3 * i), cny = gld(col.n, 3 * i + 1), cnz = gld(col.n, 3 * i + 2);
+        const Real cqx = gld(col.q, 3 * i), cqy = gld(col.q, 3 * i + 1), cqz = gld(col.q, 3 * i + 2);
+        const Real dd = ((xn[i] - cqx) + ux) * cnx + ((xn[np + i] - cqy) + uy) * cny + ((xn[2 * np + i] - cqz) + uz) * cnz;
+        const Real dm = dd < Real(0) ? dd : Real(0);
+        ox += wc * dm * cnx;
+        oy += wc * dm * cny;
+        oz += wc * dm * cnz;
+        accB[1] += 0.5 * col.w * (double)dm * dm;
+      }
+      gout[i] = ox;
+      gout[np + i] = oy;
+      gout[2 * np + i] = oz;
+      accB[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
+                 - ((double)ux * bx + (double)uy * by + (double)uz * bz);
     }
-    const Real mi = mass * inv_h2;
-    const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
-    const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
-    Real ox = kb * gx + (mi * ux - bx), oy = kb * gy + (mi * uy - by), oz = kb * gz + (mi * uz - bz);
-    if (EXT && col.n) {
-      const Real cnx = gld(col.n, 3 * i), cny = gld(col.n, 3 * i + 1), cnz = gld(col.n, 3 * i + 2);
-      const Real cqx = gld(col.q, 3 * i), cqy = gld(col.q, 3 * i + 1), cqz = gld(col.q, 3 * i + 2);
-      const Real dd = ((xn[i] - cqx) + ux) * cnx + ((xn[np + i] - cqy) + uy) * cny + ((xn[2 * np + i] - cqz) + uz) * cnz;
-      const Real dm = dd < Real(0) ? dd : Real(0);
-      ox += wc * dm * cnx;
-      oy += wc * dm * cny;
-      oz += wc * dm * cnz;
-      accB[1] += 0.5 * col.w * (double)dm * dm;
-    }
-    gout[i] = ox;
-    gout[np + i] = oy;
-    gout[2 * np + i] = oz;
-    accB[0] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
-               - ((double)ux * bx + (double)uy * by + (double)uz * bz);
-  }
-  sumB.set(set, accB);
+    sumB.set(set, accB);
   }
   for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
   __syncthreads();   // work (R) is reused for the corner chunks below
@@ -896,66 +896,66 @@ __device__ __attribute__((always_inline)) inline void evaluate(const MeshC<Real>
     const bool last = t0 + ch >= nt;
 #pragma unroll 1
     for (int set = 0; set < kSets; ++set) {
-    double accD[5];
-    sumD.get(set, accD);
-    for (int i = tid() + set * kThreads; i < n; i += kWide) {
-      Real gx = 0, gy = 0, gz = 0, vx = 0, vy = 0, vz = 0;
-      // Branch-free, so that the reads of all corners are in flight together: a padding
-      // entry, or a corner outside this chunk, reads the chunk's first triangle and adds
-      // zero; corner k adds g_a, g_b or -g_a and -g_b, in the order and with the roundings of
-      // evaluate_resident (a cell's bits do not depend on the other meshes of its batch).
-      Real mass = 0;
-      for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
-        int cc[kEllGroup];
+      double accD[5];
+      sumD.get(set, accD);
+      for (int i = tid() + set * kThreads; i < n; i += kWide) {
+        Real gx = 0, gy = 0, gz = 0, vx = 0, vy = 0, vz = 0;
+        // Branch-free, so that the reads of all corners are in flight together: a padding
+        // entry, or a corner outside this chunk, reads the chunk's first triangle and adds
+        // zero; corner k adds g_a, g_b or -g_a and -g_b, in the order and with the roundings of
+        // evaluate_resident (a cell's bits do not depend on the other meshes of its batch).
+        Real mass = 0;
+        for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
+          int cc[kEllGroup];
 #pragma unroll
-        for (int u = 0; u < kEllGroup; ++u) cc[u] = gld(M.vc_ell + (q0 + u) * np, i);
-        if (q0 == 0 && last) mass = gld(M.mass, i);      // with the first group
-        __builtin_amdgcn_sched_barrier(0);
+          for (int u = 0; u < kEllGroup; ++u) cc[u] = gld(M.vc_ell + (q0 + u) * np, i);
+          if (q0 == 0 && last) mass = gld(M.mass, i);      // with the first group
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < kEllGroup; ++u) {
-          const int cid = cc[u];
-          const int tri = cid / 3, k = cid - 3 * tri, t = tri - t0;
-          const bool ok = cid >= 0 && t >= 0 && t < tn;
-          const int tc = ok ? t : 0;
-          const Real ax = work[tc], ay = work[ch + tc], az = work[2 * ch + tc];
-          const Real bx = work[3 * ch + tc], by = work[4 * ch + tc], bz = work[5 * ch + tc];
-          const Real nx = work[6 * ch + tc], ny = work[7 * ch + tc], nz = work[8 * ch + tc];
-          const Real wa = !ok || k == 1 ? Real(0) : (k == 0 ? Real(1) : Real(-1));
-          const Real wb = !ok || k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
-          gx += wa * ax;
-          gy += wa * ay;
-          gz += wa * az;
-          gx += wb * bx;
-          gy += wb * by;
-          gz += wb * bz;
-          vx += ok ? nx : Real(0);
-          vy += ok ? ny : Real(0);
-          vz += ok ? nz : Real(0);
+          for (int u = 0; u < kEllGroup; ++u) {
+            const int cid = cc[u];
+            const int tri = cid / 3, k = cid - 3 * tri, t = tri - t0;
+            const bool ok = cid >= 0 && t >= 0 && t < tn;
+            const int tc = ok ? t : 0;
+            const Real ax = work[tc], ay = work[ch + tc], az = work[2 * ch + tc];
+            const Real bx = work[3 * ch + tc], by = work[4 * ch + tc], bz = work[5 * ch + tc];
+            const Real nx = work[6 * ch + tc], ny = work[7 * ch + tc], nz = work[8 * ch + tc];
+            const Real wa = !ok || k == 1 ? Real(0) : (k == 0 ? Real(1) : Real(-1));
+            const Real wb = !ok || k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
+            gx += wa * ax;
+            gy += wa * ay;
+            gz += wa * az;
+            gx += wb * bx;
+            gy += wb * by;
+            gz += wb * bz;
+            vx += ok ? nx : Real(0);
+            vy += ok ? ny : Real(0);
+            vz += ok ? nz : Real(0);
+          }
+        }
+        gx += coef * vx;
+        gy += coef * vy;
+        gz += coef * vz;
+        gx += gout[i];
+        gy += gout[np + i];
+        gz += gout[2 * np + i];
+        gout[i] = gx;
+        gout[np + i] = gy;
+        gout[2 * np + i] = gz;
+        if (last) {
+          const Real mi = mass * inv_h2;
+          const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
+          const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
+          const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
+          const double fx = gx - (mux - bx), fy = gy - (muy - by), fz = gz - (muz - bz);
+          accD[0] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+          accD[1] += (double)gx * gx + (double)gy * gy + (double)gz * gz;
+          accD[2] += mux * mux + muy * muy + muz * muz;
+          accD[3] += (double)bx * bx + (double)by * by + (double)bz * bz;
+          accD[4] += fx * fx + fy * fy + fz * fz;
         }
       }
-      gx += coef * vx;
-      gy += coef * vy;
-      gz += coef * vz;
-      gx += gout[i];
-      gy += gout[np + i];
-      gz += gout[2 * np + i];
-      gout[i] = gx;
-      gout[np + i] = gy;
-      gout[2 * np + i] = gz;
-      if (last) {
-        const Real mi = mass * inv_h2;
-        const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
-        const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
-        const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
-        const double fx = gx - (mux - bx), fy = gy - (muy - by), fz = gz - (muz - bz);
-        accD[0] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
-        accD[1] += (double)gx * gx + (double)gy * gy + (double)gz * gz;
-        accD[2] += mux * mux + muy * muy + muz * muz;
-        accD[3] += (double)bx * bx + (double)by * by + (double)bz * bz;
-        accD[4] += fx * fx + fy * fy + fz * fz;
-      }
-    }
-    sumD.set(set, accD);
+      sumD.set(set, accD);
     }
     __syncthreads();
   }
@@ -1013,19 +1013,19 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
     double a2[1];
 #pragma unroll 1
     for (int set = 0; set < kSets; ++set) {
-    double as[1] = {0.0};
-    for (int t = tid() + set * kThreads; t < nt; t += kWide) {
-      const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
-      double N[3], E1[3], E2[3];
+      double as[1] = {0.0};
+      for (int t = tid() + set * kThreads; t < nt; t += kWide) {
+        const int a = gld(M.tri, 3 * t), b = gld(M.tri, 3 * t + 1), c = gld(M.tri, 3 * t + 2);
+        double N[3], E1[3], E2[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        E1[k] = ((double)xn[k * np + a] - (double)xn[k * np + c]) + ((double)ut[k * np + a] - (double)ut[k * np + c]);
-        E2[k] = ((double)xn[k * np + b] - (double)xn[k * np + c]) + ((double)ut[k * np + b] - (double)ut[k * np + c]);
+        for (int k = 0; k < 3; ++k) {
+          E1[k] = ((double)xn[k * np + a] - (double)xn[k * np + c]) + ((double)ut[k * np + a] - (double)ut[k * np + c]);
+          E2[k] = ((double)xn[k * np + b] - (double)xn[k * np + c]) + ((double)ut[k * np + b] - (double)ut[k * np + c]);
+        }
+        N[0] = E1[1] * E2[2] - E1[2] * E2[1], N[1] = E1[2] * E2[0] - E1[0] * E2[2], N[2] = E1[0] * E2[1] - E1[1] * E2[0];
+        as[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
       }
-      N[0] = E1[1] * E2[2] - E1[2] * E2[1], N[1] = E1[2] * E2[0] - E1[0] * E2[2], N[2] = E1[0] * E2[1] - E1[1] * E2[0];
-      as[0] += sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
-    }
-    red.put(set, as);
+      red.put(set, as);
     }
     red.finish(a2);
     area64 = 0.5 * a2[0];
@@ -1039,56 +1039,56 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   if (tid() < 9) work[9 * nt + tid()] = Real(0);
 #pragma unroll 1
   for (int set = 0; set < kSets; ++set) {
-  double accC[C::N] = {};
-  for (int i = tid() + set * kThreads; i < n; i += kWide) {
-    Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
-    const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
-    const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
-    Real Ai = 0, l0 = 0;
-    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
-      // a group's neighbours and weights (padding: the vertex itself, weight 0) are all
-      // requested before the first is used; the scheduling barrier keeps them together
-      int jj[kEllGroup];
-      Real ww[kEllGroup];
+    double accC[C::N] = {};
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
+      Real lx = 0, ly = 0, lz = 0, ux = 0, uy = 0, uz = 0;
+      const Real xix = xn[i], xiy = xn[np + i], xiz = xn[2 * np + i];
+      const Real uix = ut[i], uiy = ut[np + i], uiz = ut[2 * np + i];
+      Real Ai = 0, l0 = 0;
+      for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+        // a group's neighbours and weights (padding: the vertex itself, weight 0) are all
+        // requested before the first is used; the scheduling barrier keeps them together
+        int jj[kEllGroup];
+        Real ww[kEllGroup];
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
-        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
-      }
-      if (q0 == 0) {
-        Ai = gld(M.vor_area, i);
-        l0 = gld(M.ell0, i);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < kEllGroup; ++u) {
+          jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+          ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
+        }
+        if (q0 == 0) {
+          Ai = gld(M.vor_area, i);
+          l0 = gld(M.ell0, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        const int j = jj[u];
-        const Real w = ww[u];
-        const Real dux = ut[j] - uix, duy = ut[np + j] - uiy, duz = ut[2 * np + j] - uiz;
-        lx += w * ((xn[j] - xix) + dux);
-        ly += w * ((xn[np + j] - xiy) + duy);
-        lz += w * ((xn[2 * np + j] - xiz) + duz);
-        ux += w * dux;
-        uy += w * duy;
-        uz += w * duz;
+        for (int u = 0; u < kEllGroup; ++u) {
+          const int j = jj[u];
+          const Real w = ww[u];
+          const Real dux = ut[j] - uix, duy = ut[np + j] - uiy, duz = ut[2 * np + j] - uiz;
+          lx += w * ((xn[j] - xix) + dux);
+          ly += w * ((xn[np + j] - xiy) + duy);
+          lz += w * ((xn[2 * np + j] - xiz) + duz);
+          ux += w * dux;
+          uy += w * duy;
+          uz += w * duz;
+        }
       }
+      const Real inv_A = rcp_(Ai);
+      lx *= inv_A; ly *= inv_A; lz *= inv_A;
+      ux *= inv_A; uy *= inv_A; uz *= inv_A;
+      const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
+      const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
+      const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
+      accC[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
+      accC[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
+      rb[i] = rx + beta * ux;
+      rb[np + i] = ry + beta * uy;
+      rb[2 * np + i] = rz + beta * uz;
     }
-    const Real inv_A = rcp_(Ai);
-    lx *= inv_A; ly *= inv_A; lz *= inv_A;
-    ux *= inv_A; uy *= inv_A; uz *= inv_A;
-    const Real nrm = sqrt_(lx * lx + ly * ly + lz * lz);
-    const Real sc = nrm > Real(1e-30) ? l0 * rcp_(nrm) : Real(0);
-    const Real rx = lx - sc * lx, ry = ly - sc * ly, rz = lz - sc * lz;
-    accC[C::B] += 0.5 * (double)(kb * Ai) * ((double)rx * rx + (double)ry * ry + (double)rz * rz);
-    accC[C::BR] += 0.5 * (double)(beta * kb * Ai) * ((double)ux * ux + (double)uy * uy + (double)uz * uz);
-    rb[i] = rx + beta * ux;
-    rb[np + i] = ry + beta * uy;
-    rb[2 * np + i] = rz + beta * uz;
-  }
-  // ---- triangles -> corner buffer -----------------------------------------------------
-  for (int t = tid() + set * kThreads; t < nt; t += kWide)
-    triangle_terms<Real, EXT, TERMS>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
-  red.put(set, accC);
+    // ---- triangles -> corner buffer -----------------------------------------------------
+    for (int t = tid() + set * kThreads; t < nt; t += kWide)
+      triangle_terms<Real, EXT, TERMS>(M, Cst, Bsk, Dsk, beta, area_on, ca, xn, ut, np, t, accC, work + 9 * t, 1);
+    red.put(set, accC);
   }
   red.finish(sumC);
   const double vol = sumC[C::V] / 6.0, area = area_on ? area64 : sumC[C::A];   // the area whose gradient is taken
@@ -1101,87 +1101,87 @@ __device__ __attribute__((always_inline)) inline void evaluate_resident(
   const Real wc = Real(col.w);
 #pragma unroll 1
   for (int set = 0; set < kSets; ++set) {
-  double accD[ND] = {};
-  for (int i = tid() + set * kThreads; i < n; i += kWide) {
-    const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
-    const Real rix = rb[i], riy = rb[np + i], riz = rb[2 * np + i];
-    Real gx = 0, gy = 0, gz = 0, mass = 0;
-    for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
-      int jj[kEllGroup];
-      Real ww[kEllGroup];
+    double accD[ND] = {};
+    for (int i = tid() + set * kThreads; i < n; i += kWide) {
+      const Real bx = bvec[i], by = bvec[np + i], bz = bvec[2 * np + i];
+      const Real rix = rb[i], riy = rb[np + i], riz = rb[2 * np + i];
+      Real gx = 0, gy = 0, gz = 0, mass = 0;
+      for (int q0 = 0; q0 < M.nb_deg; q0 += kEllGroup) {
+        int jj[kEllGroup];
+        Real ww[kEllGroup];
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
-        ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
+        for (int u = 0; u < kEllGroup; ++u) {
+          jj[u] = gld(M.nb_ell + (q0 + u) * np, i);
+          ww[u] = gld(M.nbw_ell + (q0 + u) * np, i);
+        }
+        if (q0 == 0) mass = gld(M.mass, i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kEllGroup; ++u) {
+          const int j = jj[u];
+          const Real w = ww[u];
+          gx += w * (rb[j] - rix);
+          gy += w * (rb[np + j] - riy);
+          gz += w * (rb[2 * np + j] - riz);
+        }
       }
-      if (q0 == 0) mass = gld(M.mass, i);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        const int j = jj[u];
-        const Real w = ww[u];
-        gx += w * (rb[j] - rix);
-        gy += w * (rb[np + j] - riy);
-        gz += w * (rb[2 * np + j] - riz);
+      const Real mi = mass * inv_h2;
+      const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
+      Real ox = kb * gx + (mi * ux - bx), oy = kb * gy + (mi * uy - by), oz = kb * gz + (mi * uz - bz);
+      if (EXT && col.n) {
+        // (w/2) min(d, 0)^2 with d = (x - q) . n: gradient w min(d, 0) n, zero once out
+        const Real cnx = gld(col.n, 3 * i), cny = gld(col.n, 3 * i + 1), cnz = gld(col.n, 3 * i + 2);
+        const Real cqx = gld(col.q, 3 * i), cqy = gld(col.q, 3 * i + 1), cqz = gld(col.q, 3 * i + 2);
+        const Real dd = ((xn[i] - cqx) + ux) * cnx + ((xn[np + i] - cqy) + uy) * cny + ((xn[2 * np + i] - cqz) + uz) * cnz;
+        const Real dm = dd < Real(0) ? dd : Real(0);
+        ox += wc * dm * cnx;
+        oy += wc * dm * cny;
+        oz += wc * dm * cnz;
+        if constexpr (EXT) accD[D_COL] += 0.5 * col.w * (double)dm * dm;
       }
-    }
-    const Real mi = mass * inv_h2;
-    const Real ux = ut[i], uy = ut[np + i], uz = ut[2 * np + i];
-    Real ox = kb * gx + (mi * ux - bx), oy = kb * gy + (mi * uy - by), oz = kb * gz + (mi * uz - bz);
-    if (EXT && col.n) {
-      // (w/2) min(d, 0)^2 with d = (x - q) . n: gradient w min(d, 0) n, zero once out
-      const Real cnx = gld(col.n, 3 * i), cny = gld(col.n, 3 * i + 1), cnz = gld(col.n, 3 * i + 2);
-      const Real cqx = gld(col.q, 3 * i), cqy = gld(col.q, 3 * i + 1), cqz = gld(col.q, 3 * i + 2);
-      const Real dd = ((xn[i] - cqx) + ux) * cnx + ((xn[np + i] - cqy) + uy) * cny + ((xn[2 * np + i] - cqz) + uz) * cnz;
-      const Real dm = dd < Real(0) ? dd : Real(0);
-      ox += wc * dm * cnx;
-      oy += wc * dm * cny;
-      oz += wc * dm * cnz;
-      if constexpr (EXT) accD[D_COL] += 0.5 * col.w * (double)dm * dm;
-    }
-    accD[D_IN] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
-               - ((double)ux * bx + (double)uy * by + (double)uz * bz);
-    // corners: k = 0 adds g_a, 1 g_b, 2 -(g_a + g_b), all of them the volume normal
-    Real cx = 0, cy = 0, cz = 0, vx = 0, vy = 0, vz = 0;
-    for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
-      unsigned cc[kEllGroup];
+      accD[D_IN] += 0.5 * (double)mi * ((double)ux * ux + (double)uy * uy + (double)uz * uz)
+                 - ((double)ux * bx + (double)uy * by + (double)uz * bz);
+      // corners: k = 0 adds g_a, 1 g_b, 2 -(g_a + g_b), all of them the volume normal
+      Real cx = 0, cy = 0, cz = 0, vx = 0, vy = 0, vz = 0;
+      for (int q0 = 0; q0 < M.vc_deg; q0 += kEllGroup) {
+        unsigned cc[kEllGroup];
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u)
-        cc[u] = gld(M.vc_pk + (q0 + u) * np, i);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < kEllGroup; ++u)
+          cc[u] = gld(M.vc_pk + (q0 + u) * np, i);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < kEllGroup; ++u) {
-        const Real* g = work + (cc[u] >> 2);
-        const unsigned k = cc[u] & 3u;
-        const Real wa = k == 0 ? Real(1) : (k == 1 ? Real(0) : Real(-1));
-        const Real wb = k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
-        cx += wa * g[0];
-        cy += wa * g[1];
-        cz += wa * g[2];
-        cx += wb * g[3];
-        cy += wb * g[4];
-        cz += wb * g[5];
-        vx += g[6];
-        vy += g[7];
-        vz += g[8];
+        for (int u = 0; u < kEllGroup; ++u) {
+          const Real* g = work + (cc[u] >> 2);
+          const unsigned k = cc[u] & 3u;
+          const Real wa = k == 0 ? Real(1) : (k == 1 ? Real(0) : Real(-1));
+          const Real wb = k == 0 ? Real(0) : (k == 1 ? Real(1) : Real(-1));
+          cx += wa * g[0];
+          cy += wa * g[1];
+          cz += wa * g[2];
+          cx += wb * g[3];
+          cy += wb * g[4];
+          cz += wb * g[5];
+          vx += g[6];
+          vy += g[7];
+          vz += g[8];
+        }
       }
+      cx += coef * vx;
+      cy += coef * vy;
+      cz += coef * vz;
+      const Real tx = cx + ox, ty = cy + oy, tz = cz + oz;
+      gout[i] = tx;
+      gout[np + i] = ty;
+      gout[2 * np + i] = tz;
+      const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
+      const double fx = tx - (mux - bx), fy = ty - (muy - by), fz = tz - (muz - bz);
+      accD[D_UB] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
+      accD[D_G2] += (double)tx * tx + (double)ty * ty + (double)tz * tz;
+      accD[D_MU2] += mux * mux + muy * muy + muz * muz;
+      accD[D_B2] += (double)bx * bx + (double)by * by + (double)bz * bz;
+      accD[D_F2] += fx * fx + fy * fy + fz * fz;
     }
-    cx += coef * vx;
-    cy += coef * vy;
-    cz += coef * vz;
-    const Real tx = cx + ox, ty = cy + oy, tz = cz + oz;
-    gout[i] = tx;
-    gout[np + i] = ty;
-    gout[2 * np + i] = tz;
-    const double mux = (double)mi * ux, muy = (double)mi * uy, muz = (double)mi * uz;
-    const double fx = tx - (mux - bx), fy = ty - (muy - by), fz = tz - (muz - bz);
-    accD[D_UB] += fabs((double)ux * bx + (double)uy * by + (double)uz * bz);
-    accD[D_G2] += (double)tx * tx + (double)ty * ty + (double)tz * tz;
-    accD[D_MU2] += mux * mux + muy * muy + muz * muz;
-    accD[D_B2] += (double)bx * bx + (double)by * by + (double)bz * bz;
-    accD[D_F2] += fx * fx + fy * fy + fz * fz;
-  }
-  red.put_sets(set, accD, held);
+    red.put_sets(set, accD, held);
   }
   for (int i = n + tid(); i < np; i += kThreads) gout[i] = gout[np + i] = gout[2 * np + i] = Real(0);
   red.finish(sumD);                                          // also orders the gradient
@@ -1274,7 +1274,8 @@ template <typename Real, int MB, bool STAGED>
 struct DenseProduct {
   static constexpr bool F32 = std::is_same<Real, float>::value;
   typedef Real Frag __attribute__((ext_vector_type(4)));
-  typedef Real Frag16 __attribute__((ext_vector_type(4), aligned(16)));      // rows are 16-byte aligned
+  typedef Real Frag16 __attribute__((ext_vector_type(4), aligned(16)));      // the matrix and the staged rows
+  typedef Real FragIn __attribute__((ext_vector_type(4), aligned(sizeof(Real))));   // a caller's rows may start anywhere
   typedef Frag Acc;
   struct Block { const NPFEM_GLOBAL Real* a; int cb, ns; };
   struct Ends {};
@@ -1294,7 +1295,7 @@ struct DenseProduct {
   __device__ Frag rows(const Block& b, int s, int mb) const {
     const int k = 16 * max(min(s, b.ns - 1), 0) + 4 * kq, r = mb * 16 + l16;
     if constexpr (STAGED) return *reinterpret_cast<const NPFEM_LDS Frag16*>(stage + r * ld + k);
-    else return *reinterpret_cast<const NPFEM_GLOBAL Frag16*>(In + (min(r, n_rows - 1) * np + k));
+    else return *reinterpret_cast<const NPFEM_GLOBAL FragIn*>(In + (min(r, n_rows - 1) * np + k));
   }
   __device__ Ends pre(const Block&) const { return Ends{}; }
   __device__ void mma(Acc& c, const Frag& a, const Frag& b) const {
@@ -1327,13 +1328,14 @@ __device__ __attribute__((always_inline)) inline void dense_product(const Real* 
   const bool staged = mbn * 16 * ld * (int)sizeof(Real) <= stage_bytes;
   if (staged) {
     typedef Real V __attribute__((ext_vector_type(kDensePad<Real>)));
+    typedef Real VIn __attribute__((ext_vector_type(kDensePad<Real>), aligned(sizeof(Real))));
     constexpr int W = kDensePad<Real>, B = 4;
     const int q = np / W, total = rows * q;
     __syncthreads();
     for (int e0 = tid(); e0 < total; e0 += B * kThreads) {
       V v[B];
 #pragma unroll
-      for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const NPFEM_GLOBAL V*>(Ig + W * min(e0 + u * kThreads, total - 1));
+      for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const NPFEM_GLOBAL VIn*>(Ig + W * min(e0 + u * kThreads, total - 1));
 #pragma unroll
       for (int u = 0; u < B; ++u) {
         const int e = e0 + u * kThreads, r = e / q, c = e - r * q;
@@ -1443,6 +1445,7 @@ __device__ __attribute__((always_inline)) inline void band_product(const uint16_
     const int ldk = kc + 8;
     const int ng = np >> 2, total = ng * 4 * mbn;
     constexpr int B = kWaves == 8 ? 2 : 3;
+    typedef float VIn __attribute__((ext_vector_type(4), aligned(4)));      // a caller's rows may start anywhere
     __syncthreads();
     for (int e0 = tid(); e0 < total; e0 += B * kThreads) {
       floatx4 v[B][4];
@@ -1453,7 +1456,7 @@ __device__ __attribute__((always_inline)) inline void band_product(const uint16_
         pos[u] = *reinterpret_cast<const NPFEM_GLOBAL intx4*>(ip + 4 * g);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          v[u][i] = *reinterpret_cast<const NPFEM_GLOBAL floatx4*>(Ig + (min(4 * rq + i, rows - 1) * np + 4 * g));
+          v[u][i] = *reinterpret_cast<const NPFEM_GLOBAL VIn*>(Ig + (min(4 * rq + i, rows - 1) * np + 4 * g));
       }
 #pragma unroll
       for (int u = 0; u < B; ++u) {
@@ -1535,18 +1538,18 @@ __device__ __attribute__((always_inline)) inline void finalize_cell(const StepAr
     double s1[7];
 #pragma unroll 1
     for (int set = 0; set < kSets; ++set) {
-    double sv[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int i = tid() + set * kThreads; i < n; i += kWide) {
-      const double m = gld(M.mass, i);
-      sv[0] += m;
+      double sv[7] = {0, 0, 0, 0, 0, 0, 0};
+      for (int i = tid() + set * kThreads; i < n; i += kWide) {
+        const double m = gld(M.mass, i);
+        sv[0] += m;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const double x = (double)xn[c * np + i] + (double)U[c * np + i];
-        sv[1 + c] += m * x;
-        sv[4 + c] += m * ((double)U[c * np + i] / h);
+        for (int c = 0; c < 3; ++c) {
+          const double x = (double)xn[c * np + i] + (double)U[c * np + i];
+          sv[1 + c] += m * x;
+          sv[4 + c] += m * ((double)U[c * np + i] / h);
+        }
       }
-    }
-    red.put(set, sv);
+      red.put(set, sv);
     }
     red.finish(s1);
     const double xc[3] = {s1[1] / s1[0], s1[2] / s1[0], s1[3] / s1[0]};
@@ -1554,24 +1557,24 @@ __device__ __attribute__((always_inline)) inline void finalize_cell(const StepAr
     Folded<9> fold2;
 #pragma unroll 1
     for (int set = 0; set < kSets; ++set) {
-    double s2[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // L (3), I_xx I_yy I_zz I_xy I_xz I_yz
-    for (int i = tid() + set * kThreads; i < n; i += kWide) {
-      const double m = gld(M.mass, i);
-      const double rx = (double)xn[i] + (double)U[i] - xc[0];
-      const double ry = (double)xn[np + i] + (double)U[np + i] - xc[1];
-      const double rz = (double)xn[2 * np + i] + (double)U[2 * np + i] - xc[2];
-      const double vx = (double)U[i] / h, vy = (double)U[np + i] / h, vz = (double)U[2 * np + i] / h;
-      s2[0] += m * (ry * vz - rz * vy);
-      s2[1] += m * (rz * vx - rx * vz);
-      s2[2] += m * (rx * vy - ry * vx);
-      s2[3] += m * (ry * ry + rz * rz);
-      s2[4] += m * (rx * rx + rz * rz);
-      s2[5] += m * (rx * rx + ry * ry);
-      s2[6] -= m * rx * ry;
-      s2[7] -= m * rx * rz;
-      s2[8] -= m * ry * rz;
-    }
-    fold2.fold(set, s2);
+      double s2[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // L (3), I_xx I_yy I_zz I_xy I_xz I_yz
+      for (int i = tid() + set * kThreads; i < n; i += kWide) {
+        const double m = gld(M.mass, i);
+        const double rx = (double)xn[i] + (double)U[i] - xc[0];
+        const double ry = (double)xn[np + i] + (double)U[np + i] - xc[1];
+        const double rz = (double)xn[2 * np + i] + (double)U[2 * np + i] - xc[2];
+        const double vx = (double)U[i] / h, vy = (double)U[np + i] / h, vz = (double)U[2 * np + i] / h;
+        s2[0] += m * (ry * vz - rz * vy);
+        s2[1] += m * (rz * vx - rx * vz);
+        s2[2] += m * (rx * vy - ry * vx);
+        s2[3] += m * (ry * ry + rz * rz);
+        s2[4] += m * (rx * rx + rz * rz);
+        s2[5] += m * (rx * rx + ry * ry);
+        s2[6] -= m * rx * ry;
+        s2[7] -= m * rx * rz;
+        s2[8] -= m * ry * rz;
+      }
+      fold2.fold(set, s2);
     }
     double s2[9];
     fold2.sum(s2, red);

@@ -38,7 +38,7 @@ __device__ inline bf16x8 zero8() {
   return bf16x8{z, z, z, z, z, z, z, z};
 }
 
-template <int N, int NW = 4>
+template <int N>
 __device__ inline void wg_sum(double (&v)[N], double* red) {
   static_assert(N <= kRS, "wg_sum: too many values");
 #pragma unroll
@@ -59,7 +59,7 @@ __device__ inline void wg_sum(double (&v)[N], double* red) {
   for (int i = 0; i < N; ++i) {
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) t += red[w * kRS + i];
+    for (int w = 0; w < kBlock / 64; ++w) t += red[w * kRS + i];
     v[i] = t;
   }
 }
@@ -119,12 +119,12 @@ __device__ void polar3(const double* C, double* R) {
 // Frame (mass-weighted centroids, covariance with the rest shape, Kabsch) and the node
 // features of cell k, written as BF16 rows of 32 (zero padded) to feat.  Leaves R and
 // s in fr[0..9] (LDS) and ends with a barrier.
-template <typename Real, int NT>
+template <typename Real>
 __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, int k, const Real* x, const Real* v,
-                              const Real* f, uint16_t* feat, uint16_t* feat2, double* red, double* fr) {
+                              const Real* f, uint16_t* feat, double* red, double* fr) {
   const int n = M.n, np = M.n_pad;
   double s1[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = tid(); i < n; i += NT) {
+  for (int i = tid(); i < n; i += kBlock) {
     const double m = M.mass[i];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -133,13 +133,13 @@ __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, in
       s1[6 + c] += (double)f[3 * i + c];
     }
   }
-  wg_sum<9, NT / 64>(s1, red);
+  wg_sum<9>(s1, red);
   const double ims = 1.0 / M.mass_sum;
   const double xc[3] = {s1[0] * ims, s1[1] * ims, s1[2] * ims};
   const double vc[3] = {s1[3] * ims, s1[4] * ims, s1[5] * ims};
   const double ac[3] = {s1[6] * ims, s1[7] * ims, s1[8] * ims};
   double s2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = tid(); i < n; i += NT) {
+  for (int i = tid(); i < n; i += kBlock) {
     const double m = M.mass[i];
     double d[3], fd[3];
 #pragma unroll
@@ -153,7 +153,7 @@ __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, in
       for (int b = 0; b < 3; ++b) s2[3 * a + b] += m * d[a] * M.Xc[3 * i + b];
     s2[9] += fd[0] * fd[0] + fd[1] * fd[1] + fd[2] * fd[2];
   }
-  wg_sum<10, NT / 64>(s2, red);
+  wg_sum<10>(s2, red);
   if (tid() == 0) {
     double R[9];
     polar3(s2, R);
@@ -172,7 +172,7 @@ __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, in
   for (int q = 0; q < 9; ++q) R[q] = fr[q];
   const double s = fr[9];
   const double hs = A.h / s, h2s = A.h * A.h / s, iq = 1.0 / A.W.shape_scale;
-  for (int i = tid(); i < np; i += NT) {
+  for (int i = tid(); i < np; i += kBlock) {
     float fv[kNetFeat];
 #pragma unroll
     for (int q = 0; q < kNetFeat; ++q) fv[q] = 0.f;
@@ -206,23 +206,18 @@ __device__ void cell_features(const NetFwdArgs<Real>& A, const NetMeshDev& M, in
     for (int e = 0; e < 8; ++e) w0[e] = (__bf16)fv[e];
 #pragma unroll
     for (int e = 0; e < 8; ++e) w1[e] = (__bf16)(e < 4 ? fv[8 + e] : 0.f);
-    for (uint16_t* base : {feat, feat2}) {
-      if (!base) continue;
-      uint16_t* fp = base + (size_t)i * kNetFeatPad;
-      *reinterpret_cast<bf16x8*>(fp) = w0;
-      *reinterpret_cast<bf16x8*>(fp + 8) = w1;
-      *reinterpret_cast<bf16x8*>(fp + 16) = zero8();
-      *reinterpret_cast<bf16x8*>(fp + 24) = zero8();
-    }
+    uint16_t* fp = feat + (size_t)i * kNetFeatPad;
+    *reinterpret_cast<bf16x8*>(fp) = w0;
+    *reinterpret_cast<bf16x8*>(fp + 8) = w1;
+    *reinterpret_cast<bf16x8*>(fp + 16) = zero8();
+    *reinterpret_cast<bf16x8*>(fp + 24) = zero8();
   }
   __syncthreads();
 }
 
-// Encoder rows of the waves w = wave, wave + NWV, ...: h0 = relu(W_e f + b_e) into
-// H (row pitch hp); training also stores h0 and z0 (pitch kNetH) to Hg / Zg.
-template <int NWV>
-__device__ void encoder_rows(const NetWeights& W, const uint16_t* feat, int n, int np, uint16_t* H, int hp,
-                             uint16_t* Hg, uint16_t* Zg) {
+// Encoder rows of this wave: h0 = relu(W_e f + b_e) into H; training also stores z0 to Z.
+__device__ void encoder_rows(const NetWeights& W, const uint16_t* feat, int n, int np, uint16_t* H,
+                             uint16_t* Z) {
   const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
   bf16x8 bq[4];
   float bias[4];
@@ -231,7 +226,7 @@ __device__ void encoder_rows(const NetWeights& W, const uint16_t* feat, int n, i
     bq[cb] = ld8(W.We + (size_t)(cb * 16 + l16) * kNetFeatPad + 8 * kq);
     bias[cb] = W.theta[W.lay.off_be + cb * 16 + l16];
   }
-  for (int rb = wave; rb < (np >> 4); rb += NWV) {
+  for (int rb = wave; rb < (np >> 4); rb += kBlock / 64) {
     const bf16x8 aq = ld8(feat + (size_t)(rb * 16 + l16) * kNetFeatPad + 8 * kq);
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
@@ -240,12 +235,8 @@ __device__ void encoder_rows(const NetWeights& W, const uint16_t* feat, int n, i
       for (int i = 0; i < 4; ++i) {
         const int row = rb * 16 + 4 * kq + i, col = cb * 16 + l16;
         const float z = row < n ? acc[i] + bias[cb] : 0.f;
-        const uint16_t hb = f2bf(fmaxf(z, 0.f));
-        H[(size_t)row * hp + col] = hb;
-        if (Hg) {
-          Hg[(size_t)row * kNetH + col] = hb;
-          Zg[(size_t)row * kNetH + col] = f2bf(z);
-        }
+        H[(size_t)row * kNetH + col] = f2bf(fmaxf(z, 0.f));
+        if (Z) Z[(size_t)row * kNetH + col] = f2bf(z);
       }
     }
   }
@@ -254,9 +245,9 @@ __device__ void encoder_rows(const NetWeights& W, const uint16_t* feat, int n, i
 // Decoder on the matrix cores: o = W_d h + b_d (3 outputs padded to one 16-column
 // block); lanes l16 = 0, 1, 2 of each 16-lane group hold the components of a row and
 // exchange them to form the correction s R o (world frame) and/or store o.
-template <typename Real, int NWV>
+template <typename Real>
 __device__ void decoder_rows(const NetFwdArgs<Real>& A, int k, int64_t voff, int n, int np, const uint16_t* H,
-                             int hp, const double* fr) {
+                             const double* fr) {
   const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
   double R[9];
 #pragma unroll
@@ -266,11 +257,11 @@ __device__ void decoder_rows(const NetFwdArgs<Real>& A, int k, int64_t voff, int
 #pragma unroll
   for (int s2 = 0; s2 < 2; ++s2) bq[s2] = l16 < 3 ? ld8(A.W.Wd + (size_t)l16 * kNetH + 32 * s2 + 8 * kq) : zero8();
   const float bias = l16 < 3 ? A.W.theta[A.W.lay.off_bd + l16] : 0.f;
-  for (int rb = wave; rb < (np >> 4); rb += NWV) {
+  for (int rb = wave; rb < (np >> 4); rb += kBlock / 64) {
     const int row = rb * 16 + l16;
-    floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(H + (size_t)row * hp + 8 * kq), bq[0],
+    floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(H + (size_t)row * kNetH + 8 * kq), bq[0],
                                                           floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(H + (size_t)row * hp + 32 + 8 * kq), bq[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(H + (size_t)row * kNetH + 32 + 8 * kq), bq[1], acc, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float o = acc[i] + bias;                    // o[4kq + i][l16]
@@ -287,11 +278,11 @@ __device__ void decoder_rows(const NetFwdArgs<Real>& A, int k, int64_t voff, int
   }
 }
 
-// One message-passing layer over the row blocks of this wave: reads h (row pitch hp)
-// and its neighbour means, writes h + relu(z) to Hout (pitch kNetH) and z to Zout.
+// One message-passing layer over the row blocks of this wave: reads h and its
+// neighbour means, writes h + relu(z) to Hout and z to Zout.
 // Neighbour j of row i: nbr(q, i) for q < deg(i).
-template <int NWV, typename NbrF, typename DegF>
-__device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width, const uint16_t* Hin, int hp,
+template <typename NbrF, typename DegF>
+__device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width, const uint16_t* Hin,
                            uint16_t* Hout, uint16_t* Zout, NbrF nbr, DegF deg) {
   const int lane = tid() & 63, wave = tid() >> 6, l16 = lane & 15, kq = lane >> 4;
   const uint16_t* Wl = W.Wl + (size_t)l * kNetH * 2 * kNetH;
@@ -303,12 +294,12 @@ __device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width,
     for (int s4 = 0; s4 < 4; ++s4) bq[s4][cb] = ld8(Wl + (size_t)(cb * 16 + l16) * 2 * kNetH + 32 * s4 + 8 * kq);
     bias[cb] = W.theta[W.lay.b(l) + cb * 16 + l16];
   }
-  for (int rb = wave; rb < (np >> 4); rb += NWV) {
+  for (int rb = wave; rb < (np >> 4); rb += kBlock / 64) {
     const int row = rb * 16 + l16;
     bf16x8 aq[4];
     if (row < n) {
-      aq[0] = ld8(Hin + (size_t)row * hp + 8 * kq);
-      aq[1] = ld8(Hin + (size_t)row * hp + 32 + 8 * kq);
+      aq[0] = ld8(Hin + (size_t)row * kNetH + 8 * kq);
+      aq[1] = ld8(Hin + (size_t)row * kNetH + 32 + 8 * kq);
       float g0[8], g1[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) g0[e] = g1[e] = 0.f;
@@ -320,8 +311,8 @@ __device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width,
       for (int q = 0; q < kNetUnrollDeg; ++q) {
         const int j = q < width ? nbr(q, row) : row;
         const float w = q < dg ? 1.f : 0.f;
-        const bf16x8 h0 = ld8(Hin + (size_t)j * hp + 8 * kq);
-        const bf16x8 h1 = ld8(Hin + (size_t)j * hp + 32 + 8 * kq);
+        const bf16x8 h0 = ld8(Hin + (size_t)j * kNetH + 8 * kq);
+        const bf16x8 h1 = ld8(Hin + (size_t)j * kNetH + 32 + 8 * kq);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           g0[e] += w * (float)h0[e];
@@ -330,8 +321,8 @@ __device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width,
       }
       for (int q = kNetUnrollDeg; q < dg; ++q) {
         const int j = nbr(q, row);
-        const bf16x8 h0 = ld8(Hin + (size_t)j * hp + 8 * kq);
-        const bf16x8 h1 = ld8(Hin + (size_t)j * hp + 32 + 8 * kq);
+        const bf16x8 h0 = ld8(Hin + (size_t)j * kNetH + 8 * kq);
+        const bf16x8 h1 = ld8(Hin + (size_t)j * kNetH + 32 + 8 * kq);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           g0[e] += (float)h0[e];
@@ -361,7 +352,7 @@ __device__ void layer_rows(const NetWeights& W, int l, int n, int np, int width,
       for (int i = 0; i < 4; ++i) {
         const int r2 = rb * 16 + 4 * kq + i, col = cb * 16 + l16;
         const float z = r2 < n ? acc[cb][i] + bias[cb] : 0.f;
-        const float hn = r2 < n ? bf2f(Hin[(size_t)r2 * hp + col]) + fmaxf(z, 0.f) : 0.f;
+        const float hn = r2 < n ? bf2f(Hin[(size_t)r2 * kNetH + col]) + fmaxf(z, 0.f) : 0.f;
         Hout[(size_t)r2 * kNetH + col] = f2bf(hn);
         if (Zout) Zout[(size_t)r2 * kNetH + col] = f2bf(z);
       }
@@ -387,24 +378,20 @@ __global__ void __launch_bounds__(kBlock) net_forward_kernel(NetFwdArgs<Real> A)
     uint16_t* feat = A.S.feat + slot * A.S.n_pad_max * kNetFeatPad;
     uint16_t* Hs = A.S.H + slot * nh * plane;
     uint16_t* Zs = train ? A.S.Z + slot * (L.layers + 1) * plane : nullptr;
-    cell_features<Real, kBlock>(A, M, k, A.x + 3 * voff, A.v + 3 * voff, A.f + 3 * voff, feat, nullptr, red, fr);
-    encoder_rows<kBlock / 64>(A.W, feat, n, np, Hs, kNetH, nullptr, nullptr);
-    if (train) {                              // z0 for the backward pass
-      __syncthreads();
-      encoder_rows<kBlock / 64>(A.W, feat, n, np, Hs, kNetH, Hs, Zs);
-    }
+    cell_features<Real>(A, M, k, A.x + 3 * voff, A.v + 3 * voff, A.f + 3 * voff, feat, red, fr);
+    encoder_rows(A.W, feat, n, np, Hs, Zs);   // training: z0 for the backward pass
     __syncthreads();
     auto nbr = [&](int q, int i) { return M.nb_ell[q * np + i]; };
     auto deg = [&](int i) { return M.nb_ptr[i + 1] - M.nb_ptr[i]; };
     for (int l = 0; l < L.layers; ++l) {
       const uint16_t* Hin = Hs + (size_t)(train ? l : (l & 1)) * plane;
       uint16_t* Hout = Hs + (size_t)(train ? l + 1 : ((l + 1) & 1)) * plane;
-      layer_rows<kBlock / 64>(A.W, l, n, np, M.nb_deg, Hin, kNetH, Hout, train ? Zs + (size_t)(l + 1) * plane : nullptr,
+      layer_rows(A.W, l, n, np, M.nb_deg, Hin, Hout, train ? Zs + (size_t)(l + 1) * plane : nullptr,
                               nbr, deg);
       __syncthreads();
     }
     const uint16_t* HL = Hs + (size_t)(train ? L.layers : (L.layers & 1)) * plane;
-    decoder_rows<Real, kBlock / 64>(A, k, voff, n, np, HL, kNetH, fr);
+    decoder_rows<Real>(A, k, voff, n, np, HL, fr);
     __syncthreads();
   }
 }
