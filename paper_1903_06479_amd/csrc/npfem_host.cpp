@@ -1786,6 +1786,7 @@ struct npfem_net {
   const NetMeshDev* d_meshes = nullptr;
   int n_pad_max = 0;
   bool resident = false;                    // every mesh fits the resident kernels
+  bool tresident = false;                   // the training scratch is the resident kernels'
   bool features32 = true;                   // inference: features in FP32
   int adam_t = 0;
   // inference scratch: per workgroup, features and two activation planes
@@ -1927,10 +1928,21 @@ npfem_status net_inference_scratch(npfem_net* net) {
   return NPFEM_OK;
 }
 
+// The resident kernels keep two fifths more per cell (the neighbour means) than the any-size ones,
+// which take a minibatch that is too large for that; a later one of at most half its cells
+// goes back to the resident kernels.
+npfem_status net_training_alloc(npfem_net* net, int cells, bool resident);
 npfem_status net_training_scratch(npfem_net* net, int cells) {
-  if (cells <= net->tcap) return NPFEM_OK;
+  if (cells <= net->tcap && (net->tresident == net->resident || cells > net->tcap / 2)) return NPFEM_OK;
+  npfem_status s = net_training_alloc(net, cells, net->resident);
+  if (s == NPFEM_E_OOM && net->resident) s = net_training_alloc(net, cells, false);
+  return s;
+}
+
+npfem_status net_training_alloc(npfem_net* net, int cells, bool resident) {
   net->tbuf.release();
   net->tcap = 0;
+  net->tresident = resident;
   const size_t np = (size_t)net->n_pad_max, L1 = (size_t)net->lay.layers + 1, C = (size_t)cells;
   const size_t P = (size_t)net->lay.count;
   npfem_status s;
@@ -1947,7 +1959,7 @@ npfem_status net_training_scratch(npfem_net* net, int cells) {
   get(C * sizeof(double), &net->tloss);
   get(C * np * 3 * sizeof(float), &net->tout);
   get(C * np * 3 * sizeof(float), &net->tdout);
-  if (net->resident) {
+  if (resident) {
     // weight-gradient slots: enough workgroups per layer to keep the memory busy, few enough
     // that summing them stays cheap
     net->bgrid = std::max(1, std::min(cells, kNetGradSlots));
@@ -2064,7 +2076,7 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   a.S.train = 1;
   a.cells = cells;
   a.n_cells = n_cells;
-  if (net->resident) HIP_TRY(launch_net_resident<Real>(a, net_fwd_grid(net, n_cells), 1, s));
+  if (net->tresident) HIP_TRY(launch_net_resident<Real>(a, net_fwd_grid(net, n_cells), 1, s));
   else HIP_TRY(launch_net_forward<Real>(a, std::min(n_cells, 4 * net->plan->cu_count), s));
   NetLossArgs<Real> la{};
   la.S = a.S;
@@ -2081,7 +2093,7 @@ npfem_status net_loss_grad_now(npfem_net* net, npfem_batch* b, const int32_t* ce
   la.cell_loss = net->tloss;
   HIP_TRY(launch_net_loss<Real>(la, s));
   const int g = std::max(1, std::min(net->bgrid, n_cells));
-  if (net->resident) {
+  if (net->tresident) {
     NetChainArgs ca{};
     ca.W = net->weights();
     ca.S = a.S;
