@@ -96,3 +96,23 @@ def test_four_waves_match_oracle(mesh, bf16, lbfgs_m, terms):
         extra = {"contacts": (contacts[0][k], contacts[1][k], w)} if contacts else {}
         xr, _, _ = ostep.step(m, x[k], v[k], f[k], ostep.Params(tol=1e-12, polish=True), literal=terms == "literal", **extra)
         assert np.abs(xo[k] - xr).max() <= 1e-5 * np.ptp(X[:, 0]), c
+
+
+@pytest.mark.parametrize("lbfgs_m,optional", [(2, False), (5, True)])
+def test_bits_in_fp64_do_not_depend_on_the_batch(lbfgs_m, optional):
+    from paper_1903_06479_amd import Mesh, Plan, default_material, default_params
+    small, big = mesh_of("642"), mesh_of("1026")                   # 1026: gradient and chunks in the workspace
+    n, cells = len(small[0]), 7
+
+    def plan(*ms):
+        return Plan([Mesh(*m) for m in ms], DT, material=default_material(k_area_global=20.0 if optional else 0.0),
+                    params=default_params(precision="fp64", volume_normaliser=int(optional), max_iter=12, lbfgs_m=lbfgs_m))
+
+    x, v, f = (T(a, torch.float64) for a in cells_of(small[0], cells, 31))
+    ref = run(plan(small), np.zeros(cells), x, v, f, 1)
+    for tile in (3, 7):
+        got = run(plan(small), np.zeros(cells), x, v, f, tile)
+        assert all(torch.equal(a, b) for a, b in zip(got[1:], ref[1:])), tile
+    xb, vb, fb = (T(a, torch.float64) for a in cells_of(big[0], 1, 33))
+    mixed = run(plan(small, big), [0] * cells + [1], torch.cat([x, xb]), torch.cat([v, vb]), torch.cat([f, fb]), 3)
+    assert torch.equal(mixed[1][:cells * n], ref[1]) and torch.equal(mixed[2][:cells * n], ref[2])
