@@ -1599,7 +1599,8 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
   const int T0 = b->T, m0 = b->m;
   int bT = T0, bm = m0;
   // tiles of 2 or 3 cells only for batches that leave workgroups idle at 5 cells per tile; each
-  // size spread over idle workgroups and as it is, every resulting tile size once
+  // size spread over idle workgroups (where that is more than a fifth less, of ten or more) and
+  // as it is, every resulting tile size once
   const int Ts[] = {2, 3, 5, 10, 16, 21};
   const int ms[] = {2, 3, 5, 8};
   const bool small = b->n_cells < 5 * 2 * (int64_t)b->plan->cu_count;
@@ -1610,7 +1611,7 @@ npfem_status npfem_batch_autotune(npfem_batch* b, const void* x, const void* v, 
     if ((int64_t)T > b->n_cells && T != 5) continue;
     for (int sp = 1; sp >= 0 && !st; --sp) {
       const int Tt = sp ? spread_tile(b, T) : T;
-      if (std::find(tried.begin(), tried.end(), Tt) != tried.end()) continue;
+      if (std::find(tried.begin(), tried.end(), Tt) != tried.end() || (Tt < T && T >= 10 && 5 * Tt > 4 * T)) continue;
       tried.push_back(Tt);
       for (int m : ms) {
         if (m > max_lbfgs_m && !(m == 2 && max_lbfgs_m < 2)) continue;
